@@ -232,7 +232,8 @@ essa_status essa_theta_to_sigma(essa_ctx* ctx, int P, int r, int n_top, const fl
  * amax_i / 32639, error at most delta_i / 2 per entry) and the base term runs on the int8 MFMA with exact int32
  * accumulation, one pass per limb (4-bit weights likewise, their nibbles unpacked in registers, each group of 128 rescaled in fp32 and the
  * zero-point term added as a low-rank product); ESSA_COMPUTE_BF16 selects exact bf16 products on the bf16 MFMA
- * (fp32 accumulation) instead.  With ESSA_COMPUTE_W8A8 the base term uses x quantised per row to one int8
+ * (fp32 accumulation) instead, and int8 weights of 128 channels or more take them by themselves from a few hundred rows on,
+ * where they are the faster ones (their error is a hundredth of the fixed point's).  With ESSA_COMPUTE_W8A8 the base term uses x quantised per row to one int8
  * (amax/127, round to nearest even).  The LoRA term always sees the unquantised x.
  * A row of X that holds an Inf or a NaN gives a row of NaN (W_deq x + B_k A_k x is then non-finite in every element: NaN,
  * or an infinity of either sign).  A row whose largest magnitude is at most 2^-100 counts as zero in the base term.

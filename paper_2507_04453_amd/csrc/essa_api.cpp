@@ -228,7 +228,7 @@ extern "C" void essa_proj_destroy(essa_proj* p) {
     if (!p) return;
     (void)hipSetDevice(p->device);
     (void)hipDeviceSynchronize();
-    void* ptrs[] = {p->Wq, p->scale, p->zero, p->VA32, p->VA16, p->UB32, p->UB16, p->M, p->Wt, p->VAp, p->St, p->SZ16};
+    void* ptrs[] = {p->Wq, p->scale, p->zero, p->VA32, p->VA16, p->UB32, p->UB16, p->M, p->Wt, p->VAp, p->St, p->SZ16, p->W16, p->US16, p->scale16};
     for (void* q : ptrs)
         if (q) (void)hipFree(q);
     delete p;
@@ -343,6 +343,35 @@ extern "C" essa_status essa_proj_create(essa_ctx* ctx, const essa_proj_desc* d, 
                 }
             }
         ESSA_TRY(upload(&p->Wt, Wt.data(), Wt.size()));
+        // exact-product kernel: the weights as bf16, U_B over the channel scale.  Channels with scale 0 take scale 1 and zero
+        // weights; a scale so extreme that U_B / s could leave the range of bf16 keeps the projection on the other kernels.
+        const float* sc = (const float*)d->scales;
+        const int nk64 = (din + 63) / 64;
+        const size_t w16 = (size_t)nk64 * p->n_blocks * 4096;
+        bool usable = w16 < (1u << 31);            // the kernel's 32-bit offsets
+        for (int o = 0; o < dout; ++o) usable = usable && (sc[o] == 0.f || (std::fabs(sc[o]) >= 0x1p-60f && std::fabs(sc[o]) <= 0x1p60f));
+        if (usable) {
+            std::vector<float> s16(sc, sc + dout);
+            std::vector<uint16_t> US(UB16.size(), 0);
+            for (int o = 0; o < dout; ++o) {
+                if (s16[o] == 0.f) s16[o] = 1.f;
+                for (int j = 0; j < r; ++j) {
+                    const float v = (float)(UB[(size_t)o * r + j] / (double)s16[o]);
+                    const uint16_t hi = f32_to_bf16_rne(v);
+                    uint32_t hb = (uint32_t)hi << 16;
+                    float hf;
+                    std::memcpy(&hf, &hb, 4);
+                    US[(size_t)o * 2 * rp + j] = hi;
+                    US[(size_t)o * 2 * rp + rp + j] = f32_to_bf16_rne(v - hf);
+                }
+            }
+            ESSA_TRY(upload(&p->US16, US.data(), US.size()));
+            ESSA_TRY(upload(&p->scale16, s16.data(), s16.size()));
+            hipError_t e = hipMalloc((void**)&p->W16, w16);
+            if (e != hipSuccess) return essa_fail(ESSA_ERR_OOM, "hipMalloc of %zu bytes: %s", w16, hipGetErrorString(e));
+            ESSA_HIP(essa_k::expand_weights(nullptr, p->Wt, p->scale, dout, p->n_blocks, nk64, p->W16));
+            ESSA_HIP(hipStreamSynchronize(nullptr));
+        }
     } else {
         p->groups = din / 128;
         uint8_t* w = nullptr;
@@ -642,7 +671,7 @@ static essa_status plan_items(essa_ctx* ctx, const essa_fwd_item* items, int n_i
         k.d_in = p->d_in; k.d_out = p->d_out; k.r = p->r; k.rp = p->rp; k.quant = p->quant; k.groups = p->groups;
         k.Wq = p->Wq; k.scale = p->scale; k.zero = p->zero; k.VA32 = p->VA32; k.VA16 = p->VA16;
         k.UB32 = p->UB32; k.UB16 = p->UB16; k.M = p->M;
-        k.Wt = p->Wt; k.VAp = p->VAp; k.d_in_pad = p->d_in_pad; k.n_blocks = p->n_blocks;
+        k.Wt = p->Wt; k.W16 = p->W16; k.US16 = p->US16; k.scale16 = p->scale16; k.VAp = p->VAp; k.d_in_pad = p->d_in_pad; k.n_blocks = p->n_blocks;
         k.St = p->St; k.SZ16 = p->SZ16; k.Gp = p->Gp;
         if (rv) {
             k.rv = rv[i];
@@ -707,17 +736,36 @@ static bool takes_stream(const essa_k::fwd_item& k, int x_dtype, unsigned flags)
            !(k.quant == ESSA_QUANT_INT4_G128 && (flags & ESSA_COMPUTE_W8A8));
 }
 
+// Rows beyond which an int8 item in the default mode takes the exact-product kernel instead of the int8 limbs: where the 64 x 128
+// limb tiles of a layer need a second round on the 256 CUs.  The line depends on the item alone, not on what it is grouped with,
+// so that grouped and single calls agree bit for bit.  us per group of q, k, v, o, limbs / exact: 3584 wide 28 / 49 at 256
+// rows, 47 / 49 at 384, 54 / 49 at 512, 103 / 63 at 1024; 5120 wide 71 / 67 at 256; 8192 wide 92 / 111 at 192, 131 / 117 at 256;
+// 2048 wide 34 / 32 at 512, 41 / 33 at 768; 512 wide 16 / 16 at 512, 21 / 16 at 1024.
+// Fewer than 128 output channels would leave most of that kernel's narrowest tile to padding.
+static bool takes_exact_product(const essa_k::fwd_item& k) {
+    return k.d_out >= 128 && k.R > (k.d_in >= 5120 ? 192 : k.d_in >= 3072 ? 256 : 512);
+}
+
 static essa_status run_items(essa_ctx* ctx, item_list& ks, int x_dtype, int y_dtype, unsigned flags) {
-    // three launch groups: int8 and 4-bit items on the int8-limb kernels (different instantiations of the GEMM), and the
-    // rest on the generic kernels
-    item_list f8, f4, rest;
+    // four launch groups: int8 items on the exact-product kernel, int8 and 4-bit items on the int8-limb kernels (different
+    // instantiations of the GEMM), and the rest on the generic kernels
+    item_list ex, f8, f4, rest;
+    const bool exact_ok = x_dtype == ESSA_BF16 && !(flags & ESSA_COMPUTE_W8A8);
     for (int i = 0; i < ks.n; ++i) {
         const essa_k::fwd_item& k = ks.it[i];
-        if (!takes_stream(k, x_dtype, flags)) rest.push(k);
+        const bool exact_can = exact_ok && essa_k::prefill_takes(k);
+        // (the rank-r term alone, a test hook, has the same bits at every row count: it stays with the limb kernels)
+        if (exact_can && takes_exact_product(k) && !(flags & ESSA_LORA_ONLY)) ex.push(k);
+        else if (!takes_stream(k, x_dtype, flags)) (exact_can ? ex : rest).push(k);
         else (k.quant == ESSA_QUANT_INT8_PERCH ? f8 : f4).push(k);
     }
     const unsigned kflags = flags & ~(ESSA_COMPUTE_BF16 | ESSA_VALIDATE);
     // while profiling, every GEMM launch of the call gets its own pair of events
+    if (ex.n > 0) {
+        hipEvent_t e0, e1;
+        ESSA_TRY(next_events(ctx, &e0, &e1));
+        ESSA_HIP(essa_k::forward_prefill(ctx->stream, ex.it, ex.n, y_dtype, kflags, e0, e1));
+    }
     for (item_list* grp : {&f8, &f4}) {
         if (grp->n == 0) continue;
         for (int i = 0; i < grp->n; ++i) {                  // every set of limbs needs exactly one producer in its launch

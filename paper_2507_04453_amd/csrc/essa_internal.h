@@ -75,6 +75,11 @@ struct essa_proj {
     float* St = nullptr;       // [d_in_pad/128][n_blocks*32] group scales, group major
     uint16_t* SZ16 = nullptr;  // [n_blocks*32][2][Gp] bf16 head and tail of -scale*zero
     int Gp = 0;                // groups rounded up to 16
+    // int8 weights once more as bf16 (exact), for the exact-product kernel: [ceil(d_in/64)][n_blocks][2][2][64 lanes][8],
+    // block (kt, nb), half, sub-step j, lane (kg, l16) = channel 32 nb + 16 half + l16, columns 64 kt + 32 j + 8 kg .. + 7
+    uint16_t* W16 = nullptr;
+    uint16_t* US16 = nullptr;  // [d_out, 2, rp]  bf16 head and tail of U_B / scale16
+    float* scale16 = nullptr;  // [d_out]  the channel scale; 1 where it is zero (W16's channel is then zero)
     std::vector<float> sA, sB; // own singular values, host copies
 };
 
@@ -163,48 +168,55 @@ hipError_t ars_prepare(hipStream_t st, const float* rewards, int N, int b, float
 constexpr int prep_slice_cols(int d_in) { return d_in <= 4096 ? 512 : 1024; }
 constexpr int prep_slices(int d_in) { return (d_in + prep_slice_cols(d_in) - 1) / prep_slice_cols(d_in); }
 
-struct fwd_item {              // one projection of a grouped forward, device pointers only
+// One projection of a grouped forward, device pointers only.  The part that the limb kernels (kernels_stream.hip) fetch from the
+// kernel arguments comes first and is kept small: every cache line of it is time before a workgroup's first load.
+struct stream_item {
     const void* X;
     const int32_t* row2cand;
     const float* sigmaA;
     const float* sigmaB;
     void* Y;
     long long sigma_stride;
-    int R, K;
-    // projection
-    int d_in, d_out, r, rp, quant, groups;
-    const void* Wq;
+    int R, d_in, d_out, r, rp, quant;
+    int d_in_pad, n_blocks;
+    int Gp;
+    int x_owner;               // 1: this item's rows are quantised by the prep kernel (first user of that X)
+    int tslices;               // prep_slices(d_in)
+    int pad_;
     const float* scale;
-    const float* zero;
-    const float* VA32;
-    const uint16_t* VA16;
-    const float* UB32;
     const uint16_t* UB16;
     const float* M;
-    // scratch of this item
-    float* U32;                // [R, rp]  fp32 rank-space vector u_i
-    uint16_t* U16;             // [R, 2, rp]  bf16 head and tail of u_i
-    float* xsum;               // [R, max(groups,1)] group sums of x (int4) / unused
-    int8_t* Xq;                // [R, d_in] (W8A8)
-    float* xscale;             // [R]      (W8A8)
-    // fast path
     const int8_t* Wt;
     const uint16_t* VAp;
-    int d_in_pad, n_blocks;
+    const float* St;
+    const uint16_t* SZ16;
+    uint16_t* U16;             // [R, 2, rp]  bf16 head and tail of u_i
     int8_t* Xh;                // [R rounded up to 256, d_in_pad] high limb (or the single int8 code)
     int8_t* Xl;                // same, low limb
     float* xdelta;             // [R] value of one unit of the fixed-point row
-    int x_owner;               // 1: this item's rows are quantised by the prep kernel (first user of that X)
-    const float* St;
-    const uint16_t* SZ16;
-    int Gp;
     uint16_t* XS16;            // [R][2][Gp] bf16 head and tail of delta_i * (sum of the row's fixed-point activations over a group)
     float* Tpart;              // [R rounded up to 32][rp][8] the K slices' shares of sA_c * (V_A^T x); slots past tslices hold zeros
-    int tslices;               // prep_slices(d_in)
     float* SBrow;              // [R, rp] the row's candidate's sigma_B (gathered by the prep kernel)
     // fused reward (optional)
     const float* rv;           // [d_out] reward vector, or null
     float* rowpart;            // [ceil(d_out / 128)][R] partial <Y, v> over blocks of 128 output channels
+};
+struct fwd_item : stream_item {
+    int K, groups;
+    const void* Wq;
+    const float* zero;
+    const float* VA32;
+    const uint16_t* VA16;
+    const float* UB32;
+    // scratch of the generic kernels
+    float* U32;                // [R, rp]  fp32 rank-space vector u_i
+    float* xsum;               // [R, max(groups,1)] group sums of x (int4) / unused
+    int8_t* Xq;                // [R, d_in] (W8A8)
+    float* xscale;             // [R]      (W8A8)
+    // exact-product kernel
+    const uint16_t* W16;
+    const uint16_t* US16;
+    const float* scale16;
 };
 hipError_t forward_group(hipStream_t st, const fwd_item* items, int n_items, int x_dtype, int y_dtype,
                          unsigned flags, hipEvent_t ev_start, hipEvent_t ev_stop);
@@ -212,6 +224,12 @@ hipError_t w8a8_accumulators(hipStream_t st, const fwd_item& it, int x_dtype, in
 // fast path for int8 weights x bf16 activations (kernels_stream.hip)
 hipError_t forward_stream(hipStream_t st, const fwd_item* items, int n_items, int y_dtype, unsigned flags,
                           hipEvent_t ev_start, hipEvent_t ev_stop);
+// int8 weights x bf16 activations, exact bf16 products (kernels_prefill.hip): whether it can take an item, and the launches
+bool prefill_takes(const fwd_item& it);
+hipError_t forward_prefill(hipStream_t st, const fwd_item* items, int n_items, int y_dtype, unsigned flags, hipEvent_t ev_start,
+                           hipEvent_t ev_stop);
+// Wt (int8 operand tiles) -> W16; channels of scale 0 become zero
+hipError_t expand_weights(hipStream_t st, const int8_t* Wt, const float* scale, int dout, int n_blocks, int nk, uint16_t* W16);
 hipError_t w8a8_accumulators_stream(hipStream_t st, const fwd_item& it, int32_t* acc_out);
 // rowpart[b][i] = <Y_g[i, 128 b ..], v_g[128 b ..]> for the items that carry a reward vector (any forward path)
 hipError_t rowdot_blocks(hipStream_t st, const fwd_item* items, int n_items, int y_dtype);

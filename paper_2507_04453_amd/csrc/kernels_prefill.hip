@@ -1,0 +1,617 @@
+// Forward for int8 base weights and bf16 activations at prompt-sized row counts: exact bf16 products on the bf16 MFMA.
+//
+// An int8 weight is exact in bf16, so W_deq x_i = s_o <q_o, x_i> needs no quantised activations at all when the products run
+// on the bf16 MFMA with fp32 accumulation.  One bf16 pass costs the matrix cores what the two int8 passes of the
+// fixed-point limbs cost, and everything around the product gets cheaper: no pass that re-expresses the rows, one
+// accumulator per output instead of two (which is what lets a wave own a 128 x 128 patch), and x is read as it is.
+// The projection keeps a bf16 copy of its weights in MFMA-operand tiles for this.
+//
+// Three launches: rank_down (t = V_A^T x, K split over workgroups), rank_finish (u = sB_c * (M (sA_c * t)) as bf16 head and
+// tail), gemm_bf16 (base product, scale, U_B u, output tile, reward partials).
+#include "forward_device.h"
+#include <hip/hip_ext.h>
+#include <algorithm>
+#include <utility>
+
+namespace {
+
+struct prefill_item {                      // the fields of one projection that these kernels use
+    const uint16_t *X, *W16, *US16, *VAp;
+    const float *scale16, *M, *sigmaA, *sigmaB, *rv;
+    const int32_t* row2cand;
+    void* Y;
+    uint16_t* U16;
+    float *Tpart, *rowpart;
+    long long sigma_stride;
+    int R, d_in, d_out, r, rp, n_blocks;
+};
+
+struct prefill_args {
+    prefill_item it[ESSA_MAX_GROUP];
+    int tile_start[ESSA_MAX_GROUP + 1];    // workgroups per item (prefix sums)
+    int n_items;
+    unsigned flags;
+    int ksplit[ESSA_MAX_GROUP];            // rank_down: the item's K is cut in this many parts (at most 8)
+};
+
+// ---- loads that go from memory into LDS without passing through registers ------------------------------------------
+// A wave instruction moves 64 x 16 bytes: lane i's 16 bytes land at lds + 16 i, so the order in LDS is fixed and any
+// permutation is made by the lanes' global addresses.  Written as one asm block because the compiler, which cannot tell
+// the LDS stages apart, would otherwise wait for every such load in front of every LDS read; the waits are placed by hand.
+typedef __attribute__((address_space(3))) unsigned char lds_byte;
+__device__ __forceinline__ void load_lds16(uint32_t lds, uint32_t lane_off, i32x4 rsrc, uint32_t scalar_off) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 :: "s"(lds), "v"(lane_off), "s"(rsrc), "s"(scalar_off) : "memory", "m0");
+}
+__device__ __forceinline__ i32x4 buffer_words(const void* base) {
+    const uint64_t p = reinterpret_cast<uint64_t>(base);
+    i32x4 r;
+    r[0] = __builtin_amdgcn_readfirstlane((int)(uint32_t)p);
+    r[1] = __builtin_amdgcn_readfirstlane((int)(uint32_t)(p >> 32)) & 0xffff;
+    r[2] = 0x7fffffff;
+    r[3] = 0x00020000;
+    return r;
+}
+template <int N> __device__ __forceinline__ void wait_loads_and_meet() {
+    // all but the last N loads of this wave have landed, this wave's LDS reads are done, and so are everybody else's
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(N) : "memory");
+}
+
+// f(0), f(1), ... f(N - 1) with the index as a compile-time constant: the K loops are one straight-line schedule
+template <class F, int... I>
+__device__ __forceinline__ void static_for_seq(F&& f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
+template <int N, class F>
+__device__ __forceinline__ void static_for(F&& f) { static_for_seq(f, std::make_integer_sequence<int, N>{}); }
+
+// Workgroups go round-robin over the 8 XCDs: XCD x takes a contiguous range of the T tiles.
+__device__ __forceinline__ int xcd_contiguous(int b, int T) {
+    const int x = b & 7, q = T >> 3, rem = T & 7;
+    return x * q + min(x, rem) + (b >> 3);
+}
+
+// ------------------------------------------------------------------------------------------------
+// t = V_A^T x: one workgroup per item, 128 rows and K part; each of its 4 waves owns 32 rows for all columns.  x tiles
+// (128 bytes of each row per step, the 16-byte parts of row r at part ^ ((r >> 1) & 7)) and the operand tiles of V_A
+// (bf16 head and tail) go through LDS, three steps deep.
+// ------------------------------------------------------------------------------------------------
+constexpr int RD_ROWS = 128;
+
+template <int RP>
+__global__ __launch_bounds__(256, 2) void rank_down_kernel(prefill_args a) {
+    constexpr int NBV = RP / 16;                           // 32-column blocks of [heads | tails]
+    constexpr int XST = RD_ROWS * 128, VST = 4 * NBV * 1024, ST = XST + VST;
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[3 * ST];
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_byte*)smem;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, h = lane >> 5;
+    int g = 0;
+#pragma unroll
+    for (int i = 1; i < ESSA_MAX_GROUP; ++i) g += (i < a.n_items && (int)blockIdx.x >= a.tile_start[i]) ? 1 : 0;
+    const prefill_item it = fetch_item(a.it[g]);
+    if (it.rp != RP) return;
+    const int ksplit = a.ksplit[g], rel = blockIdx.x - a.tile_start[g], part = rel % ksplit;
+    const int m0 = (rel / ksplit) * RD_ROWS;
+    const int R = it.R, din = it.d_in;
+    const int nk_all = (din + 63) / 64;
+    const int k_lo = (int)((long long)nk_all * part / ksplit), k_hi = (int)((long long)nk_all * (part + 1) / ksplit);
+    const int ksteps = din / 16;
+
+    const i32x4 xres = buffer_words(it.X + (size_t)m0 * din);
+    const i32x4 vres = buffer_words(it.VAp);
+    uint32_t xoff[4];
+    int xpart[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int row = wave * 32 + e * 8 + (lane >> 3);
+        xpart[e] = (lane & 7) ^ ((row >> 1) & 7);
+        xoff[e] = (uint32_t)min(row, R - 1 - m0) * (uint32_t)(din * 2) + xpart[e] * 16;
+    }
+    auto issue = [&](int kt, int stage) {
+        const int k = min(kt, k_hi - 1);
+        const uint32_t sx = lds0 + stage * ST + wave * 4096, sv = lds0 + stage * ST + XST;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            // columns past the row read the row's last 16 bytes instead: V_A's tiles are zeroed there
+            const int over = max(0, k * 64 + xpart[e] * 8 + 8 - din);
+            load_lds16(sx + e * 1024, xoff[e] - over * 2, xres, (uint32_t)k * 128);
+        }
+#pragma unroll
+        for (int e = 0; e < NBV; ++e) {
+            const int q = wave * NBV + e, ks = min(4 * k + q / NBV, ksteps - 1);
+            load_lds16(sv + q * 1024, lane * 16, vres, (uint32_t)((ks * NBV + q % NBV) * 1024));
+        }
+    };
+    f32x16 acc[NBV];
+#pragma unroll
+    for (int b = 0; b < NBV; ++b)
+#pragma unroll
+        for (int q = 0; q < 16; ++q) acc[b][q] = 0.f;
+    if (k_lo < k_hi) {
+        issue(k_lo, 0);
+        issue(k_lo + 1, 1);
+        int st = 0;
+        const uint32_t xrow = wave * 4096 + l32 * 128, sw = (l32 >> 1) & 7;
+        for (int kt = k_lo; kt < k_hi; ++kt) {
+            wait_loads_and_meet<4 + NBV>();
+            issue(kt + 2, st == 0 ? 2 : st - 1);
+            const unsigned char* sx = smem + st * ST;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const bool live = 4 * kt + j < ksteps;      // steps past the row multiply by zeros
+                const bf16x8 xf = *reinterpret_cast<const bf16x8*>(sx + xrow + (((2 * j + h) ^ sw) * 16));
+#pragma unroll
+                for (int b = 0; b < NBV; ++b) {
+                    u32x4 vf = *reinterpret_cast<const u32x4*>(sx + XST + (j * NBV + b) * 1024 + lane * 16);
+                    if (!live) vf = (u32x4){0, 0, 0, 0};
+                    acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf, __builtin_bit_cast(bf16x8, vf), acc[b], 0, 0, 0);
+                }
+            }
+            st = st == 2 ? 0 : st + 1;
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    }
+    const gptr<float> out = as_global_w(it.Tpart) + ((size_t)part * R + m0) * RP;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+        const int row = wave * 32 + 8 * (q >> 2) + 4 * h + (q & 3);
+        float t;
+        if (RP == 32) t = acc[0][q] + acc[NBV - 1][q];
+        else t = acc[0][q] + __shfl_xor(acc[0][q], 16, 64);   // columns j and 16 + j: head and tail of V_A's column j
+        if (m0 + row < R && l32 < RP) out[(size_t)row * RP + l32] = t;
+    }
+}
+
+// u = sB_c * (M (sA_c * t)), the K parts of t added in ascending order; bf16 head and tail per row.  Latency and a few
+// bytes per row: one thread per element.
+template <int RP>
+__global__ __launch_bounds__(256) void rank_finish_kernel(prefill_args a) {
+    constexpr int ROWS = 256 / RP, P = RP + 4;
+    __shared__ float tv[ROWS][P], Ms[RP][P];
+    const prefill_item& it = a.it[blockIdx.y];
+    if (it.rp != RP) return;
+    const int tid = threadIdx.x, lr = tid / RP, j = tid % RP;
+    const int R = it.R, i = blockIdx.x * ROWS + lr, ic = min(i, R - 1);
+    if (blockIdx.x * ROWS >= R) return;
+    const int c = as_global(it.row2cand)[ic];
+    const gptr<const float> tp = as_global(it.Tpart);
+    float t = tp[(size_t)ic * RP + j];
+    for (int s = 1; s < a.ksplit[blockIdx.y]; ++s) t += tp[((size_t)s * R + ic) * RP + j];
+    const size_t at = (size_t)c * it.sigma_stride + min(j, it.r - 1);
+    const float sa = as_global(it.sigmaA)[at], sb = as_global(it.sigmaB)[at];
+    for (int e = tid; e < RP * RP; e += 256) Ms[e / RP][e % RP] = as_global(it.M)[e];
+    tv[lr][j] = (j < it.r ? sa : 0.f) * t;
+    __syncthreads();
+    float u = 0.f;
+    if (!(a.flags & ESSA_BASE_ONLY)) {
+#pragma unroll
+        for (int l = 0; l < RP; ++l) u = fmaf(Ms[j][l], tv[lr][l], u);
+        u *= j < it.r ? sb : 0.f;
+    }
+    if (i < R) {
+        const uint16_t hi = f32_to_bf16_bits(u);
+        const gptr<uint16_t> ur = as_global_w(it.U16) + (size_t)i * 2 * RP;
+        ur[j] = hi;
+        ur[RP + j] = f32_to_bf16_bits(u - bf16_bits_to_f32(hi));
+    }
+}
+
+// ------------------------------------------------------------------------------------------------
+// Base product on the bf16 MFMA.  256 threads = 4 waves in a 2 x 2 grid, tile = 64 MB rows x 64 NB channels, a wave owns a
+// patch of 32 MB rows x 32 NB channels (128 x 128 at MB = NB = 4: 256 accumulator registers, one wave per SIMD).  The weights
+// are the MFMA's row operand and the activations its column operand, so a lane's accumulators run along the channels and
+// the output tile is written 8 or 16 bytes at a time.
+//
+// K advances in steps of 64, two sub-steps of 32.  Both operands go memory -> LDS directly; weights keep their operand tiles
+// (1 KB per 16 channels x 32 columns, read back contiguously), an activation row is 128 bytes with its 16-byte parts swizzled.
+// XS activation and WS weight stages; one step (kt):
+//   sub-step 0: MFMAs; fragments of sub-step 1; the activations of step kt + XS - 1
+//   meet: step kt + 1 is complete in LDS, nobody reads step kt any more
+//   sub-step 1: MFMAs; fragments of sub-step 0 of step kt + 1; the weights of step kt + WS
+// with the reads and loads spread between the MFMAs.  The 16 x 16 x 32 form of the MFMA, not 32 x 32 x 16: same rate on
+// paper, but the chip runs these kernels at its power limit and the smaller form does more per watt (MFMAs alone, operands
+// in registers, all CUs: 2026 against 1714 TFLOP/s; this kernel on 32768 x 5120 x 12288: 3.13 against 3.39 ms).
+//
+// Measured (256 x 256 tile, 32768 rows, 5120 -> 12288, one MI355X): 3.13 ms with its rank kernels, 1.32 PFLOP/s; the int8-limb
+// tile it replaces took 3.99 + 0.65 ms.  A tile of K = 3584 spends 70 us in its loop (135.8 k cycles at 1.94 GHz, 114.7 k of
+// them MFMA; the direct-to-LDS loads block the wave's issue for about 15 cycles each), 2 us before and 7 us after it.
+// ------------------------------------------------------------------------------------------------
+thread_local hipEvent_t tl_pre_start = nullptr, tl_pre_stop = nullptr;   // events of the GEMM launch being timed
+
+template <int MB, int NB, int XS, int WS>
+constexpr size_t bf16_smem_bytes(bool ybf16) {
+    constexpr size_t BM = 64 * MB, BN = 64 * NB;
+    const size_t stages = XS * BM * 128 + WS * BN * 128;
+    const size_t ctile = ybf16 ? BM * (BN * 2 + 16) : BM * (BN / 2 * 4 + 16);
+    return stages > ctile ? stages : ctile;
+}
+
+// acc += A B with the accumulator pinned to the accumulation registers.  Left to choose, the register allocator moves some of
+// a 128 x 128 patch's accumulators to and fro inside the loop (48 moves per step: 145 k cycles for a 56-step loop, 135 k
+// without; the smaller patches likewise), so the instruction is written out.
+__device__ __forceinline__ void mfma_pinned(const bf16x8& A, const bf16x8& B, f32x4& acc) {
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(A), "v"(B));
+}
+
+template <int MB, int NB, int XS, int WS, bool YBF16>
+__global__ __launch_bounds__(256, (bf16_smem_bytes<MB, NB, XS, WS>(true) > 80 * 1024 ? 1 : 2)) void gemm_bf16_kernel(prefill_args a) {
+    constexpr int BM = 64 * MB, BN = 64 * NB, NBT = BN / 32;
+    constexpr uint32_t XST = BM * 128, WST = BN * 128, W0 = XS * XST;
+    constexpr int NR = 2 * MB, NC = 2 * NB;                // 16-row and 16-channel blocks of a wave
+    constexpr int NMF = NR * NC, NRD = NR + NC, XL = 2 * MB, WL = 2 * NB;     // per wave: MFMAs and fragment reads of a sub-step, loads of a step
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_byte*)smem;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wr = wave >> 1, wc = wave & 1, l16 = lane & 15, kg = lane >> 4;
+
+    const int b = xcd_contiguous(blockIdx.x, a.tile_start[ESSA_MAX_GROUP]);
+    int g = 0;
+#pragma unroll
+    for (int i = 1; i < ESSA_MAX_GROUP; ++i) g += (i < a.n_items && b >= a.tile_start[i]) ? 1 : 0;
+    const prefill_item it = fetch_item(a.it[g]);
+    const int R = it.R, dout = it.d_out, din = it.d_in, rp = it.rp;
+    const int tiles_m = (R + BM - 1) / BM, tiles_n = (it.n_blocks + NBT - 1) / NBT;
+    int tm, tn;
+    {   // patches of 4 row tiles x all column tiles, rows fastest: the 32 tiles an XCD runs at a time are about 4 x 8
+        const int tile = b - a.tile_start[g], per = 4 * tiles_n, grp = tile / per, rem = tile % per;
+        const int rows = min(4, tiles_m - 4 * grp);
+        tn = rem / rows;
+        tm = 4 * grp + rem % rows;
+    }
+    const int m0 = tm * BM, nb0 = tn * NBT;
+    const int nk = (din + 63) / 64;
+
+    const i32x4 xres = buffer_words(it.X + (size_t)m0 * din);
+    const i32x4 wres = buffer_words(it.W16);
+    uint32_t xoff[XL];
+#pragma unroll
+    for (int e = 0; e < XL; ++e) {
+        const int row = (wave * XL + e) * 8 + (lane >> 3);
+        xoff[e] = (uint32_t)min(row, R - 1 - m0) * (uint32_t)(din * 2) + (((lane & 7) ^ ((row >> 1) & 7)) * 16);
+    }
+    // in the last step of a row that is not a multiple of 64 wide, lanes past its end read its last 16 bytes (the weights
+    // are zero there); even and odd loads of a wave differ in their swizzle
+    uint32_t back[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        const int part = (lane & 7) ^ ((((wave * XL + e) * 8 + (lane >> 3)) >> 1) & 7);
+        back[e] = (uint32_t)max(0, (nk - 1) * 64 + part * 8 + 8 - din) * 2u;
+    }
+    uint32_t wsoff[WL];                                    // scalar: where load e's kilobyte starts inside a K step
+#pragma unroll
+    for (int e = 0; e < WL; ++e) {
+        const int q = wave * WL + e;
+        wsoff[e] = (uint32_t)(min(nb0 + (q >> 2), it.n_blocks - 1) * 4 + (q & 3)) * 1024u;
+    }
+    const uint32_t wstep = (uint32_t)it.n_blocks * 4096u, lane16 = lane * 16;
+    auto load_x = [&](int e, int kt, uint32_t stage) {
+        const int k = min(kt, nk - 1);
+        const uint32_t off = xoff[e] - (back[e & 1] & (uint32_t)(k < nk - 1 ? 0 : -1));
+        load_lds16(lds0 + stage + (wave * XL + e) * 1024, off, xres, (uint32_t)k * 128u);
+    };
+    auto load_w = [&](int e, int kt, uint32_t stage) {
+        load_lds16(lds0 + stage + (wave * WL + e) * 1024, lane16, wres, (uint32_t)min(kt, nk - 1) * wstep + wsoff[e]);
+    };
+
+    f32x4 acc[NC][NR];
+#pragma unroll
+    for (int n = 0; n < NC; ++n)
+#pragma unroll
+        for (int m = 0; m < NR; ++m) acc[n][m] = (f32x4){0.f, 0.f, 0.f, 0.f};
+
+    // the steps the loop finds on their way, in the order its own iterations would have asked for them
+    static_for<(XS > WS ? XS : WS)>([&](auto tc) {
+        constexpr int t = decltype(tc)::value - (XS > WS ? XS : WS), x = t + XS - 1, w = t + WS;
+        if constexpr (x >= 0) {
+#pragma unroll
+            for (int e = 0; e < XL; ++e) load_x(e, x, x * XST);
+        }
+        if constexpr (w >= 0) {
+#pragma unroll
+            for (int e = 0; e < WL; ++e) load_w(e, w, W0 + w * WST);
+        }
+    });
+    // loads still on their way when step 0 has to be there, and when step kt + 1 has to be there in the middle of step kt
+    constexpr int FIRST = (XS > WS ? (WS - 1) * XL + (WS - 1) * WL : (XS - 2) * XL + (XS - 1) * WL);
+    constexpr int AHEAD_X = (XS - 2) * (XL + WL), AHEAD_W = (WS - 1) * XL + (WS - 2) * WL, AHEAD = AHEAD_X < AHEAD_W ? AHEAD_X : AHEAD_W;
+    static_assert(FIRST < 64 && AHEAD < 64, "the load counter has six bits");
+
+    uint32_t xr[2];                                        // this lane's fragment of sub-step j inside an activation stage
+#pragma unroll
+    for (int j = 0; j < 2; ++j) xr[j] = (wr * 32 * MB + l16) * 128 + (((4 * j + kg) ^ ((l16 >> 1) & 7)) * 16);
+    const uint32_t wfr = W0 + wc * NB * 4096 + lane16;
+    bf16x8 fx[2][NR], fw[2][NC];
+    auto read_frag = [&](int set, int i, uint32_t xs, uint32_t ws, int j) {
+        // in the order the MFMAs want them: weights 0, the activations, the other weights
+        if (i == 0 || i > NR) fw[set][i == 0 ? 0 : i - NR] = *reinterpret_cast<const bf16x8*>(smem + ws + wfr + (i == 0 ? 0 : i - NR) * 2048 + j * 1024);
+        else fx[set][i - 1] = *reinterpret_cast<const bf16x8*>(smem + xs + xr[j] + (i - 1) * 2048);
+    };
+    wait_loads_and_meet<FIRST>();
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < NRD; ++i) read_frag(0, i, 0, 0, 0);
+
+    uint32_t x_cur = 0, x_nxt = XST, x_far = (XS - 1) * XST, w_cur = 0, w_nxt = WST;
+    for (int kt = 0; kt < nk; ++kt) {
+        static_for<2>([&](auto jc) {
+            constexpr int j = jc;
+            if constexpr (j == 1) {
+                __builtin_amdgcn_sched_barrier(0);
+                wait_loads_and_meet<AHEAD>();
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            static_for<NMF>([&](auto ic) {
+                constexpr int i = ic;
+                mfma_pinned(fw[j][i / NR], fx[j][i % NR], acc[i / NR][i % NR]);
+                static_for<NRD>([&](auto rc) {
+                    constexpr int r = rc;
+                    if constexpr (r * NMF / NRD == i) read_frag(j ^ 1, r, j == 1 ? x_nxt : x_cur, j == 1 ? w_nxt : w_cur, j ^ 1);
+                });
+                // one load every few MFMAs, never a burst; the weights, which have the shorter way to go, as early as they can
+                if constexpr (j == 1) {
+                    static_for<WL>([&](auto ec) {
+                        constexpr int e = ec;
+                        if constexpr (e * NMF / (2 * WL) + 1 == i) load_w(e, kt + WS, W0 + w_cur);
+                    });
+                } else {
+                    static_for<XL>([&](auto ec) {
+                        constexpr int e = ec;
+                        if constexpr (e * NMF / XL + 1 == i) load_x(e, kt + XS - 1, x_far);
+                    });
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        });
+        x_far = x_cur;                                     // its last reader was this step
+        x_cur = x_nxt;
+        x_nxt = x_nxt == (XS - 1) * XST ? 0 : x_nxt + XST;
+        w_cur = w_nxt;
+        w_nxt = w_nxt == (WS - 1) * WST ? 0 : w_nxt + WST;
+    }
+    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");   // the pinned MFMAs' results are not tracked by the compiler
+    // ---- epilogue: rank-r term, scale, LDS tile, rows out.  Y = s_o (<q_o, x> + (U_B / s_o) u): with U_B divided by the channel
+    // scale beforehand the rank-r term (bf16 head+tail: lo*hi + hi*lo + hi*hi per 16 rank columns) is three more MFMAs on the
+    // accumulators where they are, and one multiplication per output is all the vector ALU has to do.
+    // What it reads from memory is asked for in one batch; rank 16 and 32 are separate straight-line code, so that the
+    // blocks' MFMA chains, conversions and LDS writes overlap.
+    constexpr int ESZ = YBF16 ? 2 : 4, EPV = 16 / ESZ, HALVES = YBF16 ? 1 : 2, CW = BN / HALVES;
+    constexpr int CROW = CW * ESZ + 16, PPR = CW / EPV, NH = NC / HALVES;   // a half holds blocks NH half .. of both wave columns
+    const bool with_reward = it.rv != nullptr;
+    const bool vec_ok = (dout % EPV == 0) && ((reinterpret_cast<uintptr_t>(it.Y) & 15) == 0);
+    const gptr<unsigned char> Yb = as_global_w(reinterpret_cast<unsigned char*>(it.Y));
+    auto to_tile = [&](int n, int m, const f32x4& v) {
+        unsigned char* dst = smem + (size_t)((wr * NR + m) * 16 + l16) * CROW + (size_t)((wc * NH + n % NH) * 16 + 4 * kg) * ESZ;
+        if (YBF16) {
+            typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+            *reinterpret_cast<bf16x4*>(dst) = __builtin_convertvector(v, bf16x4);
+        } else {
+            *reinterpret_cast<f32x4*>(dst) = v;
+        }
+    };
+    // the rank columns as the K of 16 x 16 x 32 products: at rank 16 head and tail of U_B sit side by side in one fragment
+    // and meet the head of u, then its tail; at rank 32 each is a fragment of its own and lo*lo is left out
+    auto finish = [&](auto ks_count, auto half_index) {
+        constexpr int KS = decltype(ks_count)::value, N0 = decltype(half_index)::value * NH;
+        bf16x8 uu[NR][2], ub[2][KS];                       // head and tail of u; U_B and scales one block ahead
+        f32x4 sc[2];
+        auto ask = [&](int n) {
+            const int o = min((nb0 + wc * NB) * 32 + n * 16 + l16, dout - 1);
+            const gptr<const uint16_t> bp = as_global(it.US16) + (size_t)o * (32 * KS) + 8 * kg;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) ub[n & 1][ks] = *reinterpret_cast<gptr<const bf16x8>>(bp + 32 * ks);
+            // the slack behind the array covers a last block that is not full
+            sc[n & 1] = *as_global(reinterpret_cast<const f32x4*>(it.scale16 + min((nb0 + wc * NB) * 32 + n * 16, it.n_blocks * 32 - 16) + 4 * kg));
+        };
+#pragma unroll
+        for (int m = 0; m < NR; ++m) {
+            const gptr<const uint16_t> up = as_global(it.U16) + (size_t)min(m0 + (wr * NR + m) * 16 + l16, R - 1) * (32 * KS) + 8 * (KS == 1 ? kg & 1 : kg);
+#pragma unroll
+            for (int e = 0; e < 2; ++e) uu[m][e] = *reinterpret_cast<gptr<const bf16x8>>(up + e * 16 * KS);
+        }
+        ask(N0);
+        if (a.flags & ESSA_BASE_ONLY) {
+#pragma unroll
+            for (int m = 0; m < NR; ++m) uu[m][0] = uu[m][1] = __builtin_bit_cast(bf16x8, (u32x4){0, 0, 0, 0});
+        }
+        if constexpr (N0 == 0) wait_loads_and_meet<0>();   // the stages become the output tile
+#pragma unroll
+        for (int n = N0; n < N0 + NH; ++n) {
+            __builtin_amdgcn_sched_barrier(0);
+            if (n + 1 < N0 + NH) ask(n + 1);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int m = 0; m < NR; ++m) {
+                acc[n][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ub[n & 1][0], uu[m][1], acc[n][m], 0, 0, 0);
+                if (KS == 2) acc[n][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ub[n & 1][KS - 1], uu[m][0], acc[n][m], 0, 0, 0);
+                acc[n][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ub[n & 1][0], uu[m][0], acc[n][m], 0, 0, 0);
+            }
+#pragma unroll
+            for (int m = 0; m < NR; ++m) to_tile(n, m, acc[n][m] * sc[n & 1]);
+        }
+    };
+    if (a.flags & ESSA_LORA_ONLY) {
+#pragma unroll
+        for (int n = 0; n < NC; ++n)
+#pragma unroll
+            for (int m = 0; m < NR; ++m) acc[n][m] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    }
+    static_for<HALVES>([&](auto half_c) {
+        constexpr int half = half_c;
+        if (rp == 16) finish(std::integral_constant<int, 1>{}, half_c);
+        else finish(std::integral_constant<int, 2>{}, half_c);
+        __syncthreads();
+        // full rows, 16 bytes per thread; with a reward vector the row's share over each 128-channel block goes to rowpart
+        const int piece = tid % PPR, c0 = piece * EPV;
+        const int o = nb0 * 32 + (c0 / (NH * 16)) * (NC * 16) + half * NH * 16 + c0 % (NH * 16);
+        float rvp[EPV];
+#pragma unroll
+        for (int e = 0; e < EPV; ++e) rvp[e] = (with_reward && o + e < dout) ? as_global(it.rv)[o + e] : 0.f;
+        static_assert(256 % PPR == 0 && (BM * PPR) % 256 == 0, "a thread keeps its piece from row to row");
+#pragma unroll 8
+        for (int p0 = 0; p0 < BM * PPR; p0 += 256) {
+            const int row = (p0 + tid) / PPR, i = m0 + row;
+            const bool valid = i < R && o < dout;
+            const u32x4 val = *reinterpret_cast<const u32x4*>(smem + (size_t)row * CROW + piece * 16);
+            if (valid) {
+                if (vec_ok && o + EPV <= dout) {
+                    __builtin_nontemporal_store(val, reinterpret_cast<gptr<u32x4>>(Yb + ((size_t)i * dout + o) * ESZ));
+                } else {
+                    for (int e = 0; e < EPV && o + e < dout; ++e) {
+                        if (YBF16) reinterpret_cast<gptr<uint16_t>>(Yb)[(size_t)i * dout + o + e] = (uint16_t)(val[e >> 1] >> (16 * (e & 1)));
+                        else reinterpret_cast<gptr<uint32_t>>(Yb)[(size_t)i * dout + o + e] = val[e];
+                    }
+                }
+            }
+            if (with_reward) {
+                constexpr int LPB = 128 / HALVES / EPV;    // lanes per 128-channel block
+                float s = 0.f;
+                if (valid) {
+#pragma unroll
+                    for (int e = 0; e < EPV; ++e) {
+                        const float y = YBF16 ? __uint_as_float((e & 1) ? (val[e >> 1] & 0xffff0000u) : (val[e >> 1] << 16)) : __uint_as_float(val[e]);
+                        s = fmaf(o + e < dout ? y : 0.f, rvp[e], s);
+                    }
+                }
+#pragma unroll
+                for (int off = LPB / 2; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+                if (piece % LPB == 0 && valid) {
+                    const gptr<float> dst = as_global_w(it.rowpart) + (size_t)(o >> 7) * R + i;
+                    *dst = half == 0 ? s : *dst + s;       // the second half of the block's channels: this thread wrote the first
+                }
+            }
+        }
+        if constexpr (half + 1 < HALVES) __syncthreads();
+    });
+}
+
+template <int MB, int NB, int XS, int WS, bool YBF16>
+hipError_t launch_bf16(hipStream_t st, prefill_args& a) {
+    int total = 0;
+    for (int g = 0; g < a.n_items; ++g) {
+        a.tile_start[g] = total;
+        total += ((a.it[g].R + 64 * MB - 1) / (64 * MB)) * ((a.it[g].n_blocks + 2 * NB - 1) / (2 * NB));
+    }
+    for (int g = a.n_items; g <= ESSA_MAX_GROUP; ++g) a.tile_start[g] = total;
+    constexpr size_t smem = bf16_smem_bytes<MB, NB, XS, WS>(YBF16);
+    static_assert(smem <= 160 * 1024, "tile does not fit the LDS of a CU");
+    auto kern = gemm_bf16_kernel<MB, NB, XS, WS, YBF16>;
+    static bool attr_done = false;   // one flag per instantiation
+    if (!attr_done) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+        if (e != hipSuccess) return e;
+        attr_done = true;
+    }
+    if (tl_pre_start) hipExtLaunchKernelGGL(kern, dim3(total), dim3(256), (uint32_t)smem, st, tl_pre_start, tl_pre_stop, 0, a);
+    else hipLaunchKernelGGL(kern, dim3(total), dim3(256), smem, st, a);
+    return hipGetLastError();
+}
+
+// Which tile takes a group.  Tiles go to the 256 CUs in rounds, so the time is (rounds) x (K steps) x (time of a step), plus
+// what does not depend on K.  Microseconds as measured on groups of four projections, 2048 to 8192 wide, 72 to 32768 rows,
+// with weights coming from HBM (a few per cent to a tenth off everywhere in that range):
+//   256 x 256  18 + steps x rounds x (1.12 .. 1.47 as the last round fills: the clock falls)   82 us at 1024 x 3584
+//   256 x 128  13 + steps x rounds x 0.85                                                       59 us at  512 x 3584
+//   128 x 128  11.5 + steps x 0.53 x (tiles per CU), two workgroups per CU                      75 us at 1024 x 3584
+//   128 x 128 with five LDS stages, one workgroup per CU: 11.5 + steps x 0.7, one round only    49 us at  512 x 3584
+enum bf16_tile { TILE_256x256, TILE_256x128, TILE_128x128, TILE_128x128_DEEP };
+bf16_tile pick_tile(const prefill_item* items, int n_items) {
+    auto tiles = [&](int bm, int bn) {
+        long long t = 0;
+        for (int g = 0; g < n_items; ++g) t += (long long)((items[g].R + bm - 1) / bm) * ((items[g].n_blocks * 32 + bn - 1) / bn);
+        return t;
+    };
+    int nk = 1;
+    for (int g = 0; g < n_items; ++g) nk = std::max(nk, (items[g].d_in + 63) / 64);
+    auto rounds = [](long long t) { return (double)((t + 255) / 256); };
+    const long long t44 = tiles(256, 256), t42 = tiles(256, 128), t22 = tiles(128, 128);
+    const double fill = (double)t44 / (256.0 * rounds(t44));
+    const double c[4] = {18.0 + nk * rounds(t44) * (1.12 + 0.35 * fill), 13.0 + nk * rounds(t42) * 0.85, 11.5 + nk * rounds(t22) * 0.53,
+                         t22 <= 256 ? 11.5 + nk * 0.7 : 1e30};
+    int best = 0;
+    for (int i = 1; i < 4; ++i)
+        if (c[i] < c[best]) best = i;
+    return (bf16_tile)best;
+}
+
+// the rank-space vectors of every row
+hipError_t launch_rank(hipStream_t st, prefill_args& a) {
+    int total = 0, maxR = 0;
+    bool has16 = false, has32 = false;
+    for (int g = 0; g < a.n_items; ++g) {
+        // K parts: enough workgroups for two per CU in a group of four projections, no part shorter than four steps; by the
+        // item's own size only, so that an item's sums do not depend on what it is grouped with
+        const int blocks = (a.it[g].R + RD_ROWS - 1) / RD_ROWS, nk = (a.it[g].d_in + 63) / 64;
+        a.ksplit[g] = std::max(1, std::min({8, nk / 4, (128 + blocks - 1) / blocks}));
+        a.tile_start[g] = total;
+        total += blocks * a.ksplit[g];
+        maxR = std::max(maxR, a.it[g].R);
+        (a.it[g].rp == 16 ? has16 : has32) = true;
+    }
+    for (int g = a.n_items; g <= ESSA_MAX_GROUP; ++g) a.tile_start[g] = total;
+    if (has16) hipLaunchKernelGGL(rank_down_kernel<16>, dim3(total), dim3(256), 0, st, a);
+    if (has32) hipLaunchKernelGGL(rank_down_kernel<32>, dim3(total), dim3(256), 0, st, a);
+    if (has16) hipLaunchKernelGGL(rank_finish_kernel<16>, dim3((maxR + 15) / 16, a.n_items), dim3(256), 0, st, a);
+    if (has32) hipLaunchKernelGGL(rank_finish_kernel<32>, dim3((maxR + 7) / 8, a.n_items), dim3(256), 0, st, a);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+namespace essa_k {
+
+__global__ __launch_bounds__(256) void expand_weights_kernel(const int8_t* __restrict__ Wt, const float* __restrict__ scale, int dout, int n_blocks,
+                                                             long long pieces, uint16_t* __restrict__ W16) {
+    for (long long p = (long long)blockIdx.x * 256 + threadIdx.x; p < pieces; p += (long long)gridDim.x * 256) {
+        const int lane = (int)(p & 63), j = (int)(p >> 6) & 1, half = (int)(p >> 7) & 1, kg = lane >> 4, l = 16 * half + (lane & 15);
+        const long long blk = p >> 8, kt = blk / n_blocks, nb = blk % n_blocks;
+        // columns 64 kt + 32 j + 8 kg .. + 7 of channel 32 nb + l
+        const int8_t* src = Wt + ((2 * kt + j) * n_blocks + nb) * 1024 + ((kg >> 1) * 32 + l) * 16 + 8 * (kg & 1);
+        const int o = (int)nb * 32 + l;
+        const bool live = o < dout && scale[o] != 0.f;     // a channel of scale 0 contributes nothing
+        uint16_t v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = live ? f32_to_bf16_bits((float)src[e]) : 0;
+        __builtin_memcpy(W16 + p * 8, v, 16);
+    }
+}
+
+hipError_t expand_weights(hipStream_t st, const int8_t* Wt, const float* scale, int dout, int n_blocks, int nk, uint16_t* W16) {
+    const long long pieces = (long long)nk * n_blocks * 256;
+    hipLaunchKernelGGL(expand_weights_kernel, dim3((unsigned)std::min<long long>((pieces + 255) / 256, 4096)), dim3(256), 0, st, Wt, scale, dout, n_blocks, pieces, W16);
+    return hipGetLastError();
+}
+
+bool prefill_takes(const fwd_item& it) {
+    return it.quant == ESSA_QUANT_INT8_PERCH && it.W16 && it.d_in % 16 == 0 && ((uintptr_t)it.X & 15) == 0;
+}
+
+hipError_t forward_prefill(hipStream_t st, const fwd_item* items, int n_items, int y_dtype, unsigned flags, hipEvent_t ev_start,
+                           hipEvent_t ev_stop) {
+    prefill_args a{};
+    for (int g = 0; g < n_items; ++g) {
+        const fwd_item& k = items[g];
+        a.it[g] = prefill_item{(const uint16_t*)k.X, k.W16, k.US16, k.VAp, k.scale16, k.M, k.sigmaA, k.sigmaB, k.rv, k.row2cand, k.Y,
+                               k.U16, k.Tpart, k.rowpart, k.sigma_stride, k.R, k.d_in, k.d_out, k.r, k.rp, k.n_blocks};
+    }
+    a.n_items = n_items;
+    a.flags = flags;
+    if (!(flags & ESSA_BASE_ONLY)) {
+        hipError_t e = launch_rank(st, a);
+        if (e != hipSuccess) return e;
+    }
+    tl_pre_start = ev_start;
+    tl_pre_stop = ev_stop;
+    const bool yb = y_dtype == ESSA_BF16;
+    hipError_t e;
+    switch (pick_tile(a.it, n_items)) {
+        case TILE_256x256: e = yb ? launch_bf16<4, 4, 3, 2, true>(st, a) : launch_bf16<4, 4, 3, 2, false>(st, a); break;
+        case TILE_256x128: e = yb ? launch_bf16<4, 2, 3, 4, true>(st, a) : launch_bf16<4, 2, 3, 4, false>(st, a); break;
+        case TILE_128x128: e = yb ? launch_bf16<2, 2, 3, 2, true>(st, a) : launch_bf16<2, 2, 3, 2, false>(st, a); break;
+        default: e = yb ? launch_bf16<2, 2, 5, 5, true>(st, a) : launch_bf16<2, 2, 5, 5, false>(st, a); break;
+    }
+    tl_pre_start = tl_pre_stop = nullptr;
+    return e;
+}
+
+}  // namespace essa_k

@@ -10,15 +10,8 @@
 // contiguous per load instruction, k-chunk major), while the activation limbs of all the rows of the tile are staged
 // through LDS and shared by the four waves.  With one limb (ESSA_COMPUTE_W8A8) the same kernel is the
 // plain W8A8 mode.  The rank-r term is added by bf16 head+tail MFMA steps in the epilogue.
-#include "essa_internal.h"
+#include "forward_device.h"
 #include <hip/hip_ext.h>
-
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((ext_vector_type(4))) float f32x4;
-typedef __attribute__((ext_vector_type(4))) int i32x4;
-typedef __attribute__((ext_vector_type(16))) int i32x16;
-typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 
 // Phase stamps of wave 0 of every workgroup (shader-clock and 100 MHz counters), read back by a test harness: compiled in
 // only with -DESSA_DEBUG_STAMPS, never in the shipped library.
@@ -40,10 +33,8 @@ extern "C" void essa_dbg_prep_read(unsigned long long* out) { (void)hipMemcpyFro
 
 namespace {
 
-using essa_k::fwd_item;
-
 struct stream_args {
-    fwd_item it[ESSA_MAX_GROUP];
+    stream_item it[ESSA_MAX_GROUP];
     int tile_start[ESSA_MAX_GROUP + 1];    // GEMM tiles per item (prefix sums)
     int quant_start[ESSA_MAX_GROUP + 1];   // prep kernel: rows to quantise per item (0 for items sharing an X)
     int lora_start[ESSA_MAX_GROUP + 1];    // prep kernel: 32-row blocks per item
@@ -68,53 +59,6 @@ struct stream_args {
     // (one contiguous kilobyte per wave load), for the kernel that streams them straight into registers
     int limb_tiled;
 };
-
-__device__ __forceinline__ float bf16_bits_to_f32(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
-__device__ __forceinline__ uint16_t f32_to_bf16_bits(float f) {
-    // round to nearest even in one instruction (v_cvt_pk_bf16_f32)
-    return __builtin_bit_cast(uint16_t, (__bf16)f);
-}
-
-// The descriptor of one item, fetched from the kernel arguments in one batch of scalar loads: left to itself the
-// compiler loads every field where it is first used, and each of those loads is a separate wait on the way to the
-// first tile.
-__device__ __forceinline__ fwd_item fetch_item(const fwd_item& src) {
-    constexpr int NW = sizeof(fwd_item) / 4;
-    static_assert(sizeof(fwd_item) % 4 == 0, "descriptor is a whole number of words");
-    int raw[NW];
-    const int* p = reinterpret_cast<const int*>(&src);
-#pragma unroll
-    for (int i = 0; i < NW; ++i) raw[i] = p[i];
-#pragma unroll
-    for (int i = 0; i < NW; ++i) asm volatile("" : "+s"(raw[i]));      // all words are in scalar registers from here on
-    fwd_item it;
-    __builtin_memcpy(&it, raw, sizeof(fwd_item));
-    return it;
-}
-
-// Pointers that come out of a descriptor are generic; memory instructions through them would be flat ones, which
-// count against both the vector-memory and the LDS counter and force full waits.  These name the global address space.
-template <class T> using gptr = __attribute__((address_space(1))) T*;
-template <class T> __device__ __forceinline__ gptr<const T> as_global(const T* p) { return (gptr<const T>)p; }
-template <class T> __device__ __forceinline__ gptr<T> as_global_w(T* p) { return (gptr<T>)p; }
-
-// A workgroup barrier that orders LDS traffic only.  __syncthreads() also waits for every outstanding access to
-// global memory (one counter serves loads and stores), which would put loads that are meant to fly across the
-// barrier back on the critical path.
-__device__ __forceinline__ void lds_barrier() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
-// N consecutive words of the kernel arguments in one batch of scalar loads.
-template <int N>
-__device__ __forceinline__ void fetch_words(const int* p, int (&out)[N]) {
-#pragma unroll
-    for (int i = 0; i < N; ++i) out[i] = p[i];
-#pragma unroll
-    for (int i = 0; i < N; ++i) asm volatile("" : "+s"(out[i]));
-}
 
 // ------------------------------------------------------------------------------------------------
 // prep kernel (512 threads): two kinds of workgroups in one launch.
@@ -154,7 +98,7 @@ __device__ __forceinline__ uint32_t amax_join(uint32_t mlo, uint32_t mhi) { retu
 // for rows up to 4096 wide; beyond, with more arithmetic per wave between its loads and its stores, the two-row form is
 // the faster one.
 template <int NK>
-__device__ __forceinline__ void quantise_row_wave(const fwd_item& it, int i, int lane, int a_limbs) {
+__device__ __forceinline__ void quantise_row_wave(const stream_item& it, int i, int lane, int a_limbs) {
     typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
     const int din = it.d_in, dpad = it.d_in_pad;
     const int nch = din / 8, kd = dpad / 512;             // 16-byte chunks of the row; trips of 64 chunks up to the padded width
@@ -280,7 +224,7 @@ __global__ __launch_bounds__(PREP_NT, FULLK ? 4 : 1) void prep_kernel(stream_arg
         }
         rel = (quant_role ? b : lb) - first;
     }
-    const fwd_item it = fetch_item(a.it[g]);
+    const stream_item it = fetch_item(a.it[g]);
     if (quant_role && qw == 4) {
         const int i = rel * 8 + wave;
         if (i < it.R) quantise_row_wave<8>(it, i, lane, a_limbs);
@@ -588,18 +532,6 @@ constexpr int PD = 4;              // weight prefetch distance in K tiles; d_in_
 constexpr int NT = 512;            // threads per workgroup
 constexpr int UROW = 144;          // LDS row of the u tile: 2 * rp bf16 (at most 128 B) + pad
 
-// Loads of the main loop are buffer loads: (wave-uniform base in a resource descriptor) + (scalar offset that moves
-// with the K tile) + (32-bit lane offset, fixed for the whole loop).  All address arithmetic is scalar, and the vector
-// ALU, which the MFMAs also issue through, stays free.
-typedef __amdgpu_buffer_rsrc_t rsrc_t;
-__device__ __forceinline__ rsrc_t make_rsrc(const void* base_uniform) {
-    // raw buffer (stride 0), 32-bit data format; 2 GB window: offsets used here are far below it
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base_uniform), 0, 0x7fffffff, 0x00020000);
-}
-__device__ __forceinline__ u32x4 load16(rsrc_t r, uint32_t lane_off, uint32_t scalar_off) {
-    return __builtin_amdgcn_raw_buffer_load_b128(r, lane_off, scalar_off, 0);
-}
-
 // lane offsets of the activation-tile loads: vector e of thread tid is 16-byte part `part` of row `row` of limb e's tile
 template <int LIMBS, int BM, int XV>
 __device__ __forceinline__ void x_lane_offsets(uint32_t (&xoff)[XV], int dpad, int tid) {
@@ -752,7 +684,7 @@ constexpr size_t gemm_smem_bytes() {
 // sA_c * (V_A^T x_i) shares, kept in LDS as bf16 head+tail rows of UROW bytes.  Two parts, so that a caller can put
 // other loads between them: the global loads, then the arithmetic (which contains one workgroup barrier).
 template <int BM, int EU>
-__device__ __forceinline__ void u_tile_loads(const fwd_item& it, int m0, int tid, f32x4 (&tp)[EU][2], float (&sb)[EU], float (&mreg)[2]) {
+__device__ __forceinline__ void u_tile_loads(const stream_item& it, int m0, int tid, f32x4 (&tp)[EU][2], float (&sb)[EU], float (&mreg)[2]) {
     const int R = it.R, rp = it.rp, rpad = (R + 31) / 32 * 32;
     const int rsh = rp == 16 ? 4 : 5;                     // rp is 16 or 32: divisions become shifts
     const gptr<const f32x4> tpart = as_global(reinterpret_cast<const f32x4*>(it.Tpart));
@@ -775,7 +707,7 @@ __device__ __forceinline__ void u_tile_loads(const fwd_item& it, int m0, int tid
 }
 
 template <int BM, int EU, bool LDS_ONLY = false>
-__device__ __forceinline__ void u_tile_finish(const fwd_item& it, unsigned flags, int tid, const f32x4 (&tp)[EU][2], const float (&sb)[EU],
+__device__ __forceinline__ void u_tile_finish(const stream_item& it, unsigned flags, int tid, const f32x4 (&tp)[EU][2], const float (&sb)[EU],
                                               const float (&mreg)[2], float* tvec, float* Ms, unsigned char* utile) {
     const int rp = it.rp, rsh = rp == 16 ? 4 : 5;
 #pragma unroll
@@ -832,7 +764,7 @@ __device__ __forceinline__ void u_tile_finish(const fwd_item& it, unsigned flags
 template <bool YBF16>
 struct rv_piece { float v[YBF16 ? 8 : 4]; };
 template <bool YBF16>
-__device__ __forceinline__ rv_piece<YBF16> load_rv_piece(const fwd_item& it, int n0, int tid) {
+__device__ __forceinline__ rv_piece<YBF16> load_rv_piece(const stream_item& it, int n0, int tid) {
     constexpr int EPV = YBF16 ? 8 : 4, PPR = 128 / EPV;
     static_assert(NT % PPR == 0, "a thread keeps its piece from row to row");
     rv_piece<YBF16> r;
@@ -858,7 +790,7 @@ __device__ __forceinline__ rv_piece<YBF16> load_rv_piece(const fwd_item& it, int
 }
 
 template <bool YBF16, int BM>
-__device__ __forceinline__ void store_ctile(const unsigned char* ctile, const fwd_item& it, int m0, int n0, int blk, int tid,
+__device__ __forceinline__ void store_ctile(const unsigned char* ctile, const stream_item& it, int m0, int n0, int blk, int tid,
                                             const rv_piece<YBF16>& rvp) {
     constexpr int ESZ = YBF16 ? 2 : 4, EPV = 16 / ESZ, PPR = 128 / EPV;     // elements per vector, vectors per row
     constexpr int CROW = 128 * ESZ + 16;
@@ -928,7 +860,7 @@ __global__ __launch_bounds__(NT, (Q4 && MB == 2) ? 4 : 1) void gemm_i8_kernel(st
     int g = 0;
 #pragma unroll
     for (int i = 1; i < ESSA_MAX_GROUP; ++i) g += (i < a.n_items && b >= a.tile_start[i]) ? 1 : 0;
-    const fwd_item it = fetch_item(a.it[g]);
+    const stream_item it = fetch_item(a.it[g]);
     const int ntile = a.tile_start[g + 1] - a.tile_start[g];
     int tile = b - a.tile_start[g];
     if (!by_group && (ntile & 7) == 0 && (a.tile_start[g] & 7) == 0) tile = (tile & 7) * (ntile >> 3) + (tile >> 3);   // per item, where that works
@@ -1322,7 +1254,7 @@ __global__ __launch_bounds__(NT, 1) void gemm_i8_stream_kernel(stream_args a) {
     int g = 0;
 #pragma unroll
     for (int i = 1; i < ESSA_MAX_GROUP; ++i) g += (i < a.n_items && (int)blockIdx.x >= a.tile_start[i]) ? 1 : 0;
-    const fwd_item it = fetch_item(a.it[g]);
+    const stream_item it = fetch_item(a.it[g]);
     const int nb = blockIdx.x - a.tile_start[g];           // this workgroup's block of 32 channels
     const int R = it.R, dout = it.d_out, dpad = it.d_in_pad, rp = it.rp;
     const int nkc = dpad >> 5;                             // chunks of 32 columns; a multiple of 16
@@ -1516,7 +1448,7 @@ constexpr size_t q4w_smem_bytes() {
 }
 
 template <int LIMBS, bool YBF16, int RB>
-__device__ __forceinline__ void q4w_tile(const stream_args& a, const fwd_item& it, const int m0, const int nb0) {
+__device__ __forceinline__ void q4w_tile(const stream_args& a, const stream_item& it, const int m0, const int nb0) {
     constexpr int BM = 32 * RB;
     constexpr int XV = (LIMBS * BM * 8 + NT - 1) / NT;
     constexpr size_t BIG = q4w_smem_bytes<LIMBS, YBF16, RB>() - BM * 4 - (size_t)BM * UROW;
@@ -1706,7 +1638,7 @@ __global__ __launch_bounds__(NT, 4) void gemm_q4_wide_kernel(stream_args a) {
     int g = 0;
 #pragma unroll
     for (int i = 1; i < ESSA_MAX_GROUP; ++i) g += (i < a.n_items && bb >= (small ? a.q4_small_start[i] : a.tile_start[i])) ? 1 : 0;
-    const fwd_item it = fetch_item(a.it[g]);
+    const stream_item it = fetch_item(a.it[g]);
     const int start = small ? a.q4_small_start[g] : a.tile_start[g];
     const int ntile = (small ? a.q4_small_start[g + 1] : a.tile_start[g + 1]) - start;
     int tile = bb - start;
@@ -1767,7 +1699,7 @@ __global__ __launch_bounds__(NT) void gemm_i8_big_kernel(stream_args a, int32_t*
     int g = 0;
 #pragma unroll
     for (int i = 1; i < ESSA_MAX_GROUP; ++i) g += (i < a.n_items && (int)blockIdx.x >= a.tile_start[i]) ? 1 : 0;
-    const fwd_item it = fetch_item(a.it[g]);
+    const stream_item it = fetch_item(a.it[g]);
     const int R = it.R, dout = it.d_out, dpad = it.d_in_pad, rp = it.rp;
     const int tiles_m = (R + BM - 1) / BM, tiles_n = (it.n_blocks + BIG_NB - 1) / BIG_NB;
     // blocks go round-robin over the 8 XCDs: give each XCD a contiguous range of tiles, and inside it walk patches of
@@ -2168,8 +2100,10 @@ int pick_q4_wide(const stream_args& a) {
     return tiles >= 256 ? 64 : 0;
 }
 
-// the 128 x 256 tile pays off once it fills the chip a few times over
+// one limb: the 128 x 256 tile pays off once it fills the chip a few times over (two-limb groups of that size take the
+// exact-product kernel instead)
 bool takes_big(const stream_args& a) {
+    if (a.limbs != 1) return false;
     long long tiles = 0;
     for (int g = 0; g < a.n_items; ++g)
         tiles += (long long)((a.it[g].R + BIG_BM - 1) / BIG_BM) * ((a.it[g].n_blocks + BIG_NB - 1) / BIG_NB);
@@ -2247,8 +2181,7 @@ hipError_t forward_stream(hipStream_t st, const fwd_item* items, int n_items, in
         // the reward partials (one per 128 channels and row) span four of this kernel's workgroups: a pass of their own
         return essa_k::rowdot_blocks(st, items, n_items, y_dtype);
     } else if (to_big) {
-        if (a.limbs == 2) e = y_dtype == ESSA_BF16 ? launch_gemm_big<2, true>(st, a) : launch_gemm_big<2, false>(st, a);
-        else e = y_dtype == ESSA_BF16 ? launch_gemm_big<1, true>(st, a) : launch_gemm_big<1, false>(st, a);
+        e = y_dtype == ESSA_BF16 ? launch_gemm_big<1, true>(st, a) : launch_gemm_big<1, false>(st, a);
     } else if (q4_rows == 64)
         e = y_dtype == ESSA_BF16 ? launch_gemm_q4_wide<2, true>(st, a) : launch_gemm_q4_wide<2, false>(st, a);
     else if (items[0].quant == ESSA_QUANT_INT4_G128)

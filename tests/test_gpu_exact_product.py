@@ -1,0 +1,70 @@
+"""GPU parity of the exact-product kernel (int8 weights as bf16, fp32 accumulation) at the edges of its tiles and K steps.
+
+Its products are exact; what is left is fp32 accumulation (one rounding of 2^-24 per 32 columns of a random-sign sum:
+2^-24 sqrt(d_in / 32), 1e-6 at the widest row here) and the bf16 head + tail operands of the rank-r term (2^-17 of a term that is
+a twentieth of the output), so the repository's bar for exact products applies, and a tenth of it to the base term alone."""
+import numpy as np
+import pytest
+import torch
+
+import essa_workloads as wl
+import oracle as orc
+from helpers import bf16_dev, bf16_host, candidate_sigmas, gpu_proj, oracle_proj, to_dev
+
+pytestmark = pytest.mark.gpu
+
+EXACT_RMS, EXACT_MAX = 2e-5, 2e-4
+BF16_RMS, BF16_MAX = 1e-3, 2e-2
+
+
+@pytest.mark.parametrize("R,d_in,d_out,r,flags", [
+    (1, 48, 129, 5, 8),            # one row, less than one K step, asked for by the flag
+    (129, 64, 128, 32, 8),         # exactly one K step and one tile of channels, one row past a tile
+    (513, 1040, 300, 32, 0),       # taken by itself: the first row count, K ends 16 columns into a step
+    (1030, 528, 9001, 16, 0),      # two 128 x 128 tiles per CU, odd output width (element-wise stores)
+    (700, 2064, 8200, 16, 0),      # 256 x 128 tiles
+    (2050, 4112, 5000, 24, 0),     # 256 x 256 tiles, ragged rows and channels
+])
+def test_exact_product_tiles(essa, R, d_in, d_out, r, flags):
+    ctx = essa.Context(0)
+    K = 3
+    print("exact product: R=%d d_in=%d d_out=%d r=%d" % (R, d_in, d_out, r), flush=True)
+    p = wl.make_projection("t", d_in, d_out, r, "int8", layer=11, proj=1)
+    p.scales[d_out // 2] = 0.0                             # a channel that has no base term at all
+    W, f = oracle_proj(p)
+    gp = gpu_proj(essa, ctx, p)
+    sA, sB = candidate_sigmas(f, K, 0.05)
+    xb, xv = wl.make_x_bf16(R, d_in, x_id=31)
+    r2c = np.random.default_rng(6).integers(0, K, R).astype(np.int32)
+    ref = orc.svdlora_forward(W, f, xv, r2c, sA, sB)
+    Xd, rd, sAd, sBd = bf16_dev(xb), to_dev(r2c), to_dev(sA), to_dev(sB)
+    v = torch.randn(d_out, device="cuda", generator=torch.Generator(device="cuda").manual_seed(1))
+    nblk = (d_out + 127) // 128
+    for dtype in (torch.float32, torch.bfloat16):
+        Y = torch.full((R, d_out), float("nan"), device="cuda", dtype=dtype)
+        rowpart = torch.full((nblk, R), float("nan"), device="cuda")
+        essa.essa_svdlora_forward_reward_group(ctx, [(gp, Xd, rd, sAd, sBd, Y)], [v], rowpart, 0, flags)
+        if dtype == torch.float32:
+            e_max, e_rms = orc.rel_errors(Y.cpu().numpy(), ref)
+            assert e_rms <= EXACT_RMS and e_max <= EXACT_MAX, (e_rms, e_max)
+        else:
+            e_max, e_rms = orc.rel_errors(bf16_host(Y), orc.round_to_bf16(ref))
+            assert e_rms <= BF16_RMS and e_max <= BF16_MAX, (e_rms, e_max)
+        # the partials are sums of 128 products of the outputs as written, in fp32
+        pad = torch.zeros(R, nblk * 128 - d_out, device="cuda", dtype=torch.float64)
+        want = (torch.cat([Y.double() * v.double(), pad], 1)).view(R, nblk, 128)
+        assert torch.all((rowpart.T.double() - want.sum(2)).abs() <= 128 * 2.0 ** -24 * want.abs().sum(2) + 1e-30)
+    Y = torch.empty(R, d_out, device="cuda")
+    essa.essa_svdlora_forward(ctx, gp, Xd, rd, sAd, sBd, Y, flags | essa.BASE_ONLY)
+    e_max, e_rms = orc.rel_errors(Y.cpu().numpy(), orc.svdlora_forward(W, f, xv, r2c, sA, sB, base_only=True))
+    assert e_rms <= EXACT_RMS / 10 and e_max <= EXACT_MAX / 10, (e_rms, e_max)
+    # a non-finite entry spoils its own row and nothing else
+    Xbad = Xd.clone()
+    Xbad[R // 2, d_in - 1] = float("inf")
+    Ybad, Y = torch.empty(R, d_out, device="cuda"), torch.empty(R, d_out, device="cuda")
+    essa.essa_svdlora_forward(ctx, gp, Xbad, rd, sAd, sBd, Ybad, flags)
+    essa.essa_svdlora_forward(ctx, gp, Xd, rd, sAd, sBd, Y, flags)
+    keep = torch.arange(R, device="cuda") != R // 2
+    assert not torch.isfinite(Ybad[R // 2]).any() and torch.equal(Ybad[keep], Y[keep])
+    gp.close()
+    ctx.close()
