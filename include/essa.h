@@ -336,12 +336,15 @@ essa_status essa_cmaes_update(essa_ctx* ctx, essa_cma* cma, const uint32_t* seed
  * D the square roots of the eigenvalues (negative round-off clamped to zero).  C itself is left alone (it is read as
  * (C + C^T) / 2).  One-sided block Jacobi in fp64; sweeps until the largest |a_i . a_j| / (|a_i| |a_j|) over all
  * pairs of columns of C V met during a sweep is <= tol, at most max_sweeps (1..64) times; pairs already below tol / 100
- * are left alone, so a C that has not moved since the last refresh costs one pass over it.  The state keeps the basis of
- * its last refresh in fp64 and the next refresh starts from it (a few sweeps when C has moved little); after
+ * are left alone, so a C that has not moved since the last refresh costs one pass over it.  Where the columns are close
+ * to the eigenvectors (a C that has moved little, the end of a cold start), simultaneous corrections of all columns take
+ * the place of the sweeps, to the same measure.  The state keeps the basis of
+ * its last refresh in fp64 and the next refresh starts from it; after
  * essa_cma_set_basis or essa_cma_import the next refresh starts from the identity.  Off the per-generation
  * path: the tutorial refreshes the basis every 1 / (10 n (c_1 + c_mu)) generations.  The call waits for the device
- * after every sweep; it cannot be recorded into a graph.
- *   sweeps_out, off_out   HOST, optional: sweeps done and the last measure
+ * after every sweep or correction; it cannot be recorded into a graph.
+ *   sweeps_out, off_out   HOST, optional: sweeps and corrections done (the latter do not count against max_sweeps) and
+ *                         the last measure
  * ESSA_ERR_STATE if the measure is still above tol after max_sweeps (B, D then hold the last iterate). */
 essa_status essa_cma_refresh_basis(essa_ctx* ctx, essa_cma* cma, int max_sweeps, float tol, int* sweeps_out,
                                    float* off_out);

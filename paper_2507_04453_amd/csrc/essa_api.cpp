@@ -960,7 +960,11 @@ extern "C" essa_status essa_cma_refresh_basis(essa_ctx* ctx, essa_cma* cma, int 
     if (ctx->capturing) return essa_fail(ESSA_ERR_STATE, "essa_cma_refresh_basis: waits for the device after every sweep and cannot be recorded");
     if (max_sweeps < 1 || max_sweeps > 64 || !(tol >= 0.f)) return essa_fail(ESSA_ERR_INVALID_ARG, "essa_cma_refresh_basis: max_sweeps=%d tol=%g", max_sweeps, (double)tol);
     ESSA_HIP(hipSetDevice(ctx->device));
-    ESSA_TRY(essa_ws_reserve(ctx, essa_k::eig_workspace_bytes(cma->n)));
+    // the correction steps want one n x n matrix more; where the scratch cannot have it (recorded graphs pin its size, the card
+    // is full) the sweeps do the whole work in what they always used
+    const size_t with_steps = essa_k::eig_workspace_bytes(cma->n, true);
+    bool refine = with_steps <= ctx->ws_bytes || (ctx->graphs.empty() && essa_ws_reserve(ctx, with_steps) == ESSA_OK);
+    if (!refine) ESSA_TRY(essa_ws_reserve(ctx, essa_k::eig_workspace_bytes(cma->n, false)));
     if (!cma->eigV) {
         hipError_t e = hipMalloc((void**)&cma->eigV, essa_k::eig_basis_bytes(cma->n));
         if (e != hipSuccess) return essa_fail(ESSA_ERR_OOM, "fp64 basis of %zu bytes: %s", essa_k::eig_basis_bytes(cma->n), hipGetErrorString(e));
@@ -968,7 +972,7 @@ extern "C" essa_status essa_cma_refresh_basis(essa_ctx* ctx, essa_cma* cma, int 
     }
     int sweeps = 0;
     float off = 0.f;
-    ESSA_HIP(essa_k::eig_refresh(ctx->stream, cma->C, cma->n, ctx->ws, cma->eigV, cma->eigV_valid ? 1 : 0, max_sweeps, tol, cma->B, cma->D,
+    ESSA_HIP(essa_k::eig_refresh(ctx->stream, cma->C, cma->n, ctx->ws, refine, cma->eigV, cma->eigV_valid ? 1 : 0, max_sweeps, tol, cma->B, cma->D,
                                  &sweeps, &off));
     cma->eigV_valid = true;
     if (sweeps_out) *sweeps_out = sweeps;

@@ -131,11 +131,12 @@ hipError_t theta_to_sigma(hipStream_t st, int P, int r, int n_top, const float* 
                           const float* theta, int K, float* sA, float* sB);
 hipError_t rank_rewards(hipStream_t st, const float* F, int K, int32_t* order);
 // C (n x n, fp32, symmetric) -> B (eigenvectors in columns), D (square roots of the eigenvalues); ws: eig_workspace_bytes(n).
-// Synchronises the stream once per sweep (the convergence measure comes back to the host).
+// Synchronises the stream once per sweep or correction step (the convergence measure comes back to the host).
+// refine: ws has room for the correction steps as well (eig_workspace_bytes(n, true)).
 // Vt: the basis in fp64 (eig_basis_bytes(n)), kept by the state from one refresh to the next; warm = it holds the last result.
-size_t eig_workspace_bytes(int n);
+size_t eig_workspace_bytes(int n, bool refine);
 size_t eig_basis_bytes(int n);
-hipError_t eig_refresh(hipStream_t st, const float* C, int n, void* ws, double* Vt, int warm, int max_sweeps, float tol, float* B, float* D,
+hipError_t eig_refresh(hipStream_t st, const float* C, int n, void* ws, bool refine, double* Vt, int warm, int max_sweeps, float tol, float* B, float* D,
                        int* sweeps_done, float* off_final);
 
 struct cma_consts {
