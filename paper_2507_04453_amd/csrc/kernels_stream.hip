@@ -1426,6 +1426,205 @@ __global__ __launch_bounds__(NT, 1) void gemm_i8_stream_kernel(stream_args a) {
 }
 
 // ------------------------------------------------------------------------------------------------
+// 4-bit weights at the row counts of the kernel above, on the same plan: one workgroup per block of 32 output channels and
+// block of 32 rows, the whole K; weights and limbs go memory -> MFMA operand registers.  A wave takes whole quantisation
+// groups, g = wave, wave + 8, ..., asks for the weights of all of them at once (at most 8 groups a wave: rows of 8192 columns)
+// (six, and the others as registers come free) and lets their limbs stream past, four chunks ahead of the MFMAs.
+// A group's integer sums have to be scaled before they are added to another group's, and a row's result must not depend on
+// the kernel that took it, so the groups' fp32 FMAs keep the tile kernels' order: after each round of 8 groups the waves leave
+// their sums (hi limb, shift, lo limb on top: the tile kernels' integer) in LDS, and every thread folds two outputs
+// over the 8 groups in ascending order.  Two buffers, one barrier per round.
+// What the epilogue wants from memory (zero-point and rank operands) is asked for in the first round, a piece per thread, and
+// waits in registers until its place in LDS is free.
+// 128 registers and half the LDS: two workgroups per CU, one loading while the other folds or finishes.
+// One layer at 16 rows, with its prep launch: 8192 wide (18432 channels) 76 us with the 32 x 128 tiles, 42 now (1.9 TB/s of
+// weights and scales); 3584 wide 38 and 17.  Two row blocks per workgroup, with 148 registers and one workgroup per CU, took 68
+// at 33 rows of 8192 against 49 for two workgroups.
+// ------------------------------------------------------------------------------------------------
+constexpr int QS_ROUNDS = 8;                               // rounds of 8 groups: up to 64 groups
+constexpr int QS_PITCH = 16 * QS_ROUNDS * 2 + 16;          // LDS row of a zero-point operand: head and tail of up to 64 groups, pad
+
+constexpr size_t Q4S_SMEM = (size_t)2 * 8 * 4096 + (size_t)QS_ROUNDS * 8 * 32 * 4 + 32 * 4 + (size_t)32 * UROW;
+
+template <bool YBF16>
+__global__ __launch_bounds__(NT, 4) void gemm_q4_stream_kernel(stream_args a) {
+    typedef __attribute__((ext_vector_type(2))) float f32x2;
+    constexpr int BM = 32, DX = 4;
+    constexpr size_t BUF = (size_t)8 * 4096;               // one round's sums: [wave][pair of q][lane][2]
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    float* ssc = reinterpret_cast<float*>(smem + 2 * BUF); // [group][32] scales
+    float* xd = ssc + QS_ROUNDS * 8 * 32;
+    unsigned char* utile = reinterpret_cast<unsigned char*>(xd + BM);
+    float* tvec = reinterpret_cast<float*>(smem + BUF);    // the prologue's matrices: the second buffer is free until the first barrier
+    float* Ms = tvec + BM * UTP;
+    static_assert((size_t)(BM + 32) * UTP * 4 <= BUF, "the prologue's matrices fit a buffer");
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, h = lane >> 5;
+    int g = 0;
+#pragma unroll
+    for (int i = 1; i < ESSA_MAX_GROUP; ++i) g += (i < a.n_items && (int)blockIdx.x >= a.tile_start[i]) ? 1 : 0;
+    const stream_item it = fetch_item(a.it[g]);
+    // block of 32 channels and block of 32 rows; the row blocks of a channel block on one XCD (the weights meet in its L2)
+    const int rel = blockIdx.x - a.tile_start[g], row_blocks = (it.R + 31) / 32;
+    const int nb = (rel >> 3) / row_blocks * 8 + (rel & 7), m0 = (rel >> 3) % row_blocks * 32;
+    if (nb >= it.n_blocks) return;                         // the grid counts whole sets of 8
+    const int R = it.R, dout = it.d_out, dpad = it.d_in_pad, rp = it.rp, Gp = it.Gp;
+    const int groups = dpad >> 7, nkc = dpad >> 5, n = (groups + 7) >> 3;
+    const uint32_t wstride_b = (uint32_t)it.n_blocks * 1024;
+    const rsrc_t wbase = make_rsrc(reinterpret_cast<const unsigned char*>(it.Wt) + (size_t)nb * 1024);
+    const rsrc_t xbase[2] = {make_rsrc(it.Xh), make_rsrc(it.Xl)};
+    constexpr uint32_t OUT_OF_RANGE = 0x80000000u;         // beyond the descriptor's 2 GB: the load returns zeros, no memory access
+    const uint32_t lane16 = lane * 16;
+    const uint32_t xoff = m0 + l32 < R ? (uint32_t)((m0 >> 5) * nkc) * 1024u + lane16 : OUT_OF_RANGE;
+
+    constexpr int EU = (BM * 32 + NT - 1) / NT;
+    f32x4 tp[EU][2];
+    float sb[EU], mreg[2];
+    u_tile_loads<BM, EU>(it, m0, tid, tp, sb, mreg);
+    const float xdreg = as_global(it.xdelta)[min(m0 + min(tid, BM - 1), R - 1)];
+    float sreg[4];                                         // scales of groups (tid >> 5) + 16 i
+#pragma unroll
+    for (int i = 0; i < 4; ++i) sreg[i] = as_global(it.St)[(size_t)min((tid >> 5) + 16 * i, groups - 1) * it.n_blocks * 32 + nb * 32 + (tid & 31)];
+    __builtin_amdgcn_sched_barrier(0);
+
+    // round j of this wave is group wave + 8 j = K chunks 4 (wave + 8 j) .. + 3; past the last group: zeros
+    u32x4 wr[QS_ROUNDS][2], xr[DX];
+    auto issue_w = [&](int j) {
+        const int grp = wave + 8 * j;
+        const uint32_t gone = grp < groups ? 0u : OUT_OF_RANGE;
+#pragma unroll
+        for (int e = 0; e < 2; ++e) wr[j][e] = load16(wbase, lane16 | gone, (uint32_t)(2 * grp + e) * wstride_b);
+    };
+#pragma unroll
+    for (int j = 0; j < QS_ROUNDS - 2; ++j) issue_w(j);    // the last two as registers come free
+    auto issue_x = [&](int j, int limb, int c) {
+        const int grp = wave + 8 * j;
+        const uint32_t gone = grp < groups ? 0u : OUT_OF_RANGE;
+        xr[c] = load16(xbase[limb], xoff | gone, (uint32_t)(4 * grp + c) * 1024u);
+    };
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int c = 0; c < DX; ++c) issue_x(0, 0, c);
+    __builtin_amdgcn_sched_barrier(0);
+
+    u_tile_finish<BM, EU, true>(it, a.flags, tid, tp, sb, mreg, tvec, Ms, utile);
+    if (tid < BM) xd[tid] = xdreg;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) ssc[tid + NT * i] = (tid >> 5) + 16 * i < groups ? sreg[i] : 0.f;
+
+    // operands of the epilogue, 16 bytes per thread: rows of 4 Gp bytes (zero-point term) and 4 rp bytes (U_B); asked for in round 0
+    const int gpr = Gp >> 2, rpr = rp >> 2;                // 16-byte pieces of such a row
+    const int sz_row = tid / gpr, sz_at = tid % gpr, ub_row = tid / rpr, ub_at = tid % rpr;
+    u32x4 szreg, ubreg, xsreg;
+    f32x2 tot = {0.f, 0.f};
+    const u32x4 m4 = {0x0f0f0f0fu, 0x0f0f0f0fu, 0x0f0f0f0fu, 0x0f0f0f0fu};
+#pragma unroll
+    for (int j = 0; j < QS_ROUNDS; ++j) {
+        if (j == 0 || j < n) {
+            f32x2* buf = reinterpret_cast<f32x2*>(smem + (j & 1) * BUF);
+            i32x16 t = {0};
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int c = i & 3;
+                if (i == 4) {
+#pragma unroll
+                    for (int q = 0; q < 16; ++q) t[q] <<= 8;
+                }
+                const u32x4 w = (c & 1) ? (wr[j][c >> 1] >> 4) & m4 : wr[j][c >> 1] & m4;
+                t = __builtin_amdgcn_mfma_i32_32x32x32_i8((i32x4)xr[c], (i32x4)w, t, 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                if (i < 4) issue_x(j, 1, c);
+                else if (j + 1 < QS_ROUNDS) issue_x(j + 1, 0, c);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (j == 0) {
+                szreg = *as_global(reinterpret_cast<const u32x4*>(it.SZ16 + (size_t)(nb * 32 + min(sz_row, 31)) * 2 * Gp + 8 * sz_at));
+                ubreg = *as_global(reinterpret_cast<const u32x4*>(it.UB16 + (size_t)min(nb * 32 + min(ub_row, 31), dout - 1) * 2 * rp + 8 * ub_at));
+                xsreg = *as_global(reinterpret_cast<const u32x4*>(it.XS16 + (size_t)min(m0 + min(sz_row, 31), R - 1) * 2 * Gp + 8 * sz_at));
+            } else if (j <= 2) {
+                issue_w(QS_ROUNDS - 3 + j);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int q = 0; q < 8; ++q) buf[(wave * 8 + q) * 64 + lane] = (f32x2){(float)t[2 * q], (float)t[2 * q + 1]};
+            lds_barrier();
+            // thread (wave, lane) folds outputs q = 2 wave and 2 wave + 1 over the round's groups, ascending
+#pragma unroll
+            for (int w = 0; w < 8; ++w) {
+                const float s = ssc[(8 * j + w) * 32 + l32];
+                const f32x2 v = buf[(w * 8 + wave) * 64 + lane];
+                tot[0] = fmaf(s, v[0], tot[0]);
+                tot[1] = fmaf(s, v[1], tot[1]);
+            }
+        }
+    }
+    // the buffer that the last round did not use: its readers are done
+    unsigned char* fin = smem + (n & 1) * BUF;
+    float* totb = reinterpret_cast<float*>(fin);           // [q][lane]
+    unsigned char* xs_l = fin + 4096;
+    unsigned char* sz_l = xs_l + BM * QS_PITCH;
+    unsigned char* ub_l = sz_l + 32 * QS_PITCH;
+    static_assert(4096 + (BM + 32) * QS_PITCH + 32 * UROW <= BUF, "the epilogue's operands fit a buffer");
+    totb[2 * wave * 64 + lane] = tot[0];
+    totb[(2 * wave + 1) * 64 + lane] = tot[1];
+    if (sz_row < 32) {
+        *reinterpret_cast<u32x4*>(xs_l + sz_row * QS_PITCH + 16 * sz_at) = xsreg;
+        *reinterpret_cast<u32x4*>(sz_l + sz_row * QS_PITCH + 16 * sz_at) = szreg;
+    }
+    if (ub_row < 32) *reinterpret_cast<u32x4*>(ub_l + ub_row * UROW + 16 * ub_at) = ubreg;
+    lds_barrier();
+    if (wave > 0) return;
+    f32x16 v;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+        const int rl = 8 * (q >> 2) + 4 * h + (q & 3);
+        v[q] = (a.flags & ESSA_LORA_ONLY) ? 0.f : totb[q * 64 + lane] * xd[rl];
+    }
+    if (!(a.flags & ESSA_LORA_ONLY)) {
+        // zero-point term, as in the tile kernels: a low-rank product over the groups, bf16 head+tail operands
+        const unsigned char* xs = xs_l + l32 * QS_PITCH + 16 * h;
+        const unsigned char* sz = sz_l + l32 * QS_PITCH + 16 * h;
+        for (int ks = 0; ks < Gp / 16; ++ks) {
+            const bf16x8 xa_hi = *reinterpret_cast<const bf16x8*>(xs + ks * 32);
+            const bf16x8 xa_lo = *reinterpret_cast<const bf16x8*>(xs + 2 * Gp + ks * 32);
+            const bf16x8 zb_hi = *reinterpret_cast<const bf16x8*>(sz + ks * 32);
+            const bf16x8 zb_lo = *reinterpret_cast<const bf16x8*>(sz + 2 * Gp + ks * 32);
+            v = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xa_lo, zb_hi, v, 0, 0, 0);
+            v = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xa_hi, zb_lo, v, 0, 0, 0);
+            v = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xa_hi, zb_hi, v, 0, 0, 0);
+        }
+    }
+    if (!(a.flags & ESSA_BASE_ONLY)) {
+        // rank-r term U_B u_i: bf16 head+tail operands, lo*hi + hi*lo + hi*hi per 16 rank columns
+        const unsigned char* up = utile + (size_t)l32 * UROW + 16 * h;
+        const unsigned char* ub = ub_l + l32 * UROW + 16 * h;
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            if (ks * 16 < rp) {
+                const bf16x8 ua_hi = *reinterpret_cast<const bf16x8*>(up + ks * 32);
+                const bf16x8 ua_lo = *reinterpret_cast<const bf16x8*>(up + 2 * rp + ks * 32);
+                const bf16x8 ub_hi = *reinterpret_cast<const bf16x8*>(ub + ks * 32);
+                const bf16x8 ub_lo = *reinterpret_cast<const bf16x8*>(ub + 2 * rp + ks * 32);
+                v = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ua_lo, ub_hi, v, 0, 0, 0);
+                v = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ua_hi, ub_lo, v, 0, 0, 0);
+                v = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ua_hi, ub_hi, v, 0, 0, 0);
+            }
+        }
+    }
+    const int o = nb * 32 + l32;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+        const int i = m0 + 8 * (q >> 2) + 4 * h + (q & 3);
+        if (i < R && o < dout) {
+            if (YBF16) __builtin_nontemporal_store(f32_to_bf16_bits(v[q]), as_global_w(reinterpret_cast<uint16_t*>(it.Y)) + (size_t)i * dout + o);
+            else __builtin_nontemporal_store(v[q], as_global_w(reinterpret_cast<float*>(it.Y)) + (size_t)i * dout + o);
+        }
+    }
+}
+
+// ------------------------------------------------------------------------------------------------
 // 4-bit weights, once the group fills the chip with tiles of 64 rows x 256 channels.  What bounds this format next to
 // the vector-ALU scaling is the number of 128-byte requests a workgroup sends to the L2 per K tile; with 256 channels
 // per tile the activation limbs (as many bytes per K tile as the nibbles of 256 channels) are asked for half as often
@@ -2026,17 +2225,19 @@ hipError_t launch_gemm(hipStream_t st, stream_args& a, int32_t* acc_out) {
     return hipGetLastError();
 }
 
-template <int MB, int LIMBS, bool YBF16>
+template <int MB, int LIMBS, bool YBF16, bool Q4 = false>
 hipError_t launch_gemm_stream(hipStream_t st, stream_args& a) {
     int total = 0;
     for (int g = 0; g < a.n_items; ++g) {
         a.tile_start[g] = total;
-        total += a.it[g].n_blocks;
+        total += Q4 ? (a.it[g].n_blocks + 7) / 8 * 8 * ((a.it[g].R + 31) / 32) : a.it[g].n_blocks;
     }
     for (int g = a.n_items; g <= ESSA_MAX_GROUP; ++g) a.tile_start[g] = total;
-    constexpr size_t smem = stream_smem_bytes<MB, LIMBS>();
-    static_assert(smem <= 160 * 1024, "does not fit the LDS of a CU");
-    auto kern = gemm_i8_stream_kernel<MB, LIMBS, YBF16>;
+    constexpr size_t smem = Q4 ? Q4S_SMEM : stream_smem_bytes<MB, LIMBS>();
+    static_assert(smem <= 160 * 1024 && !(Q4 && 2 * smem > 160 * 1024), "does not fit the LDS of a CU");
+    void (*kern)(stream_args);
+    if constexpr (Q4) kern = gemm_q4_stream_kernel<YBF16>;
+    else kern = gemm_i8_stream_kernel<MB, LIMBS, YBF16>;
     static bool attr_done = false;   // one flag per instantiation
     if (!attr_done && smem > 48 * 1024) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
@@ -2053,9 +2254,19 @@ hipError_t launch_gemm_stream(hipStream_t st, stream_args& a) {
 // gemm_i8_kernel; the activation limbs, which every workgroup loads for all its rows, are then four fifths of the bytes a
 // CU takes in, and four row blocks (128 rows) would need more registers than a wave has.
 constexpr int STREAM_MAX_ROWS = 64;
+// 4-bit weights: a workgroup per row block, so the limbs cost each of them the same at any row count and the weights come out of
+// the L2 again for every row block after the first.  us per layer (q, k, v, o, with the prep launch), tile kernels / this kernel:
+// 8192 wide 76 / 42 at 16 rows, 81 / 64 at 64, 88 / 81 at 96, 90 / 99 at 128; 5120 wide 53 / 27, 53 / 35, 56 / 48, 57 / 56;
+// 3584 wide 38 / 17, 39 / 22, 38 / 27, 39 / 32; 1024 wide 15 / 11, 15 / 12, 15 / 14, 15 / 14.
+// With a reward vector the pass over Y that the tile kernels do without comes on top: 3072 wide 27 / 18 at 8 rows, 28 / 22 at 64;
+// 3584 wide 31 / 19 and 31 / 24; 8192 wide 76 / 45 and 81 / 68; at 1024 wide it takes more than there is to gain.
+int q4_stream_max_rows(const stream_item& it) {
+    if (it.rv) return it.d_in >= 3072 ? 64 : 0;
+    return it.d_in <= 4096 ? 128 : 96;
+}
 bool takes_stream_kernel(const stream_args& a) {
     for (int g = 0; g < a.n_items; ++g)
-        if (a.it[g].quant != ESSA_QUANT_INT8_PERCH || a.it[g].R > STREAM_MAX_ROWS) return false;
+        if (a.it[g].R > (a.it[g].quant == ESSA_QUANT_INT8_PERCH ? STREAM_MAX_ROWS : q4_stream_max_rows(a.it[g]))) return false;
     return a.n_items > 0;
 }
 int stream_row_blocks(const stream_args& a) {
@@ -2171,7 +2382,9 @@ hipError_t forward_stream(hipStream_t st, const fwd_item* items, int n_items, in
     const int q4_rows = items[0].quant == ESSA_QUANT_INT4_G128 ? pick_q4_wide(a) : 0;   // all items of a call share the weight format
     if (to_stream) {
         const bool yb = y_dtype == ESSA_BF16;
-        if (stream_row_blocks(a) == 2) {
+        if (items[0].quant == ESSA_QUANT_INT4_G128) {
+            e = yb ? launch_gemm_stream<1, 2, true, true>(st, a) : launch_gemm_stream<1, 2, false, true>(st, a);
+        } else if (stream_row_blocks(a) == 2) {
             if (a.limbs == 2) e = yb ? launch_gemm_stream<2, 2, true>(st, a) : launch_gemm_stream<2, 2, false>(st, a);
             else e = yb ? launch_gemm_stream<2, 1, true>(st, a) : launch_gemm_stream<2, 1, false>(st, a);
         } else if (a.limbs == 2) e = yb ? launch_gemm_stream<1, 2, true>(st, a) : launch_gemm_stream<1, 2, false>(st, a);
