@@ -90,6 +90,7 @@ __global__ __launch_bounds__(1024) void cma_vectors_kernel(essa_k::cma_consts c,
 // Every rank-one term enters as (s sqrt|coef| v)(sqrt|coef| v)^T, s the sign of its weight, so that C stays exactly
 // symmetric.  A negative weight (tutorial, Eq. 46-47) is first rescaled by n / |C^-1/2 y|^2 = n / |z|^2.
 constexpr int CV_T = 64, CV_CH = 32;
+typedef float quad __attribute__((ext_vector_type(4), aligned(4)));
 __global__ __launch_bounds__(256) void cma_cov_kernel(essa_k::cma_consts c, const float* __restrict__ w, const float* __restrict__ BY,
                                                      const float* __restrict__ p_c, const essa_cma_scalars* __restrict__ sc,
                                                      const float* __restrict__ zn2, float* __restrict__ C) {
@@ -101,13 +102,13 @@ __global__ __launch_bounds__(256) void cma_cov_kernel(essa_k::cma_consts c, cons
     float acc[4][4] = {};
     // the tile of C is asked for first: it comes from HBM while the rank-one terms are added up
     const int j = j0 + tx * 4;
-    const bool vec = (n % 4 == 0) && j + 3 < n;
-    float4 cold[4];
+    const bool vec = j + 3 < n;                            // 16-byte accesses need 4-byte alignment only: any n
+    quad cold[4];
 #pragma unroll
     for (int x = 0; x < 4; ++x) {
         const int i = i0 + ty * 4 + x;
-        cold[x] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (vec && i < n) cold[x] = *reinterpret_cast<const float4*>(C + (size_t)i * n + j);
+        cold[x] = quad{0.f, 0.f, 0.f, 0.f};
+        if (vec && i < n) cold[x] = *reinterpret_cast<const quad*>(C + (size_t)i * n + j);
     }
     const int nvec = mu + 1;   // vector mu is p_c with coefficient c_1
     for (int v0 = 0; v0 < nvec; v0 += CV_CH) {
@@ -150,13 +151,10 @@ __global__ __launch_bounds__(256) void cma_cov_kernel(essa_k::cma_consts c, cons
         const int i = i0 + ty * 4 + x;
         if (i >= n) continue;
         if (vec) {
-            float4* p = reinterpret_cast<float4*>(C + (size_t)i * n + j);
-            float4 cv = cold[x];
-            cv.x = decay * cv.x + acc[x][0];
-            cv.y = decay * cv.y + acc[x][1];
-            cv.z = decay * cv.z + acc[x][2];
-            cv.w = decay * cv.w + acc[x][3];
-            *p = cv;
+            quad cv = cold[x];
+#pragma unroll
+            for (int y = 0; y < 4; ++y) cv[y] = decay * cv[y] + acc[x][y];
+            *reinterpret_cast<quad*>(C + (size_t)i * n + j) = cv;
         } else {
 #pragma unroll
             for (int y = 0; y < 4; ++y)

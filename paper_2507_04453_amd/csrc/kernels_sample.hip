@@ -139,7 +139,7 @@ constexpr int SG_WAVES = 8;
 constexpr int SG_BUNCH = 14;         // chunks of B a wave asks for at once (n = 3584: 28 chunks per wave, two bunches)
 constexpr int SG_AHEAD = 4;          // chunks of S in flight ahead of their MFMAs
 typedef __attribute__((ext_vector_type(4))) float f32x4;
-template <bool ALIGNED, int JB>
+template <bool TAIL, int JB>
 __global__ __launch_bounds__(SG_WAVES * 64) void skinny_gemm_nt_kernel(const float* __restrict__ S, int J, const float* __restrict__ B,
                                                                       int n, const float* __restrict__ bias,
                                                                       const essa_cma_scalars* __restrict__ sc, int use_sigma,
@@ -153,26 +153,16 @@ __global__ __launch_bounds__(SG_WAVES * 64) void skinny_gemm_nt_kernel(const flo
 #pragma unroll
     for (int jb = 0; jb < JB; ++jb) acc[jb] = (f32x4){0.f, 0.f, 0.f, 0.f};
     const int nchunks = (n + 15) / 16;
-    auto load4 = [&](const float* base, int row, int rows, int l) {
-        f32x4 v = {0.f, 0.f, 0.f, 0.f};
-        if (row < rows) {
-            if (ALIGNED) {
-                if (l < n) v = *reinterpret_cast<const f32x4*>(base + (size_t)row * n + l);
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (l + e < n) v[e] = base[(size_t)row * n + l + e];
-            }
-        }
-        return v;
-    };
     // A wave walks its chunks (wave, wave + 8, ...) in ascending order.
-    if constexpr (ALIGNED) {
+    {
         // Buffer loads: a row or a chunk past the end is an offset outside the descriptor and comes back as zeros, so there
         // is no branch around any load and the compiler can count them.  The B fragments of SG_BUNCH chunks are asked for
         // together and the S fragments then stream past them a few chunks ahead of their MFMAs: a CU's loads complete in
         // order, B comes from HBM and S out of the L2, and S loads spread evenly between B loads would all move at HBM
-        // latency.  (n <= 16384 on this path: both matrices stay below the descriptor's 2 GB.)
+        // latency.  (n <= 16384: both matrices stay below the descriptor's 2 GB.)
+        // The loads need 4-byte alignment only, so any n takes this path.  TAIL: n is not a multiple of 4, and the quad that
+        // crosses the end of a row is the row's last four elements, moved into place (update and next candidates, us, against single loads behind branches and a covariance pass without 16-byte accesses:
+        // 66 -> 55 at n = 1001, 138 -> 93 at 3169, 511 -> 266 at 5998; 32, 24 and 32 candidates).
         typedef __amdgpu_buffer_rsrc_t rsrc_t;
         constexpr uint32_t OUT_OF_RANGE = 0x80000000u;
         const rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(B), 0, (uint32_t)n * (uint32_t)n * 4u, 0x00020000);
@@ -183,11 +173,29 @@ __global__ __launch_bounds__(SG_WAVES * 64) void skinny_gemm_nt_kernel(const flo
         for (int jb = 0; jb < JB; ++jb) srow[jb] = (uint32_t)(j0 + 16 * jb + l16) * (uint32_t)n * 4u;
         auto ld = [&](rsrc_t r, uint32_t row_off, int chunk) {
             const int l = chunk * 16 + 4 * kq;
-            const uint32_t off = l < n ? row_off + (uint32_t)l * 4u : OUT_OF_RANGE;
-            const auto v = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
             f32x4 f;
+            if (TAIL && n < 4) {                            // a row shorter than one load
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    f[e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, l + e < n ? row_off + (uint32_t)(l + e) * 4u : OUT_OF_RANGE, 0, 0));
+                return f;
+            }
+            const uint32_t off = l < n ? row_off + (uint32_t)(TAIL ? min(l, n - 4) : l) * 4u : OUT_OF_RANGE;
+            const auto v = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
             __builtin_memcpy(&f, &v, 16);
             return f;
+        };
+        const int over = 4 - (n & 3);                       // TAIL: elements by which a row's last quad starts early
+        auto place = [&](const f32x4& f, int chunk) {
+            if (!TAIL) return f;
+            const int l = chunk * 16 + 4 * kq;
+            const bool cross = n >= 4 && l < n && l + 4 > n;
+            f32x4 v;
+            v[0] = cross ? (over == 3 ? f[3] : over == 2 ? f[2] : f[1]) : f[0];
+            v[1] = cross ? (over == 3 ? 0.f : over == 2 ? f[3] : f[2]) : f[1];
+            v[2] = cross ? (over == 1 ? f[3] : 0.f) : f[2];
+            v[3] = cross ? 0.f : f[3];
+            return v;
         };
         for (int base = wave; base < nchunks; base += SG_BUNCH * SG_WAVES) {
             f32x4 a[SG_BUNCH], sv[SG_AHEAD][JB];
@@ -203,7 +211,8 @@ __global__ __launch_bounds__(SG_WAVES * 64) void skinny_gemm_nt_kernel(const flo
             for (int u = 0; u < SG_BUNCH; ++u) {
                 f32x4 cur[JB];
 #pragma unroll
-                for (int jb = 0; jb < JB; ++jb) cur[jb] = sv[u % SG_AHEAD][jb];
+                for (int jb = 0; jb < JB; ++jb) cur[jb] = place(sv[u % SG_AHEAD][jb], base + u * SG_WAVES);
+                const f32x4 au = place(a[u], base + u * SG_WAVES);
                 if (u + SG_AHEAD < SG_BUNCH) {
 #pragma unroll
                     for (int jb = 0; jb < JB; ++jb) sv[u % SG_AHEAD][jb] = ld(rs, srow[jb], base + (u + SG_AHEAD) * SG_WAVES);
@@ -211,27 +220,9 @@ __global__ __launch_bounds__(SG_WAVES * 64) void skinny_gemm_nt_kernel(const flo
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
 #pragma unroll
-                    for (int jb = 0; jb < JB; ++jb) acc[jb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][e], cur[jb][e], acc[jb], 0, 0, 0);
+                    for (int jb = 0; jb < JB; ++jb) acc[jb] = __builtin_amdgcn_mfma_f32_16x16x4f32(au[e], cur[jb][e], acc[jb], 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
             }
-        }
-    } else {
-        for (int ch0 = wave; ch0 < nchunks; ch0 += 2 * SG_WAVES) {
-            // two chunks per trip: all their loads are issued before the first MFMA
-            f32x4 a[2], sv[2][JB];
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int l = (ch0 + u * SG_WAVES) * 16 + 4 * kq;      // past the end: l >= n, everything loads as zero
-                a[u] = load4(B, i, n, l);
-#pragma unroll
-                for (int jb = 0; jb < JB; ++jb) sv[u][jb] = load4(S, j0 + 16 * jb + l16, J, l);
-            }
-#pragma unroll
-            for (int u = 0; u < 2; ++u)
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-#pragma unroll
-                    for (int jb = 0; jb < JB; ++jb) acc[jb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][e], sv[u][jb][e], acc[jb], 0, 0, 0);
         }
     }
 #pragma unroll
@@ -282,7 +273,7 @@ template <int JB>
 static void launch_skinny(hipStream_t st, const float* S, int J, const float* B, int n, const float* bias, const essa_cma_scalars* sc,
                           int use_sigma, float* Out) {
     dim3 grid((n + 15) / 16, (J + 16 * JB - 1) / (16 * JB));
-    if (n % 4 == 0)
+    if (n % 4 != 0)
         hipLaunchKernelGGL((skinny_gemm_nt_kernel<true, JB>), grid, dim3(SG_WAVES * 64), 0, st, S, J, B, n, bias, sc, use_sigma, Out);
     else
         hipLaunchKernelGGL((skinny_gemm_nt_kernel<false, JB>), grid, dim3(SG_WAVES * 64), 0, st, S, J, B, n, bias, sc, use_sigma, Out);
