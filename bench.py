@@ -29,8 +29,9 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
-# the default path multiplies on the int8 MFMA, one pass per limb: two passes cost what one bf16 pass would, so its
-# algorithmic flops are priced at the bf16 figure (2.5 PFLOP/s); the one-limb mode at the int8 figure
+# the default path multiplies on the int8 MFMA, one pass per limb (two passes cost what one bf16 pass would), or, with int8
+# weights at prompt-sized row counts, on the bf16 MFMA: its algorithmic flops are priced at the bf16 figure (2.5 PFLOP/s), those
+# of the one-limb mode at the int8 figure
 MFMA_PEAK_TFLOPS = {"w8a16": 2500.0, "w8a8": 5000.0}
 INT8_PEAK_TOPS = 5000.0
 WORKLOADS = ["c2_7b_decode", "c3_32b_prefill", "c4_72b_decode", "c5_7b_es_iter"]
@@ -276,11 +277,13 @@ class Bench:
         roof.update({"kernel": self.kernel_name(), "avg_launch_us": avg_s * 1e6, "launches": gemm_launches,
                      "flops_per_launch": flops_per_launch, "bytes_per_launch": bytes_per_launch,
                      "achieved_GBs": bytes_per_launch / avg_s / 1e9, "achieved_TFLOPs": flops_per_launch / avg_s / 1e12,
-                     "frac_of_hbm": bytes_per_launch / avg_s / 1e9 / HBM_PEAK_GBS,
-                     # the unit the contraction really runs on: int8 MFMA, `limbs` passes over the weights
-                     "int8_mfma": {"passes": limbs, "executed_TOPs": limbs * flops_per_launch / avg_s / 1e12, "peak_TOPs": INT8_PEAK_TOPS,
-                                   "frac_executed": limbs * flops_per_launch / avg_s / 1e12 / INT8_PEAK_TOPS,
-                                   "frac_algorithmic": flops_per_launch / avg_s / 1e12 / INT8_PEAK_TOPS}})
+                     "frac_of_hbm": bytes_per_launch / avg_s / 1e9 / HBM_PEAK_GBS})
+        # the unit the contraction really runs on: int8 MFMA, `limbs` passes over the weights (null on the bf16 MFMA)
+        roof["int8_mfma"] = None
+        if roof["kernel"] != "gemm_bf16_kernel":
+            roof["int8_mfma"] = {"passes": limbs, "executed_TOPs": limbs * flops_per_launch / avg_s / 1e12, "peak_TOPs": INT8_PEAK_TOPS,
+                                 "frac_executed": limbs * flops_per_launch / avg_s / 1e12 / INT8_PEAK_TOPS,
+                                 "frac_algorithmic": flops_per_launch / avg_s / 1e12 / INT8_PEAK_TOPS}
         return roof
 
     def kernel_name(self):
@@ -288,7 +291,9 @@ class Bench:
         projs, R = self.projs[:4], self.R
         col256 = sum(-(-(-(-p.d_out // 32)) // 8) for p in projs)
         if self.cfg.quant == "int8":
-            if -(-R // 128) * col256 >= 512:
+            if self.args.mode == "w8a16" and R > (192 if self.hidden >= 5120 else 256 if self.hidden >= 3072 else 512):
+                return "gemm_bf16_kernel"
+            if self.args.mode == "w8a8" and -(-R // 128) * col256 >= 512:
                 return "gemm_i8_big_kernel"
             return "gemm_i8_stream_kernel" if R <= 64 else "gemm_i8_kernel"
         return "gemm_q4_wide_kernel" if -(-R // 64) * col256 >= 256 else "gemm_i8_kernel<Q4>"
