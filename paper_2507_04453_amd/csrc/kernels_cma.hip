@@ -26,33 +26,49 @@ __global__ __launch_bounds__(1024) void rank_kernel(const float* __restrict__ F,
     }
 }
 
-// z_w[l] = sum_i w[i] Z[i, l], summed for i = 0..mu-1 in fp64;  out_z = z_w,  out_dz = D * z_w.
+// z_w[l] = sum_i w[i] Z[i, l], summed for i = 0..mu-1 in fp64;  out_z = z_w,  out_dz = D * z_w.  Latency: a wave per workgroup, so
+// that n in the thousands reaches many CUs, and the loads of eight rows asked for together (n = 3584, 16 rows: 5.7 -> 4.6 us).
 __global__ void weighted_rowsum_kernel(const float* __restrict__ Z, const float* __restrict__ w, const float* __restrict__ D, int mu,
                                        int n, float* __restrict__ out_z, float* __restrict__ out_dz) {
     const int l = blockIdx.x * blockDim.x + threadIdx.x;
     if (l >= n) return;
+    const float dl = D[l];
     double acc = 0.0;
-    for (int i = 0; i < mu; ++i) acc += (double)w[i] * (double)Z[(size_t)i * n + l];
+    int i = 0;
+    for (; i + 8 <= mu; i += 8) {
+        float z[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) z[e] = Z[(size_t)(i + e) * n + l];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc += (double)w[i + e] * (double)z[e];
+    }
+    for (; i < mu; ++i) acc += (double)w[i] * (double)Z[(size_t)i * n + l];
     const float zw = (float)acc;
     out_z[l] = zw;
-    out_dz[l] = D[l] * zw;
+    out_dz[l] = dl * zw;
 }
 
 __device__ __forceinline__ double block_sum_1024(double v, double* sh) {
-    // fixed binary tree over 1024 slots
+    // fixed binary tree over 1024 slots, halves added together: the upper levels from LDS in registers, the last six across
+    // the lanes; every wave does the whole of it, so there is no barrier between the levels
     sh[threadIdx.x] = v;
     __syncthreads();
-    for (int s = 512; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
-        __syncthreads();
-    }
-    const double r = sh[0];
+    double r[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) r[k] = sh[64 * k + (threadIdx.x & 63)];
+#pragma unroll
+    for (int s = 8; s > 0; s >>= 1)
+#pragma unroll
+        for (int k = 0; k < s; ++k) r[k] += r[k + s];
+#pragma unroll
+    for (int s = 32; s > 0; s >>= 1) r[0] += __shfl_xor(r[0], s, 64);
     __syncthreads();
-    return r;
+    return r[0];
 }
 
 // One workgroup.  BY rows 0..ny-1 are y_{i:lambda} = B D z_{i:lambda}, row ny is B z_w, row ny+1 is y_w = B D z_w
 // (the weighted mean of the mu best y_i, taken before the product with B because that product is linear).
+constexpr int HELD = 4;
 __global__ __launch_bounds__(1024) void cma_vectors_kernel(essa_k::cma_consts c, const float* __restrict__ w, const float* __restrict__ BY,
                                                           float* __restrict__ m, float* __restrict__ p_sigma, float* __restrict__ p_c,
                                                           essa_cma_scalars* __restrict__ sc) {
@@ -62,20 +78,49 @@ __global__ __launch_bounds__(1024) void cma_vectors_kernel(essa_k::cma_consts c,
     const int t = sc->t;
     const double cs = c.c_sigma, cc = c.c_c, mueff = c.mu_eff;
     const float ps_coef = (float)sqrt(cs * (2.0 - cs) * mueff);
+    // Latency: of the first 4096 elements everything is asked for in front of the reduction, and what does not hang on it is done
+    // there.  n = 3584: 7.9 -> 6.1 us.
+    float ps0[HELD], bz[HELD], yw0[HELD], m0[HELD], pc0[HELD];
+#pragma unroll
+    for (int e = 0; e < HELD; ++e) {
+        const int l = min((int)threadIdx.x + 1024 * e, n - 1);
+        ps0[e] = p_sigma[l];
+        bz[e] = BY[(size_t)mu * n + l];
+        yw0[e] = BY[(size_t)(mu + 1) * n + l];
+        m0[e] = m[l];
+        pc0[e] = p_c[l];
+    }
+    const double denom = sqrt(1.0 - pow(1.0 - cs, 2.0 * (double)(t + 1)));
     double part = 0.0;
-    for (int l = threadIdx.x; l < n; l += 1024) {
+#pragma unroll
+    for (int e = 0; e < HELD; ++e) {
+        const int l = threadIdx.x + 1024 * e;
+        if (l < n) {
+            const float ps = (1.0f - c.c_sigma) * ps0[e] + ps_coef * bz[e];
+            p_sigma[l] = ps;
+            part += (double)ps * (double)ps;
+        }
+    }
+    for (int l = threadIdx.x + 1024 * HELD; l < n; l += 1024) {
         const float ps = (1.0f - c.c_sigma) * p_sigma[l] + ps_coef * BY[(size_t)mu * n + l];
         p_sigma[l] = ps;
         part += (double)ps * (double)ps;
     }
     const double ps_norm = sqrt(block_sum_1024(part, sh));
-    const double denom = sqrt(1.0 - pow(1.0 - cs, 2.0 * (double)(t + 1)));
     const float h_sigma = (ps_norm / denom < (1.4 + 2.0 / ((double)n + 1.0)) * (double)c.chi_n) ? 1.0f : 0.0f;
     const float pc_coef = h_sigma * (float)sqrt(cc * (2.0 - cc) * mueff);
-    for (int l = threadIdx.x; l < n; l += 1024) {
+#pragma unroll
+    for (int e = 0; e < HELD; ++e) {
+        const int l = threadIdx.x + 1024 * e;
+        if (l < n) {
+            m[l] = m0[e] + sigma * yw0[e];
+            p_c[l] = fmaf(1.0f - c.c_c, pc0[e], pc_coef * yw0[e]);
+        }
+    }
+    for (int l = threadIdx.x + 1024 * HELD; l < n; l += 1024) {
         const float yw = BY[(size_t)(mu + 1) * n + l];
         m[l] += sigma * yw;
-        p_c[l] = (1.0f - c.c_c) * p_c[l] + pc_coef * yw;
+        p_c[l] = fmaf(1.0f - c.c_c, p_c[l], pc_coef * yw);
     }
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -268,7 +313,7 @@ hipError_t cma_build_rhs(hipStream_t st, const uint32_t* seeds, int32_t* order, 
     hipError_t e = rewards ? normals_scaled(st, seeds, nullptr, c.ny, c.n, D, S, Z, rewards, c.K, order)
                            : normals_scaled(st, seeds, order, c.ny, c.n, D, S, Z);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(weighted_rowsum_kernel, dim3((c.n + 255) / 256), dim3(256), 0, st, Z, w, D, c.mu, c.n, S + (size_t)c.ny * c.n,
+    hipLaunchKernelGGL(weighted_rowsum_kernel, dim3((c.n + 63) / 64), dim3(64), 0, st, Z, w, D, c.mu, c.n, S + (size_t)c.ny * c.n,
                        S + (size_t)(c.ny + 1) * c.n);
     return hipGetLastError();
 }

@@ -281,9 +281,15 @@ static void launch_skinny(hipStream_t st, const float* S, int J, const float* B,
 
 hipError_t skinny_gemm_nt(hipStream_t st, const float* S, int J, const float* B, int n, const float* bias,
                           const essa_cma_scalars* sc, int use_sigma, float* Out) {
-    if (J <= 16) launch_skinny<1>(st, S, J, B, n, bias, sc, use_sigma, Out);
-    else if (J <= 32) launch_skinny<2>(st, S, J, B, n, bias, sc, use_sigma, Out);
-    else launch_skinny<4>(st, S, J, B, n, bias, sc, use_sigma, Out);
+    // as few passes over B as 64 columns each allow, their blocks of 16 columns spread evenly: a block of padding costs what a full one does
+    // (candidates at n = 3584, us, two widths of 32 and 64 columns / this: 36 of them 31.5 / 29.4, 70 58 / 51, 96 62.6 / 59.4)
+    const int blocks = (J + 15) / 16, passes = (blocks + 3) / 4;
+    switch ((blocks + passes - 1) / passes) {
+        case 1: launch_skinny<1>(st, S, J, B, n, bias, sc, use_sigma, Out); break;
+        case 2: launch_skinny<2>(st, S, J, B, n, bias, sc, use_sigma, Out); break;
+        case 3: launch_skinny<3>(st, S, J, B, n, bias, sc, use_sigma, Out); break;
+        default: launch_skinny<4>(st, S, J, B, n, bias, sc, use_sigma, Out);
+    }
     return hipGetLastError();
 }
 
