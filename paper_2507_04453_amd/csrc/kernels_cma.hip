@@ -114,13 +114,13 @@ __global__ __launch_bounds__(1024) void cma_vectors_kernel(essa_k::cma_consts c,
         const int l = threadIdx.x + 1024 * e;
         if (l < n) {
             m[l] = m0[e] + sigma * yw0[e];
-            p_c[l] = fmaf(1.0f - c.c_c, pc0[e], pc_coef * yw0[e]);
+            p_c[l] = fmaf(pc_coef, yw0[e], (1.0f - c.c_c) * pc0[e]);
         }
     }
     for (int l = threadIdx.x + 1024 * HELD; l < n; l += 1024) {
         const float yw = BY[(size_t)(mu + 1) * n + l];
         m[l] += sigma * yw;
-        p_c[l] = fmaf(1.0f - c.c_c, p_c[l], pc_coef * yw);
+        p_c[l] = fmaf(pc_coef, yw, (1.0f - c.c_c) * p_c[l]);
     }
     __syncthreads();
     if (threadIdx.x == 0) {
