@@ -338,7 +338,8 @@ essa_status essa_cmaes_update(essa_ctx* ctx, essa_cma* cma, const uint32_t* seed
  * pairs of columns of C V met during a sweep is <= tol, at most max_sweeps (1..64) times; pairs already below tol / 100
  * are left alone, so a C that has not moved since the last refresh costs one pass over it.  Where the columns are close
  * to the eigenvectors (a C that has moved little, the end of a cold start), simultaneous corrections of all columns take
- * the place of the sweeps, to the same measure.  The state keeps the basis of
+ * the place of the sweeps, to the same measure; they want one n x n fp64 matrix of scratch more, and where that cannot be had
+ * (recorded graphs pin the context's scratch, the card is full) the sweeps go on alone, to the same measure.  The state keeps the basis of
  * its last refresh in fp64 and the next refresh starts from it; after
  * essa_cma_set_basis or essa_cma_import the next refresh starts from the identity.  Off the per-generation
  * path: the tutorial refreshes the basis every 1 / (10 n (c_1 + c_mu)) generations.  The call waits for the device

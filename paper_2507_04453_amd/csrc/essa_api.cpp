@@ -170,6 +170,17 @@ static essa_status next_events(essa_ctx* ctx, hipEvent_t* a, hipEvent_t* b) {
     return ESSA_OK;
 }
 
+// A refused allocation is reported by the return value alone: left behind as the thread's last error it would be picked up by
+// the next launch check, and a call that falls back on less memory would fail after all.
+static hipError_t device_alloc(void** p, size_t bytes) {
+    const hipError_t e = hipMalloc(p, bytes);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        *p = nullptr;
+    }
+    return e;
+}
+
 essa_status essa_ws_reserve(essa_ctx* ctx, size_t bytes) {
     if (bytes <= ctx->ws_bytes) return ESSA_OK;
     if (ctx->capturing)
@@ -181,7 +192,7 @@ essa_status essa_ws_reserve(essa_ctx* ctx, size_t bytes) {
     ctx->ws = nullptr;
     ctx->ws_bytes = 0;
     size_t want = bytes + bytes / 4 + (1u << 20);
-    hipError_t e = hipMalloc(&ctx->ws, want);
+    hipError_t e = device_alloc(&ctx->ws, want);
     if (e != hipSuccess) return essa_fail(ESSA_ERR_OOM, "scratch of %zu bytes: %s", want, hipGetErrorString(e));
     ctx->ws_bytes = want;
     return ESSA_OK;
@@ -190,7 +201,7 @@ essa_status essa_ws_reserve(essa_ctx* ctx, size_t bytes) {
 template <class T>
 static essa_status upload(T** dst, const T* src, size_t count) {
     *dst = nullptr;
-    hipError_t e = hipMalloc((void**)dst, count * sizeof(T) + 256);   // slack: kernels may over-read a vector
+    hipError_t e = device_alloc((void**)dst, count * sizeof(T) + 256);   // slack: kernels may over-read a vector
     if (e != hipSuccess) return essa_fail(ESSA_ERR_OOM, "hipMalloc of %zu bytes: %s", count * sizeof(T), hipGetErrorString(e));
     ESSA_HIP(hipMemset(*dst, 0, count * sizeof(T) + 256));
     ESSA_HIP(hipMemcpy(*dst, src, count * sizeof(T), hipMemcpyHostToDevice));
@@ -367,13 +378,10 @@ extern "C" essa_status essa_proj_create(essa_ctx* ctx, const essa_proj_desc* d, 
             }
             ESSA_TRY(upload(&p->US16, US.data(), US.size()));
             ESSA_TRY(upload(&p->scale16, s16.data(), s16.size()));
-            if (hipMalloc((void**)&p->W16, w16) == hipSuccess) {
+            if (device_alloc((void**)&p->W16, w16) == hipSuccess) {
                 ESSA_HIP(essa_k::expand_weights(nullptr, p->Wt, p->scale, dout, p->n_blocks, nk64, p->W16));
                 ESSA_HIP(hipStreamSynchronize(nullptr));
-            } else {                               // a card too full for the copy: the projection works without it, on the limb kernels
-                (void)hipGetLastError();
-                p->W16 = nullptr;
-            }
+            }                                      // a card too full for the copy: the projection works without it, on the limb kernels
         }
     } else {
         p->groups = din / 128;
@@ -969,7 +977,7 @@ extern "C" essa_status essa_cma_refresh_basis(essa_ctx* ctx, essa_cma* cma, int 
     bool refine = with_steps <= ctx->ws_bytes || (ctx->graphs.empty() && essa_ws_reserve(ctx, with_steps) == ESSA_OK);
     if (!refine) ESSA_TRY(essa_ws_reserve(ctx, essa_k::eig_workspace_bytes(cma->n, false)));
     if (!cma->eigV) {
-        hipError_t e = hipMalloc((void**)&cma->eigV, essa_k::eig_basis_bytes(cma->n));
+        hipError_t e = device_alloc((void**)&cma->eigV, essa_k::eig_basis_bytes(cma->n));
         if (e != hipSuccess) return essa_fail(ESSA_ERR_OOM, "fp64 basis of %zu bytes: %s", essa_k::eig_basis_bytes(cma->n), hipGetErrorString(e));
         cma->eigV_valid = false;
     }

@@ -126,3 +126,46 @@ def test_scratch_pinned_by_a_graph(essa):
     _check(cma.export(), C)
     cma.close()
     ctx.close()
+
+
+def test_card_too_full_for_the_steps(essa):
+    """A card with room for the sweeps' scratch but not for the steps' as well: the refresh does its work on the sweeps."""
+    n = 8192
+    ctx = essa.Context(0)
+    warm = essa.CmaState(ctx, 64, 0.32, None)
+    warm.refresh_basis(ctx)                                # the kernels are loaded before the card fills up
+    cma = essa.CmaState(ctx, n, 0.32, None)
+    d = np.linspace(1, 2, n).astype(np.float32)
+    zero = np.zeros(n, np.float32)
+    cma.import_blob(essa.CmaState.pack_blob(n, 3, 0.5, zero, zero, zero, np.ones(n, np.float32), np.diag(d), np.eye(n, dtype=np.float32)))
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    # the refresh wants scratch (a quarter more than it uses) and the fp64 basis: 1391 + 537 MB with the sweeps alone, 2098 + 537 MB
+    # with the steps; the card is filled until 2098 MB can no longer be had at once and the first two still can
+    def fits(*mb):
+        try:
+            held = [torch.empty(m * 10 ** 6, dtype=torch.uint8, device="cuda") for m in mb]
+        except torch.OutOfMemoryError:
+            held = None
+        ok = held is not None
+        del held
+        torch.cuda.empty_cache()
+        return ok
+
+    fill = [torch.empty(torch.cuda.mem_get_info()[0] - 5 * 10 ** 9, dtype=torch.uint8, device="cuda")]
+    try:
+        while fits(2099):
+            fill.append(torch.empty(48 << 20, dtype=torch.uint8, device="cuda"))
+        assert fits(1392, 538), "no such filling found"
+        print("card filled", flush=True)
+        cma.refresh_basis(ctx)
+    finally:
+        del fill
+        torch.cuda.empty_cache()
+    st = cma.export()
+    assert np.array_equal(st["B"], np.eye(n, dtype=np.float32))
+    np.testing.assert_allclose(st["D"], np.sqrt(d.astype(np.float64)), rtol=2e-7)
+    warm.refresh_basis(ctx)                                # and no error is left behind for the next call
+    cma.close()
+    warm.close()
+    ctx.close()
