@@ -376,12 +376,15 @@ __global__ __launch_bounds__(256, (bf16_smem_bytes<MB, NB, XS, WS>(true) > 80 * 
     // What it reads from memory is asked for in one batch; rank 16 and 32 are separate straight-line code, so that the
     // blocks' MFMA chains, conversions and LDS writes overlap.
     constexpr int ESZ = YBF16 ? 2 : 4, EPV = 16 / ESZ, HALVES = YBF16 ? 1 : 2, CW = BN / HALVES;
-    constexpr int CROW = CW * ESZ + 16, PPR = CW / EPV, NH = NC / HALVES;   // a half holds blocks NH half .. of both wave columns
+    constexpr int CROW = CW * ESZ + 16, PPR = CW / EPV, NH = NC / HALVES;
+    // A half holds NH of the NC 16-channel blocks of both wave columns: of every 128 channels 0..31 and 64..95, then the others, on
+    // either tile width, so that a reward partial is added up in one order whatever tile its group got.
+    auto block = [](int half, int k) { return HALVES == 1 ? k : 4 * (k >> 1) + 2 * half + (k & 1); };
     const bool with_reward = it.rv != nullptr;
     const bool vec_ok = (dout % EPV == 0) && ((reinterpret_cast<uintptr_t>(it.Y) & 15) == 0);
     const gptr<unsigned char> Yb = as_global_w(reinterpret_cast<unsigned char*>(it.Y));
-    auto to_tile = [&](int n, int m, const f32x4& v) {
-        unsigned char* dst = smem + (size_t)((wr * NR + m) * 16 + l16) * CROW + (size_t)((wc * NH + n % NH) * 16 + 4 * kg) * ESZ;
+    auto to_tile = [&](int k, int m, const f32x4& v) {     // k: the block's place in the half
+        unsigned char* dst = smem + (size_t)((wr * NR + m) * 16 + l16) * CROW + (size_t)((wc * NH + k) * 16 + 4 * kg) * ESZ;
         if (YBF16) {
             typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
             *reinterpret_cast<bf16x4*>(dst) = __builtin_convertvector(v, bf16x4);
@@ -392,16 +395,17 @@ __global__ __launch_bounds__(256, (bf16_smem_bytes<MB, NB, XS, WS>(true) > 80 * 
     // the rank columns as the K of 16 x 16 x 32 products: at rank 16 head and tail of U_B sit side by side in one fragment
     // and meet the head of u, then its tail; at rank 32 each is a fragment of its own and lo*lo is left out
     auto finish = [&](auto ks_count, auto half_index) {
-        constexpr int KS = decltype(ks_count)::value, N0 = decltype(half_index)::value * NH;
+        constexpr int KS = decltype(ks_count)::value, HALF = decltype(half_index)::value;
         bf16x8 uu[NR][2], ub[2][KS];                       // head and tail of u; U_B and scales one block ahead
         f32x4 sc[2];
-        auto ask = [&](int n) {
+        auto ask = [&](int k) {
+            const int n = block(HALF, k);
             const int o = min((nb0 + wc * NB) * 32 + n * 16 + l16, dout - 1);
             const gptr<const uint16_t> bp = as_global(it.US16) + (size_t)o * (32 * KS) + 8 * kg;
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) ub[n & 1][ks] = *reinterpret_cast<gptr<const bf16x8>>(bp + 32 * ks);
+            for (int ks = 0; ks < KS; ++ks) ub[k & 1][ks] = *reinterpret_cast<gptr<const bf16x8>>(bp + 32 * ks);
             // the slack behind the array covers a last block that is not full
-            sc[n & 1] = *as_global(reinterpret_cast<const f32x4*>(it.scale16 + min((nb0 + wc * NB) * 32 + n * 16, it.n_blocks * 32 - 16) + 4 * kg));
+            sc[k & 1] = *as_global(reinterpret_cast<const f32x4*>(it.scale16 + min((nb0 + wc * NB) * 32 + n * 16, it.n_blocks * 32 - 16) + 4 * kg));
         };
 #pragma unroll
         for (int m = 0; m < NR; ++m) {
@@ -409,25 +413,26 @@ __global__ __launch_bounds__(256, (bf16_smem_bytes<MB, NB, XS, WS>(true) > 80 * 
 #pragma unroll
             for (int e = 0; e < 2; ++e) uu[m][e] = *reinterpret_cast<gptr<const bf16x8>>(up + e * 16 * KS);
         }
-        ask(N0);
+        ask(0);
         if (a.flags & ESSA_BASE_ONLY) {
 #pragma unroll
             for (int m = 0; m < NR; ++m) uu[m][0] = uu[m][1] = __builtin_bit_cast(bf16x8, (u32x4){0, 0, 0, 0});
         }
-        if constexpr (N0 == 0) wait_loads_and_meet<0>();   // the stages become the output tile
+        if constexpr (HALF == 0) wait_loads_and_meet<0>();   // the stages become the output tile
 #pragma unroll
-        for (int n = N0; n < N0 + NH; ++n) {
+        for (int k = 0; k < NH; ++k) {
+            const int n = block(HALF, k);
             __builtin_amdgcn_sched_barrier(0);
-            if (n + 1 < N0 + NH) ask(n + 1);
+            if (k + 1 < NH) ask(k + 1);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int m = 0; m < NR; ++m) {
-                acc[n][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ub[n & 1][0], uu[m][1], acc[n][m], 0, 0, 0);
-                if (KS == 2) acc[n][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ub[n & 1][KS - 1], uu[m][0], acc[n][m], 0, 0, 0);
-                acc[n][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ub[n & 1][0], uu[m][0], acc[n][m], 0, 0, 0);
+                acc[n][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ub[k & 1][0], uu[m][1], acc[n][m], 0, 0, 0);
+                if (KS == 2) acc[n][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ub[k & 1][KS - 1], uu[m][0], acc[n][m], 0, 0, 0);
+                acc[n][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ub[k & 1][0], uu[m][0], acc[n][m], 0, 0, 0);
             }
 #pragma unroll
-            for (int m = 0; m < NR; ++m) to_tile(n, m, acc[n][m] * sc[n & 1]);
+            for (int m = 0; m < NR; ++m) to_tile(k, m, acc[n][m] * sc[k & 1]);
         }
     };
     if (a.flags & ESSA_LORA_ONLY) {
@@ -443,7 +448,7 @@ __global__ __launch_bounds__(256, (bf16_smem_bytes<MB, NB, XS, WS>(true) > 80 * 
         __syncthreads();
         // full rows, 16 bytes per thread; with a reward vector the row's share over each 128-channel block goes to rowpart
         const int piece = tid % PPR, c0 = piece * EPV;
-        const int o = nb0 * 32 + (c0 / (NH * 16)) * (NC * 16) + half * NH * 16 + c0 % (NH * 16);
+        const int o = nb0 * 32 + (c0 / (NH * 16)) * (NC * 16) + block(half, c0 % (NH * 16) / 16) * 16 + c0 % 16;
         float rvp[EPV];
 #pragma unroll
         for (int e = 0; e < EPV; ++e) rvp[e] = (with_reward && o + e < dout) ? as_global(it.rv)[o + e] : 0.f;

@@ -68,3 +68,35 @@ def test_exact_product_tiles(essa, R, d_in, d_out, r, flags):
     assert not torch.isfinite(Ybad[R // 2]).any() and torch.equal(Ybad[keep], Y[keep])
     gp.close()
     ctx.close()
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_grouped_and_single_calls_agree(essa, dtype):
+    """Which tile a projection gets hangs on its group (here 256 x 256 together, narrower ones alone); its outputs and reward
+    partials do not, to the bit.  Ranks 16 and 32 in one launch, odd widths."""
+    ctx = essa.Context(0)
+    R, K, d_in = 1187, 5, 3584
+    specs = [(3584, 16), (520, 32), (513, 7), (3600, 24)]
+    Xs = [bf16_dev(wl.make_x_bf16(R, d_in, x_id=60 + i)[0]) for i in range(2)]
+    rd = to_dev(np.random.default_rng(8).integers(0, K, R).astype(np.int32))
+    items, vecs = [], []
+    for i, (d_out, r) in enumerate(specs):
+        p = wl.make_projection("t", d_in, d_out, r, "int8", layer=14, proj=i)
+        _, f = oracle_proj(p)
+        sA, sB = candidate_sigmas(f, K, 0.05, i)
+        items.append([gpu_proj(essa, ctx, p), Xs[i == 3], rd, to_dev(sA), to_dev(sB), torch.empty(R, d_out, device="cuda", dtype=dtype)])
+        vecs.append(torch.randn(d_out, device="cuda", generator=torch.Generator(device="cuda").manual_seed(i)))
+    blocks = [(d_out + 127) // 128 for d_out, _ in specs]
+    together = torch.full((sum(blocks), R), float("nan"), device="cuda")
+    essa.essa_svdlora_forward_reward_group(ctx, [tuple(it) for it in items], vecs, together, 0)
+    at = 0
+    for it, v, nb in zip(items, vecs, blocks):
+        Y, alone = torch.empty_like(it[5]), torch.full((nb, R), float("nan"), device="cuda")
+        essa.essa_svdlora_forward_reward_group(ctx, [tuple(it[:5]) + (Y,)], [v], alone, 0)
+        print("d_out=%d" % it[0].d_out, flush=True)
+        assert torch.equal(Y, it[5])
+        assert torch.equal(alone, together[at:at + nb])
+        at += nb
+    for it in items:
+        it[0].close()
+    ctx.close()
