@@ -239,7 +239,7 @@ extern "C" void essa_proj_destroy(essa_proj* p) {
     if (!p) return;
     (void)hipSetDevice(p->device);
     (void)hipDeviceSynchronize();
-    void* ptrs[] = {p->Wq, p->scale, p->zero, p->VA32, p->VA16, p->UB32, p->UB16, p->M, p->Wt, p->VAp, p->St, p->SZ16, p->W16, p->US16, p->scale16};
+    void* ptrs[] = {p->Wq, p->scale, p->zero, p->VA32, p->VA16, p->UB32, p->UB16, p->M, p->Wt, p->VAp, p->St, p->SZ16, p->W16, p->US16, p->scale16, p->VA3p};
     for (void* q : ptrs)
         if (q) (void)hipFree(q);
     delete p;
@@ -376,6 +376,23 @@ extern "C" essa_status essa_proj_create(essa_ctx* ctx, const essa_proj_desc* d, 
                     US[(size_t)o * 2 * rp + rp + j] = f32_to_bf16_rne(v - hf);
                 }
             }
+            // what head and tail leave of V_A's fp32 values (eight bits more: the three together are exact), for the calls that multiplied
+            // by fp32 V_A before they came to this kernel; tiled like VAp, one block of 32 rows per step
+            std::vector<uint16_t> VA3((size_t)((din + 15) / 16) * 512, 0);
+            for (int i = 0; i < din; ++i)
+                for (int j = 0; j < r; ++j) {
+                    float v = VA32[(size_t)i * rp + j];
+                    uint16_t part = 0;
+                    for (int e = 0; e < 3; ++e) {
+                        part = f32_to_bf16_rne(v);
+                        const uint32_t b = (uint32_t)part << 16;
+                        float f;
+                        std::memcpy(&f, &b, 4);
+                        v -= f;
+                    }
+                    VA3[(((size_t)(i / 16) * 2 + (i % 16) / 8) * 32 + j) * 8 + i % 8] = part;
+                }
+            ESSA_TRY(upload(&p->VA3p, VA3.data(), VA3.size()));
             ESSA_TRY(upload(&p->US16, US.data(), US.size()));
             ESSA_TRY(upload(&p->scale16, s16.data(), s16.size()));
             if (device_alloc((void**)&p->W16, w16) == hipSuccess) {
@@ -682,7 +699,7 @@ static essa_status plan_items(essa_ctx* ctx, const essa_fwd_item* items, int n_i
         k.d_in = p->d_in; k.d_out = p->d_out; k.r = p->r; k.rp = p->rp; k.quant = p->quant; k.groups = p->groups;
         k.Wq = p->Wq; k.scale = p->scale; k.zero = p->zero; k.VA32 = p->VA32; k.VA16 = p->VA16;
         k.UB32 = p->UB32; k.UB16 = p->UB16; k.M = p->M;
-        k.Wt = p->Wt; k.W16 = p->W16; k.US16 = p->US16; k.scale16 = p->scale16; k.VAp = p->VAp; k.d_in_pad = p->d_in_pad; k.n_blocks = p->n_blocks;
+        k.Wt = p->Wt; k.W16 = p->W16; k.US16 = p->US16; k.scale16 = p->scale16; k.VA3p = p->VA3p; k.VAp = p->VAp; k.d_in_pad = p->d_in_pad; k.n_blocks = p->n_blocks;
         k.St = p->St; k.SZ16 = p->SZ16; k.Gp = p->Gp;
         if (rv) {
             k.rv = rv[i];
@@ -763,11 +780,12 @@ static essa_status run_items(essa_ctx* ctx, item_list& ks, int x_dtype, int y_dt
     item_list ex, f8, f4, rest;
     const bool exact_ok = x_dtype == ESSA_BF16 && !(flags & ESSA_COMPUTE_W8A8);
     for (int i = 0; i < ks.n; ++i) {
-        const essa_k::fwd_item& k = ks.it[i];
-        const bool exact_can = exact_ok && essa_k::prefill_takes(k);
+        essa_k::fwd_item& k = ks.it[i];
+        const bool exact_can = exact_ok && essa_k::prefill_takes(k), limbs = takes_stream(k, x_dtype, flags);
+        if (limbs) k.VA3p = nullptr;                        // V_A as bf16 head and tail, as in the limb kernels; otherwise all of its bits
         // (the rank-r term alone, a test hook, has the same bits at every row count: it stays with the limb kernels)
         if (exact_can && takes_exact_product(k) && !(flags & ESSA_LORA_ONLY)) ex.push(k);
-        else if (!takes_stream(k, x_dtype, flags)) (exact_can ? ex : rest).push(k);
+        else if (!limbs) (exact_can ? ex : rest).push(k);
         else (k.quant == ESSA_QUANT_INT8_PERCH ? f8 : f4).push(k);
     }
     const unsigned kflags = flags & ~(ESSA_COMPUTE_BF16 | ESSA_VALIDATE);

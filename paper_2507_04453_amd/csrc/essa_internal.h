@@ -79,6 +79,7 @@ struct essa_proj {
     // block (kt, nb), half, sub-step j, lane (kg, l16) = channel 32 nb + 16 half + l16, columns 64 kt + 32 j + 8 kg .. + 7
     uint16_t* W16 = nullptr;
     uint16_t* US16 = nullptr;  // [d_out, 2, rp]  bf16 head and tail of U_B / scale16
+    uint16_t* VA3p = nullptr;  // [ceil(d_in/16)][64 lanes][8]  V_A minus its bf16 head and tail, tiled like VAp
     float* scale16 = nullptr;  // [d_out]  the channel scale; 1 where it is zero (W16's channel is then zero)
     std::vector<float> sA, sB; // own singular values, host copies
 };
@@ -218,6 +219,7 @@ struct fwd_item : stream_item {
     const uint16_t* W16;
     const uint16_t* US16;
     const float* scale16;
+    const uint16_t* VA3p;      // not null: V_A with all its fp32 bits
 };
 hipError_t forward_group(hipStream_t st, const fwd_item* items, int n_items, int x_dtype, int y_dtype,
                          unsigned flags, hipEvent_t ev_start, hipEvent_t ev_stop);

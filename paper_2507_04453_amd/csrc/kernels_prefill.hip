@@ -16,7 +16,7 @@
 namespace {
 
 struct prefill_item {                      // the fields of one projection that these kernels use
-    const uint16_t *X, *W16, *US16, *VAp;
+    const uint16_t *X, *W16, *US16, *VAp, *VA3p;
     const float *scale16, *M, *sigmaA, *sigmaB, *rv;
     const int32_t* row2cand;
     void* Y;
@@ -72,13 +72,14 @@ __device__ __forceinline__ int xcd_contiguous(int b, int T) {
 // ------------------------------------------------------------------------------------------------
 // t = V_A^T x: one workgroup per item, 128 rows and K part; each of its 4 waves owns 32 rows for all columns.  x tiles
 // (128 bytes of each row per step, the 16-byte parts of row r at part ^ ((r >> 1) & 7)) and the operand tiles of V_A
-// (bf16 head and tail) go through LDS, three steps deep.
+// (bf16 head and tail; THIRD: and what they leave of the fp32 value, so that every product has all of V_A's bits) go through
+// LDS, three steps deep.
 // ------------------------------------------------------------------------------------------------
 constexpr int RD_ROWS = 128;
 
-template <int RP>
-__global__ __launch_bounds__(256, 2) void rank_down_kernel(prefill_args a) {
-    constexpr int NBV = RP / 16;                           // 32-column blocks of [heads | tails]
+template <int RP, bool THIRD>
+__global__ __launch_bounds__(256, THIRD && RP == 32 ? 1 : 2) void rank_down_kernel(prefill_args a) {
+    constexpr int NBH = RP / 16, NBV = NBH + (THIRD ? 1 : 0);   // 32-column blocks of [heads | tails], of the third parts
     constexpr int XST = RD_ROWS * 128, VST = 4 * NBV * 1024, ST = XST + VST;
     __shared__ __attribute__((aligned(1024))) unsigned char smem[3 * ST];
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_byte*)smem;
@@ -89,7 +90,7 @@ __global__ __launch_bounds__(256, 2) void rank_down_kernel(prefill_args a) {
 #pragma unroll
     for (int i = 1; i < ESSA_MAX_GROUP; ++i) g += (i < a.n_items && (int)blockIdx.x >= a.tile_start[i]) ? 1 : 0;
     const prefill_item it = fetch_item(a.it[g]);
-    if (it.rp != RP) return;
+    if (it.rp != RP || (it.VA3p != nullptr) != THIRD) return;
     const int ksplit = a.ksplit[g], rel = blockIdx.x - a.tile_start[g], part = rel % ksplit;
     const int m0 = (rel / ksplit) * RD_ROWS;
     const int R = it.R, din = it.d_in;
@@ -98,7 +99,7 @@ __global__ __launch_bounds__(256, 2) void rank_down_kernel(prefill_args a) {
     const int ksteps = din / 16;
 
     const i32x4 xres = buffer_words(it.X + (size_t)m0 * din);
-    const i32x4 vres = buffer_words(it.VAp);
+    const i32x4 vres = buffer_words(it.VAp), vres3 = buffer_words(THIRD ? it.VA3p : it.VAp);
     uint32_t xoff[4];
     int xpart[4];
 #pragma unroll
@@ -118,8 +119,9 @@ __global__ __launch_bounds__(256, 2) void rank_down_kernel(prefill_args a) {
         }
 #pragma unroll
         for (int e = 0; e < NBV; ++e) {
-            const int q = wave * NBV + e, ks = min(4 * k + q / NBV, ksteps - 1);
-            load_lds16(sv + q * 1024, lane * 16, vres, (uint32_t)((ks * NBV + q % NBV) * 1024));
+            const int q = wave * NBV + e, ks = min(4 * k + wave, ksteps - 1);
+            if (e < NBH) load_lds16(sv + q * 1024, lane * 16, vres, (uint32_t)((ks * NBH + e) * 1024));
+            else load_lds16(sv + q * 1024, lane * 16, vres3, (uint32_t)ks * 1024);
         }
     };
     f32x16 acc[NBV];
@@ -155,9 +157,9 @@ __global__ __launch_bounds__(256, 2) void rank_down_kernel(prefill_args a) {
 #pragma unroll
     for (int q = 0; q < 16; ++q) {
         const int row = wave * 32 + 8 * (q >> 2) + 4 * h + (q & 3);
-        float t;
-        if (RP == 32) t = acc[0][q] + acc[NBV - 1][q];
-        else t = acc[0][q] + __shfl_xor(acc[0][q], 16, 64);   // columns j and 16 + j: head and tail of V_A's column j
+        float t = RP == 32 ? acc[NBH - 1][q] : __shfl_xor(acc[0][q], 16, 64);   // rank 16: columns j and 16 + j hold head and tail of V_A's column j
+        if (THIRD) t += acc[NBV - 1][q];
+        t = acc[0][q] + t;
         if (m0 + row < R && l32 < RP) out[(size_t)row * RP + l32] = t;
     }
 }
@@ -542,7 +544,7 @@ bf16_tile pick_tile(const prefill_item* items, int n_items) {
 // the rank-space vectors of every row
 hipError_t launch_rank(hipStream_t st, prefill_args& a) {
     int total = 0, maxR = 0;
-    bool has16 = false, has32 = false;
+    bool has16[2] = {false, false}, has32[2] = {false, false};   // [V_A with all its bits]
     for (int g = 0; g < a.n_items; ++g) {
         // K parts: enough workgroups for two per CU in a group of four projections, no part shorter than four steps; by the
         // item's own size only, so that an item's sums do not depend on what it is grouped with
@@ -551,13 +553,15 @@ hipError_t launch_rank(hipStream_t st, prefill_args& a) {
         a.tile_start[g] = total;
         total += blocks * a.ksplit[g];
         maxR = std::max(maxR, a.it[g].R);
-        (a.it[g].rp == 16 ? has16 : has32) = true;
+        (a.it[g].rp == 16 ? has16 : has32)[a.it[g].VA3p != nullptr] = true;
     }
     for (int g = a.n_items; g <= ESSA_MAX_GROUP; ++g) a.tile_start[g] = total;
-    if (has16) hipLaunchKernelGGL(rank_down_kernel<16>, dim3(total), dim3(256), 0, st, a);
-    if (has32) hipLaunchKernelGGL(rank_down_kernel<32>, dim3(total), dim3(256), 0, st, a);
-    if (has16) hipLaunchKernelGGL(rank_finish_kernel<16>, dim3((maxR + 15) / 16, a.n_items), dim3(256), 0, st, a);
-    if (has32) hipLaunchKernelGGL(rank_finish_kernel<32>, dim3((maxR + 7) / 8, a.n_items), dim3(256), 0, st, a);
+    if (has16[0]) hipLaunchKernelGGL((rank_down_kernel<16, false>), dim3(total), dim3(256), 0, st, a);
+    if (has16[1]) hipLaunchKernelGGL((rank_down_kernel<16, true>), dim3(total), dim3(256), 0, st, a);
+    if (has32[0]) hipLaunchKernelGGL((rank_down_kernel<32, false>), dim3(total), dim3(256), 0, st, a);
+    if (has32[1]) hipLaunchKernelGGL((rank_down_kernel<32, true>), dim3(total), dim3(256), 0, st, a);
+    if (has16[0] || has16[1]) hipLaunchKernelGGL(rank_finish_kernel<16>, dim3((maxR + 15) / 16, a.n_items), dim3(256), 0, st, a);
+    if (has32[0] || has32[1]) hipLaunchKernelGGL(rank_finish_kernel<32>, dim3((maxR + 7) / 8, a.n_items), dim3(256), 0, st, a);
     return hipGetLastError();
 }
 
@@ -596,7 +600,7 @@ hipError_t forward_prefill(hipStream_t st, const fwd_item* items, int n_items, i
     prefill_args a{};
     for (int g = 0; g < n_items; ++g) {
         const fwd_item& k = items[g];
-        a.it[g] = prefill_item{(const uint16_t*)k.X, k.W16, k.US16, k.VAp, k.scale16, k.M, k.sigmaA, k.sigmaB, k.rv, k.row2cand, k.Y,
+        a.it[g] = prefill_item{(const uint16_t*)k.X, k.W16, k.US16, k.VAp, k.VA3p, k.scale16, k.M, k.sigmaA, k.sigmaB, k.rv, k.row2cand, k.Y,
                                k.U16, k.Tpart, k.rowpart, k.sigma_stride, k.R, k.d_in, k.d_out, k.r, k.rp, k.n_blocks};
     }
     a.n_items = n_items;

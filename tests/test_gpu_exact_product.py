@@ -100,3 +100,37 @@ def test_grouped_and_single_calls_agree(essa, dtype):
     for it in items:
         it[0].close()
     ctx.close()
+
+
+@pytest.mark.parametrize("R,d_in,d_out,r", [
+    (3, 400, 150, 8),              # fewer than eight K steps: one K part
+    (3, 400, 150, 24),
+    (130, 2064, 300, 16),          # eight K parts, the last step not full; a row block of two rows
+    (130, 2064, 300, 32),
+    (40, 8208, 64, 8),             # wider than the limb kernels go
+])
+def test_rank_term_of_the_exact_mode(essa, R, d_in, d_out, r):
+    """The rank-r term alone, from the kernels of the exact product, with every bit of V_A's fp32 values.
+
+    Rows (nearly) orthogonal to the columns of V_A: rounded to bf16 (2^-9 / sqrt(3) rms) they keep about 2^-10 of the t = V_A^T x
+    that a row of that length would have, so an error of V_A shows 2^10 times as large as in an ordinary row.  fp32 V_A leaves
+    2^-25 2^10 = 3e-5, the fp32 sums over the K steps as much again or twice, the bf16 head + tail of u and U_B 2^-17: 2e-4 is a bound.
+    V_A as bf16 head + tail (2^-18) would leave 2e-3."""
+    ctx = essa.Context(0)
+    K = 3
+    p = wl.make_projection("t", d_in, d_out, r, "int8", layer=15, proj=1)
+    W, f = oracle_proj(p)
+    gp = gpu_proj(essa, ctx, p)
+    sA, sB = candidate_sigmas(f, K, 0.05)
+    x = wl.make_x_bf16(R, d_in, x_id=61)[1].astype(np.float64)
+    x -= (x @ f["V_A"]) @ f["V_A"].T
+    X = torch.from_numpy(x).to(torch.bfloat16).cuda()
+    r2c = np.random.default_rng(6).integers(0, K, R).astype(np.int32)
+    ref = orc.svdlora_forward(np.zeros_like(W), f, X.double().cpu().numpy(), r2c, sA, sB)
+    Y = torch.full((R, d_out), float("nan"), device="cuda")
+    essa.essa_svdlora_forward(ctx, gp, X, to_dev(r2c), to_dev(sA), to_dev(sB), Y, essa.COMPUTE_BF16 | essa.LORA_ONLY)
+    e_max, e_rms = orc.rel_errors(Y.cpu().numpy(), ref)
+    print("rank term: R=%d d_in=%d r=%d rms %.3g max %.3g" % (R, d_in, r, e_rms, e_max), flush=True)
+    assert e_rms <= 2e-4
+    gp.close()
+    ctx.close()
