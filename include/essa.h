@@ -236,7 +236,8 @@ essa_status essa_theta_to_sigma(essa_ctx* ctx, int P, int r, int n_top, const fl
  * where they are the faster ones (their error is a hundredth of the fixed point's).  With ESSA_COMPUTE_W8A8 the base term uses x quantised per row to one int8
  * (amax/127, round to nearest even).  The LoRA term always sees the unquantised x.
  * A row of X that holds an Inf or a NaN gives a row of NaN (W_deq x + B_k A_k x is then non-finite in every element: NaN,
- * or an infinity of either sign).  A row whose largest magnitude is at most 2^-100 counts as zero in the base term.
+ * or an infinity of either sign).  The fixed point takes a row whose largest magnitude is at most 2^-100 as zero in the base
+ * term; exact products keep what it is.
  * R = 0 is a no-op.
  * ------------------------------------------------------------------------------------------- */
 essa_status essa_svdlora_forward(essa_ctx* ctx, const essa_proj* proj, const void* X, int x_dtype, int R,

@@ -354,18 +354,19 @@ extern "C" essa_status essa_proj_create(essa_ctx* ctx, const essa_proj_desc* d, 
                 }
             }
         ESSA_TRY(upload(&p->Wt, Wt.data(), Wt.size()));
-        // exact-product kernel: the weights as bf16, U_B over the channel scale.  Channels with scale 0 take scale 1 and zero
-        // weights; a scale so extreme that U_B / s could leave the range of bf16 keeps the projection on the other kernels.
+        // exact-product kernel: s_o = m_o 2^(e_o - 8) with 2^8 <= |m_o| < 2^9; the weights as bf16 with the power of two folded in (as exact as
+        // without), U_B over m.  A partial sum is then 2^8 to 2^9 below the output that it grows into, and overflows only if that
+        // does.  Channels with scale 0 take m = 1 and zero weights; scales outside 2^-100 .. 2^100 keep the projection on the other kernels.
         const float* sc = (const float*)d->scales;
         const int nk64 = (din + 63) / 64;
         const size_t w16 = (size_t)nk64 * p->n_blocks * 4096;
         bool usable = w16 < (1u << 31);            // the kernel's 32-bit offsets
-        for (int o = 0; o < dout; ++o) usable = usable && (sc[o] == 0.f || (std::fabs(sc[o]) >= 0x1p-60f && std::fabs(sc[o]) <= 0x1p60f));
+        for (int o = 0; o < dout; ++o) usable = usable && (sc[o] == 0.f || (std::fabs(sc[o]) >= 0x1p-100f && std::fabs(sc[o]) <= 0x1p100f));
         if (usable) {
             std::vector<float> s16(sc, sc + dout);
             std::vector<uint16_t> US(UB16.size(), 0);
             for (int o = 0; o < dout; ++o) {
-                if (s16[o] == 0.f) s16[o] = 1.f;
+                s16[o] = s16[o] == 0.f ? 1.f : std::ldexp(s16[o], 8 - std::ilogb(s16[o]));
                 for (int j = 0; j < r; ++j) {
                     const float v = (float)(UB[(size_t)o * r + j] / (double)s16[o]);
                     const uint16_t hi = f32_to_bf16_rne(v);

@@ -75,12 +75,12 @@ struct essa_proj {
     float* St = nullptr;       // [d_in_pad/128][n_blocks*32] group scales, group major
     uint16_t* SZ16 = nullptr;  // [n_blocks*32][2][Gp] bf16 head and tail of -scale*zero
     int Gp = 0;                // groups rounded up to 16
-    // int8 weights once more as bf16 (exact), for the exact-product kernel: [ceil(d_in/64)][n_blocks][2][2][64 lanes][8],
+    // int8 weights once more as bf16 (exact, times the channel's power of two), for the exact-product kernel: [ceil(d_in/64)][n_blocks][2][2][64 lanes][8],
     // block (kt, nb), half, sub-step j, lane (kg, l16) = channel 32 nb + 16 half + l16, columns 64 kt + 32 j + 8 kg .. + 7
     uint16_t* W16 = nullptr;
     uint16_t* US16 = nullptr;  // [d_out, 2, rp]  bf16 head and tail of U_B / scale16
     uint16_t* VA3p = nullptr;  // [ceil(d_in/16)][64 lanes][8]  V_A minus its bf16 head and tail, tiled like VAp
-    float* scale16 = nullptr;  // [d_out]  the channel scale; 1 where it is zero (W16's channel is then zero)
+    float* scale16 = nullptr;  // [d_out]  what is left of the channel scale; 1 where it is zero (W16's channel is then zero)
     std::vector<float> sA, sB; // own singular values, host copies
 };
 

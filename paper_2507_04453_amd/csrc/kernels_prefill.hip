@@ -1,7 +1,7 @@
 // Forward for int8 base weights and bf16 activations at prompt-sized row counts: exact bf16 products on the bf16 MFMA.
 //
-// An int8 weight is exact in bf16, so W_deq x_i = s_o <q_o, x_i> needs no quantised activations at all when the products run
-// on the bf16 MFMA with fp32 accumulation.  One bf16 pass costs the matrix cores what the two int8 passes of the
+// An int8 weight is exact in bf16, with any power of two, so W_deq x_i = m_o <2^e_o q_o, x_i> needs no quantised activations at all
+// when the products run on the bf16 MFMA with fp32 accumulation.  One bf16 pass costs the matrix cores what the two int8 passes of the
 // fixed-point limbs cost, and everything around the product gets cheaper: no pass that re-expresses the rows, one
 // accumulator per output instead of two (which is what lets a wave own a 128 x 128 patch), and x is read as it is.
 // The projection keeps a bf16 copy of its weights in MFMA-operand tiles for this.
@@ -372,7 +372,7 @@ __global__ __launch_bounds__(256, (bf16_smem_bytes<MB, NB, XS, WS>(true) > 80 * 
         w_nxt = w_nxt == (WS - 1) * WST ? 0 : w_nxt + WST;
     }
     asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");   // the pinned MFMAs' results are not tracked by the compiler
-    // ---- epilogue: rank-r term, scale, LDS tile, rows out.  Y = s_o (<q_o, x> + (U_B / s_o) u): with U_B divided by the channel
+    // ---- epilogue: rank-r term, scale, LDS tile, rows out.  Y = m_o (<2^e_o q_o, x> + (U_B / m_o) u): with U_B divided by the channel
     // scale beforehand the rank-r term (bf16 head+tail: lo*hi + hi*lo + hi*hi per 16 rank columns) is three more MFMAs on the
     // accumulators where they are, and one multiplication per output is all the vector ALU has to do.
     // What it reads from memory is asked for in one batch; rank 16 and 32 are separate straight-line code, so that the
@@ -577,10 +577,11 @@ __global__ __launch_bounds__(256) void expand_weights_kernel(const int8_t* __res
         // columns 64 kt + 32 j + 8 kg .. + 7 of channel 32 nb + l
         const int8_t* src = Wt + ((2 * kt + j) * n_blocks + nb) * 1024 + ((kg >> 1) * 32 + l) * 16 + 8 * (kg & 1);
         const int o = (int)nb * 32 + l;
-        const bool live = o < dout && scale[o] != 0.f;     // a channel of scale 0 contributes nothing
+        const float s = o < dout ? scale[o] : 0.f;         // a channel of scale 0 contributes nothing
+        const float two = s != 0.f ? ldexpf(1.f, ilogbf(s) - 8) : 0.f;
         uint16_t v[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = live ? f32_to_bf16_bits((float)src[e]) : 0;
+        for (int e = 0; e < 8; ++e) v[e] = f32_to_bf16_bits((float)src[e] * two);
         __builtin_memcpy(W16 + p * 8, v, 16);
     }
 }

@@ -134,3 +134,38 @@ def test_rank_term_of_the_exact_mode(essa, R, d_in, d_out, r):
     assert e_rms <= 2e-4
     gp.close()
     ctx.close()
+
+
+def test_rows_at_the_ends_of_the_range(essa):
+    """Rows of 2^-90, 2^100 and 2^120 whose outputs are ordinary finite numbers, and channel scales of 2^-95 and 2^90 beside the usual
+    ones: unscaled sums (70 sqrt(d_in) 2^120) or U_B over the scale would leave fp32.  Every row is held to the bar by itself."""
+    ctx = essa.Context(0)
+    R, d_in, d_out, r, K = 520, 1040, 300, 8, 3
+    p = wl.make_projection("t", d_in, d_out, r, "int8", layer=16, proj=1)
+    W, f = oracle_proj(p)
+    sA, sB = candidate_sigmas(f, K, 0.05)
+    xv = wl.make_x_bf16(R, d_in, x_id=62)[1].astype(np.float64)
+    power = np.array([0, -90, 100, 120])[np.arange(R) % 4]
+    X = torch.from_numpy(np.ldexp(xv, power[:, None])).to(torch.bfloat16).cuda()
+    r2c = np.random.default_rng(6).integers(0, K, R).astype(np.int32)
+    rd, sAd, sBd = to_dev(r2c), to_dev(sA), to_dev(sB)
+    ref = orc.svdlora_forward(W, f, X.double().cpu().numpy(), r2c, sA, sB)
+    gp = gpu_proj(essa, ctx, p)
+    for flags in (0, essa.COMPUTE_BF16):
+        Y = torch.empty(R, d_out, device="cuda")
+        essa.essa_svdlora_forward(ctx, gp, X, rd, sAd, sBd, Y, flags)
+        err = np.linalg.norm(Y.double().cpu().numpy() - ref, axis=1) / np.linalg.norm(ref, axis=1)
+        assert np.all(err <= EXACT_RMS), (flags, err.max())
+    gp.close()
+    p.scales[7], p.scales[8] = 2.0 ** -95, -(2.0 ** 90)     # ordinary rows against extreme channels
+    W, f = oracle_proj(p)
+    gp = gpu_proj(essa, ctx, p)
+    rows = power == 0
+    Xs, refs = X[torch.from_numpy(rows).cuda()].repeat(4, 1).contiguous(), np.tile(orc.svdlora_forward(W, f, X.double().cpu().numpy()[rows], r2c[rows], sA, sB), (4, 1))
+    Y = torch.empty(R, d_out, device="cuda")
+    essa.essa_svdlora_forward(ctx, gp, Xs, to_dev(np.tile(r2c[rows], 4)), sAd, sBd, Y, 0)
+    got = Y.double().cpu().numpy()
+    for cols in (slice(7, 8), slice(8, 9), np.r_[0:7, 9:d_out]):
+        assert np.linalg.norm(got[:, cols] - refs[:, cols]) <= EXACT_RMS * np.linalg.norm(refs[:, cols])
+    gp.close()
+    ctx.close()
