@@ -185,17 +185,33 @@ __global__ __launch_bounds__(256) void rank_finish_kernel(prefill_args a) {
     tv[lr][j] = (j < it.r ? sa : 0.f) * t;
     __syncthreads();
     float u = 0.f;
-    if (!(a.flags & ESSA_BASE_ONLY)) {
 #pragma unroll
-        for (int l = 0; l < RP; ++l) u = fmaf(Ms[j][l], tv[lr][l], u);
-        u *= j < it.r ? sb : 0.f;
-    }
+    for (int l = 0; l < RP; ++l) u = fmaf(Ms[j][l], tv[lr][l], u);
+    u *= j < it.r ? sb : 0.f;
     if (i < R) {
         const uint16_t hi = f32_to_bf16_bits(u);
         const gptr<uint16_t> ur = as_global_w(it.U16) + (size_t)i * 2 * RP;
         ur[j] = hi;
         ur[RP + j] = f32_to_bf16_bits(u - bf16_bits_to_f32(hi));
     }
+}
+
+// The base term alone: u = 0, and NaN for a row that holds an Inf or a NaN, which makes its whole output row NaN as in the full
+// forward (there V_A^T x is non-finite for such a row).  One wave per row.
+__global__ __launch_bounds__(256) void rank_none_kernel(prefill_args a) {
+    const prefill_item& it = a.it[blockIdx.y];
+    const int lane = threadIdx.x & 63, i = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (i >= it.R) return;
+    const gptr<const u32x4> x = as_global(reinterpret_cast<const u32x4*>(it.X + (size_t)i * it.d_in));
+    uint32_t top = 0;                                      // sign gone, bf16 bits order like the values; Inf and NaN lie above
+    for (int k = lane; k < it.d_in / 8; k += 64) {
+        const u32x4 v = x[k];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) top = max(top, max(v[e] & 0x7fff0000u, v[e] << 17 >> 1));
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) top = max(top, (uint32_t)__shfl_xor((int)top, off, 64));
+    if (lane < it.rp) reinterpret_cast<gptr<uint32_t>>(as_global_w(it.U16))[(size_t)i * it.rp + lane] = top < 0x7f800000u ? 0u : 0x7fc07fc0u;
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -416,10 +432,6 @@ __global__ __launch_bounds__(256, (bf16_smem_bytes<MB, NB, XS, WS>(true) > 80 * 
             for (int e = 0; e < 2; ++e) uu[m][e] = *reinterpret_cast<gptr<const bf16x8>>(up + e * 16 * KS);
         }
         ask(0);
-        if (a.flags & ESSA_BASE_ONLY) {
-#pragma unroll
-            for (int m = 0; m < NR; ++m) uu[m][0] = uu[m][1] = __builtin_bit_cast(bf16x8, (u32x4){0, 0, 0, 0});
-        }
         if constexpr (HALF == 0) wait_loads_and_meet<0>();   // the stages become the output tile
 #pragma unroll
         for (int k = 0; k < NH; ++k) {
@@ -606,7 +618,11 @@ hipError_t forward_prefill(hipStream_t st, const fwd_item* items, int n_items, i
     }
     a.n_items = n_items;
     a.flags = flags;
-    if (!(flags & ESSA_BASE_ONLY)) {
+    if (flags & ESSA_BASE_ONLY) {
+        int maxR = 0;
+        for (int g = 0; g < n_items; ++g) maxR = std::max(maxR, a.it[g].R);
+        hipLaunchKernelGGL(rank_none_kernel, dim3((maxR + 3) / 4, n_items), dim3(256), 0, st, a);
+    } else {
         hipError_t e = launch_rank(st, a);
         if (e != hipSuccess) return e;
     }
