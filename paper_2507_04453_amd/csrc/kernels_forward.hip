@@ -143,7 +143,7 @@ __global__ __launch_bounds__(256) void rowquant_kernel(fwd_args a) {
 // ------------------------------------------------------------------------------------------------
 // 2a. generic fp32 GEMM (fp32 activations, or shapes the MFMA kernels do not take)
 // ------------------------------------------------------------------------------------------------
-// Four consecutive columns k .. k + 3 of an activation row and of a weight row as fp32, for any alignment and format; columns past
+// Four consecutive columns k .. k + 3 of an activation row and of a row of int8 weights as fp32, for any alignment; columns past
 // d_in and rows past the last are zeros.
 template <bool XBF16>
 __device__ __forceinline__ f32x4 x_quad(const essa_k::fwd_item& it, int i, int k) {
@@ -161,18 +161,9 @@ __device__ __forceinline__ f32x4 w_quad(const essa_k::fwd_item& it, int o, int k
     f32x4 v = {0.f, 0.f, 0.f, 0.f};
     if (o >= it.d_out || k >= it.d_in) return v;
     const size_t at = (size_t)o * it.d_in + k;
-    if (it.quant == ESSA_QUANT_INT8_PERCH) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-            if (k + e < it.d_in) v[e] = (float)((const int8_t*)it.Wq)[at + e];
-        return v;
-    }
-    // 4-bit: d_in is a multiple of 128, so the four columns share a group and two whole bytes
-    const uint32_t b = *reinterpret_cast<const uint16_t*>((const uint8_t*)it.Wq + (at >> 1));
-    const size_t gi = (size_t)o * it.groups + (k >> 7);
-    const float sc = it.scale[gi], z = it.zero[gi];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = sc * ((float)((b >> (4 * e)) & 15u) - z);
+    for (int e = 0; e < 4; ++e)
+        if (k + e < it.d_in) v[e] = (float)((const int8_t*)it.Wq)[at + e];
     return v;
 }
 
@@ -261,8 +252,10 @@ __global__ __launch_bounds__(512) void gemm_f32_kernel(fwd_args a) {
                         for (int n = 0; n < MT; ++n) acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[s][m][j], wv[s][n][j], acc[m][n], 0, 0, 0);
         }
     };
-    // 4-bit weights: a wave takes whole groups of 128 columns, so that their scales and zeros are fetched once
-    auto loop_q4 = [&]() {
+    // 4-bit weights: a wave takes whole groups of 128 columns, so that their scales and zeros are fetched once.  The order of the sums
+    // is the same whether the rows can be loaded 16 bytes at a time (FAST) or not.
+    auto loop_q4 = [&](auto fast_c) {
+        constexpr bool FAST = decltype(fast_c)::value;
         size_t xrow[MT], wrow[MT];
         int o[MT];
 #pragma unroll
@@ -287,7 +280,9 @@ __global__ __launch_bounds__(512) void gemm_f32_kernel(fwd_args a) {
                     const int k = grp * 128 + half * 64 + 16 * s + 4 * kg;
 #pragma unroll
                     for (int m = 0; m < MT; ++m) {
-                        if (XBF16) {
+                        if (!FAST) {
+                            xv[s][m] = x_quad<XBF16>(it, m0 + 16 * m + l16, k);
+                        } else if (XBF16) {
                             const uint2 b = *reinterpret_cast<const uint2*>((const uint16_t*)it.X + xrow[m] + k);
                             xv[s][m] = (f32x4){__uint_as_float(b.x << 16), __uint_as_float(b.x & 0xffff0000u), __uint_as_float(b.y << 16), __uint_as_float(b.y & 0xffff0000u)};
                         } else {
@@ -312,9 +307,11 @@ __global__ __launch_bounds__(512) void gemm_f32_kernel(fwd_args a) {
         }
     };
     const bool x_quads = din % 4 == 0 && ((uintptr_t)it.X & (XBF16 ? 7 : 15)) == 0;
-    if (!x_quads) loop(std::false_type{});
-    else if (it.quant == ESSA_QUANT_INT8_PERCH) loop(std::true_type{});
-    else loop_q4();
+    if (it.quant == ESSA_QUANT_INT8_PERCH) {
+        if (x_quads) loop(std::true_type{});
+        else loop(std::false_type{});
+    } else if (x_quads) loop_q4(std::true_type{});
+    else loop_q4(std::false_type{});
 #pragma unroll
     for (int m = 0; m < MT; ++m)
 #pragma unroll

@@ -25,6 +25,7 @@ pytestmark = pytest.mark.gpu
     (20, 1152, 40, 8, "int4", False, 0),     # nine groups: the first wave takes two
     (520, 128, 1100, 8, "int4", False, 0),   # 4-bit weights on the 32 x 32 tiles
     (9, 256, 24, 8, "int4", False, 1),       # and with rows not aligned for 16-byte loads
+    (21, 1152, 40, 8, "int4", False, 1),     # nine groups
     (33, 328, 96, 4, "int8", True, 0),       # bf16 rows of 8-byte multiples
     (33, 326, 96, 24, "int8", True, 0),      # bf16 rows of odd words
 ])
@@ -59,7 +60,7 @@ def test_f32_product(essa, R, d_in, d_out, r, quant, bf16, shift):
     essa.essa_svdlora_forward(ctx, gp, Xbad, rd, sAd, sBd, bad)
     keep = torch.arange(R, device="cuda") != R // 2
     assert not torch.isfinite(bad[R // 2]).any()
-    if shift == 0:
-        assert torch.equal(bad[keep], good[keep])
+    # (with shift the clone is aligned and the rows themselves are not: the order of the sums does not hang on it)
+    assert torch.equal(bad[keep], good[keep])
     gp.close()
     ctx.close()
