@@ -2282,7 +2282,7 @@ hipError_t launch_gemm_mb(hipStream_t st, stream_args& a, int mb) {
         case 2: return launch_gemm<2, LIMBS, YBF16, false, Q4>(st, a, nullptr);
         default:
             // no taller tile: with int8 weights its double-buffered fragments do not fit the register file (row counts
-            // that large take the 128 x 256 kernel anyway), and with 4-bit weights, whose loop runs its MFMA, scaling
+            // that large take the exact product or the 128 x 256 kernel anyway), and with 4-bit weights, whose loop runs its MFMA, scaling
             // and LDS phases one after the other, two 64-row workgroups per CU overlap each other's phases and beat
             // one 128-row workgroup (c4: 290 -> 240 us per launch)
             return launch_gemm<2, LIMBS, YBF16, false, Q4>(st, a, nullptr);
@@ -2311,10 +2311,10 @@ int pick_q4_wide(const stream_args& a) {
     return tiles >= 256 ? 64 : 0;
 }
 
-// one limb: the 128 x 256 tile pays off once it fills the chip a few times over (two-limb groups of that size take the
-// exact-product kernel instead)
+// the 128 x 256 tile pays off once it fills the chip a few times over.  With two limbs it is for what the exact-product kernel
+// cannot take at such sizes (extreme channel scales, fewer than 128 channels, 2 GB of weights) and for the rank-r term alone:
+// q, k, v, o of a 5120-wide layer at 32768 rows 4.4 ms, with 64 x 128 tiles 6.7; 3584 wide at 8192 rows 0.59 and 0.77
 bool takes_big(const stream_args& a) {
-    if (a.limbs != 1) return false;
     long long tiles = 0;
     for (int g = 0; g < a.n_items; ++g)
         tiles += (long long)((a.it[g].R + BIG_BM - 1) / BIG_BM) * ((a.it[g].n_blocks + BIG_NB - 1) / BIG_NB);
@@ -2394,7 +2394,8 @@ hipError_t forward_stream(hipStream_t st, const fwd_item* items, int n_items, in
         // the reward partials (one per 128 channels and row) span four of this kernel's workgroups: a pass of their own
         return essa_k::rowdot_blocks(st, items, n_items, y_dtype);
     } else if (to_big) {
-        e = y_dtype == ESSA_BF16 ? launch_gemm_big<1, true>(st, a) : launch_gemm_big<1, false>(st, a);
+        if (a.limbs == 2) e = y_dtype == ESSA_BF16 ? launch_gemm_big<2, true>(st, a) : launch_gemm_big<2, false>(st, a);
+        else e = y_dtype == ESSA_BF16 ? launch_gemm_big<1, true>(st, a) : launch_gemm_big<1, false>(st, a);
     } else if (q4_rows == 64)
         e = y_dtype == ESSA_BF16 ? launch_gemm_q4_wide<2, true>(st, a) : launch_gemm_q4_wide<2, false>(st, a);
     else if (items[0].quant == ESSA_QUANT_INT4_G128)

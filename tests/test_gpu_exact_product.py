@@ -173,3 +173,33 @@ def test_rows_at_the_ends_of_the_range(essa):
         assert np.linalg.norm(got[:, cols] - refs[:, cols]) <= EXACT_RMS * np.linalg.norm(refs[:, cols])
     gp.close()
     ctx.close()
+
+
+def test_what_the_exact_product_cannot_take(essa):
+    """A channel scale below its range keeps a projection on the fixed-point kernels at every row count, here on the 128 x 256 tile:
+    two limbs, ragged rows and channels, both output types, the reward partials."""
+    ctx = essa.Context(0)
+    R, d_in, d_out, r, K = 2050, 192, 15400, 16, 3
+    p = wl.make_projection("t", d_in, d_out, r, "int8", layer=17, proj=1)
+    p.scales[5] = 1e-36
+    W, f = oracle_proj(p)
+    gp = gpu_proj(essa, ctx, p)
+    sA, sB = candidate_sigmas(f, K, 0.05)
+    xb, xv = wl.make_x_bf16(R, d_in, x_id=63)
+    r2c = np.random.default_rng(6).integers(0, K, R).astype(np.int32)
+    Xd, rd, sAd, sBd = bf16_dev(xb), to_dev(r2c), to_dev(sA), to_dev(sB)
+    Y = torch.empty(R, d_out, device="cuda")
+    essa.essa_svdlora_forward(ctx, gp, Xd, rd, sAd, sBd, Y)
+    ref = orc.svdlora_forward(W, f, xv, r2c, sA, sB)
+    assert orc.rel_errors(Y.cpu().numpy(), ref)[1] <= 2e-4      # the repository's bar for the fixed point
+    assert np.abs(Y[:, 5].double().cpu().numpy() - ref[:, 5]).max() <= 2e-3 * np.abs(ref).max()      # the rank-r term alone in that channel
+    Yb, v = torch.empty(R, d_out, device="cuda", dtype=torch.bfloat16), torch.randn(d_out, device="cuda")
+    nblk = (d_out + 127) // 128
+    rowpart = torch.full((nblk, R), float("nan"), device="cuda")
+    essa.essa_svdlora_forward_reward_group(ctx, [(gp, Xd, rd, sAd, sBd, Yb)], [v], rowpart, 0)
+    assert torch.equal(Yb, Y.to(torch.bfloat16))
+    pad = torch.zeros(R, nblk * 128 - d_out, device="cuda", dtype=torch.float64)
+    want = torch.cat([Yb.double() * v.double(), pad], 1).view(R, nblk, 128)
+    assert torch.all((rowpart.T.double() - want.sum(2)).abs() <= 128 * 2.0 ** -24 * want.abs().sum(2) + 1e-30)
+    gp.close()
+    ctx.close()
