@@ -7,7 +7,7 @@
 // The projection keeps a bf16 copy of its weights in MFMA-operand tiles for this.
 //
 // Three launches: rank_down (t = V_A^T x, K split over workgroups), rank_finish (u = sB_c * (M (sA_c * t)) as bf16 head and
-// tail), gemm_bf16 (base product, scale, U_B u, output tile, reward partials).
+// tail; the 64-row tile does this itself), gemm_bf16 (base product, scale, U_B u, output tile, reward partials).
 #include "forward_device.h"
 #include <hip/hip_ext.h>
 #include <algorithm>
@@ -164,36 +164,64 @@ __global__ __launch_bounds__(256, THIRD && RP == 32 ? 1 : 2) void rank_down_kern
     }
 }
 
-// u = sB_c * (M (sA_c * t)), the K parts of t added in ascending order; bf16 head and tail per row.  Latency and a few
-// bytes per row: one thread per element.
+// u = sB_c * (M (sA_c * t)) of ROWS rows from i0 on by 256 threads, the K parts of t added in ascending order; put(row, j, head, tail)
+// gets every element as two bf16.  With several elements a thread the parts are asked for without a branch between them (26.8 -> 25.5 us,
+// 3584 -> 512 at 512 rows); with one, and rows in the thousands, no more of them than there are.  tv: ROWS x (RP + 4) floats of LDS, Ms: RP x (RP + 4).
+template <int RP, int ROWS, class F>
+__device__ __forceinline__ void rank_rows(const prefill_item& it, int ksplit, int i0, float* tv, float* Ms, F&& put) {
+    constexpr int P = RP + 4, EU = ROWS * RP / 256;
+    const int tid = threadIdx.x, j = tid % RP, R = it.R;
+    const gptr<const float> tp = as_global(it.Tpart);
+    float part[EU][8], sa[EU], sb[EU], m[(RP * RP + 255) / 256];
+#pragma unroll
+    for (int k = 0; k < EU; ++k) {
+        const int ic = min(i0 + (tid + 256 * k) / RP, R - 1);
+        const size_t at = (size_t)as_global(it.row2cand)[ic] * it.sigma_stride + min(j, it.r - 1);
+        sa[k] = as_global(it.sigmaA)[at];
+        sb[k] = as_global(it.sigmaB)[at];
+#pragma unroll
+        for (int s = 0; s < 8; ++s)
+            if (EU > 1 || s < ksplit) part[k][s] = tp[((size_t)min(s, ksplit - 1) * R + ic) * RP + j];
+    }
+#pragma unroll
+    for (int k = 0; k < (RP * RP + 255) / 256; ++k) m[k] = as_global(it.M)[tid + 256 * k];
+#pragma unroll
+    for (int k = 0; k < (RP * RP + 255) / 256; ++k) Ms[(tid + 256 * k) / RP * P + j] = m[k];
+#pragma unroll
+    for (int k = 0; k < EU; ++k) {
+        float t = part[k][0];
+#pragma unroll
+        for (int s = 1; s < 8; ++s)
+            if (s < ksplit) t += part[k][s];
+        tv[(tid + 256 * k) / RP * P + j] = (j < it.r ? sa[k] : 0.f) * t;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < EU; ++k) {
+        const int lr = (tid + 256 * k) / RP;
+        float u = 0.f;
+#pragma unroll
+        for (int l = 0; l < RP; ++l) u = fmaf(Ms[j * P + l], tv[lr * P + l], u);
+        u *= j < it.r ? sb[k] : 0.f;
+        const uint16_t hi = f32_to_bf16_bits(u);
+        put(lr, j, hi, f32_to_bf16_bits(u - bf16_bits_to_f32(hi)));
+    }
+}
+
+// The rows' u for the tiles that do not form it themselves.  Latency and a few bytes per row: one thread per element.
 template <int RP>
 __global__ __launch_bounds__(256) void rank_finish_kernel(prefill_args a) {
     constexpr int ROWS = 256 / RP, P = RP + 4;
-    __shared__ float tv[ROWS][P], Ms[RP][P];
+    __shared__ float tv[ROWS * P], Ms[RP * P];
     const prefill_item& it = a.it[blockIdx.y];
-    if (it.rp != RP) return;
-    const int tid = threadIdx.x, lr = tid / RP, j = tid % RP;
-    const int R = it.R, i = blockIdx.x * ROWS + lr, ic = min(i, R - 1);
-    if (blockIdx.x * ROWS >= R) return;
-    const int c = as_global(it.row2cand)[ic];
-    const gptr<const float> tp = as_global(it.Tpart);
-    float t = tp[(size_t)ic * RP + j];
-    for (int s = 1; s < a.ksplit[blockIdx.y]; ++s) t += tp[((size_t)s * R + ic) * RP + j];
-    const size_t at = (size_t)c * it.sigma_stride + min(j, it.r - 1);
-    const float sa = as_global(it.sigmaA)[at], sb = as_global(it.sigmaB)[at];
-    for (int e = tid; e < RP * RP; e += 256) Ms[e / RP][e % RP] = as_global(it.M)[e];
-    tv[lr][j] = (j < it.r ? sa : 0.f) * t;
-    __syncthreads();
-    float u = 0.f;
-#pragma unroll
-    for (int l = 0; l < RP; ++l) u = fmaf(Ms[j][l], tv[lr][l], u);
-    u *= j < it.r ? sb : 0.f;
-    if (i < R) {
-        const uint16_t hi = f32_to_bf16_bits(u);
-        const gptr<uint16_t> ur = as_global_w(it.U16) + (size_t)i * 2 * RP;
+    const int i0 = blockIdx.x * ROWS;
+    if (it.rp != RP || i0 >= it.R) return;
+    rank_rows<RP, ROWS>(it, a.ksplit[blockIdx.y], i0, tv, Ms, [&](int lr, int j, uint16_t hi, uint16_t lo) {
+        if (i0 + lr >= it.R) return;
+        const gptr<uint16_t> ur = as_global_w(it.U16) + (size_t)(i0 + lr) * 2 * RP;
         ur[j] = hi;
-        ur[RP + j] = f32_to_bf16_bits(u - bf16_bits_to_f32(hi));
-    }
+        ur[RP + j] = lo;
+    });
 }
 
 // The base term alone: u = 0, and NaN for a row that holds an Inf or a NaN, which makes its whole output row NaN as in the full
@@ -226,7 +254,8 @@ __global__ __launch_bounds__(256) void rank_none_kernel(prefill_args a) {
 //   sub-step 0: MFMAs; fragments of sub-step 1; the activations of step kt + XS - 1
 //   meet: step kt + 1 is complete in LDS, nobody reads step kt any more
 //   sub-step 1: MFMAs; fragments of sub-step 0 of step kt + 1; the weights of step kt + WS
-// with the reads and loads spread between the MFMAs.  The 16 x 16 x 32 form of the MFMA, not 32 x 32 x 16: same rate on
+// with the reads and loads spread between the MFMAs (the eight MFMAs of the 64-row tile's sub-step are over before an LDS read
+// comes back, so it asks for everything in front of them: 28.4 against 29.5 us, 3584 -> 512 at 512 rows).  The 16 x 16 x 32 form of the MFMA, not 32 x 32 x 16: same rate on
 // paper, but the chip runs these kernels at its power limit and the smaller form does more per watt (MFMAs alone, operands
 // in registers, all CUs: 2026 against 1714 TFLOP/s; this kernel on 32768 x 5120 x 12288: 3.13 against 3.39 ms).
 //
@@ -236,10 +265,13 @@ __global__ __launch_bounds__(256) void rank_none_kernel(prefill_args a) {
 // ------------------------------------------------------------------------------------------------
 thread_local hipEvent_t tl_pre_start = nullptr, tl_pre_stop = nullptr;   // events of the GEMM launch being timed
 
+// The 64-row tile forms the u of its rows itself, in LDS behind its stages: the rows (head and tail), M, sA t.
+constexpr size_t OWN_UROW = 144, OWN_MS = 64 * OWN_UROW, OWN_TV = OWN_MS + 32 * 36 * 4, OWN_BYTES = OWN_TV + 64 * 36 * 4;
+
 template <int MB, int NB, int XS, int WS>
 constexpr size_t bf16_smem_bytes(bool ybf16) {
     constexpr size_t BM = 64 * MB, BN = 64 * NB;
-    const size_t stages = XS * BM * 128 + WS * BN * 128;
+    const size_t stages = XS * BM * 128 + WS * BN * 128 + (MB == 1 ? OWN_BYTES : 0);
     const size_t ctile = ybf16 ? BM * (BN * 2 + 16) : BM * (BN / 2 * 4 + 16);
     return stages > ctile ? stages : ctile;
 }
@@ -254,7 +286,8 @@ __device__ __forceinline__ void mfma_pinned(const bf16x8& A, const bf16x8& B, f3
 template <int MB, int NB, int XS, int WS, bool YBF16>
 __global__ __launch_bounds__(256, (bf16_smem_bytes<MB, NB, XS, WS>(true) > 80 * 1024 ? 1 : 2)) void gemm_bf16_kernel(prefill_args a) {
     constexpr int BM = 64 * MB, BN = 64 * NB, NBT = BN / 32;
-    constexpr uint32_t XST = BM * 128, WST = BN * 128, W0 = XS * XST;
+    constexpr uint32_t XST = BM * 128, WST = BN * 128, W0 = XS * XST, U0 = W0 + WS * WST;
+    constexpr bool OWN_U = MB == 1;
     constexpr int NR = 2 * MB, NC = 2 * NB;                // 16-row and 16-channel blocks of a wave
     constexpr int NMF = NR * NC, NRD = NR + NC, XL = 2 * MB, WL = 2 * NB;     // per wave: MFMAs and fragment reads of a sub-step, loads of a step
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
@@ -335,6 +368,23 @@ __global__ __launch_bounds__(256, (bf16_smem_bytes<MB, NB, XS, WS>(true) > 80 * 
     constexpr int AHEAD_X = (XS - 2) * (XL + WL), AHEAD_W = (WS - 1) * XL + (WS - 2) * WL, AHEAD = AHEAD_X < AHEAD_W ? AHEAD_X : AHEAD_W;
     static_assert(FIRST < 64 && AHEAD < 64, "the load counter has six bits");
 
+    if constexpr (OWN_U) {                                 // u of the tile's rows, while the first steps are on their way
+        static_assert(bf16_smem_bytes<MB, NB, XS, WS>(true) == U0 + OWN_BYTES && BM * (BN * 2 + 16) <= U0, "behind the stages and the output tile");
+        const auto own = [&](int row, int j, uint16_t hi, uint16_t lo) {
+            uint16_t* ur = reinterpret_cast<uint16_t*>(smem + U0 + (size_t)row * OWN_UROW);
+            ur[j] = hi;
+            ur[rp + j] = lo;
+        };
+        float *tv = reinterpret_cast<float*>(smem + U0 + OWN_TV), *Ms = reinterpret_cast<float*>(smem + U0 + OWN_MS);
+        if (a.flags & ESSA_BASE_ONLY) {                    // zeros, or NaN for a row that is not finite
+            for (int e = tid; e < BM * rp; e += 256) {
+                const gptr<const uint16_t> ur = as_global(it.U16) + (size_t)min(m0 + e / rp, R - 1) * 2 * rp + e % rp;
+                own(e / rp, e % rp, ur[0], ur[rp]);
+            }
+        } else if (rp == 16) rank_rows<16, BM>(it, a.ksplit[g], m0, tv, Ms, own);
+        else rank_rows<32, BM>(it, a.ksplit[g], m0, tv, Ms, own);
+    }
+
     uint32_t xr[2];                                        // this lane's fragment of sub-step j inside an activation stage
 #pragma unroll
     for (int j = 0; j < 2; ++j) xr[j] = (wr * 32 * MB + l16) * 128 + (((4 * j + kg) ^ ((l16 >> 1) & 7)) * 16);
@@ -364,7 +414,7 @@ __global__ __launch_bounds__(256, (bf16_smem_bytes<MB, NB, XS, WS>(true) > 80 * 
                 mfma_pinned(fw[j][i / NR], fx[j][i % NR], acc[i / NR][i % NR]);
                 static_for<NRD>([&](auto rc) {
                     constexpr int r = rc;
-                    if constexpr (r * NMF / NRD == i) read_frag(j ^ 1, r, j == 1 ? x_nxt : x_cur, j == 1 ? w_nxt : w_cur, j ^ 1);
+                    if constexpr ((MB == 1 ? r / 2 : r * NMF / NRD) == i) read_frag(j ^ 1, r, j == 1 ? x_nxt : x_cur, j == 1 ? w_nxt : w_cur, j ^ 1);
                 });
                 // one load every few MFMAs, never a burst; the weights, which have the shorter way to go, as early as they can
                 if constexpr (j == 1) {
@@ -427,9 +477,13 @@ __global__ __launch_bounds__(256, (bf16_smem_bytes<MB, NB, XS, WS>(true) > 80 * 
         };
 #pragma unroll
         for (int m = 0; m < NR; ++m) {
-            const gptr<const uint16_t> up = as_global(it.U16) + (size_t)min(m0 + (wr * NR + m) * 16 + l16, R - 1) * (32 * KS) + 8 * (KS == 1 ? kg & 1 : kg);
+            const int row = (wr * NR + m) * 16 + l16, at = 8 * (KS == 1 ? kg & 1 : kg);
+            const gptr<const uint16_t> up = as_global(it.U16) + (size_t)min(m0 + row, R - 1) * (32 * KS) + at;
 #pragma unroll
-            for (int e = 0; e < 2; ++e) uu[m][e] = *reinterpret_cast<gptr<const bf16x8>>(up + e * 16 * KS);
+            for (int e = 0; e < 2; ++e) {
+                if constexpr (OWN_U) uu[m][e] = *reinterpret_cast<const bf16x8*>(smem + U0 + (size_t)row * OWN_UROW + 2 * (at + e * 16 * KS));
+                else uu[m][e] = *reinterpret_cast<gptr<const bf16x8>>(up + e * 16 * KS);
+            }
         }
         ask(0);
         if constexpr (HALF == 0) wait_loads_and_meet<0>();   // the stages become the output tile
@@ -527,13 +581,18 @@ hipError_t launch_bf16(hipStream_t st, prefill_args& a) {
 }
 
 // Which tile takes a group.  Tiles go to the 256 CUs in rounds, so the time is (rounds) x (K steps) x (time of a step), plus
-// what does not depend on K.  Microseconds as measured on groups of four projections, 2048 to 8192 wide, 72 to 32768 rows,
-// with weights coming from HBM (a few per cent to a tenth off everywhere in that range):
+// what does not depend on K.  Microseconds of a whole call as measured on single projections and groups of up to four, 512 to
+// 18944 columns, 8 to 32768 rows, weights from HBM (a few per cent to a tenth off everywhere in that range, more where the
+// weights alone are HBM time):
 //   256 x 256  18 + steps x rounds x (1.12 .. 1.47 as the last round fills: the clock falls)   82 us at 1024 x 3584
-//   256 x 128  13 + steps x rounds x 0.85                                                       59 us at  512 x 3584
-//   128 x 128  11.5 + steps x 0.53 x (tiles per CU), two workgroups per CU                      75 us at 1024 x 3584
-//   128 x 128 with five LDS stages, one workgroup per CU: 11.5 + steps x 0.7, one round only    49 us at  512 x 3584
-enum bf16_tile { TILE_256x256, TILE_256x128, TILE_128x128, TILE_128x128_DEEP };
+//   256 x 128  13 + steps x rounds x 0.85                                                       54 us at  512 x 3584
+//   128 x 128  11.5 + steps x 0.53 x (tiles per CU), two workgroups per CU                      59 us at 1024 x 3584
+// and while there is no more than one tile per CU, which leaves each of them waiting for its own LDS reads and loads:
+//   128 x 128 with five stages of each operand  10.5 + steps x (0.46 .. 0.56)                   40 us at  512 x 3584
+//   64 x 128, u formed by the tile itself        7 + steps x (0.34 .. 0.44)                     27 us at  512 x 3584, q alone
+// (128 x 128 with three and two stages takes 39 us for q alone there, 111 for 8192 x 8192 where five take 88, and 230 for 18944 ->
+// 3584 at 64 rows where the 64-row tile takes 143; the launch of rank_finish and its wait that the 64-row tile saves are 3 us.)
+enum bf16_tile { TILE_256x256, TILE_256x128, TILE_128x128, TILE_128x128_DEEP, TILE_64x128 };
 bf16_tile pick_tile(const prefill_item* items, int n_items) {
     auto tiles = [&](int bm, int bn) {
         long long t = 0;
@@ -543,18 +602,18 @@ bf16_tile pick_tile(const prefill_item* items, int n_items) {
     int nk = 1;
     for (int g = 0; g < n_items; ++g) nk = std::max(nk, (items[g].d_in + 63) / 64);
     auto rounds = [](long long t) { return (double)((t + 255) / 256); };
-    const long long t44 = tiles(256, 256), t42 = tiles(256, 128), t22 = tiles(128, 128);
-    const double fill = (double)t44 / (256.0 * rounds(t44));
-    const double c[4] = {18.0 + nk * rounds(t44) * (1.12 + 0.35 * fill), 13.0 + nk * rounds(t42) * 0.85, 11.5 + nk * rounds(t22) * 0.53,
-                         t22 <= 256 ? 11.5 + nk * 0.7 : 1e30};
+    const long long t44 = tiles(256, 256), t42 = tiles(256, 128), t22 = tiles(128, 128), t12 = tiles(64, 128);
+    const double fill = (double)t44 / (256.0 * rounds(t44)), never = 1e30;
+    const double c[5] = {18.0 + nk * rounds(t44) * (1.12 + 0.35 * fill), 13.0 + nk * rounds(t42) * 0.85, t22 > 256 ? 11.5 + nk * rounds(t22) * 0.53 : never,
+                         t22 <= 256 ? 10.5 + nk * (0.46 + 0.1 * (t22 / 256.0)) : never, t12 <= 256 ? 7.0 + nk * (0.34 + 0.1 * (t12 / 256.0)) : never};
     int best = 0;
-    for (int i = 1; i < 4; ++i)
+    for (int i = 1; i < 5; ++i)
         if (c[i] < c[best]) best = i;
     return (bf16_tile)best;
 }
 
 // the rank-space vectors of every row
-hipError_t launch_rank(hipStream_t st, prefill_args& a) {
+hipError_t launch_rank(hipStream_t st, prefill_args& a, bool finish) {
     int total = 0, maxR = 0;
     bool has16[2] = {false, false}, has32[2] = {false, false};   // [V_A with all its bits]
     for (int g = 0; g < a.n_items; ++g) {
@@ -572,6 +631,7 @@ hipError_t launch_rank(hipStream_t st, prefill_args& a) {
     if (has16[1]) hipLaunchKernelGGL((rank_down_kernel<16, true>), dim3(total), dim3(256), 0, st, a);
     if (has32[0]) hipLaunchKernelGGL((rank_down_kernel<32, false>), dim3(total), dim3(256), 0, st, a);
     if (has32[1]) hipLaunchKernelGGL((rank_down_kernel<32, true>), dim3(total), dim3(256), 0, st, a);
+    if (!finish) return hipGetLastError();
     if (has16[0] || has16[1]) hipLaunchKernelGGL(rank_finish_kernel<16>, dim3((maxR + 15) / 16, a.n_items), dim3(256), 0, st, a);
     if (has32[0] || has32[1]) hipLaunchKernelGGL(rank_finish_kernel<32>, dim3((maxR + 7) / 8, a.n_items), dim3(256), 0, st, a);
     return hipGetLastError();
@@ -618,23 +678,25 @@ hipError_t forward_prefill(hipStream_t st, const fwd_item* items, int n_items, i
     }
     a.n_items = n_items;
     a.flags = flags;
+    const bf16_tile tile = pick_tile(a.it, n_items);
     if (flags & ESSA_BASE_ONLY) {
         int maxR = 0;
         for (int g = 0; g < n_items; ++g) maxR = std::max(maxR, a.it[g].R);
         hipLaunchKernelGGL(rank_none_kernel, dim3((maxR + 3) / 4, n_items), dim3(256), 0, st, a);
     } else {
-        hipError_t e = launch_rank(st, a);
+        hipError_t e = launch_rank(st, a, tile != TILE_64x128);
         if (e != hipSuccess) return e;
     }
     tl_pre_start = ev_start;
     tl_pre_stop = ev_stop;
     const bool yb = y_dtype == ESSA_BF16;
     hipError_t e;
-    switch (pick_tile(a.it, n_items)) {
+    switch (tile) {
         case TILE_256x256: e = yb ? launch_bf16<4, 4, 3, 2, true>(st, a) : launch_bf16<4, 4, 3, 2, false>(st, a); break;
         case TILE_256x128: e = yb ? launch_bf16<4, 2, 3, 4, true>(st, a) : launch_bf16<4, 2, 3, 4, false>(st, a); break;
         case TILE_128x128: e = yb ? launch_bf16<2, 2, 3, 2, true>(st, a) : launch_bf16<2, 2, 3, 2, false>(st, a); break;
-        default: e = yb ? launch_bf16<2, 2, 5, 5, true>(st, a) : launch_bf16<2, 2, 5, 5, false>(st, a); break;
+        case TILE_128x128_DEEP: e = yb ? launch_bf16<2, 2, 5, 5, true>(st, a) : launch_bf16<2, 2, 5, 5, false>(st, a); break;
+        default: e = yb ? launch_bf16<1, 2, 5, 4, true>(st, a) : launch_bf16<1, 2, 5, 4, false>(st, a); break;
     }
     tl_pre_start = tl_pre_stop = nullptr;
     return e;

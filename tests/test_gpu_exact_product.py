@@ -106,6 +106,37 @@ def test_grouped_and_single_calls_agree(essa, dtype):
     ctx.close()
 
 
+@pytest.mark.parametrize("r,flags,dtype", [(7, 0, torch.bfloat16), (24, 0, torch.float32), (16, 8, torch.float32), (32, 8, torch.bfloat16)])
+def test_row_counts_that_change_the_tile(essa, r, flags, dtype):
+    """1000 rows take the 64 x 128 tile, which forms u itself, 2000 the 128 x 128 one with five stages, 3700 the 256 x 128 one: the
+    rows that they share have the same bits, outputs and reward partials, with and without the rank-r term."""
+    ctx = essa.Context(0)
+    K, d_in, d_out, Rs = 5, 1040, 1050, (1000, 2000, 3700)
+    p = wl.make_projection("t", d_in, d_out, r, "int8", layer=18, proj=1)
+    W, f = oracle_proj(p)
+    gp = gpu_proj(essa, ctx, p)
+    sA, sB = candidate_sigmas(f, K, 0.05)
+    xb, xv = wl.make_x_bf16(Rs[-1], d_in, x_id=64)
+    X, v = bf16_dev(xb), torch.randn(d_out, device="cuda")
+    r2c = np.random.default_rng(6).integers(0, K, Rs[-1]).astype(np.int32)
+    rd, sAd, sBd = to_dev(r2c), to_dev(sA), to_dev(sB)
+    for more in (0, essa.BASE_ONLY):
+        got = []
+        for R in Rs:
+            print("r=%d flags=%d R=%d" % (r, flags | more, R), flush=True)
+            Y = torch.full((R, d_out), float("nan"), device="cuda", dtype=dtype)
+            part = torch.full(((d_out + 127) // 128, R), float("nan"), device="cuda")
+            essa.essa_svdlora_forward_reward_group(ctx, [(gp, X[:R], rd[:R], sAd, sBd, Y)], [v], part, 0, flags | more)
+            got.append((Y[:Rs[0]], part[:, :Rs[0]]))
+        for Y, part in got[1:]:
+            assert torch.equal(Y, got[0][0]) and torch.equal(part, got[0][1])
+        ref = orc.svdlora_forward(W, f, xv[:Rs[0]], r2c[:Rs[0]], sA, sB, base_only=more != 0)
+        if dtype == torch.float32:
+            assert orc.rel_errors(got[0][0].cpu().numpy(), ref)[1] <= EXACT_RMS
+    gp.close()
+    ctx.close()
+
+
 @pytest.mark.parametrize("R,d_in,d_out,r", [
     (3, 400, 150, 8),              # fewer than eight K steps: one K part
     (3, 400, 150, 24),
