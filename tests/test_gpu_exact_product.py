@@ -20,7 +20,7 @@ BF16_RMS, BF16_MAX = 1e-3, 2e-2
 @pytest.mark.parametrize("R,d_in,d_out,r,flags", [
     (1, 48, 129, 5, 8),            # one row, less than one K step, asked for by the flag
     (129, 64, 128, 32, 8),         # exactly one K step and one tile of channels, one row past a tile
-    (513, 1040, 300, 32, 0),       # taken by itself: the first row count, K ends 16 columns into a step
+    (513, 1040, 300, 32, 0),       # taken by itself, K ends 16 columns into a step
     (1030, 528, 9001, 16, 0),      # two 128 x 128 tiles per CU, odd output width (element-wise stores)
     (700, 2064, 8200, 16, 0),      # 256 x 128 tiles
     (2050, 4112, 5000, 24, 0),     # 256 x 256 tiles, ragged rows and channels
@@ -133,6 +133,28 @@ def test_row_counts_that_change_the_tile(essa, r, flags, dtype):
         ref = orc.svdlora_forward(W, f, xv[:Rs[0]], r2c[:Rs[0]], sA, sB, base_only=more != 0)
         if dtype == torch.float32:
             assert orc.rel_errors(got[0][0].cpu().numpy(), ref)[1] <= EXACT_RMS
+    gp.close()
+    ctx.close()
+
+
+@pytest.mark.parametrize("d_in,first", [(2048, 512), (3072, 385), (6144, 385), (6160, 512)])
+def test_where_exact_products_begin(essa, d_in, first):
+    """The line depends on rows and columns alone: exact products from it on, the fixed point's 3e-5 below it."""
+    ctx = essa.Context(0)
+    K, d_out, r = 3, 136, 8
+    p = wl.make_projection("t", d_in, d_out, r, "int8", layer=19, proj=1)
+    W, f = oracle_proj(p)
+    gp = gpu_proj(essa, ctx, p)
+    sA, sB = candidate_sigmas(f, K, 0.05)
+    xb, xv = wl.make_x_bf16(first, d_in, x_id=65)
+    r2c = np.random.default_rng(6).integers(0, K, first).astype(np.int32)
+    X, rd, sAd, sBd, ref = bf16_dev(xb), to_dev(r2c), to_dev(sA), to_dev(sB), orc.svdlora_forward(W, f, xv, r2c, sA, sB)
+    rms = []
+    for R in (first - 1, first):
+        Y = torch.empty(R, d_out, device="cuda")
+        essa.essa_svdlora_forward(ctx, gp, X[:R], rd[:R], sAd, sBd, Y)
+        rms.append(orc.rel_errors(Y.cpu().numpy(), ref[:R])[1])
+    assert rms[1] <= 2e-6 < 1e-5 <= rms[0] <= 2e-4, rms     # 2^-24 sqrt(d_in / 32) and the 2^-17 of the rank-r term; half a unit of 16 bits
     gp.close()
     ctx.close()
 
