@@ -121,6 +121,10 @@ typedef struct essa_proj_desc {
     const float* lora_B;      /* float [d_out, r]                                                     */
 } essa_proj_desc;
 
+/* Device memory: two bytes per int8 weight (one and a quarter per 4-bit weight), and two more per int8 weight for the bf16 copy that
+ * exact products read, while that leaves half of the card's memory free.  A projection created on a fuller card, with a channel scale
+ * outside 2^-100 .. 2^100 or with more than 2 GB of such a copy works without it: by itself it then stays with the fixed point at
+ * every row count, and ESSA_COMPUTE_BF16 takes the generic kernels. */
 essa_status essa_proj_create(essa_ctx* ctx, const essa_proj_desc* desc, essa_proj** out);
 void essa_proj_destroy(essa_proj* proj);
 /* Copies the factors' own singular values S_A[r], S_B[r] (descending) to HOST arrays. */

@@ -181,6 +181,17 @@ static hipError_t device_alloc(void** p, size_t bytes) {
     return e;
 }
 
+// Memory that makes calls faster but that they can do without is taken while it leaves half of the card free: what a program has to
+// have (other projections, scratch, its own tensors) comes after it and must not find it gone.
+static bool room_for_copy(size_t bytes) {
+    size_t free_bytes = 0, total = 0;
+    if (hipMemGetInfo(&free_bytes, &total) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return free_bytes >= total / 2 && free_bytes - total / 2 >= bytes;
+}
+
 essa_status essa_ws_reserve(essa_ctx* ctx, size_t bytes) {
     if (bytes <= ctx->ws_bytes) return ESSA_OK;
     if (ctx->capturing)
@@ -396,10 +407,10 @@ extern "C" essa_status essa_proj_create(essa_ctx* ctx, const essa_proj_desc* d, 
             ESSA_TRY(upload(&p->VA3p, VA3.data(), VA3.size()));
             ESSA_TRY(upload(&p->US16, US.data(), US.size()));
             ESSA_TRY(upload(&p->scale16, s16.data(), s16.size()));
-            if (device_alloc((void**)&p->W16, w16) == hipSuccess) {
+            if (room_for_copy(w16) && device_alloc((void**)&p->W16, w16) == hipSuccess) {
                 ESSA_HIP(essa_k::expand_weights(nullptr, p->Wt, p->scale, dout, p->n_blocks, nk64, p->W16));
                 ESSA_HIP(hipStreamSynchronize(nullptr));
-            }                                      // a card too full for the copy: the projection works without it, on the limb kernels
+            }                                      // otherwise the projection works without it, on the limb kernels
         }
     } else {
         p->groups = din / 128;

@@ -256,3 +256,48 @@ def test_what_the_exact_product_cannot_take(essa):
     assert torch.all((rowpart.T.double() - want.sum(2)).abs() <= 128 * 2.0 ** -24 * want.abs().sum(2) + 1e-30)
     gp.close()
     ctx.close()
+
+
+def test_copy_of_the_weights_leaves_half_of_the_card(essa):
+    """A projection created while less than half of the card is free takes no bf16 copy (2 bytes a weight on top of 2) and works all
+    the same: the fixed point's error by itself, exact products by the flag."""
+    ctx = essa.Context(0)
+    R, d_in, d_out, r, K = 520, 4096, 4096, 8, 3
+    p = wl.make_projection("t", d_in, d_out, r, "int8", layer=20, proj=1)
+    W, f = oracle_proj(p)
+    sA, sB = candidate_sigmas(f, K, 0.05)
+    xb, xv = wl.make_x_bf16(R, d_in, x_id=66)
+    r2c = np.random.default_rng(6).integers(0, K, R).astype(np.int32)
+    X, rd, sAd, sBd = bf16_dev(xb), to_dev(r2c), to_dev(sA), to_dev(sB)
+    Y = torch.empty(R, d_out, device="cuda")
+    sample = np.arange(0, R, 37)
+    ref = orc.svdlora_forward(W, f, xv[sample], r2c[sample], sA, sB)
+
+    def error(gp, flags):
+        essa.essa_svdlora_forward(ctx, gp, X, rd, sAd, sBd, Y, flags)
+        return orc.rel_errors(Y.cpu().numpy()[sample], ref)[1]
+
+    def create():
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info()[0]
+        gp = gpu_proj(essa, ctx, p)
+        return gp, before - torch.cuda.mem_get_info()[0]
+
+    roomy, taken = create()
+    assert taken >= 4 * d_in * d_out and error(roomy, 0) <= 2e-6
+    free, total = torch.cuda.mem_get_info()
+    fill = [torch.empty(free - total // 2, dtype=torch.uint8, device="cuda")]
+    while torch.cuda.mem_get_info()[0] >= total // 2:
+        fill.append(torch.empty(64 << 20, dtype=torch.uint8, device="cuda"))
+    try:
+        tight, taken = create()
+    finally:
+        del fill
+        torch.cuda.empty_cache()
+    assert 2 * d_in * d_out <= taken < 3 * d_in * d_out
+    assert 1e-5 <= error(tight, 0) <= 2e-4                  # the repository's bar for the fixed point
+    assert error(tight, essa.COMPUTE_BF16) <= EXACT_RMS
+    assert error(roomy, 0) <= 2e-6                          # a copy that is there stays
+    tight.close()
+    roomy.close()
+    ctx.close()
