@@ -291,11 +291,14 @@ class Bench:
         projs, R = self.projs[:4], self.R
         col256 = sum(-(-(-(-p.d_out // 32)) // 8) for p in projs)
         if self.cfg.quant == "int8":
-            if self.args.mode == "w8a16" and R > (192 if self.hidden >= 5120 else 256 if self.hidden >= 3072 else 512):
+            if self.args.mode == "w8a16" and R > (384 if 3072 <= self.hidden <= 6144 else 511):
                 return "gemm_bf16_kernel"
             if self.args.mode == "w8a8" and -(-R // 128) * col256 >= 512:
                 return "gemm_i8_big_kernel"
             return "gemm_i8_stream_kernel" if R <= 64 else "gemm_i8_kernel"
+        few = (128 if self.hidden <= 4096 else 96) if self.forward_only else (64 if self.hidden >= 3072 else 0)
+        if R <= few:
+            return "gemm_q4_stream_kernel"
         return "gemm_q4_wide_kernel" if -(-R // 64) * col256 >= 256 else "gemm_i8_kernel<Q4>"
 
     def config(self):

@@ -2312,7 +2312,7 @@ int pick_q4_wide(const stream_args& a) {
 }
 
 // the 128 x 256 tile pays off once it fills the chip a few times over.  With two limbs it is for what the exact-product kernel
-// cannot take at such sizes (extreme channel scales, fewer than 128 channels, 2 GB of weights) and for the rank-r term alone:
+// cannot take at such sizes (no bf16 copy of the weights, fewer than 128 channels) and for the rank-r term alone:
 // q, k, v, o of a 5120-wide layer at 32768 rows 4.4 ms, with 64 x 128 tiles 6.7; 3584 wide at 8192 rows 0.59 and 0.77
 bool takes_big(const stream_args& a) {
     long long tiles = 0;
