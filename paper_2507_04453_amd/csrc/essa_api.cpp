@@ -250,7 +250,7 @@ extern "C" void essa_proj_destroy(essa_proj* p) {
     if (!p) return;
     (void)hipSetDevice(p->device);
     (void)hipDeviceSynchronize();
-    void* ptrs[] = {p->Wq, p->scale, p->zero, p->VA32, p->VA16, p->UB32, p->UB16, p->M, p->Wt, p->VAp, p->St, p->SZ16, p->W16, p->US16, p->scale16, p->VA3p};
+    void* ptrs[] = {p->Wq, p->scale, p->zero, p->VA32, p->VA16, p->UB32, p->UB16, p->M, p->Wt, p->VAp, p->St, p->SZ16, p->W16, p->E16};
     for (void* q : ptrs)
         if (q) (void)hipFree(q);
     delete p;
@@ -404,9 +404,19 @@ extern "C" essa_status essa_proj_create(essa_ctx* ctx, const essa_proj_desc* d, 
                     }
                     VA3[(((size_t)(i / 16) * 2 + (i % 16) / 8) * 32 + j) * 8 + i % 8] = part;
                 }
-            ESSA_TRY(upload(&p->VA3p, VA3.data(), VA3.size()));
-            ESSA_TRY(upload(&p->US16, US.data(), US.size()));
-            ESSA_TRY(upload(&p->scale16, s16.data(), s16.size()));
+            // one upload for the three: creation is mostly these calls for a small projection
+            std::vector<uint8_t> all;
+            auto add = [&](const void* src, size_t bytes) {
+                const size_t at = all.size();
+                all.resize(at + (bytes + 511) / 256 * 256);    // zeros behind each: kernels may over-read a vector
+                std::memcpy(all.data() + at, src, bytes);
+                return at;
+            };
+            const size_t us_at = add(US.data(), US.size() * 2), sc_at = add(s16.data(), s16.size() * 4), va_at = add(VA3.data(), VA3.size() * 2);
+            ESSA_TRY(upload(&p->E16, all.data(), all.size()));
+            p->US16 = (uint16_t*)(p->E16 + us_at);
+            p->scale16 = (float*)(p->E16 + sc_at);
+            p->VA3p = (uint16_t*)(p->E16 + va_at);
             if (room_for_copy(w16) && device_alloc((void**)&p->W16, w16) == hipSuccess) {
                 ESSA_HIP(essa_k::expand_weights(nullptr, p->Wt, p->scale, dout, p->n_blocks, nk64, p->W16));
                 ESSA_HIP(hipStreamSynchronize(nullptr));

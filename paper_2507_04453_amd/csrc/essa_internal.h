@@ -78,6 +78,7 @@ struct essa_proj {
     // int8 weights once more as bf16 (exact, times the channel's power of two), for the exact-product kernel: [ceil(d_in/64)][n_blocks][2][2][64 lanes][8],
     // block (kt, nb), half, sub-step j, lane (kg, l16) = channel 32 nb + 16 half + l16, columns 64 kt + 32 j + 8 kg .. + 7
     uint16_t* W16 = nullptr;
+    uint8_t* E16 = nullptr;    // the allocation that the next three lie in
     uint16_t* US16 = nullptr;  // [d_out, 2, rp]  bf16 head and tail of U_B / scale16
     uint16_t* VA3p = nullptr;  // [ceil(d_in/16)][64 lanes][8]  V_A minus its bf16 head and tail, tiled like VAp
     float* scale16 = nullptr;  // [d_out]  what is left of the channel scale; 1 where it is zero (W16's channel is then zero)
