@@ -788,23 +788,23 @@ static bool takes_stream(const essa_k::fwd_item& k, int x_dtype, unsigned flags)
 
 // Rows from which an int8 item in the default mode takes the exact-product kernel instead of the int8 limbs: where the 64 x 128
 // limb tiles of a layer need one round on the 256 CUs more than they do below.  The line depends on the item's rows and columns
-// alone, not on what it is grouped with, so that grouped and single calls agree bit for bit; a projection with few channels
-// called alone loses a little just above it and a layer loses less just below.  us a call, limbs / exact (q, k, v, o of 2048, 3584,
-// 5120 and 8192 columns, k and v with 256, 512, 1024 and 1024 channels):
+// alone, not on what it is grouped with, so that grouped and single calls agree bit for bit; above it a projection or a pair alone
+// is no slower than on the limbs either.  us a call, limbs / exact (q, k, v, o of 2048, 3584, 5120 and 8192 columns, k and v with
+// 256, 512, 1024 and 1024 channels):
 //            q, k, v, o     q, k, v        q or o         k and v        k or v
-//   2048     512  30 / 27                  513  20 / 20                  513 17 / 19, 1187 21 / 20
-//   3584     257  39 / 36   257  35 / 28   257  27 / 27   384  21 / 26   384  22 / 26
-//            384  42 / 36   384  30 / 29   512  28 / 27   512  23 / 26   512  23 / 26
-//            448  48 / 44   512  43 / 37   577  41 / 36   640  25 / 26   768  26 / 26
-//            768  67 / 54   768  46 / 39   768  43 / 35   1187 39 / 27   1187 29 / 26
-//   5120     256  54 / 65   512  61 / 65   320  34 / 39   256  25 / 32   512  28 / 32
-//            320  58 / 73   640  83 / 71   512  54 / 45   768  44 / 35   1024 35 / 33
+//   2048     512  30 / 27                  513  20 / 20                  513 17 / 16, 1187 21 / 16
+//   3584     257  39 / 36   257  35 / 28   257  27 / 26   385  21 / 21   385  22 / 21
+//            384  42 / 36   384  30 / 28   385  32 / 27   512  22 / 21   512  23 / 21
+//            448  48 / 44   512  43 / 37   512  28 / 27   768  26 / 22   768  26 / 21
+//            768  67 / 54   768  46 / 39   768  43 / 35   1187 38 / 26   1187 29 / 21
+//   5120     256  54 / 65   512  61 / 65   320  34 / 39   385  28 / 28   385  27 / 26
+//            320  58 / 73   640  83 / 71   512  54 / 45   512  29 / 28   1024 34 / 27
 //            512  84 / 79
-//   8192     256 119 / 114  384  89 / 110  320  70 / 76   512  40 / 47   256  33 / 44
-//            384 162 / 145  512 125 / 109  512  80 / 88   768  60 / 49   512  37 / 44
-//            512 200 / 163  640 148 / 118  576 110 / 103                 1024 43 / 45
+//   8192     256 119 / 114  384  89 / 110  320  70 / 76   512  42 / 40   512  37 / 36
+//            384 162 / 145  512 125 / 109  512  80 / 88   768  60 / 49   1024 45 / 37
+//            512 200 / 163  640 148 / 118  576 110 / 103
 // Groups of 4096 (384 rows 55 / 58, 512 70 / 62) and 6144 columns (256 70 / 88, 384 99 / 95, 512 129 / 98) go with those of 3584
-// and 5120.  Fewer than 128 output channels would leave most of that kernel's narrowest tile to padding.
+// and 5120.  Fewer than 128 output channels would leave much of that kernel's tiles to padding.
 static bool takes_exact_product(const essa_k::fwd_item& k) {
     return k.d_out >= 128 && k.R > (k.d_in >= 3072 && k.d_in <= 6144 ? 384 : 511);
 }

@@ -7,7 +7,7 @@
 // The projection keeps a bf16 copy of its weights in MFMA-operand tiles for this.
 //
 // Three launches: rank_down (t = V_A^T x, K split over workgroups), rank_finish (u = sB_c * (M (sA_c * t)) as bf16 head and
-// tail; the 64-row tile does this itself), gemm_bf16 (base product, scale, U_B u, output tile, reward partials).
+// tail; the 64-row tiles do this themselves), gemm_bf16 (base product, scale, U_B u, output tile, reward partials).
 #include "forward_device.h"
 #include <hip/hip_ext.h>
 #include <algorithm>
@@ -254,8 +254,8 @@ __global__ __launch_bounds__(256) void rank_none_kernel(prefill_args a) {
 //   sub-step 0: MFMAs; fragments of sub-step 1; the activations of step kt + XS - 1
 //   meet: step kt + 1 is complete in LDS, nobody reads step kt any more
 //   sub-step 1: MFMAs; fragments of sub-step 0 of step kt + 1; the weights of step kt + WS
-// with the reads and loads spread between the MFMAs (the eight MFMAs of the 64-row tile's sub-step are over before an LDS read
-// comes back, so it asks for everything in front of them: 28.4 against 29.5 us, 3584 -> 512 at 512 rows).  The 16 x 16 x 32 form of the MFMA, not 32 x 32 x 16: same rate on
+// with the reads and loads spread between the MFMAs (the four or eight MFMAs of a 64-row tile's sub-step are over before an LDS
+// read comes back, so they ask for everything in front of them: 28.4 against 29.5 us, 3584 -> 512 at 512 rows, 64 x 128).  The 16 x 16 x 32 form of the MFMA, not 32 x 32 x 16: same rate on
 // paper, but the chip runs these kernels at its power limit and the smaller form does more per watt (MFMAs alone, operands
 // in registers, all CUs: 2026 against 1714 TFLOP/s; this kernel on 32768 x 5120 x 12288: 3.13 against 3.39 ms).
 //
@@ -265,14 +265,14 @@ __global__ __launch_bounds__(256) void rank_none_kernel(prefill_args a) {
 // ------------------------------------------------------------------------------------------------
 thread_local hipEvent_t tl_pre_start = nullptr, tl_pre_stop = nullptr;   // events of the GEMM launch being timed
 
-// The 64-row tile forms the u of its rows itself, in LDS behind its stages: the rows (head and tail), M, sA t.
+// A 64-row tile forms the u of its rows itself, in LDS behind its stages: the rows (head and tail), M, sA t.
 constexpr size_t OWN_UROW = 144, OWN_MS = 64 * OWN_UROW, OWN_TV = OWN_MS + 32 * 36 * 4, OWN_BYTES = OWN_TV + 64 * 36 * 4;
 
 template <int MB, int NB, int XS, int WS>
 constexpr size_t bf16_smem_bytes(bool ybf16) {
     constexpr size_t BM = 64 * MB, BN = 64 * NB;
     const size_t stages = XS * BM * 128 + WS * BN * 128 + (MB == 1 ? OWN_BYTES : 0);
-    const size_t ctile = ybf16 ? BM * (BN * 2 + 16) : BM * (BN / 2 * 4 + 16);
+    const size_t ctile = ybf16 ? BM * (BN * 2 + 16) : BM * ((NB == 1 ? BN : BN / 2) * 4 + 16);
     return stages > ctile ? stages : ctile;
 }
 
@@ -443,10 +443,10 @@ __global__ __launch_bounds__(256, (bf16_smem_bytes<MB, NB, XS, WS>(true) > 80 * 
     // accumulators where they are, and one multiplication per output is all the vector ALU has to do.
     // What it reads from memory is asked for in one batch; rank 16 and 32 are separate straight-line code, so that the
     // blocks' MFMA chains, conversions and LDS writes overlap.
-    constexpr int ESZ = YBF16 ? 2 : 4, EPV = 16 / ESZ, HALVES = YBF16 ? 1 : 2, CW = BN / HALVES;
+    constexpr int ESZ = YBF16 ? 2 : 4, EPV = 16 / ESZ, HALVES = YBF16 || NB == 1 ? 1 : 2, CW = BN / HALVES;
     constexpr int CROW = CW * ESZ + 16, PPR = CW / EPV, NH = NC / HALVES;
-    // A half holds NH of the NC 16-channel blocks of both wave columns: of every 128 channels 0..31 and 64..95, then the others, on
-    // either tile width, so that a reward partial is added up in one order whatever tile its group got.
+    // An fp32 tile leaves in two halves (64 channels wide: at once).  A half holds NH of the NC 16-channel blocks of both wave columns:
+    // of every 128 channels 0..31 and 64..95, then the others, on either tile width, so that a reward partial is added up in one order whatever tile its group got.
     auto block = [](int half, int k) { return HALVES == 1 ? k : 4 * (k >> 1) + 2 * half + (k & 1); };
     const bool with_reward = it.rv != nullptr;
     const bool vec_ok = (dout % EPV == 0) && ((reinterpret_cast<uintptr_t>(it.Y) & 15) == 0);
@@ -587,12 +587,15 @@ hipError_t launch_bf16(hipStream_t st, prefill_args& a) {
 //   256 x 256  18 + steps x rounds x (1.12 .. 1.47 as the last round fills: the clock falls)   82 us at 1024 x 3584
 //   256 x 128  13 + steps x rounds x 0.85                                                       54 us at  512 x 3584
 //   128 x 128  11.5 + steps x 0.53 x (tiles per CU), two workgroups per CU                      59 us at 1024 x 3584
-// and while there is no more than one tile per CU, which leaves each of them waiting for its own LDS reads and loads:
+// and while there is no more than one tile per CU, whose time is what the CU's load path takes for a step's operands (24 KB in
+// 0.3 us; weights straight into registers instead of LDS, a wave per 32 channels, took as long):
 //   128 x 128 with five stages of each operand  10.5 + steps x (0.46 .. 0.56)                   40 us at  512 x 3584
 //   64 x 128, u formed by the tile itself        7 + steps x (0.34 .. 0.44)                     27 us at  512 x 3584, q alone
+//   64 x 64, likewise                            7 + steps x (0.24 .. 0.32)                     21 us at  512 x 3584, k alone (64 x 128: 25.6)
+// The last is half of a reward partial wide, so it is for calls without reward vectors.
 // (128 x 128 with three and two stages takes 39 us for q alone there, 111 for 8192 x 8192 where five take 88, and 230 for 18944 ->
 // 3584 at 64 rows where the 64-row tile takes 143; the launch of rank_finish and its wait that the 64-row tile saves are 3 us.)
-enum bf16_tile { TILE_256x256, TILE_256x128, TILE_128x128, TILE_128x128_DEEP, TILE_64x128 };
+enum bf16_tile { TILE_256x256, TILE_256x128, TILE_128x128, TILE_128x128_DEEP, TILE_64x128, TILE_64x64 };
 bf16_tile pick_tile(const prefill_item* items, int n_items) {
     auto tiles = [&](int bm, int bn) {
         long long t = 0;
@@ -602,12 +605,15 @@ bf16_tile pick_tile(const prefill_item* items, int n_items) {
     int nk = 1;
     for (int g = 0; g < n_items; ++g) nk = std::max(nk, (items[g].d_in + 63) / 64);
     auto rounds = [](long long t) { return (double)((t + 255) / 256); };
-    const long long t44 = tiles(256, 256), t42 = tiles(256, 128), t22 = tiles(128, 128), t12 = tiles(64, 128);
+    const long long t44 = tiles(256, 256), t42 = tiles(256, 128), t22 = tiles(128, 128), t12 = tiles(64, 128), t11 = tiles(64, 64);
+    bool rewards = false;
+    for (int g = 0; g < n_items; ++g) rewards = rewards || items[g].rv;
     const double fill = (double)t44 / (256.0 * rounds(t44)), never = 1e30;
-    const double c[5] = {18.0 + nk * rounds(t44) * (1.12 + 0.35 * fill), 13.0 + nk * rounds(t42) * 0.85, t22 > 256 ? 11.5 + nk * rounds(t22) * 0.53 : never,
-                         t22 <= 256 ? 10.5 + nk * (0.46 + 0.1 * (t22 / 256.0)) : never, t12 <= 256 ? 7.0 + nk * (0.34 + 0.1 * (t12 / 256.0)) : never};
+    const double c[6] = {18.0 + nk * rounds(t44) * (1.12 + 0.35 * fill), 13.0 + nk * rounds(t42) * 0.85, t22 > 256 ? 11.5 + nk * rounds(t22) * 0.53 : never,
+                         t22 <= 256 ? 10.5 + nk * (0.46 + 0.1 * (t22 / 256.0)) : never, t12 <= 256 ? 7.0 + nk * (0.34 + 0.1 * (t12 / 256.0)) : never,
+                         t11 <= 256 && !rewards ? 7.0 + nk * (0.24 + 0.08 * (t11 / 256.0)) : never};
     int best = 0;
-    for (int i = 1; i < 5; ++i)
+    for (int i = 1; i < 6; ++i)
         if (c[i] < c[best]) best = i;
     return (bf16_tile)best;
 }
@@ -684,7 +690,7 @@ hipError_t forward_prefill(hipStream_t st, const fwd_item* items, int n_items, i
         for (int g = 0; g < n_items; ++g) maxR = std::max(maxR, a.it[g].R);
         hipLaunchKernelGGL(rank_none_kernel, dim3((maxR + 3) / 4, n_items), dim3(256), 0, st, a);
     } else {
-        hipError_t e = launch_rank(st, a, tile != TILE_64x128);
+        hipError_t e = launch_rank(st, a, tile < TILE_64x128);
         if (e != hipSuccess) return e;
     }
     tl_pre_start = ev_start;
@@ -696,7 +702,8 @@ hipError_t forward_prefill(hipStream_t st, const fwd_item* items, int n_items, i
         case TILE_256x128: e = yb ? launch_bf16<4, 2, 3, 4, true>(st, a) : launch_bf16<4, 2, 3, 4, false>(st, a); break;
         case TILE_128x128: e = yb ? launch_bf16<2, 2, 3, 2, true>(st, a) : launch_bf16<2, 2, 3, 2, false>(st, a); break;
         case TILE_128x128_DEEP: e = yb ? launch_bf16<2, 2, 5, 5, true>(st, a) : launch_bf16<2, 2, 5, 5, false>(st, a); break;
-        default: e = yb ? launch_bf16<1, 2, 5, 4, true>(st, a) : launch_bf16<1, 2, 5, 4, false>(st, a); break;
+        case TILE_64x128: e = yb ? launch_bf16<1, 2, 5, 4, true>(st, a) : launch_bf16<1, 2, 5, 4, false>(st, a); break;
+        default: e = yb ? launch_bf16<1, 1, 5, 4, true>(st, a) : launch_bf16<1, 1, 5, 4, false>(st, a); break;
     }
     tl_pre_start = tl_pre_stop = nullptr;
     return e;

@@ -108,8 +108,9 @@ def test_grouped_and_single_calls_agree(essa, dtype):
 
 @pytest.mark.parametrize("r,flags,dtype", [(7, 0, torch.bfloat16), (24, 0, torch.float32), (16, 8, torch.float32), (32, 8, torch.bfloat16)])
 def test_row_counts_that_change_the_tile(essa, r, flags, dtype):
-    """1000 rows take the 64 x 128 tile, which forms u itself, 2000 the 128 x 128 one with five stages, 3700 the 256 x 128 one: the
-    rows that they share have the same bits, outputs and reward partials, with and without the rank-r term."""
+    """1000 rows take the 64 x 128 tile, which forms u itself, 2000 the 128 x 128 one with five stages, 3700 the 256 x 128 one, 900
+    without reward vectors the 64 x 64 one: the rows that they share have the same bits, outputs and reward partials, with and
+    without the rank-r term."""
     ctx = essa.Context(0)
     K, d_in, d_out, Rs = 5, 1040, 1050, (1000, 2000, 3700)
     p = wl.make_projection("t", d_in, d_out, r, "int8", layer=18, proj=1)
@@ -130,6 +131,9 @@ def test_row_counts_that_change_the_tile(essa, r, flags, dtype):
             got.append((Y[:Rs[0]], part[:, :Rs[0]]))
         for Y, part in got[1:]:
             assert torch.equal(Y, got[0][0]) and torch.equal(part, got[0][1])
+        Y = torch.full((900, d_out), float("nan"), device="cuda", dtype=dtype)
+        essa.essa_svdlora_forward(ctx, gp, X[:900], rd[:900], sAd, sBd, Y, flags | more)
+        assert torch.equal(Y, got[0][0][:900])
         ref = orc.svdlora_forward(W, f, xv[:Rs[0]], r2c[:Rs[0]], sA, sB, base_only=more != 0)
         if dtype == torch.float32:
             assert orc.rel_errors(got[0][0].cpu().numpy(), ref)[1] <= EXACT_RMS
