@@ -243,8 +243,8 @@ __global__ __launch_bounds__(256) void rank_none_kernel(prefill_args a) {
 }
 
 // ------------------------------------------------------------------------------------------------
-// Base product on the bf16 MFMA.  256 threads = 4 waves in a 2 x 2 grid, tile = 64 MB rows x 64 NB channels, a wave owns a
-// patch of 32 MB rows x 32 NB channels (128 x 128 at MB = NB = 4: 256 accumulator registers, one wave per SIMD).  The weights
+// Base product on the bf16 MFMA.  256 threads = 4 waves in a 2 x 2 grid, tile = 32 NR rows x 64 NB channels, a wave owns a
+// patch of 16 NR rows x 32 NB channels (128 x 128 at NR = 8, NB = 4: 256 accumulator registers, one wave per SIMD).  The weights
 // are the MFMA's row operand and the activations its column operand, so a lane's accumulators run along the channels and
 // the output tile is written 8 or 16 bytes at a time.
 //
@@ -268,10 +268,10 @@ thread_local hipEvent_t tl_pre_start = nullptr, tl_pre_stop = nullptr;   // even
 // A 64-row tile forms the u of its rows itself, in LDS behind its stages: the rows (head and tail), M, sA t.
 constexpr size_t OWN_UROW = 144, OWN_MS = 64 * OWN_UROW, OWN_TV = OWN_MS + 32 * 36 * 4, OWN_BYTES = OWN_TV + 64 * 36 * 4;
 
-template <int MB, int NB, int XS, int WS>
+template <int NR, int NB, int XS, int WS>
 constexpr size_t bf16_smem_bytes(bool ybf16) {
-    constexpr size_t BM = 64 * MB, BN = 64 * NB;
-    const size_t stages = XS * BM * 128 + WS * BN * 128 + (MB == 1 ? OWN_BYTES : 0);
+    constexpr size_t BM = 32 * NR, BN = 64 * NB;
+    const size_t stages = XS * BM * 128 + WS * BN * 128 + (NR == 2 ? OWN_BYTES : 0);
     const size_t ctile = ybf16 ? BM * (BN * 2 + 16) : BM * ((NB == 1 ? BN : BN / 2) * 4 + 16);
     return stages > ctile ? stages : ctile;
 }
@@ -283,13 +283,13 @@ __device__ __forceinline__ void mfma_pinned(const bf16x8& A, const bf16x8& B, f3
     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(A), "v"(B));
 }
 
-template <int MB, int NB, int XS, int WS, bool YBF16>
-__global__ __launch_bounds__(256, (bf16_smem_bytes<MB, NB, XS, WS>(true) > 80 * 1024 ? 1 : 2)) void gemm_bf16_kernel(prefill_args a) {
-    constexpr int BM = 64 * MB, BN = 64 * NB, NBT = BN / 32;
+template <int NR, int NB, int XS, int WS, bool YBF16>
+__global__ __launch_bounds__(256, (bf16_smem_bytes<NR, NB, XS, WS>(true) > 80 * 1024 ? 1 : 2)) void gemm_bf16_kernel(prefill_args a) {
+    constexpr int BM = 32 * NR, BN = 64 * NB, NBT = BN / 32;
     constexpr uint32_t XST = BM * 128, WST = BN * 128, W0 = XS * XST, U0 = W0 + WS * WST;
-    constexpr bool OWN_U = MB == 1;
-    constexpr int NR = 2 * MB, NC = 2 * NB;                // 16-row and 16-channel blocks of a wave
-    constexpr int NMF = NR * NC, NRD = NR + NC, XL = 2 * MB, WL = 2 * NB;     // per wave: MFMAs and fragment reads of a sub-step, loads of a step
+    constexpr bool OWN_U = NR == 2;
+    constexpr int NC = 2 * NB;                             // 16-row (NR) and 16-channel (NC) blocks of a wave
+    constexpr int NMF = NR * NC, NRD = NR + NC, XL = NR, WL = 2 * NB;     // per wave: MFMAs and fragment reads of a sub-step, loads of a step
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_byte*)smem;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -369,7 +369,7 @@ __global__ __launch_bounds__(256, (bf16_smem_bytes<MB, NB, XS, WS>(true) > 80 * 
     static_assert(FIRST < 64 && AHEAD < 64, "the load counter has six bits");
 
     if constexpr (OWN_U) {                                 // u of the tile's rows, while the first steps are on their way
-        static_assert(bf16_smem_bytes<MB, NB, XS, WS>(true) == U0 + OWN_BYTES && BM * (BN * 2 + 16) <= U0, "behind the stages and the output tile");
+        static_assert(bf16_smem_bytes<NR, NB, XS, WS>(true) == U0 + OWN_BYTES && BM * (BN * 2 + 16) <= U0, "behind the stages and the output tile");
         const auto own = [&](int row, int j, uint16_t hi, uint16_t lo) {
             uint16_t* ur = reinterpret_cast<uint16_t*>(smem + U0 + (size_t)row * OWN_UROW);
             ur[j] = hi;
@@ -387,7 +387,7 @@ __global__ __launch_bounds__(256, (bf16_smem_bytes<MB, NB, XS, WS>(true) > 80 * 
 
     uint32_t xr[2];                                        // this lane's fragment of sub-step j inside an activation stage
 #pragma unroll
-    for (int j = 0; j < 2; ++j) xr[j] = (wr * 32 * MB + l16) * 128 + (((4 * j + kg) ^ ((l16 >> 1) & 7)) * 16);
+    for (int j = 0; j < 2; ++j) xr[j] = (wr * 16 * NR + l16) * 128 + (((4 * j + kg) ^ ((l16 >> 1) & 7)) * 16);
     const uint32_t wfr = W0 + wc * NB * 4096 + lane16;
     bf16x8 fx[2][NR], fw[2][NC];
     auto read_frag = [&](int set, int i, uint32_t xs, uint32_t ws, int j) {
@@ -414,7 +414,7 @@ __global__ __launch_bounds__(256, (bf16_smem_bytes<MB, NB, XS, WS>(true) > 80 * 
                 mfma_pinned(fw[j][i / NR], fx[j][i % NR], acc[i / NR][i % NR]);
                 static_for<NRD>([&](auto rc) {
                     constexpr int r = rc;
-                    if constexpr ((MB == 1 ? r / 2 : r * NMF / NRD) == i) read_frag(j ^ 1, r, j == 1 ? x_nxt : x_cur, j == 1 ? w_nxt : w_cur, j ^ 1);
+                    if constexpr ((NR == 2 ? r / 2 : r * NMF / NRD) == i) read_frag(j ^ 1, r, j == 1 ? x_nxt : x_cur, j == 1 ? w_nxt : w_cur, j ^ 1);
                 });
                 // one load every few MFMAs, never a burst; the weights, which have the shorter way to go, as early as they can
                 if constexpr (j == 1) {
@@ -558,17 +558,17 @@ __global__ __launch_bounds__(256, (bf16_smem_bytes<MB, NB, XS, WS>(true) > 80 * 
     });
 }
 
-template <int MB, int NB, int XS, int WS, bool YBF16>
+template <int NR, int NB, int XS, int WS, bool YBF16>
 hipError_t launch_bf16(hipStream_t st, prefill_args& a) {
     int total = 0;
     for (int g = 0; g < a.n_items; ++g) {
         a.tile_start[g] = total;
-        total += ((a.it[g].R + 64 * MB - 1) / (64 * MB)) * ((a.it[g].n_blocks + 2 * NB - 1) / (2 * NB));
+        total += ((a.it[g].R + 32 * NR - 1) / (32 * NR)) * ((a.it[g].n_blocks + 2 * NB - 1) / (2 * NB));
     }
     for (int g = a.n_items; g <= ESSA_MAX_GROUP; ++g) a.tile_start[g] = total;
-    constexpr size_t smem = bf16_smem_bytes<MB, NB, XS, WS>(YBF16);
+    constexpr size_t smem = bf16_smem_bytes<NR, NB, XS, WS>(YBF16);
     static_assert(smem <= 160 * 1024, "tile does not fit the LDS of a CU");
-    auto kern = gemm_bf16_kernel<MB, NB, XS, WS, YBF16>;
+    auto kern = gemm_bf16_kernel<NR, NB, XS, WS, YBF16>;
     static bool attr_done = false;   // one flag per instantiation
     if (!attr_done) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
@@ -580,41 +580,56 @@ hipError_t launch_bf16(hipStream_t st, prefill_args& a) {
     return hipGetLastError();
 }
 
-// Which tile takes a group.  Tiles go to the 256 CUs in rounds, so the time is (rounds) x (K steps) x (time of a step), plus
-// what does not depend on K.  Microseconds of a whole call as measured on single projections and groups of up to four, 512 to
-// 18944 columns, 8 to 32768 rows, weights from HBM (a few per cent to a tenth off everywhere in that range, more where the
-// weights alone are HBM time):
-//   256 x 256  18 + steps x rounds x (1.12 .. 1.47 as the last round fills: the clock falls)   82 us at 1024 x 3584
-//   256 x 128  13 + steps x rounds x 0.85                                                       54 us at  512 x 3584
-//   128 x 128  11.5 + steps x 0.53 x (tiles per CU), two workgroups per CU                      59 us at 1024 x 3584
-// and while there is no more than one tile per CU, whose time is what the CU's load path takes for a step's operands (24 KB in
-// 0.3 us; weights straight into registers instead of LDS, a wave per 32 channels, took as long):
-//   128 x 128 with five stages of each operand  10.5 + steps x (0.46 .. 0.56)                   40 us at  512 x 3584
-//   64 x 128, u formed by the tile itself        7 + steps x (0.34 .. 0.44)                     27 us at  512 x 3584, q alone
-//   64 x 64, likewise                            7 + steps x (0.24 .. 0.32)                     21 us at  512 x 3584, k alone (64 x 128: 25.6)
-// The last is half of a reward partial wide, so it is for calls without reward vectors.
-// (128 x 128 with three and two stages takes 39 us for q alone there, 111 for 8192 x 8192 where five take 88, and 230 for 18944 ->
-// 3584 at 64 rows where the 64-row tile takes 143; the launch of rank_finish and its wait that the 64-row tile saves are 3 us.)
-enum bf16_tile { TILE_256x256, TILE_256x128, TILE_128x128, TILE_128x128_DEEP, TILE_64x128, TILE_64x64 };
+// Which tile takes a group.  Tiles go to the 256 CUs in rounds, so the time is what does not depend on K, per call and per round, plus
+// (K steps) x (time of a step) for every full round and the last one, which runs faster the emptier it is (one CU in two or
+// fewer: no faster than that; the clock falls as the chip fills), plus a share of the weights' way from HBM:
+//   us = call + rounds * round + steps * (full rounds * hi + last round's lo .. hi) + per_mb * (MB of bf16 weights)
+// fitted to whole calls, each with every tile forced: 57 groups and single projections of 512 to 8192 columns, 400 to 16000 rows, weights
+// from HBM.  The tile it names is within 0.2 % of the fastest on average there and 5.6 % at worst.  Two rounds of a low tile often beat
+// one and a bit of the high one, or a round that is two thirds full (q, k, v, o of 3584 columns, k and v with 512 channels, us):
+//   rows       256 x 256   224 x 256   192 x 256   160 x 256   256 x 128   160 x 128   128 x 128, two a CU   128 x 128, five stages
+//    640          78          71          64          58          54          45            53                   64
+//   1187          78          74          71          68          98          76            86                   91
+//   1536          82          80          77         114         100         104            90                   95
+//   2560         170         151         140         133         155         150           145                  159
+//   4096         182         222         202         231         207         238           211                  240
+// The 64-row tiles form u themselves (the launch of rank_finish and its wait that they save are 3 us); 64 x 64 is half of a reward
+// partial wide, so it is for calls without reward vectors (3584 -> 512 at 512 rows 21 us, 64 x 128 25.6).  Both are for calls that they finish
+// in one round; a CU's load path takes 24 KB of operands in 0.3 us, and weights straight into registers took as long.
+enum bf16_tile { TILE_256x256, TILE_224x256, TILE_192x256, TILE_160x256, TILE_256x128, TILE_160x128, TILE_128x128, TILE_128x128_DEEP, TILE_64x128, TILE_64x64 };
+struct tile_cost { int rows, channels, slots; double call, round, lo, mid, hi, per_mb; };   // slots: tiles of a round
+constexpr tile_cost TILE_COST[] = {
+    {256, 256, 256, 6.3, 16.0, 0.993, 0, 1.325, 0.048}, {224, 256, 256, 7.3, 12.8, 0.924, 0, 1.219, 0.042}, {192, 256, 256, 5.5, 12.8, 0.811, 0, 1.025, 0.059},
+    {160, 256, 256, 7.4, 10.5, 0.737, 0, 0.911, 0.022}, {256, 128, 256, 7.2, 9.6, 0.632, 0, 0.750, 0.023},  {160, 128, 256, 9.9, 5.6, 0.438, 0, 0.536, 0.024},
+    {128, 128, 512, 7.1, 7.5, 0.412, 0.62, 0.796, 0.101}, {128, 128, 256, 8.3, 5.8, 0.382, 0, 0.456, 0.039}, {64, 128, 256, 9.0, 4.7, 0.137, 0, 0.299, 0.191},
+    {64, 64, 256, 7.0, 0.0, 0.240, 0, 0.320, 0.0}};
 bf16_tile pick_tile(const prefill_item* items, int n_items) {
-    auto tiles = [&](int bm, int bn) {
-        long long t = 0;
-        for (int g = 0; g < n_items; ++g) t += (long long)((items[g].R + bm - 1) / bm) * ((items[g].n_blocks * 32 + bn - 1) / bn);
-        return t;
-    };
     int nk = 1;
-    for (int g = 0; g < n_items; ++g) nk = std::max(nk, (items[g].d_in + 63) / 64);
-    auto rounds = [](long long t) { return (double)((t + 255) / 256); };
-    const long long t44 = tiles(256, 256), t42 = tiles(256, 128), t22 = tiles(128, 128), t12 = tiles(64, 128), t11 = tiles(64, 64);
+    double mb = 0;
     bool rewards = false;
-    for (int g = 0; g < n_items; ++g) rewards = rewards || items[g].rv;
-    const double fill = (double)t44 / (256.0 * rounds(t44)), never = 1e30;
-    const double c[6] = {18.0 + nk * rounds(t44) * (1.12 + 0.35 * fill), 13.0 + nk * rounds(t42) * 0.85, t22 > 256 ? 11.5 + nk * rounds(t22) * 0.53 : never,
-                         t22 <= 256 ? 10.5 + nk * (0.46 + 0.1 * (t22 / 256.0)) : never, t12 <= 256 ? 7.0 + nk * (0.34 + 0.1 * (t12 / 256.0)) : never,
-                         t11 <= 256 && !rewards ? 7.0 + nk * (0.24 + 0.08 * (t11 / 256.0)) : never};
+    for (int g = 0; g < n_items; ++g) {
+        nk = std::max(nk, (items[g].d_in + 63) / 64);
+        mb += 2e-6 * items[g].d_in * items[g].d_out;
+        rewards = rewards || items[g].rv;
+    }
     int best = 0;
-    for (int i = 1; i < 6; ++i)
-        if (c[i] < c[best]) best = i;
+    double best_us = 0;
+    for (int i = 0; i < (int)(sizeof(TILE_COST) / sizeof(TILE_COST[0])); ++i) {
+        const tile_cost& c = TILE_COST[i];
+        long long tiles = 0;
+        for (int g = 0; g < n_items; ++g) tiles += (long long)((items[g].R + c.rows - 1) / c.rows) * ((items[g].n_blocks * 32 + c.channels - 1) / c.channels);
+        if ((i >= TILE_64x128 && tiles > c.slots) || (i == TILE_64x64 && rewards)) continue;
+        const long long full = tiles / c.slots, rest = tiles % c.slots;
+        const double over = std::max(0.0, 2.0 * rest / c.slots - 1.0);   // how far the last round is beyond half full
+        double last = 0;
+        // two workgroups a CU: up to half full a CU has one, beyond that some have two
+        if (rest) last = i == TILE_128x128 ? (over == 0 ? c.lo : c.mid + (c.hi - c.mid) * over) : c.lo + (c.hi - c.lo) * over * over;
+        const double us = c.call + c.round * (full + (rest ? 1 : 0)) + nk * (full * c.hi + last) + c.per_mb * mb;
+        if (i == 0 || us < best_us) {
+            best = i;
+            best_us = us;
+        }
+    }
     return (bf16_tile)best;
 }
 
@@ -698,12 +713,16 @@ hipError_t forward_prefill(hipStream_t st, const fwd_item* items, int n_items, i
     const bool yb = y_dtype == ESSA_BF16;
     hipError_t e;
     switch (tile) {
-        case TILE_256x256: e = yb ? launch_bf16<4, 4, 3, 2, true>(st, a) : launch_bf16<4, 4, 3, 2, false>(st, a); break;
-        case TILE_256x128: e = yb ? launch_bf16<4, 2, 3, 4, true>(st, a) : launch_bf16<4, 2, 3, 4, false>(st, a); break;
-        case TILE_128x128: e = yb ? launch_bf16<2, 2, 3, 2, true>(st, a) : launch_bf16<2, 2, 3, 2, false>(st, a); break;
-        case TILE_128x128_DEEP: e = yb ? launch_bf16<2, 2, 5, 5, true>(st, a) : launch_bf16<2, 2, 5, 5, false>(st, a); break;
-        case TILE_64x128: e = yb ? launch_bf16<1, 2, 5, 4, true>(st, a) : launch_bf16<1, 2, 5, 4, false>(st, a); break;
-        default: e = yb ? launch_bf16<1, 1, 5, 4, true>(st, a) : launch_bf16<1, 1, 5, 4, false>(st, a); break;
+        case TILE_256x256: e = yb ? launch_bf16<8, 4, 3, 2, true>(st, a) : launch_bf16<8, 4, 3, 2, false>(st, a); break;
+        case TILE_224x256: e = yb ? launch_bf16<7, 4, 3, 2, true>(st, a) : launch_bf16<7, 4, 3, 2, false>(st, a); break;
+        case TILE_192x256: e = yb ? launch_bf16<6, 4, 3, 2, true>(st, a) : launch_bf16<6, 4, 3, 2, false>(st, a); break;
+        case TILE_160x256: e = yb ? launch_bf16<5, 4, 3, 3, true>(st, a) : launch_bf16<5, 4, 3, 3, false>(st, a); break;
+        case TILE_160x128: e = yb ? launch_bf16<5, 2, 4, 4, true>(st, a) : launch_bf16<5, 2, 4, 4, false>(st, a); break;
+        case TILE_256x128: e = yb ? launch_bf16<8, 2, 3, 4, true>(st, a) : launch_bf16<8, 2, 3, 4, false>(st, a); break;
+        case TILE_128x128: e = yb ? launch_bf16<4, 2, 3, 2, true>(st, a) : launch_bf16<4, 2, 3, 2, false>(st, a); break;
+        case TILE_128x128_DEEP: e = yb ? launch_bf16<4, 2, 5, 5, true>(st, a) : launch_bf16<4, 2, 5, 5, false>(st, a); break;
+        case TILE_64x128: e = yb ? launch_bf16<2, 2, 5, 4, true>(st, a) : launch_bf16<2, 2, 5, 4, false>(st, a); break;
+        default: e = yb ? launch_bf16<2, 1, 5, 4, true>(st, a) : launch_bf16<2, 1, 5, 4, false>(st, a); break;
     }
     tl_pre_start = tl_pre_stop = nullptr;
     return e;

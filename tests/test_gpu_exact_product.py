@@ -21,9 +21,9 @@ BF16_RMS, BF16_MAX = 1e-3, 2e-2
     (1, 48, 129, 5, 8),            # one row, less than one K step, asked for by the flag
     (129, 64, 128, 32, 8),         # exactly one K step and one tile of channels, one row past a tile
     (513, 1040, 300, 32, 0),       # taken by itself, K ends 16 columns into a step
-    (1030, 528, 9001, 16, 0),      # two 128 x 128 tiles per CU, odd output width (element-wise stores)
+    (1030, 528, 9001, 16, 0),      # 160 x 256 tiles, odd output width (element-wise stores)
     (700, 2064, 8200, 16, 0),      # 256 x 128 tiles
-    (2050, 4112, 5000, 24, 0),     # 256 x 256 tiles, ragged rows and channels
+    (2050, 4112, 5000, 24, 0),     # 192 x 256 tiles, ragged rows and channels
 ])
 def test_exact_product_tiles(essa, R, d_in, d_out, r, flags):
     ctx = essa.Context(0)
@@ -76,7 +76,7 @@ def test_exact_product_tiles(essa, R, d_in, d_out, r, flags):
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_grouped_and_single_calls_agree(essa, dtype):
-    """Which tile a projection gets hangs on its group (here 256 x 256 together, narrower ones alone); its outputs and reward
+    """Which tile a projection gets hangs on its group (here 192 x 256 together, narrower ones alone); its outputs and reward
     partials do not, to the bit.  Ranks 16 and 32 in one launch, odd widths."""
     ctx = essa.Context(0)
     R, K, d_in = 1187, 5, 3584
@@ -108,7 +108,7 @@ def test_grouped_and_single_calls_agree(essa, dtype):
 
 @pytest.mark.parametrize("r,flags,dtype", [(7, 0, torch.bfloat16), (24, 0, torch.float32), (16, 8, torch.float32), (32, 8, torch.bfloat16)])
 def test_row_counts_that_change_the_tile(essa, r, flags, dtype):
-    """1000 rows take the 64 x 128 tile, which forms u itself, 2000 the 128 x 128 one with five stages, 3700 the 256 x 128 one, 900
+    """1000 rows take the 64 x 128 tile, which forms u itself, 2000 the 128 x 128 one with five stages, 3700 the 160 x 128 one, 900
     without reward vectors the 64 x 64 one: the rows that they share have the same bits, outputs and reward partials, with and
     without the rank-r term."""
     ctx = essa.Context(0)
@@ -304,4 +304,37 @@ def test_copy_of_the_weights_leaves_half_of_the_card(essa):
     assert error(roomy, 0) <= 2e-6                          # a copy that is there stays
     tight.close()
     roomy.close()
+    ctx.close()
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_tile_heights(essa, dtype):
+    """Every tile that a row count can be given: at 1040 -> 4200 these take, in turn, 128 x 128 tiles with five stages, 160 x 128, 128 x 128
+    twice a CU, 160 x 256, 192 x 256, 224 x 256 and 256 x 256.  The rows repeat the first 600, so each has the bits of the row that it
+    repeats wherever it falls in its tile; those meet the oracle."""
+    ctx = essa.Context(0)
+    K, d_in, d_out, base = 4, 1040, 4200, 600
+    p = wl.make_projection("t", d_in, d_out, 24, "int8", layer=19, proj=2)
+    W, f = oracle_proj(p)
+    gp = gpu_proj(essa, ctx, p)
+    sA, sB = candidate_sigmas(f, K, 0.05)
+    xb, xv = wl.make_x_bf16(base, d_in, x_id=65)
+    r2c = np.random.default_rng(9).integers(0, K, base).astype(np.int32)
+    X, rd, sAd, sBd = bf16_dev(xb), to_dev(r2c), to_dev(sA), to_dev(sB)
+    v = torch.randn(d_out, device="cuda", generator=torch.Generator(device="cuda").manual_seed(3))
+    first = None
+    for R in (base, 1000, 1187, 2050, 2500, 3000, 3840):
+        print("R=%d" % R, flush=True)
+        at = torch.arange(R, device="cuda") % base
+        Y = torch.full((R, d_out), float("nan"), device="cuda", dtype=dtype)
+        part = torch.full(((d_out + 127) // 128, R), float("nan"), device="cuda")
+        essa.essa_svdlora_forward_reward_group(ctx, [(gp, X[at].contiguous(), rd[at].contiguous(), sAd, sBd, Y)], [v], part, 0)
+        first = first or (Y, part)
+        assert torch.equal(Y, first[0][at]) and torch.equal(part, first[1][:, at])
+    ref = orc.svdlora_forward(W, f, xv, r2c, sA, sB)
+    if dtype == torch.float32:
+        assert orc.rel_errors(first[0].cpu().numpy(), ref)[1] <= EXACT_RMS
+    else:
+        assert orc.rel_errors(bf16_host(first[0]), orc.round_to_bf16(ref))[1] <= BF16_RMS
+    gp.close()
     ctx.close()
