@@ -250,7 +250,7 @@ extern "C" void essa_proj_destroy(essa_proj* p) {
     if (!p) return;
     (void)hipSetDevice(p->device);
     (void)hipDeviceSynchronize();
-    void* ptrs[] = {p->Wq, p->scale, p->zero, p->VA32, p->VA16, p->UB32, p->UB16, p->M, p->Wt, p->VAp, p->St, p->SZ16, p->W16, p->E16};
+    void* ptrs[] = {p->Wq, p->scale, p->zero, p->VA32, p->VA16, p->UB32, p->UB16, p->M, p->Wt, p->VAp, p->St, p->SZ16, p->W16, p->E16, p->Wn, p->SZn};
     for (void* q : ptrs)
         if (q) (void)hipFree(q);
     delete p;
@@ -457,21 +457,33 @@ extern "C" essa_status essa_proj_create(essa_ctx* ctx, const essa_proj_desc* d, 
         ESSA_TRY(upload(&p->Wt, Wt.data(), Wt.size()));
         const int gpad = p->d_in_pad / 128;
         std::vector<float> St((size_t)gpad * nbs * 32, 0.f);
-        std::vector<uint16_t> SZ((size_t)nbs * 32 * 2 * p->Gp, 0);
+        std::vector<uint16_t> SZ((size_t)nbs * 32 * 2 * p->Gp, 0), SZn(SZ.size(), 0);
+        auto head_and_tail = [](float m, uint16_t* head, uint16_t* tail) {
+            *head = f32_to_bf16_rne(m);
+            uint32_t hb = (uint32_t)*head << 16;
+            float hf;
+            std::memcpy(&hf, &hb, 4);
+            *tail = f32_to_bf16_rne(m - hf);
+        };
         for (int o = 0; o < dout; ++o)
             for (int g = 0; g < p->groups; ++g) {
                 const float sv = s[(size_t)o * p->groups + g], zv = z[(size_t)o * p->groups + g];
                 St[(size_t)g * nbs * 32 + o] = sv;
-                const float m = -(sv * zv);
-                const uint16_t hi = f32_to_bf16_rne(m);
-                uint32_t hb = (uint32_t)hi << 16;
-                float hf;
-                std::memcpy(&hf, &hb, 4);
-                SZ[((size_t)o * 2 + 0) * p->Gp + g] = hi;
-                SZ[((size_t)o * 2 + 1) * p->Gp + g] = f32_to_bf16_rne(m - hf);
+                uint16_t* sz = &SZ[(size_t)o * 2 * p->Gp + g];
+                head_and_tail(-(sv * zv), sz, sz + p->Gp);
+                // [16 channels][16 groups][head, tail][8 groups][channel][group]
+                uint16_t* szn = &SZn[((size_t)(o / 16) * (p->Gp / 16) + g / 16) * 512 + (g / 8 % 2) * 128 + (o % 16) * 8 + g % 8];
+                head_and_tail(-(sv * (zv + 16.f)) * 0x1p-5f, szn, szn + 256);
             }
         ESSA_TRY(upload(&p->St, St.data(), St.size()));
         ESSA_TRY(upload(&p->SZ16, SZ.data(), SZ.size()));
+        // exact-product kernel: the codes once more, in its own operand tiles
+        const size_t wn = (size_t)p->groups * nbs * 2048;
+        if (wn < (1u << 31) && room_for_copy(wn + SZn.size() * 2) && device_alloc((void**)&p->Wn, wn) == hipSuccess) {
+            ESSA_TRY(upload(&p->SZn, SZn.data(), SZn.size()));
+            ESSA_HIP(essa_k::repack_nibbles(nullptr, p->Wt, p->groups, nbs, p->Wn));
+            ESSA_HIP(hipStreamSynchronize(nullptr));
+        }                                          // otherwise the projection works without it, on the limb kernels
     }
     *out = p.release();
     return ESSA_OK;
@@ -722,7 +734,7 @@ static essa_status plan_items(essa_ctx* ctx, const essa_fwd_item* items, int n_i
         k.Wq = p->Wq; k.scale = p->scale; k.zero = p->zero; k.VA32 = p->VA32; k.VA16 = p->VA16;
         k.UB32 = p->UB32; k.UB16 = p->UB16; k.M = p->M;
         k.Wt = p->Wt; k.W16 = p->W16; k.US16 = p->US16; k.scale16 = p->scale16; k.VA3p = p->VA3p; k.VAp = p->VAp; k.d_in_pad = p->d_in_pad; k.n_blocks = p->n_blocks;
-        k.St = p->St; k.SZ16 = p->SZ16; k.Gp = p->Gp;
+        k.St = p->St; k.SZ16 = p->SZ16; k.Gp = p->Gp; k.Wn = p->Wn; k.SZn = p->SZn;
         if (rv) {
             k.rv = rv[i];
             k.rowpart = rowpart + block0 * (size_t)it.R;
@@ -809,10 +821,24 @@ static bool takes_exact_product(const essa_k::fwd_item& k) {
     return k.d_out >= 128 && k.R > (k.d_in >= 3072 && k.d_in <= 6144 ? 384 : 511);
 }
 
+// The same for 4-bit weights, again by the item's own rows and columns.  The line suits layers; a projection alone that is just above it
+// takes up to a quarter longer than on the limbs until it has rows enough (us a call, limbs / exact):
+//            q, k, v, o                                q alone                      k alone
+//    640     2303  42 / 25 (80 channels)               2303  22 / 21                2303 20 / 21 (264 channels)
+//   1024     1024  32 / 24, 2048  42 / 30              1024  20 / 23, 2048 25 / 24
+//   2048      512  36 / 32, 1024  53 / 36              1024  29 / 32                2048 28 / 29, 8192 51 / 36
+//   3584      384  51 / 43,  512  52 / 46, 640 71 / 50  512  38 / 43,  768 49 / 43  1024 37 / 40, 2048 43 / 41
+//   5120      192  57 / 53,  384  85 / 64, 512 93 / 84  384  48 / 54,  512 60 / 55  1024 48 / 54, 2000 60 / 56
+//   8192      256 124 / 105, 384 143 / 126, 512 181 / 150  256 60 / 74, 384 89 / 76   512 61 / 73, 2000 80 / 76
+// (The sums of x go where the limb path keeps its own, in blocks of 16 rows: that room is enough from 60 rows on.)
+static bool takes_exact_q4(const essa_k::fwd_item& k) {
+    return k.Wn && k.R > (k.d_in > 4096 ? 256 : k.d_in >= 3072 ? 511 : k.d_in >= 2048 ? 640 : k.d_in >= 1024 ? 1023 : 2303);
+}
+
 static essa_status run_items(essa_ctx* ctx, item_list& ks, int x_dtype, int y_dtype, unsigned flags) {
-    // four launch groups: int8 items on the exact-product kernel, int8 and 4-bit items on the int8-limb kernels (different
+    // five launch groups: int8 and 4-bit items on their exact-product kernels, int8 and 4-bit items on the int8-limb kernels (different
     // instantiations of the GEMM), and the rest on the generic kernels
-    item_list ex, f8, f4, rest;
+    item_list ex, ex4, f8, f4, rest;
     const bool exact_ok = x_dtype == ESSA_BF16 && !(flags & ESSA_COMPUTE_W8A8);
     for (int i = 0; i < ks.n; ++i) {
         essa_k::fwd_item& k = ks.it[i];
@@ -821,6 +847,7 @@ static essa_status run_items(essa_ctx* ctx, item_list& ks, int x_dtype, int y_dt
         // (the rank-r term alone, a test hook, has the same bits at every row count: it stays with the limb kernels)
         if (exact_can && takes_exact_product(k) && !(flags & ESSA_LORA_ONLY)) ex.push(k);
         else if (!limbs) (exact_can ? ex : rest).push(k);
+        else if (takes_exact_q4(k) && !(flags & (ESSA_LORA_ONLY | ESSA_BASE_ONLY))) ex4.push(k);
         else (k.quant == ESSA_QUANT_INT8_PERCH ? f8 : f4).push(k);
     }
     const unsigned kflags = flags & ~(ESSA_COMPUTE_BF16 | ESSA_VALIDATE);
@@ -830,16 +857,17 @@ static essa_status run_items(essa_ctx* ctx, item_list& ks, int x_dtype, int y_dt
         ESSA_TRY(next_events(ctx, &e0, &e1));
         ESSA_HIP(essa_k::forward_prefill(ctx->stream, ex.it, ex.n, y_dtype, kflags, e0, e1));
     }
-    for (item_list* grp : {&f8, &f4}) {
+    for (item_list* grp : {&ex4, &f8, &f4}) {
         if (grp->n == 0) continue;
-        for (int i = 0; i < grp->n; ++i) {                  // every set of limbs needs exactly one producer in its launch
+        for (int i = 0; i < grp->n; ++i) {                  // every set of limbs (or group sums) needs exactly one producer in its launch
             bool found = false;
             for (int j = 0; j < i; ++j) found = found || (grp->it[j].x_owner && grp->it[j].Xh == grp->it[i].Xh);
             grp->it[i].x_owner = found ? 0 : 1;
         }
         hipEvent_t e0, e1;
         ESSA_TRY(next_events(ctx, &e0, &e1));
-        ESSA_HIP(essa_k::forward_stream(ctx->stream, grp->it, grp->n, y_dtype, kflags, e0, e1));
+        if (grp == &ex4) ESSA_HIP(essa_k::forward_prefill_q4(ctx->stream, grp->it, grp->n, y_dtype, e0, e1));
+        else ESSA_HIP(essa_k::forward_stream(ctx->stream, grp->it, grp->n, y_dtype, kflags, e0, e1));
     }
     if (rest.n > 0) {
         hipEvent_t e0, e1;

@@ -75,6 +75,10 @@ struct essa_proj {
     float* St = nullptr;       // [d_in_pad/128][n_blocks*32] group scales, group major
     uint16_t* SZ16 = nullptr;  // [n_blocks*32][2][Gp] bf16 head and tail of -scale*zero
     int Gp = 0;                // groups rounded up to 16
+    // 4-bit weights for the exact-product kernel: [groups][2 n_blocks][64 lanes][4 words], lane (kg, l16) word j of block (g, b) = the codes of
+    // columns 128 g + 32 j + 8 kg .. + 7 of channel 16 b + l16; columns 2 i and 2 i + 1 of them at bits 3 + 4 i and 19 + 4 i (mod 32)
+    uint8_t* Wn = nullptr;
+    uint16_t* SZn = nullptr;   // [2 n_blocks][Gp/16][2][2][16 channels][8 groups] bf16 head and tail of -scale (zero + 16) 2^-5
     // int8 weights once more as bf16 (exact, times the channel's power of two), for the exact-product kernel: [ceil(d_in/64)][n_blocks][2][2][64 lanes][8],
     // block (kt, nb), half, sub-step j, lane (kg, l16) = channel 32 nb + 16 half + l16, columns 64 kt + 32 j + 8 kg .. + 7
     uint16_t* W16 = nullptr;
@@ -221,6 +225,8 @@ struct fwd_item : stream_item {
     const uint16_t* US16;
     const float* scale16;
     const uint16_t* VA3p;      // not null: V_A with all its fp32 bits
+    const uint8_t* Wn;         // 4-bit weights
+    const uint16_t* SZn;
 };
 hipError_t forward_group(hipStream_t st, const fwd_item* items, int n_items, int x_dtype, int y_dtype,
                          unsigned flags, hipEvent_t ev_start, hipEvent_t ev_stop);
@@ -232,6 +238,10 @@ hipError_t forward_stream(hipStream_t st, const fwd_item* items, int n_items, in
 bool prefill_takes(const fwd_item& it);
 hipError_t forward_prefill(hipStream_t st, const fwd_item* items, int n_items, int y_dtype, unsigned flags, hipEvent_t ev_start,
                            hipEvent_t ev_stop);
+// the same for 4-bit weights (items with Wn); XS16 takes 2^-7 of the group sums of x
+hipError_t forward_prefill_q4(hipStream_t st, const fwd_item* items, int n_items, int y_dtype, hipEvent_t ev_start, hipEvent_t ev_stop);
+// Wt (4-bit operand tiles) -> Wn
+hipError_t repack_nibbles(hipStream_t st, const int8_t* Wt, int groups, int n_blocks, uint8_t* Wn);
 // Wt (int8 operand tiles) -> W16; channels of scale 0 become zero
 hipError_t expand_weights(hipStream_t st, const int8_t* Wt, const float* scale, int dout, int n_blocks, int nk, uint16_t* W16);
 hipError_t w8a8_accumulators_stream(hipStream_t st, const fwd_item& it, int32_t* acc_out);

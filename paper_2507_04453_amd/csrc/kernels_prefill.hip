@@ -32,6 +32,9 @@ struct prefill_args {
     int n_items;
     unsigned flags;
     int ksplit[ESSA_MAX_GROUP];            // rank_down: the item's K is cut in this many parts (at most 8)
+    float u_scale;                         // rank_finish leaves u times this power of two
+    uint16_t* XS16[ESSA_MAX_GROUP];        // 4-bit weights: where rank_down leaves the sums of x over groups of 128 columns (null: another item of this X does)
+    int Gp[ESSA_MAX_GROUP];
 };
 
 // ---- loads that go from memory into LDS without passing through registers ------------------------------------------
@@ -41,6 +44,11 @@ struct prefill_args {
 typedef __attribute__((address_space(3))) unsigned char lds_byte;
 __device__ __forceinline__ void load_lds16(uint32_t lds, uint32_t lane_off, i32x4 rsrc, uint32_t scalar_off) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 :: "s"(lds), "v"(lane_off), "s"(rsrc), "s"(scalar_off) : "memory", "m0");
+}
+// the same with 4 bytes a lane
+__device__ __forceinline__ void load_lds4(uint32_t lds, uint32_t lane_off, i32x4 rsrc, uint32_t scalar_off) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds"
                  :: "s"(lds), "v"(lane_off), "s"(rsrc), "s"(scalar_off) : "memory", "m0");
 }
 __device__ __forceinline__ i32x4 buffer_words(const void* base) {
@@ -77,7 +85,11 @@ __device__ __forceinline__ int xcd_contiguous(int b, int T) {
 // ------------------------------------------------------------------------------------------------
 constexpr int RD_ROWS = 128;
 
-template <int RP, bool THIRD>
+// SUMS (4-bit weights): the sums of x over groups of 128 columns as well, 2^-7 of them as bf16 head and tail, in
+// the operand tiles of the product that wants them, [16 rows][16 groups][head, tail][8 groups][row][group].  They come from
+// the x fragments that are in registers anyway, times an operand that is 2^-7 in the column of the group and zero elsewhere; 32 groups
+// fill an accumulator.  K parts then end between groups.  An Inf or a NaN reaches every sum of its row, and makes it NaN.
+template <int RP, bool THIRD, bool SUMS = false>
 __global__ __launch_bounds__(256, THIRD && RP == 32 ? 1 : 2) void rank_down_kernel(prefill_args a) {
     constexpr int NBH = RP / 16, NBV = NBH + (THIRD ? 1 : 0);   // 32-column blocks of [heads | tails], of the third parts
     constexpr int XST = RD_ROWS * 128, VST = 4 * NBV * 1024, ST = XST + VST;
@@ -95,8 +107,10 @@ __global__ __launch_bounds__(256, THIRD && RP == 32 ? 1 : 2) void rank_down_kern
     const int m0 = (rel / ksplit) * RD_ROWS;
     const int R = it.R, din = it.d_in;
     const int nk_all = (din + 63) / 64;
-    const int k_lo = (int)((long long)nk_all * part / ksplit), k_hi = (int)((long long)nk_all * (part + 1) / ksplit);
+    constexpr int UNIT = SUMS ? 2 : 1;
+    const int k_lo = (int)((long long)(nk_all / UNIT) * part / ksplit) * UNIT, k_hi = (int)((long long)(nk_all / UNIT) * (part + 1) / ksplit) * UNIT;
     const int ksteps = din / 16;
+    const bool sums = SUMS && a.XS16[g] != nullptr;
 
     const i32x4 xres = buffer_words(it.X + (size_t)m0 * din);
     const i32x4 vres = buffer_words(it.VAp), vres3 = buffer_words(THIRD ? it.VA3p : it.VAp);
@@ -129,6 +143,24 @@ __global__ __launch_bounds__(256, THIRD && RP == 32 ? 1 : 2) void rank_down_kern
     for (int b = 0; b < NBV; ++b)
 #pragma unroll
         for (int q = 0; q < 16; ++q) acc[b][q] = 0.f;
+    f32x16 acc_s;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) acc_s[q] = 0.f;
+    auto put_sums = [&](int g_end) {                       // the window of 32 groups that g_end - 1 lies in, up to g_end
+        const int Gp = a.Gp[g], gr = ((g_end - 1) & ~31) + l32;
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            const int row = m0 + wave * 32 + 8 * (q >> 2) + 4 * h + (q & 3);
+            const float v = acc_s[q];
+            const uint16_t hi = f32_to_bf16_bits(v);
+            if (row < R && gr >= k_lo / 2 && gr < g_end) {
+                const gptr<uint16_t> dst = as_global_w(a.XS16[g]) + ((size_t)(row >> 4) * (Gp >> 4) + (gr >> 4)) * 512 + (gr >> 3 & 1) * 128 + (row & 15) * 8 + (gr & 7);
+                dst[0] = hi;
+                dst[256] = f32_to_bf16_bits(v - bf16_bits_to_f32(hi));
+            }
+            acc_s[q] = 0.f;
+        }
+    };
     if (k_lo < k_hi) {
         issue(k_lo, 0);
         issue(k_lo + 1, 1);
@@ -138,6 +170,8 @@ __global__ __launch_bounds__(256, THIRD && RP == 32 ? 1 : 2) void rank_down_kern
             wait_loads_and_meet<4 + NBV>();
             issue(kt + 2, st == 0 ? 2 : st - 1);
             const unsigned char* sx = smem + st * ST;
+            const uint32_t one = l32 == ((kt >> 1) & 31) ? 0x3c003c00u : 0u;   // 2^-7 twice
+            const bf16x8 pick = __builtin_bit_cast(bf16x8, (u32x4){one, one, one, one});
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const bool live = 4 * kt + j < ksteps;      // steps past the row multiply by zeros
@@ -148,10 +182,14 @@ __global__ __launch_bounds__(256, THIRD && RP == 32 ? 1 : 2) void rank_down_kern
                     if (!live) vf = (u32x4){0, 0, 0, 0};
                     acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf, __builtin_bit_cast(bf16x8, vf), acc[b], 0, 0, 0);
                 }
+                if (SUMS && sums) acc_s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf, pick, acc_s, 0, 0, 0);
             }
+            if (SUMS && sums && (kt & 63) == 63 && kt + 1 < k_hi) put_sums((kt + 1) / 2);
             st = st == 2 ? 0 : st + 1;
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        // the last part also clears the padding, whose columns no group has touched
+        if (SUMS && sums) put_sums(k_hi == nk_all ? a.Gp[g] : k_hi / 2);
     }
     const gptr<float> out = as_global_w(it.Tpart) + ((size_t)part * R + m0) * RP;
 #pragma unroll
@@ -164,11 +202,11 @@ __global__ __launch_bounds__(256, THIRD && RP == 32 ? 1 : 2) void rank_down_kern
     }
 }
 
-// u = sB_c * (M (sA_c * t)) of ROWS rows from i0 on by 256 threads, the K parts of t added in ascending order; put(row, j, head, tail)
+// u = scale sB_c * (M (sA_c * t)) of ROWS rows from i0 on by 256 threads (scale: a power of two), the K parts of t added in ascending order; put(row, j, head, tail)
 // gets every element as two bf16.  With several elements a thread the parts are asked for without a branch between them (26.8 -> 25.5 us,
 // 3584 -> 512 at 512 rows); with one, and rows in the thousands, no more of them than there are.  tv: ROWS x (RP + 4) floats of LDS, Ms: RP x (RP + 4).
 template <int RP, int ROWS, class F>
-__device__ __forceinline__ void rank_rows(const prefill_item& it, int ksplit, int i0, float* tv, float* Ms, F&& put) {
+__device__ __forceinline__ void rank_rows(const prefill_item& it, int ksplit, float scale, int i0, float* tv, float* Ms, F&& put) {
     constexpr int P = RP + 4, EU = ROWS * RP / 256;
     const int tid = threadIdx.x, j = tid % RP, R = it.R;
     const gptr<const float> tp = as_global(it.Tpart);
@@ -202,7 +240,7 @@ __device__ __forceinline__ void rank_rows(const prefill_item& it, int ksplit, in
         float u = 0.f;
 #pragma unroll
         for (int l = 0; l < RP; ++l) u = fmaf(Ms[j * P + l], tv[lr * P + l], u);
-        u *= j < it.r ? sb[k] : 0.f;
+        u *= j < it.r ? sb[k] * scale : 0.f;
         const uint16_t hi = f32_to_bf16_bits(u);
         put(lr, j, hi, f32_to_bf16_bits(u - bf16_bits_to_f32(hi)));
     }
@@ -216,7 +254,7 @@ __global__ __launch_bounds__(256) void rank_finish_kernel(prefill_args a) {
     const prefill_item& it = a.it[blockIdx.y];
     const int i0 = blockIdx.x * ROWS;
     if (it.rp != RP || i0 >= it.R) return;
-    rank_rows<RP, ROWS>(it, a.ksplit[blockIdx.y], i0, tv, Ms, [&](int lr, int j, uint16_t hi, uint16_t lo) {
+    rank_rows<RP, ROWS>(it, a.ksplit[blockIdx.y], a.u_scale, i0, tv, Ms, [&](int lr, int j, uint16_t hi, uint16_t lo) {
         if (i0 + lr >= it.R) return;
         const gptr<uint16_t> ur = as_global_w(it.U16) + (size_t)(i0 + lr) * 2 * RP;
         ur[j] = hi;
@@ -274,6 +312,59 @@ constexpr size_t bf16_smem_bytes(bool ybf16) {
     const size_t stages = XS * BM * 128 + WS * BN * 128 + (NR == 2 ? OWN_BYTES : 0);
     const size_t ctile = ybf16 ? BM * (BN * 2 + 16) : BM * ((NB == 1 ? BN : BN / 2) * 4 + 16);
     return stages > ctile ? stages : ctile;
+}
+
+// An output tile on its way from LDS to memory: BM rows of BN channels from o0 on, of which this half's lie in LDS, NC / HALVES
+// 16-channel blocks of every wave column's NC side by side; block k of a half is the wave's block half_block(half, k).
+template <int HALVES> __device__ __forceinline__ constexpr int half_block(int half, int k) { return HALVES == 1 ? k : 4 * (k >> 1) + 2 * half + (k & 1); }
+
+template <int BM, int BN, int NC, int HALVES, bool YBF16, class ITEM>
+__device__ __forceinline__ void store_rows(const unsigned char* smem, const ITEM& it, int m0, int o0, int half) {
+    constexpr int ESZ = YBF16 ? 2 : 4, EPV = 16 / ESZ, CW = BN / HALVES, CROW = CW * ESZ + 16, PPR = CW / EPV, NH = NC / HALVES;
+    const int tid = threadIdx.x, R = it.R, dout = it.d_out;
+    const bool with_reward = it.rv != nullptr;
+    const bool vec_ok = (dout % EPV == 0) && ((reinterpret_cast<uintptr_t>(it.Y) & 15) == 0);
+    const gptr<unsigned char> Yb = as_global_w(reinterpret_cast<unsigned char*>(it.Y));
+    // full rows, 16 bytes per thread; with a reward vector the row's share over each 128-channel block goes to rowpart
+    const int piece = tid % PPR, c0 = piece * EPV;
+    const int o = o0 + (c0 / (NH * 16)) * (NC * 16) + half_block<HALVES>(half, c0 % (NH * 16) / 16) * 16 + c0 % 16;
+    float rvp[EPV];
+#pragma unroll
+    for (int e = 0; e < EPV; ++e) rvp[e] = (with_reward && o + e < dout) ? as_global(it.rv)[o + e] : 0.f;
+    static_assert(256 % PPR == 0 && (BM * PPR) % 256 == 0, "a thread keeps its piece from row to row");
+#pragma unroll 8
+    for (int p0 = 0; p0 < BM * PPR; p0 += 256) {
+        const int row = (p0 + tid) / PPR, i = m0 + row;
+        const bool valid = i < R && o < dout;
+        const u32x4 val = *reinterpret_cast<const u32x4*>(smem + (size_t)row * CROW + piece * 16);
+        if (valid) {
+            if (vec_ok && o + EPV <= dout) {
+                __builtin_nontemporal_store(val, reinterpret_cast<gptr<u32x4>>(Yb + ((size_t)i * dout + o) * ESZ));
+            } else {
+                for (int e = 0; e < EPV && o + e < dout; ++e) {
+                    if (YBF16) reinterpret_cast<gptr<uint16_t>>(Yb)[(size_t)i * dout + o + e] = (uint16_t)(val[e >> 1] >> (16 * (e & 1)));
+                    else reinterpret_cast<gptr<uint32_t>>(Yb)[(size_t)i * dout + o + e] = val[e];
+                }
+            }
+        }
+        if (with_reward) {
+            constexpr int LPB = 128 / HALVES / EPV;    // lanes per 128-channel block
+            float s = 0.f;
+            if (valid) {
+#pragma unroll
+                for (int e = 0; e < EPV; ++e) {
+                    const float y = YBF16 ? __uint_as_float((e & 1) ? (val[e >> 1] & 0xffff0000u) : (val[e >> 1] << 16)) : __uint_as_float(val[e]);
+                    s = fmaf(o + e < dout ? y : 0.f, rvp[e], s);
+                }
+            }
+#pragma unroll
+            for (int off = LPB / 2; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+            if (piece % LPB == 0 && valid) {
+                const gptr<float> dst = as_global_w(it.rowpart) + (size_t)(o >> 7) * R + i;
+                *dst = half == 0 ? s : *dst + s;       // the second half of the block's channels: this thread wrote the first
+            }
+        }
+    }
 }
 
 // acc += A B with the accumulator pinned to the accumulation registers.  Left to choose, the register allocator moves some of
@@ -381,8 +472,8 @@ __global__ __launch_bounds__(256, (bf16_smem_bytes<NR, NB, XS, WS>(true) > 80 * 
                 const gptr<const uint16_t> ur = as_global(it.U16) + (size_t)min(m0 + e / rp, R - 1) * 2 * rp + e % rp;
                 own(e / rp, e % rp, ur[0], ur[rp]);
             }
-        } else if (rp == 16) rank_rows<16, BM>(it, a.ksplit[g], m0, tv, Ms, own);
-        else rank_rows<32, BM>(it, a.ksplit[g], m0, tv, Ms, own);
+        } else if (rp == 16) rank_rows<16, BM>(it, a.ksplit[g], 1.f, m0, tv, Ms, own);
+        else rank_rows<32, BM>(it, a.ksplit[g], 1.f, m0, tv, Ms, own);
     }
 
     uint32_t xr[2];                                        // this lane's fragment of sub-step j inside an activation stage
@@ -443,14 +534,9 @@ __global__ __launch_bounds__(256, (bf16_smem_bytes<NR, NB, XS, WS>(true) > 80 * 
     // accumulators where they are, and one multiplication per output is all the vector ALU has to do.
     // What it reads from memory is asked for in one batch; rank 16 and 32 are separate straight-line code, so that the
     // blocks' MFMA chains, conversions and LDS writes overlap.
-    constexpr int ESZ = YBF16 ? 2 : 4, EPV = 16 / ESZ, HALVES = YBF16 || NB == 1 ? 1 : 2, CW = BN / HALVES;
-    constexpr int CROW = CW * ESZ + 16, PPR = CW / EPV, NH = NC / HALVES;
-    // An fp32 tile leaves in two halves (64 channels wide: at once).  A half holds NH of the NC 16-channel blocks of both wave columns:
-    // of every 128 channels 0..31 and 64..95, then the others, on either tile width, so that a reward partial is added up in one order whatever tile its group got.
-    auto block = [](int half, int k) { return HALVES == 1 ? k : 4 * (k >> 1) + 2 * half + (k & 1); };
-    const bool with_reward = it.rv != nullptr;
-    const bool vec_ok = (dout % EPV == 0) && ((reinterpret_cast<uintptr_t>(it.Y) & 15) == 0);
-    const gptr<unsigned char> Yb = as_global_w(reinterpret_cast<unsigned char*>(it.Y));
+    constexpr int HALVES = YBF16 || NB == 1 ? 1 : 2, ESZ = YBF16 ? 2 : 4, CROW = BN / HALVES * ESZ + 16, NH = NC / HALVES;
+    // An fp32 tile leaves in two halves (64 channels wide: at once): of every 128 channels 0..31 and 64..95, then the others, on
+    // either tile width, so that a reward partial is added up in one order whatever tile its group got.
     auto to_tile = [&](int k, int m, const f32x4& v) {     // k: the block's place in the half
         unsigned char* dst = smem + (size_t)((wr * NR + m) * 16 + l16) * CROW + (size_t)((wc * NH + k) * 16 + 4 * kg) * ESZ;
         if (YBF16) {
@@ -467,7 +553,7 @@ __global__ __launch_bounds__(256, (bf16_smem_bytes<NR, NB, XS, WS>(true) > 80 * 
         bf16x8 uu[NR][2], ub[2][KS];                       // head and tail of u; U_B and scales one block ahead
         f32x4 sc[2];
         auto ask = [&](int k) {
-            const int n = block(HALF, k);
+            const int n = half_block<HALVES>(HALF, k);
             const int o = min((nb0 + wc * NB) * 32 + n * 16 + l16, dout - 1);
             const gptr<const uint16_t> bp = as_global(it.US16) + (size_t)o * (32 * KS) + 8 * kg;
 #pragma unroll
@@ -489,7 +575,7 @@ __global__ __launch_bounds__(256, (bf16_smem_bytes<NR, NB, XS, WS>(true) > 80 * 
         if constexpr (HALF == 0) wait_loads_and_meet<0>();   // the stages become the output tile
 #pragma unroll
         for (int k = 0; k < NH; ++k) {
-            const int n = block(HALF, k);
+            const int n = half_block<HALVES>(HALF, k);
             __builtin_amdgcn_sched_barrier(0);
             if (k + 1 < NH) ask(k + 1);
             __builtin_amdgcn_sched_barrier(0);
@@ -514,46 +600,7 @@ __global__ __launch_bounds__(256, (bf16_smem_bytes<NR, NB, XS, WS>(true) > 80 * 
         if (rp == 16) finish(std::integral_constant<int, 1>{}, half_c);
         else finish(std::integral_constant<int, 2>{}, half_c);
         __syncthreads();
-        // full rows, 16 bytes per thread; with a reward vector the row's share over each 128-channel block goes to rowpart
-        const int piece = tid % PPR, c0 = piece * EPV;
-        const int o = nb0 * 32 + (c0 / (NH * 16)) * (NC * 16) + block(half, c0 % (NH * 16) / 16) * 16 + c0 % 16;
-        float rvp[EPV];
-#pragma unroll
-        for (int e = 0; e < EPV; ++e) rvp[e] = (with_reward && o + e < dout) ? as_global(it.rv)[o + e] : 0.f;
-        static_assert(256 % PPR == 0 && (BM * PPR) % 256 == 0, "a thread keeps its piece from row to row");
-#pragma unroll 8
-        for (int p0 = 0; p0 < BM * PPR; p0 += 256) {
-            const int row = (p0 + tid) / PPR, i = m0 + row;
-            const bool valid = i < R && o < dout;
-            const u32x4 val = *reinterpret_cast<const u32x4*>(smem + (size_t)row * CROW + piece * 16);
-            if (valid) {
-                if (vec_ok && o + EPV <= dout) {
-                    __builtin_nontemporal_store(val, reinterpret_cast<gptr<u32x4>>(Yb + ((size_t)i * dout + o) * ESZ));
-                } else {
-                    for (int e = 0; e < EPV && o + e < dout; ++e) {
-                        if (YBF16) reinterpret_cast<gptr<uint16_t>>(Yb)[(size_t)i * dout + o + e] = (uint16_t)(val[e >> 1] >> (16 * (e & 1)));
-                        else reinterpret_cast<gptr<uint32_t>>(Yb)[(size_t)i * dout + o + e] = val[e];
-                    }
-                }
-            }
-            if (with_reward) {
-                constexpr int LPB = 128 / HALVES / EPV;    // lanes per 128-channel block
-                float s = 0.f;
-                if (valid) {
-#pragma unroll
-                    for (int e = 0; e < EPV; ++e) {
-                        const float y = YBF16 ? __uint_as_float((e & 1) ? (val[e >> 1] & 0xffff0000u) : (val[e >> 1] << 16)) : __uint_as_float(val[e]);
-                        s = fmaf(o + e < dout ? y : 0.f, rvp[e], s);
-                    }
-                }
-#pragma unroll
-                for (int off = LPB / 2; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-                if (piece % LPB == 0 && valid) {
-                    const gptr<float> dst = as_global_w(it.rowpart) + (size_t)(o >> 7) * R + i;
-                    *dst = half == 0 ? s : *dst + s;       // the second half of the block's channels: this thread wrote the first
-                }
-            }
-        }
+        store_rows<BM, BN, NC, HALVES, YBF16>(smem, it, m0, nb0 * 32, half);
         if constexpr (half + 1 < HALVES) __syncthreads();
     });
 }
@@ -578,6 +625,301 @@ hipError_t launch_bf16(hipStream_t st, prefill_args& a) {
     if (tl_pre_start) hipExtLaunchKernelGGL(kern, dim3(total), dim3(256), (uint32_t)smem, st, tl_pre_start, tl_pre_stop, 0, a);
     else hipLaunchKernelGGL(kern, dim3(total), dim3(256), smem, st, a);
     return hipGetLastError();
+}
+
+// ------------------------------------------------------------------------------------------------
+// Base product for 4-bit weights on the bf16 MFMA, activations as they are.  With q the 4-bit code, (16 + q) 2^-12 is a bf16
+// number whose bits are a constant with q put into its mantissa: one shift and one and-or make two weights.  A group's sum
+// g = <(16 + q) 2^-12, x> over its 128 columns meets its scale in one fp32 FMA, and the zero points and the 16 come back as a product
+// over the groups, - s (z + 16) 2^-12 times the group's sum of x (rank_down's), both as bf16 head and tail, all four products:
+//   Y = 2^12 (sum_g s_g g_g - sum_g s_g (z_g + 16) 2^-12 X_g + U_B 2^-12 u)
+// The 2^-12 keeps every partial sum below the output that it grows into: nothing overflows that the output does not.
+//
+// What bounds it is vector-instruction issue next to the MFMAs: per 16 x 16 x 32 product one FMA, and 7 / NR instructions of
+// unpacking, since a wave of 16 NR rows x 64 channels unpacks a fragment once for NR products (the int8-limb tile needs 16 per pair
+// of its MFMAs).  256 threads = 4 waves side by side, 16 NR rows x 256 channels, so no
+// weight is unpacked twice in a workgroup; two workgroups a CU, whose unpacking, MFMAs and waits overlap.
+//
+// A step is one group.  Activations (D stages: rows of 128 bytes per half group, 16-byte parts swizzled as above), weights (D - 1,
+// a wave's own: a place is free once its codes are in registers) and scales go memory -> LDS directly, D - 1 steps ahead.
+//
+// Measured (6000 rows, q, k, v, o of 3584 columns): 260 us, 1.37 PFLOP/s at 2.0 GHz, against 376 us on the int8-limb tiles; with the launches
+// around it 298 against 456.  MFMAs are 55 % of its cycles; in copies without the unpacking and folding, or without the loads, the cycles fall by an
+// eighth or less and the clock with them: the chip is at its power limit here as in the kernel above.
+// ------------------------------------------------------------------------------------------------
+struct q4_item {
+    const uint16_t *X, *UB16, *U16, *SZn, *XS16;
+    const uint8_t* Wn;
+    const float *St, *rv;
+    void* Y;
+    float* rowpart;
+    int R, d_in, d_out, rp, n_blocks, Gp;
+};
+struct q4_args {
+    q4_item it[ESSA_MAX_GROUP];
+    int tile_start[ESSA_MAX_GROUP + 1];
+    int n_items;
+};
+
+template <int NR, int D>
+constexpr size_t q4_smem_bytes() {
+    constexpr size_t BM = 16 * NR, stages = D * BM * 256 + (D - 1) * 16384 + D * 1024, ctile = BM * (128 * 4 + 16);
+    return stages > ctile ? stages : ctile;
+}
+
+template <int NR, int D, bool YBF16>
+__global__ __launch_bounds__(256, 2) void gemm_q4_exact_kernel(q4_args a) {
+    constexpr int BM = 16 * NR, NC = 4, PATCH = 8, LOADS = NR + NC + 1;   // LOADS: of a wave and step
+    constexpr uint32_t XST = BM * 256, XH = BM * 128, W0 = D * XST, S0 = W0 + (D - 1) * 16384;
+    static_assert((D - 2) * LOADS < 64, "the load counter has six bits");
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_byte*)smem;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l16 = lane & 15, kg = lane >> 4;
+
+    const int b = xcd_contiguous(blockIdx.x, a.tile_start[ESSA_MAX_GROUP]);
+    int gi = 0;
+#pragma unroll
+    for (int i = 1; i < ESSA_MAX_GROUP; ++i) gi += (i < a.n_items && b >= a.tile_start[i]) ? 1 : 0;
+    const q4_item it = fetch_item(a.it[gi]);
+    const int R = it.R, dout = it.d_out, din = it.d_in, rp = it.rp, ng = din / 128, nb16 = it.n_blocks * 2;
+    const int tiles_m = (R + BM - 1) / BM, tiles_n = (it.n_blocks + 7) / 8;
+    int tm, tn;
+    {   // patches of 8 row tiles x all column tiles, rows fastest: the 64 tiles an XCD runs at a time are about 8 x 8
+        const int tile = b - a.tile_start[gi], per = PATCH * tiles_n, grp = tile / per, rem = tile % per;
+        const int rows = min(PATCH, tiles_m - PATCH * grp);
+        tn = rem / rows;
+        tm = PATCH * grp + rem % rows;
+    }
+    const int m0 = tm * BM, nb0 = tn * 8;
+
+    const i32x4 xres = buffer_words(it.X + (size_t)m0 * din), wres = buffer_words(it.Wn), sres = buffer_words(it.St);
+    // load q = wave NR + e of the 4 NR of a step: half group q / (2 NR), 8 rows; its swizzle hangs on the parity of q
+    const uint32_t xlim = (uint32_t)(R - 1 - m0) * (uint32_t)(din * 2), xrow = (uint32_t)(lane >> 3) * (uint32_t)(din * 2);
+    uint32_t xpart[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) xpart[e] = ((lane & 7) ^ ((4 * (wave * NR + e) + (lane >> 4)) & 7)) * 16;
+    const uint32_t lane16 = lane * 16;
+    const uint32_t soff = (uint32_t)min(nb0 * 32 + wave * 64 + lane, it.n_blocks * 32 - 1) * 4u, sstep = (uint32_t)it.n_blocks * 128u;
+    uint32_t woff[NC];
+#pragma unroll
+    for (int n = 0; n < NC; ++n) woff[n] = (uint32_t)min(nb0 * 2 + wave * NC + n, nb16 - 1) * 1024u;
+    auto load_x = [&](int e, int g, uint32_t stage) {
+        const int q = wave * NR + e, half = q >= 2 * NR ? 1 : 0;
+        load_lds16(lds0 + stage + q * 1024, min(xrow + (uint32_t)(q - half * 2 * NR) * 8u * (uint32_t)(din * 2), xlim) + xpart[e & 1], xres, (uint32_t)(g * 256 + half * 128));
+    };
+    auto load_w = [&](int n, int g, uint32_t stage) { load_lds16(lds0 + W0 + stage + (wave * NC + n) * 1024, lane16, wres, (uint32_t)g * (uint32_t)nb16 * 1024u + woff[n]); };
+    auto load_s = [&](int g, uint32_t stage) { load_lds4(lds0 + S0 + stage + wave * 256, soff, sres, (uint32_t)g * sstep); };
+    // the totals start with the zero points' and the rank-r term, whose operands are asked for in front of the first step's.  A fragment of
+    // 32 K columns holds 16 groups twice, head and tail side by side on the weights' side, head and then tail on the other
+    f32x4 tot[NC][NR];
+#pragma unroll
+    for (int n = 0; n < NC; ++n)
+#pragma unroll
+        for (int m = 0; m < NR; ++m) tot[n][m] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    {
+        const int ch0 = nb0 * 32 + wave * 64 + l16, Gp = it.Gp, nc = Gp / 16;
+        bf16x8 z[2][NC], xs[2][NR][2];
+        const rsrc_t zres = make_rsrc(it.SZn), sumres = make_rsrc(it.XS16);
+        uint32_t zoff[NC], sumoff[NR];                     // operand tiles: a kilobyte per 16 channels and 16 groups, half of one per load of sums
+#pragma unroll
+        for (int n = 0; n < NC; ++n) zoff[n] = (uint32_t)min(nb0 * 2 + wave * NC + n, nb16 - 1) * (uint32_t)nc * 1024u;
+#pragma unroll
+        for (int m = 0; m < NR; ++m) sumoff[m] = (uint32_t)min(m0 / 16 + m, (R - 1) / 16) * (uint32_t)nc * 1024u;
+        auto ask = [&](int c, int set) {
+#pragma unroll
+            for (int n = 0; n < NC; ++n) z[set][n] = __builtin_bit_cast(bf16x8, load16(zres, lane16, zoff[n] + c * 1024));
+#pragma unroll
+            for (int m = 0; m < NR; ++m)
+#pragma unroll
+                for (int e = 0; e < 2; ++e) xs[set][m][e] = __builtin_bit_cast(bf16x8, load16(sumres, lane16 & 511, sumoff[m] + c * 1024 + e * 512));
+        };
+        auto multiply = [&](int set) {
+#pragma unroll
+            for (int e = 1; e >= 0; --e)
+#pragma unroll
+                for (int n = 0; n < NC; ++n)
+#pragma unroll
+                    for (int m = 0; m < NR; ++m) tot[n][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(z[set][n], xs[set][m][e], tot[n][m], 0, 0, 0);
+        };
+        ask(0, 0);
+        ask(min(1, nc - 1), 1);
+        __builtin_amdgcn_sched_barrier(0);
+        static_for<D - 1>([&](auto tc) {
+            constexpr int t = tc;
+#pragma unroll
+            for (int n = 0; n < NC; ++n) load_w(n, min(t, ng - 1), t * 16384);
+#pragma unroll
+            for (int e = 0; e < NR; ++e) load_x(e, min(t, ng - 1), t * XST);
+            load_s(min(t, ng - 1), t * 1024);
+        });
+        for (int c = 0; c < nc; c += 2) {
+            multiply(0);
+            if (c + 2 < nc) ask(c + 2, 0);
+            if (c + 1 < nc) multiply(1);
+            if (c + 3 < nc) ask(c + 3, 1);
+        }
+        auto rank_term = [&](auto ks_count) {              // as in the kernel above, for u 2^-12
+            constexpr int KS = decltype(ks_count)::value;
+            bf16x8 ub[NC][KS], uu[NR][2];
+            const rsrc_t bres = make_rsrc(it.UB16), ures = make_rsrc(it.U16);
+#pragma unroll
+            for (int n = 0; n < NC; ++n)
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) ub[n][ks] = __builtin_bit_cast(bf16x8, load16(bres, (uint32_t)min(ch0 + n * 16, dout - 1) * (64 * KS) + 16 * kg, 64 * ks));
+#pragma unroll
+            for (int m = 0; m < NR; ++m)
+#pragma unroll
+                for (int e = 0; e < 2; ++e)
+                    uu[m][e] = __builtin_bit_cast(bf16x8, load16(ures, (uint32_t)min(m0 + m * 16 + l16, R - 1) * (64 * KS) + 16 * (KS == 1 ? kg & 1 : kg), e * 32 * KS));
+#pragma unroll
+            for (int n = 0; n < NC; ++n)
+#pragma unroll
+                for (int m = 0; m < NR; ++m) {
+                    tot[n][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ub[n][0], uu[m][1], tot[n][m], 0, 0, 0);
+                    if (KS == 2) tot[n][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ub[n][KS - 1], uu[m][0], tot[n][m], 0, 0, 0);
+                    tot[n][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ub[n][0], uu[m][0], tot[n][m], 0, 0, 0);
+                }
+        };
+        if (rp == 16) rank_term(std::integral_constant<int, 1>{});
+        else rank_term(std::integral_constant<int, 2>{});
+    }
+
+    uint32_t xr[2];                                        // this lane's fragment of the even and odd 32 columns of a half group
+#pragma unroll
+    for (int j = 0; j < 2; ++j) xr[j] = l16 * 128 + (((4 * j + kg) ^ ((l16 >> 1) & 7)) * 16);
+    const uint32_t mask = 0x00780078u;
+    uint32_t tag = 0x3b803b80u;
+    asm("" : "+v"(tag));                                   // in a vector register: one instruction takes one constant from elsewhere
+    uint32_t cur = 0, far = (D - 1) * XST, w_cur = 0, s_cur = 0, s_far = (D - 1) * 1024;
+    for (int g = 0; g < ng; ++g) {
+        wait_loads_and_meet<(D - 2) * LOADS>();            // step g is in LDS, nobody reads step g - 1 any more
+        u32x4 raw[NC];
+        f32x4 sc[NC], sum[2][NC];
+        bf16x8 xa[4], w[NC][4];
+        auto frag = [&](int m, int k) { return *reinterpret_cast<const bf16x8*>(smem + cur + (k >> 1) * XH + m * 2048 + xr[k & 1]); };
+#pragma unroll
+        for (int n = 0; n < NC; ++n) raw[n] = *reinterpret_cast<const u32x4*>(smem + W0 + w_cur + (wave * NC + n) * 1024 + lane16);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) xa[k] = frag(0, k);
+#pragma unroll
+        for (int n = 0; n < NC; ++n) sc[n] = *reinterpret_cast<const f32x4*>(smem + S0 + s_cur + (wave * 64 + n * 16 + 4 * kg) * 4);
+        const int gn = min(g + D - 1, ng - 1);             // past the end the last step is fetched again, and never read
+        auto fold = [&](int m, int i) {                    // element i of row block m's group sums, times its scale
+            tot[i >> 2][m][i & 3] = fmaf(sc[i >> 2][i & 3], sum[m & 1][i >> 2][i & 3], tot[i >> 2][m][i & 3]);
+        };
+        __builtin_amdgcn_sched_barrier(0);
+        static_for<NR>([&](auto mc) {
+            constexpr int m = mc;
+            static_for<4>([&](auto kc) {
+                constexpr int k = kc;
+                static_for<NC>([&](auto nc) {
+                    constexpr int n = nc, at = k * NC + n;
+                    if constexpr (m == 0) {
+                        // eight codes: pair i of the fragment has its codes at bits 3 + 4 i and 19 + 4 i (mod 32)
+                        const uint32_t r = raw[n][k];
+                        const u32x4 f = {(r & mask) | tag, ((r >> 4) & mask) | tag, ((r >> 8) & mask) | tag, (__builtin_amdgcn_alignbit(r, r, 12) & mask) | tag};
+                        w[n][k] = __builtin_bit_cast(bf16x8, f);
+                    }
+                    const f32x4 c = k == 0 ? (f32x4){0.f, 0.f, 0.f, 0.f} : sum[m & 1][n];
+                    sum[m & 1][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[n][k], xa[k], c, 0, 0, 0);
+                    if constexpr (m > 0) fold(m - 1, at);
+                    // the codes are all in registers by row block 1: their place is free
+                    if constexpr (m == 1 && at % 4 == 1) load_w(at / 4, gn, w_cur);
+                    if constexpr (m >= 1 && m <= 2 && at % 4 == 3) {
+                        constexpr int e = (m - 1) * 4 + k;
+                        if constexpr (e < NR) load_x(e, gn, far);
+                        if constexpr (e == NR) load_s(gn, s_far);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                });
+                if constexpr (m + 1 < NR) xa[k] = frag(m + 1, k);
+            });
+        });
+#pragma unroll
+        for (int i = 0; i < 16; ++i) fold(NR - 1, i);
+        far = cur;                                         // its last reader was this step
+        cur = cur == (D - 1) * XST ? 0 : cur + XST;
+        s_far = s_cur;
+        s_cur = s_cur == (D - 1) * 1024 ? 0 : s_cur + 1024;
+        w_cur = w_cur == (D - 2) * 16384 ? 0 : w_cur + 16384;
+    }
+    wait_loads_and_meet<0>();                              // the stages become the output tile
+    constexpr int HALVES = YBF16 ? 1 : 2, ESZ = YBF16 ? 2 : 4, CROW = 256 / HALVES * ESZ + 16, NH = NC / HALVES;
+    static_for<HALVES>([&](auto half_c) {
+        constexpr int half = half_c;
+#pragma unroll
+        for (int k = 0; k < NH; ++k)
+#pragma unroll
+            for (int m = 0; m < NR; ++m) {
+                const f32x4 v = tot[half_block<HALVES>(half, k)][m] * 0x1p12f;
+                unsigned char* dst = smem + (size_t)(m * 16 + l16) * CROW + (size_t)((wave * NH + k) * 16 + 4 * kg) * ESZ;
+                if (YBF16) {
+                    typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+                    *reinterpret_cast<bf16x4*>(dst) = __builtin_convertvector(v, bf16x4);
+                } else {
+                    *reinterpret_cast<f32x4*>(dst) = v;
+                }
+            }
+        __syncthreads();
+        store_rows<BM, 256, NC, HALVES, YBF16>(smem, it, m0, nb0 * 32, half);
+        if constexpr (half + 1 < HALVES) __syncthreads();
+    });
+}
+
+template <int NR, int D, bool YBF16>
+hipError_t launch_q4(hipStream_t st, q4_args& a) {
+    int total = 0;
+    for (int g = 0; g < a.n_items; ++g) {
+        a.tile_start[g] = total;
+        total += ((a.it[g].R + 16 * NR - 1) / (16 * NR)) * ((a.it[g].n_blocks + 7) / 8);
+    }
+    for (int g = a.n_items; g <= ESSA_MAX_GROUP; ++g) a.tile_start[g] = total;
+    constexpr size_t smem = q4_smem_bytes<NR, D>();
+    static_assert(smem <= 160 * 1024, "tile does not fit the LDS of a CU");
+    auto kern = gemm_q4_exact_kernel<NR, D, YBF16>;
+    static bool attr_done = false;   // one flag per instantiation
+    if (!attr_done) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+        if (e != hipSuccess) return e;
+        attr_done = true;
+    }
+    if (tl_pre_start) hipExtLaunchKernelGGL(kern, dim3(total), dim3(256), (uint32_t)smem, st, tl_pre_start, tl_pre_stop, 0, a);
+    else hipLaunchKernelGGL(kern, dim3(total), dim3(256), smem, st, a);
+    return hipGetLastError();
+}
+
+// Rows of its tile, by the same kind of formula as for int8 weights below, fitted to 60 groups and single projections of 512 to
+// 8192 columns with every tile forced (rms 3 to 5 %; 1 % on average from the fastest tile, 10 % at worst):
+//   us = call + rounds * round + groups * (full rounds * hi + last round's lo .. hi)
+// The tallest tile unpacks least per product, and a last round that is not full costs what it costs whatever its tiles.  Two deep
+// stages are for one workgroup a CU, which has nobody to fill its waits.  q, k, v, o, us by rows of the tile (int8-limb tiles):
+//   8192 columns  320 rows  126 at 64 (133), 512 rows  150 at 80, 158 at 96, 191 at 64 (181), 1187 rows 305 at 96, 326 at 80 (404)
+//   3584 columns  640 rows  50 at 80, 53 at 96, 61 at 64 (71), 6000 rows 298 at 96, 318 at 80, 340 at 64 (456)
+enum q4_tile { Q4_48_DEEP, Q4_64_DEEP, Q4_64, Q4_80, Q4_96 };
+struct q4_cost { int rows, slots; double call, round, lo, mid, hi; };
+constexpr q4_cost Q4_COST[] = {{48, 256, 12.9, 3.8, 0.854, 0, 0.863}, {64, 256, 12.0, 5.2, 0.977, 0, 1.002}, {64, 512, 10.9, 5.4, 1.076, 1.638, 1.638},
+                               {80, 512, 11.5, 5.9, 1.135, 1.899, 1.899}, {96, 512, 9.4, 7.9, 1.257, 2.068, 2.233}};
+q4_tile pick_q4_tile(const q4_args& a) {
+    int best = 0, ng = 1;
+    double best_us = 0;
+    for (int g = 0; g < a.n_items; ++g) ng = std::max(ng, a.it[g].d_in / 128);
+    for (int i = 0; i < (int)(sizeof(Q4_COST) / sizeof(Q4_COST[0])); ++i) {
+        const q4_cost& c = Q4_COST[i];
+        long long tiles = 0;
+        for (int g = 0; g < a.n_items; ++g) tiles += (long long)((a.it[g].R + c.rows - 1) / c.rows) * ((a.it[g].n_blocks + 7) / 8);
+        const long long full = tiles / c.slots, rest = tiles % c.slots;
+        const double over = std::max(0.0, 2.0 * rest / c.slots - 1.0);
+        double last = 0;
+        if (rest) last = c.slots == 512 ? (over == 0 ? c.lo : c.mid + (c.hi - c.mid) * over) : c.lo + (c.hi - c.lo) * over * over;
+        const double us = c.call + c.round * (full + (rest ? 1 : 0)) + ng * (full * c.hi + last);
+        if (i == 0 || us < best_us) {
+            best = i;
+            best_us = us;
+        }
+    }
+    return (q4_tile)best;
 }
 
 // Which tile takes a group.  Tiles go to the 256 CUs in rounds, so the time is what does not depend on K, per call and per round, plus
@@ -637,6 +979,7 @@ bf16_tile pick_tile(const prefill_item* items, int n_items) {
 hipError_t launch_rank(hipStream_t st, prefill_args& a, bool finish) {
     int total = 0, maxR = 0;
     bool has16[2] = {false, false}, has32[2] = {false, false};   // [V_A with all its bits]
+    const bool sums = a.Gp[0] > 0;         // 4-bit weights throughout
     for (int g = 0; g < a.n_items; ++g) {
         // K parts: enough workgroups for two per CU in a group of four projections, no part shorter than four steps; by the
         // item's own size only, so that an item's sums do not depend on what it is grouped with
@@ -648,9 +991,12 @@ hipError_t launch_rank(hipStream_t st, prefill_args& a, bool finish) {
         (a.it[g].rp == 16 ? has16 : has32)[a.it[g].VA3p != nullptr] = true;
     }
     for (int g = a.n_items; g <= ESSA_MAX_GROUP; ++g) a.tile_start[g] = total;
-    if (has16[0]) hipLaunchKernelGGL((rank_down_kernel<16, false>), dim3(total), dim3(256), 0, st, a);
+    if (sums) {
+        if (has16[0]) hipLaunchKernelGGL((rank_down_kernel<16, false, true>), dim3(total), dim3(256), 0, st, a);
+        if (has32[0]) hipLaunchKernelGGL((rank_down_kernel<32, false, true>), dim3(total), dim3(256), 0, st, a);
+    } else if (has16[0]) hipLaunchKernelGGL((rank_down_kernel<16, false>), dim3(total), dim3(256), 0, st, a);
     if (has16[1]) hipLaunchKernelGGL((rank_down_kernel<16, true>), dim3(total), dim3(256), 0, st, a);
-    if (has32[0]) hipLaunchKernelGGL((rank_down_kernel<32, false>), dim3(total), dim3(256), 0, st, a);
+    if (has32[0] && !sums) hipLaunchKernelGGL((rank_down_kernel<32, false>), dim3(total), dim3(256), 0, st, a);
     if (has32[1]) hipLaunchKernelGGL((rank_down_kernel<32, true>), dim3(total), dim3(256), 0, st, a);
     if (!finish) return hipGetLastError();
     if (has16[0] || has16[1]) hipLaunchKernelGGL(rank_finish_kernel<16>, dim3((maxR + 15) / 16, a.n_items), dim3(256), 0, st, a);
@@ -685,6 +1031,60 @@ hipError_t expand_weights(hipStream_t st, const int8_t* Wt, const float* scale, 
     return hipGetLastError();
 }
 
+// One thread per word of eight codes: block (g, 16 channels), lane (kg, l16), word j = columns 128 g + 32 j + 8 kg .. + 7 of channel l16
+__global__ __launch_bounds__(256) void repack_nibbles_kernel(const int8_t* __restrict__ Wt, int n_blocks, long long words, uint32_t* __restrict__ Wn) {
+    for (long long p = (long long)blockIdx.x * 256 + threadIdx.x; p < words; p += (long long)gridDim.x * 256) {
+        const int j = (int)(p & 3), lane = (int)(p >> 2) & 63, kg = lane >> 4;
+        const long long blk = p >> 8, g = blk / (2 * n_blocks);
+        const int ch = (int)(blk % (2 * n_blocks)) * 16 + (lane & 15);
+        // the int8 operand tile: pair of 32-column chunks 2 g + j / 2, low nibbles the even chunk's, high ones the odd one's
+        const int8_t* src = Wt + ((2 * g + (j >> 1)) * n_blocks + ch / 32) * 1024 + ((kg >> 1) * 32 + ch % 32) * 16 + 8 * (kg & 1);
+        uint32_t w = 0;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const uint32_t q = ((uint8_t)src[e] >> (4 * (j & 1))) & 15u;
+            const int at = 3 + 4 * (e >> 1) + 16 * (e & 1);
+            w |= (q << (at & 31)) | (at > 28 ? q >> (32 - at) : 0u);
+        }
+        Wn[p] = w;
+    }
+}
+
+hipError_t repack_nibbles(hipStream_t st, const int8_t* Wt, int groups, int n_blocks, uint8_t* Wn) {
+    const long long words = (long long)groups * n_blocks * 512;
+    hipLaunchKernelGGL(repack_nibbles_kernel, dim3((unsigned)std::min<long long>((words + 255) / 256, 4096)), dim3(256), 0, st, Wt, n_blocks, words, (uint32_t*)Wn);
+    return hipGetLastError();
+}
+
+hipError_t forward_prefill_q4(hipStream_t st, const fwd_item* items, int n_items, int y_dtype, hipEvent_t ev_start, hipEvent_t ev_stop) {
+    prefill_args r{};
+    q4_args a{};
+    for (int g = 0; g < n_items; ++g) {
+        const fwd_item& k = items[g];
+        r.it[g] = prefill_item{(const uint16_t*)k.X, nullptr, nullptr, k.VAp, nullptr, nullptr, k.M, k.sigmaA, k.sigmaB, nullptr, k.row2cand, nullptr,
+                               k.U16, k.Tpart, nullptr, k.sigma_stride, k.R, k.d_in, k.d_out, k.r, k.rp, k.n_blocks};
+        r.XS16[g] = k.x_owner ? k.XS16 : nullptr;
+        r.Gp[g] = k.Gp;
+        a.it[g] = q4_item{(const uint16_t*)k.X, k.UB16, k.U16, k.SZn, k.XS16, k.Wn, k.St, k.rv, k.Y, k.rowpart, k.R, k.d_in, k.d_out, k.rp, k.n_blocks, k.Gp};
+    }
+    r.n_items = a.n_items = n_items;
+    r.u_scale = 0x1p-12f;
+    hipError_t e = launch_rank(st, r, true);
+    if (e != hipSuccess) return e;
+    tl_pre_start = ev_start;
+    tl_pre_stop = ev_stop;
+    const bool yb = y_dtype == ESSA_BF16;
+    switch (pick_q4_tile(a)) {
+        case Q4_48_DEEP: e = yb ? launch_q4<3, 4, true>(st, a) : launch_q4<3, 4, false>(st, a); break;
+        case Q4_64_DEEP: e = yb ? launch_q4<4, 4, true>(st, a) : launch_q4<4, 4, false>(st, a); break;
+        case Q4_64: e = yb ? launch_q4<4, 2, true>(st, a) : launch_q4<4, 2, false>(st, a); break;
+        case Q4_80: e = yb ? launch_q4<5, 2, true>(st, a) : launch_q4<5, 2, false>(st, a); break;
+        default: e = yb ? launch_q4<6, 2, true>(st, a) : launch_q4<6, 2, false>(st, a); break;
+    }
+    tl_pre_start = tl_pre_stop = nullptr;
+    return e;
+}
+
 bool prefill_takes(const fwd_item& it) {
     return it.quant == ESSA_QUANT_INT8_PERCH && it.W16 && it.d_in % 16 == 0 && ((uintptr_t)it.X & 15) == 0;
 }
@@ -699,6 +1099,7 @@ hipError_t forward_prefill(hipStream_t st, const fwd_item* items, int n_items, i
     }
     a.n_items = n_items;
     a.flags = flags;
+    a.u_scale = 1.f;
     const bf16_tile tile = pick_tile(a.it, n_items);
     if (flags & ESSA_BASE_ONLY) {
         int maxR = 0;

@@ -1,0 +1,108 @@
+"""GPU parity of the exact-product kernel for 4-bit weights (codes as bf16, fp32 group sums) at the edges of its tiles.
+
+Products are exact and fp32 sums random-signed; what is left is the zero-point term, whose two operands (scale times zero + 16, and
+the group's sum of x) enter as bf16 head and tail: each off by 2^-17 at most, 2^-18 rms, of a term that is about
+(8 + 16) / 4.6 = 5.2 times the output's rms for the codes and zeros drawn here.  sqrt(2) 2^-18 5.2 = 2.8e-5 rms at most."""
+import numpy as np
+import pytest
+import torch
+
+import essa_workloads as wl
+import oracle as orc
+from helpers import bf16_dev, bf16_host, candidate_sigmas, gpu_proj, oracle_proj, to_dev
+
+pytestmark = pytest.mark.gpu
+
+Q4_RMS, Q4_MAX = 3e-5, 3e-4
+BF16_RMS, BF16_MAX = 1e-3, 2e-2
+
+
+@pytest.mark.parametrize("d_in,d_out,r,Rs", [
+    (2048, 2100, 24, (1029, 1360, 1805, 2260)),           # tiles of 48 and 64 rows with deep stages, 80, 96; output width not a multiple of 8
+    (1152, 1400, 16, (1100, 2030, 3001, 3400)),           # nine groups in two sixteens: 48, 64, 80, 96 rows
+    (4224, 264, 7, (513, 777)),                           # 33 groups: past one window of group sums, the last K part alone in the next
+])
+def test_q4_exact_tiles(essa, d_in, d_out, r, Rs):
+    """The rows repeat the first `base`, so each has the bits of the row that it repeats wherever it falls in whatever tile (at row counts
+    for which the rank-r term's K is cut alike)."""
+    ctx = essa.Context(0)
+    K, base = 4, 500
+    p = wl.make_projection("t", d_in, d_out, r, "int4", layer=21, proj=1)
+    W, f = oracle_proj(p)
+    gp = gpu_proj(essa, ctx, p)
+    sA, sB = candidate_sigmas(f, K, 0.05)
+    xb, xv = wl.make_x_bf16(base, d_in, x_id=71)
+    # rows at the ends of the format: nothing in between overflows or vanishes
+    big, small = np.float32(2.0) ** 114, np.float32(2.0) ** -90
+    xv = xv.copy()
+    xv[7] *= big
+    xv[8] *= small
+    X = torch.from_numpy(xv).cuda().bfloat16()
+    r2c = np.random.default_rng(9).integers(0, K, base).astype(np.int32)
+    rd, sAd, sBd = to_dev(r2c), to_dev(sA), to_dev(sB)
+    ref = orc.svdlora_forward(W, f, xv, r2c, sA, sB)
+    unit = np.ones((base, 1))
+    unit[7], unit[8] = 1.0 / float(big), 1.0 / float(small)
+    nblk = (d_out + 127) // 128
+    v = torch.randn(d_out, device="cuda", generator=torch.Generator(device="cuda").manual_seed(3))
+    for dtype in (torch.float32, torch.bfloat16):
+        first = None
+        for R in Rs:
+            print("q4 exact: d_in=%d d_out=%d r=%d R=%d %s" % (d_in, d_out, r, R, dtype), flush=True)
+            at = torch.arange(R, device="cuda") % base
+            Y = torch.full((R, d_out), float("nan"), device="cuda", dtype=dtype)
+            part = torch.full((nblk, R), float("nan"), device="cuda")
+            essa.essa_svdlora_forward_reward_group(ctx, [(gp, X[at].contiguous(), rd[at].contiguous(), sAd, sBd, Y)], [v], part, 0)
+            first = first or (Y[:base], part[:, :base])
+            assert torch.equal(Y, first[0][at]) and torch.equal(part, first[1][:, at])
+        got = (first[0].cpu().numpy() if dtype == torch.float32 else bf16_host(first[0])).astype(np.float64) * unit
+        want = (ref if dtype == torch.float32 else orc.round_to_bf16(ref)) * unit
+        e_max, e_rms = orc.rel_errors(got, want)
+        assert (e_rms <= Q4_RMS and e_max <= Q4_MAX) if dtype == torch.float32 else (e_rms <= BF16_RMS and e_max <= BF16_MAX), (e_rms, e_max)
+        for i in (7, 8):
+            assert orc.rel_errors(got[i], want[i])[1] <= (2 * Q4_RMS if dtype == torch.float32 else 3 * BF16_RMS)
+        # the partials are sums of 128 products of the outputs as written, in fp32
+        pad = torch.zeros(base, nblk * 128 - d_out, device="cuda", dtype=torch.float64)
+        parts = torch.cat([first[0].double() * v.double(), pad], 1).view(base, nblk, 128)
+        assert torch.all((first[1].T.double() - parts.sum(2)).abs() <= 128 * 2.0 ** -24 * parts.abs().sum(2) + 1e-30)
+    # a non-finite entry spoils its own row and nothing else
+    R = Rs[0]
+    at = torch.arange(R, device="cuda") % base
+    Xb = X[at].contiguous()
+    for bad in (float("inf"), float("nan")):
+        Xb[R - 2, d_in - 1] = bad
+        Y = torch.empty(R, d_out, device="cuda")
+        essa.essa_svdlora_forward(ctx, gp, Xb, rd[at].contiguous(), sAd, sBd, Y)
+        Y0 = torch.empty(R, d_out, device="cuda")
+        essa.essa_svdlora_forward(ctx, gp, X[at].contiguous(), rd[at].contiguous(), sAd, sBd, Y0)
+        keep = torch.arange(R, device="cuda") != R - 2
+        assert torch.isnan(Y[R - 2]).all() and torch.equal(Y[keep], Y0[keep])
+    gp.close()
+    ctx.close()
+
+
+def test_q4_exact_group_and_limbs(essa):
+    """A group on two inputs, ranks 16 and 32 mixed: the bits of single calls, whichever tile each gets; and next to the limb path, which
+    takes the same rows when there are fewer of them, within both paths' noise (2^-16 of the row's largest entry, 3.5e-5 here)."""
+    ctx = essa.Context(0)
+    R, K, d_in = 700, 5, 3072
+    specs = [(3072, 16), (520, 32), (40, 7), (1000, 24)]
+    Xs = [bf16_dev(wl.make_x_bf16(R, d_in, x_id=80 + i)[0]) for i in range(2)]
+    rd = to_dev(np.random.default_rng(8).integers(0, K, R).astype(np.int32))
+    items = []
+    for i, (d_out, r) in enumerate(specs):
+        p = wl.make_projection("t", d_in, d_out, r, "int4", layer=22, proj=i)
+        _, f = oracle_proj(p)
+        sA, sB = candidate_sigmas(f, K, 0.05, i)
+        items.append([gpu_proj(essa, ctx, p), Xs[i == 3], rd, to_dev(sA), to_dev(sB), torch.empty(R, d_out, device="cuda")])
+    essa.essa_svdlora_forward_group(ctx, [tuple(it) for it in items])
+    for it in items:
+        print("d_out=%d" % it[0].d_out, flush=True)
+        Y = torch.empty_like(it[5])
+        essa.essa_svdlora_forward(ctx, *it[:5], Y)
+        assert torch.equal(Y, it[5])
+        few = torch.empty(256, it[0].d_out, device="cuda")
+        essa.essa_svdlora_forward(ctx, it[0], it[1][:256].contiguous(), rd[:256].contiguous(), it[3], it[4], few)
+        assert (few - Y[:256]).norm() <= 8e-5 * few.norm()
+        it[0].close()
+    ctx.close()
