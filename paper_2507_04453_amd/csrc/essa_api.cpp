@@ -660,9 +660,9 @@ extern "C" essa_status essa_sample_candidates(essa_ctx* ctx, const essa_cma* cma
                                      theta_out, z_out));
         return ESSA_OK;
     }
-    ESSA_TRY(essa_ws_reserve(ctx, align256((size_t)K * n * sizeof(float))));
+    ESSA_TRY(essa_ws_reserve(ctx, essa_k::tiled_rows_bytes(K, n)));
     float* S = (float*)ctx->ws;
-    ESSA_HIP(essa_k::normals_scaled(ctx->stream, seeds, nullptr, K, n, cma->D, S, z_out));
+    ESSA_HIP(essa_k::normals_tiled(ctx->stream, seeds, nullptr, K, n, cma->D, S, z_out));
     ESSA_HIP(essa_k::skinny_gemm_nt(ctx->stream, S, K, cma->B, n, cma->m, cma->sc, 1, theta_out));
     return ESSA_OK;
 }
@@ -1131,10 +1131,10 @@ extern "C" essa_status essa_cmaes_update(essa_ctx* ctx, essa_cma* cma, const uin
     }
     // scratch: order[K] | zn2[ny] | S[(ny+2), n] | BY[(ny+2), n] | Z[ny, n];  S rows: D*z_i (i < ny), z_w, D*z_w
     const size_t rows = (size_t)c.ny + 2;
-    const size_t off_zn = align256((size_t)K * 4), off_S = off_zn + align256((size_t)c.ny * 4), off_BY = off_S + align256(rows * n * 4);
+    const size_t off_zn = align256((size_t)K * 4), off_S = off_zn + align256((size_t)c.ny * 4), off_BY = off_S + essa_k::tiled_rows_bytes(rows, n);
     const size_t off_Z = off_BY + align256(rows * n * 4);
     ESSA_TRY(essa_ws_reserve(ctx, off_Z + align256(rows * n * 4)));
-    int32_t* order = (int32_t*)ctx->ws;
+    int32_t* order = order_out ? order_out : (int32_t*)ctx->ws;
     float* zn2 = (float*)((char*)ctx->ws + off_zn);
     float* S = (float*)((char*)ctx->ws + off_S);
     float* BY = (float*)((char*)ctx->ws + off_BY);
@@ -1142,8 +1142,8 @@ extern "C" essa_status essa_cmaes_update(essa_ctx* ctx, essa_cma* cma, const uin
     // the ranking: inside the kernel that regenerates the normals when the population is small, else a launch of its own
     const bool rank_inside = K <= essa_k::kRankInKernelMax;
     if (!rank_inside) ESSA_HIP(essa_k::rank_rewards(ctx->stream, rewards, K, order));
-    ESSA_HIP(essa_k::cma_build_rhs(ctx->stream, seeds, order, rank_inside ? rewards : nullptr, cma->weights, c, cma->D, S, Z));
-    if (order_out) ESSA_HIP(hipMemcpyAsync(order_out, order, (size_t)K * 4, hipMemcpyDeviceToDevice, ctx->stream));
+    ESSA_HIP(essa_k::cma_build_rhs(ctx->stream, seeds, order, rank_inside ? rewards : nullptr, cma->weights, c, cma->D, S, Z,
+                                   has_matrix(cma), cma->kind == ESSA_OPT_ACTIVE_CMA));
     if (cma->kind == ESSA_OPT_SEP_CMA) {
         // B = I: the rows of S are the y_i, z_w and y_w themselves
         ESSA_HIP(essa_k::cma_vectors(ctx->stream, c, cma->weights, S, cma->m, cma->p_sigma, cma->p_c, cma->sc));

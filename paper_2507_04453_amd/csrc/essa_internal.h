@@ -127,10 +127,17 @@ constexpr int kRankInKernelMax = 256;
 hipError_t normals_scaled(hipStream_t st, const uint32_t* seeds, const int32_t* sel /*null or [J]*/, int J, int n,
                           const float* D /*null = 1*/, float* S, float* z_out, const float* rank_F = nullptr, int rank_K = 0,
                           int32_t* rank_order = nullptr);
+// the same with S in the operand tiles of skinny_gemm_nt: [rows / 16][columns / 16][4][16 rows][4 columns], columns past n zero
+hipError_t normals_tiled(hipStream_t st, const uint32_t* seeds, const int32_t* sel, int J, int n, const float* D, float* S, float* z_out,
+                         const float* rank_F = nullptr, int rank_K = 0, int32_t* rank_order = nullptr);
+constexpr size_t tiled_rows_bytes(size_t rows, size_t n) { return (rows + 15) / 16 * ((n + 15) / 16) * 1024; }
+// an update's right-hand sides in one launch (rows as for cma_build_rhs, tiles; ny <= 64 of them gain by it); Z null or [ny, n]
+hipError_t update_rhs(hipStream_t st, const uint32_t* seeds, const int32_t* sel, int ny, int mu, int n, const float* w, const float* D, float* S,
+                      float* Z, const float* rank_F, int rank_K, int32_t* rank_order);
 // theta[k, l] = m[l] + s_k sigma (D ? D[l] : 1) z[l];  pairs: candidate k uses seeds[k / 2] and s_k = +1, -1, else seeds[k], +1
 hipError_t sample_diag(hipStream_t st, const uint32_t* seeds, int K, int n, const float* m, const float* D,
                        const essa_cma_scalars* sc, int pairs, float* theta, float* z_out);
-// Out[j, i] = bias[i] + scale * sum_l S[j,l] B[i,l]; scale = use_sigma ? sc->sigma : 1; bias may be null
+// Out[j, i] = bias[i] + scale * sum_l S[j,l] B[i,l] (S in operand tiles); scale = use_sigma ? sc->sigma : 1; bias may be null
 hipError_t skinny_gemm_nt(hipStream_t st, const float* S, int J, const float* B, int n, const float* bias,
                           const essa_cma_scalars* sc, int use_sigma, float* Out);
 hipError_t theta_to_sigma(hipStream_t st, int P, int r, int n_top, const float* sftA, const float* sftB,
@@ -153,8 +160,9 @@ struct cma_consts {
 };
 // S rows 0..ny-1 = D*z_sel, row ny = z_w (the mu positive weights applied), row ny+1 = D*z_w; needs order
 // rewards non-null: the ranking is taken inside (c.K <= kRankInKernelMax) and written to order; else order is read
+// tiled: S in the tiles of skinny_gemm_nt, else in rows; Z ([ny, n] scratch) holds the z_i afterwards if want_z
 hipError_t cma_build_rhs(hipStream_t st, const uint32_t* seeds, int32_t* order, const float* rewards, const float* w,
-                         const cma_consts& c, const float* D, float* S, float* Z /*[ny,n] scratch*/);
+                         const cma_consts& c, const float* D, float* S, float* Z, bool tiled, bool want_z);
 hipError_t cma_vectors(hipStream_t st, const cma_consts& c, const float* w, const float* BY /*[ny+2,n]*/,
                        float* m, float* p_sigma, float* p_c, essa_cma_scalars* sc);
 // zn2: [ny] squared lengths of the sorted z (read for negative weights only), or null

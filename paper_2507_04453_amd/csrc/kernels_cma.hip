@@ -28,10 +28,18 @@ __global__ __launch_bounds__(1024) void rank_kernel(const float* __restrict__ F,
 
 // z_w[l] = sum_i w[i] Z[i, l], summed for i = 0..mu-1 in fp64;  out_z = z_w,  out_dz = D * z_w.  Latency: a wave per workgroup, so
 // that n in the thousands reaches many CUs, and the loads of eight rows asked for together (n = 3584, 16 rows: 5.7 -> 4.6 us).
+// The two rows go where `at` says: rows of n, or the operand tiles of the product with the basis (columns past n zero there).
+template <bool TILED>
 __global__ void weighted_rowsum_kernel(const float* __restrict__ Z, const float* __restrict__ w, const float* __restrict__ D, int mu,
-                                       int n, float* __restrict__ out_z, float* __restrict__ out_dz) {
+                                       int n, int ny, float* __restrict__ S) {
     const int l = blockIdx.x * blockDim.x + threadIdx.x;
-    if (l >= n) return;
+    auto at = [&](int j) {
+        return TILED ? (((size_t)(j >> 4) * ((n + 15) >> 4) + (l >> 4)) * 64 + (l >> 2 & 3) * 16 + (j & 15)) * 4 + (l & 3) : (size_t)j * n + l;
+    };
+    if (l >= n) {
+        if (TILED && l < (n + 15) / 16 * 16) S[at(ny)] = S[at(ny + 1)] = 0.f;
+        return;
+    }
     const float dl = D[l];
     double acc = 0.0;
     int i = 0;
@@ -44,8 +52,8 @@ __global__ void weighted_rowsum_kernel(const float* __restrict__ Z, const float*
     }
     for (; i < mu; ++i) acc += (double)w[i] * (double)Z[(size_t)i * n + l];
     const float zw = (float)acc;
-    out_z[l] = zw;
-    out_dz[l] = dl * zw;
+    S[at(ny)] = zw;
+    S[at(ny + 1)] = dl * zw;
 }
 
 __device__ __forceinline__ double block_sum_1024(double v, double* sh) {
@@ -309,12 +317,14 @@ hipError_t rank_rewards(hipStream_t st, const float* F, int K, int32_t* order) {
 }
 
 hipError_t cma_build_rhs(hipStream_t st, const uint32_t* seeds, int32_t* order, const float* rewards, const float* w, const cma_consts& c,
-                         const float* D, float* S, float* Z) {
-    hipError_t e = rewards ? normals_scaled(st, seeds, nullptr, c.ny, c.n, D, S, Z, rewards, c.K, order)
-                           : normals_scaled(st, seeds, order, c.ny, c.n, D, S, Z);
+                         const float* D, float* S, float* Z, bool tiled, bool want_z) {
+    const int32_t* sel = rewards ? nullptr : order;
+    if (tiled && c.ny <= 64) return update_rhs(st, seeds, sel, c.ny, c.mu, c.n, w, D, S, want_z ? Z : nullptr, rewards, c.K, order);
+    hipError_t e = tiled ? normals_tiled(st, seeds, sel, c.ny, c.n, D, S, Z, rewards, c.K, order)
+                         : normals_scaled(st, seeds, sel, c.ny, c.n, D, S, Z, rewards, c.K, order);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(weighted_rowsum_kernel, dim3((c.n + 63) / 64), dim3(64), 0, st, Z, w, D, c.mu, c.n, S + (size_t)c.ny * c.n,
-                       S + (size_t)(c.ny + 1) * c.n);
+    if (tiled) hipLaunchKernelGGL(weighted_rowsum_kernel<true>, dim3((c.n + 63) / 64), dim3(64), 0, st, Z, w, D, c.mu, c.n, c.ny, S);
+    else hipLaunchKernelGGL(weighted_rowsum_kernel<false>, dim3((c.n + 63) / 64), dim3(64), 0, st, Z, w, D, c.mu, c.n, c.ny, S);
     return hipGetLastError();
 }
 

@@ -41,35 +41,45 @@ __global__ void philox_words_kernel(const uint32_t* __restrict__ seeds, int K, i
     reinterpret_cast<uint4*>(out)[idx] = w;
 }
 
-// S[j, l] = D[l] * z_{cand(j)}[l],  cand(j) = sel ? sel[j] : j ; optional copy of z itself.
-// With rank_F the selection is the ranking of rank_K <= 256 rewards (larger first, ties by index, NaN last), which every
-// workgroup works out for itself in LDS -- a few hundred comparisons instead of a kernel launch of its own; the first
-// workgroup also writes it to rank_order.
+// The product with the basis takes its right-hand sides in operand tiles: 16 rows x 16 columns to a kilobyte, tile (j / 16, l / 16), inside it
+// [l / 4 % 4][j % 16][l % 4] -- a wave's load is one contiguous kilobyte.  Columns past n are zero, rows past J anything finite or not:
+// they end up in outputs that nobody stores.
+__device__ __forceinline__ size_t rhs_at(int j, int l, int n) {
+    return (((size_t)(j >> 4) * ((n + 15) >> 4) + (l >> 4)) * 64 + (l >> 2 & 3) * 16 + (j & 15)) * 4 + (l & 3);
+}
+
+// The ranking of K <= 256 rewards (larger first, ties by index, NaN last), worked out by the whole workgroup in LDS -- a few hundred
+// comparisons instead of a kernel launch of its own; the first workgroup also writes it to rank_order.
+__device__ __forceinline__ void rank_in_lds(const float* rank_F, int rank_K, int32_t* rank_order, float* key, int* ord) {
+    const int i = threadIdx.x;
+    if (i < rank_K) {
+        const float f = rank_F[i];
+        key[i] = (f != f) ? -INFINITY : f;
+    }
+    __syncthreads();
+    if (i < rank_K) {
+        const float mine = key[i];
+        int better = 0;
+        for (int j = 0; j < rank_K; ++j) {
+            const float o = key[j];
+            better += (o > mine) || (o == mine && j < i);
+        }
+        ord[better] = i;
+        if (blockIdx.x == 0 && rank_order) rank_order[better] = i;
+    }
+    __syncthreads();
+}
+
+// S[j, l] = D[l] * z_{cand(j)}[l],  cand(j) = sel ? sel[j] : j ; optional copy of z itself.  With rank_F the selection is the ranking of
+// rank_K <= 256 rewards.  TILED: S in the tiles above, else in rows.
+template <bool TILED>
 __global__ __launch_bounds__(256) void normals_scaled_kernel(const uint32_t* __restrict__ seeds, const int32_t* __restrict__ sel, int J, int n,
                                                             const float* __restrict__ D, float* __restrict__ S, float* __restrict__ z_out,
                                                             const float* __restrict__ rank_F, int rank_K, int32_t* __restrict__ rank_order) {
     __shared__ float key[256];
     __shared__ int ord[256];
-    if (rank_F) {
-        const int i = threadIdx.x;
-        if (i < rank_K) {
-            const float f = rank_F[i];
-            key[i] = (f != f) ? -INFINITY : f;
-        }
-        __syncthreads();
-        if (i < rank_K) {
-            const float mine = key[i];
-            int better = 0;
-            for (int j = 0; j < rank_K; ++j) {
-                const float o = key[j];
-                better += (o > mine) || (o == mine && j < i);
-            }
-            ord[better] = i;
-            if (blockIdx.x == 0 && rank_order) rank_order[better] = i;
-        }
-        __syncthreads();
-    }
-    const int nb = (n + 3) / 4;
+    if (rank_F) rank_in_lds(rank_F, rank_K, rank_order, key, ord);
+    const int nb = TILED ? (n + 15) / 16 * 4 : (n + 3) / 4;
     const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= (long long)J * nb) return;
     const int j = (int)(idx / nb), c = (int)(idx % nb);
@@ -78,13 +88,64 @@ __global__ __launch_bounds__(256) void normals_scaled_kernel(const uint32_t* __r
     float z[4];
     box_muller(w.x, w.y, z[0], z[1]);
     box_muller(w.z, w.w, z[2], z[3]);
+    float v[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         const int l = 4 * c + e;
+        v[e] = l < n ? (D ? D[l] * z[e] : z[e]) : 0.f;
         if (l < n) {
-            S[(size_t)j * n + l] = D ? D[l] * z[e] : z[e];
+            if (!TILED) S[(size_t)j * n + l] = v[e];
             if (z_out) z_out[(size_t)j * n + l] = z[e];
         }
+    }
+    if (TILED) *reinterpret_cast<float4*>(S + rhs_at(j, 4 * c, n)) = make_float4(v[0], v[1], v[2], v[3]);
+}
+
+// The right-hand sides of an update in one launch: rows i < ny the selected D * z_i, row ny z_w = sum_{i < mu} w[i] z_i (fp64, i ascending),
+// row ny + 1 D * z_w; z_i itself to Z when asked for.  A workgroup takes 16 blocks of four columns and 32 candidates at a time, whose normals
+// meet in LDS.  Latency: one launch in place of two (n = 3584, 16 of 32 candidates: 5.3 + 4.0 -> 6 us); beyond 64 candidates the
+// passes in a row take longer than the launch saved, and the kernels below do it.
+constexpr int RHS_C = 32, RHS_B = 16;
+__global__ __launch_bounds__(RHS_C * RHS_B) void update_rhs_kernel(const uint32_t* __restrict__ seeds, const int32_t* __restrict__ sel, int ny, int mu, int n,
+                                                                  const float* __restrict__ w, const float* __restrict__ D, float* __restrict__ S, float* __restrict__ Z,
+                                                                  const float* __restrict__ rank_F, int rank_K, int32_t* __restrict__ rank_order) {
+    __shared__ float key[256];
+    __shared__ int ord[256];
+    __shared__ float zs[RHS_C][RHS_B * 4 + 1];
+    if (rank_F) rank_in_lds(rank_F, rank_K, rank_order, key, ord);
+    const int cb = threadIdx.x % RHS_B, ci = threadIdx.x / RHS_B, c = blockIdx.x * RHS_B + cb, l0 = blockIdx.x * RHS_B * 4;
+    const bool in = c < (n + 15) / 16 * 4;
+    float d[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) d[e] = 4 * c + e < n ? D[4 * c + e] : 0.f;
+    double acc = 0.0;                                      // threads 0 .. 63: column l0 + thread
+    for (int i0 = 0; i0 < ny; i0 += RHS_C) {
+        const int i = i0 + ci;
+        float z[4] = {0.f, 0.f, 0.f, 0.f};
+        if (i < ny && in) {
+            const uint4 p = philox4x32_10(make_uint4((uint32_t)c, 0u, 0u, 0u), make_uint2(seeds[rank_F ? ord[i] : sel[i]], 0u));
+            box_muller(p.x, p.y, z[0], z[1]);
+            box_muller(p.z, p.w, z[2], z[3]);
+            float v[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                v[e] = 4 * c + e < n ? d[e] * z[e] : 0.f;
+                if (Z && 4 * c + e < n) Z[(size_t)i * n + 4 * c + e] = z[e];
+            }
+            *reinterpret_cast<float4*>(S + rhs_at(i, 4 * c, n)) = make_float4(v[0], v[1], v[2], v[3]);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) zs[ci][cb * 4 + e] = z[e];
+        __syncthreads();
+        if (threadIdx.x < RHS_B * 4)
+            for (int k = 0; k < RHS_C && i0 + k < mu; ++k) acc += (double)w[i0 + k] * (double)zs[k][threadIdx.x];
+        __syncthreads();
+    }
+    const int l = l0 + threadIdx.x;
+    if (threadIdx.x < RHS_B * 4 && l < (n + 15) / 16 * 16) {
+        const float zw = l < n ? (float)acc : 0.f;
+        S[rhs_at(ny, l, n)] = zw;
+        S[rhs_at(ny + 1, l, n)] = l < n ? D[l] * zw : 0.f;
     }
 }
 
@@ -131,13 +192,12 @@ __global__ void theta_to_sigma_kernel(int P, int r, int n_top, const float* __re
     sB[idx] = b;
 }
 
-// Out[j, i] = bias[i] + scale * sum_l S[j,l] * B[i,l]        (fp32 MFMA 16x16x4)
+// Out[j, i] = bias[i] + scale * sum_l S[j,l] * B[i,l]        (fp32 MFMA 16x16x4; S in operand tiles)
 // One workgroup = 16 rows of B x (16 * JB) rows of S.  Its 8 waves interleave over chunks of 16 columns (a lane
 // loads four consecutive floats of its row, which feed four MFMA steps) and their partial tiles are summed
 // through LDS in a fixed order (bit-reproducible).  B is read exactly once when J <= 16 * JB.
 constexpr int SG_WAVES = 8;
-constexpr int SG_BUNCH = 14;         // chunks of B a wave asks for at once (n = 3584: 28 chunks per wave, two bunches)
-constexpr int SG_AHEAD = 4;          // chunks of S in flight ahead of their MFMAs
+constexpr int SG_BUNCH = 2;          // chunks a wave asks for at once; two bunches in turn
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 template <bool TAIL, int JB>
 __global__ __launch_bounds__(SG_WAVES * 64) void skinny_gemm_nt_kernel(const float* __restrict__ S, int J, const float* __restrict__ B,
@@ -156,21 +216,29 @@ __global__ __launch_bounds__(SG_WAVES * 64) void skinny_gemm_nt_kernel(const flo
     // A wave walks its chunks (wave, wave + 8, ...) in ascending order.
     {
         // Buffer loads: a row or a chunk past the end is an offset outside the descriptor and comes back as zeros, so there
-        // is no branch around any load and the compiler can count them.  The B fragments of SG_BUNCH chunks are asked for
-        // together and the S fragments then stream past them a few chunks ahead of their MFMAs: a CU's loads complete in
-        // order, B comes from HBM and S out of the L2, and S loads spread evenly between B loads would all move at HBM
-        // latency.  (n <= 16384: both matrices stay below the descriptor's 2 GB.)
+        // is no branch around any load and the compiler can count them.  What bounds it is what the loads cost the CU's address path:
+        // 16 rows x 64 bytes of B take it 55 cycles, a contiguous kilobyte of S 16 (S in rows cost as much as B, twice over).  A wave asks
+        // for two chunks of both, and for the next two in front of the MFMAs of these: deeper bunches (14 of B, S behind them)
+        // queue everybody's B in front of everybody's S.  Product / update and next candidates, us, S in rows and bunches of 14 against this:
+        // n = 3584, 32 candidates 21.3 / 15.5 and 82 / 65; 64 candidates at n = 5121 303 / 191 (both); 896, 36 candidates 45 / 35 (both).
+        // (n <= 16384: both matrices stay below the descriptor's 2 GB.)
         // The loads need 4-byte alignment only, so any n takes this path.  TAIL: n is not a multiple of 4, and the quad that
-        // crosses the end of a row is the row's last four elements, moved into place (update and next candidates, us, against single loads behind branches and a covariance pass without 16-byte accesses:
-        // 66 -> 55 at n = 1001, 138 -> 93 at 3169, 511 -> 266 at 5998; 32, 24 and 32 candidates).
+        // crosses the end of a row is the row's last four elements, moved into place.
         typedef __amdgpu_buffer_rsrc_t rsrc_t;
         constexpr uint32_t OUT_OF_RANGE = 0x80000000u;
         const rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(B), 0, (uint32_t)n * (uint32_t)n * 4u, 0x00020000);
-        const rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(S), 0, (uint32_t)J * (uint32_t)n * 4u, 0x00020000);
+        const uint32_t tiles_l = (uint32_t)nchunks * 1024u;
+        const rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(S), 0, (uint32_t)((J + 15) / 16) * tiles_l, 0x00020000);
         const uint32_t brow = (uint32_t)i * (uint32_t)n * 4u;                    // i >= n: beyond the descriptor
-        uint32_t srow[JB];
+        uint32_t scol[JB];                                  // columns past J are not asked for
 #pragma unroll
-        for (int jb = 0; jb < JB; ++jb) srow[jb] = (uint32_t)(j0 + 16 * jb + l16) * (uint32_t)n * 4u;
+        for (int jb = 0; jb < JB; ++jb) scol[jb] = j0 + 16 * jb + l16 < J ? (uint32_t)(j0 / 16 + jb) * tiles_l + (uint32_t)lane * 16u : OUT_OF_RANGE;
+        auto ld_s = [&](int jb, int chunk) {               // a contiguous kilobyte
+            const auto v = __builtin_amdgcn_raw_buffer_load_b128(rs, chunk < nchunks ? scol[jb] + (uint32_t)chunk * 1024u : OUT_OF_RANGE, 0, 0);
+            f32x4 f;
+            __builtin_memcpy(&f, &v, 16);
+            return f;
+        };
         auto ld = [&](rsrc_t r, uint32_t row_off, int chunk) {
             const int l = chunk * 16 + 4 * kq;
             f32x4 f;
@@ -197,32 +265,35 @@ __global__ __launch_bounds__(SG_WAVES * 64) void skinny_gemm_nt_kernel(const flo
             v[3] = cross ? 0.f : f[3];
             return v;
         };
-        for (int base = wave; base < nchunks; base += SG_BUNCH * SG_WAVES) {
-            f32x4 a[SG_BUNCH], sv[SG_AHEAD][JB];
+        f32x4 a[2][SG_BUNCH], sv[2][SG_BUNCH][JB];
+        auto ask = [&](int base, int set) {
 #pragma unroll
-            for (int u = 0; u < SG_BUNCH; ++u) a[u] = ld(rb, brow, base + u * SG_WAVES);
+            for (int u = 0; u < SG_BUNCH; ++u) a[set][u] = ld(rb, brow, base + u * SG_WAVES);
             __builtin_amdgcn_sched_barrier(0);              // left alone, the compiler moves every load down to its first use
 #pragma unroll
-            for (int u = 0; u < SG_AHEAD; ++u)
+            for (int u = 0; u < SG_BUNCH; ++u)
 #pragma unroll
-                for (int jb = 0; jb < JB; ++jb) sv[u][jb] = ld(rs, srow[jb], base + u * SG_WAVES);
+                for (int jb = 0; jb < JB; ++jb) sv[set][u][jb] = ld_s(jb, base + u * SG_WAVES);
             __builtin_amdgcn_sched_barrier(0);
+        };
+        auto multiply = [&](int base, int set) {
 #pragma unroll
             for (int u = 0; u < SG_BUNCH; ++u) {
-                f32x4 cur[JB];
-#pragma unroll
-                for (int jb = 0; jb < JB; ++jb) cur[jb] = place(sv[u % SG_AHEAD][jb], base + u * SG_WAVES);
-                const f32x4 au = place(a[u], base + u * SG_WAVES);
-                if (u + SG_AHEAD < SG_BUNCH) {
-#pragma unroll
-                    for (int jb = 0; jb < JB; ++jb) sv[u % SG_AHEAD][jb] = ld(rs, srow[jb], base + (u + SG_AHEAD) * SG_WAVES);
-                }
+                const f32x4 au = place(a[set][u], base + u * SG_WAVES);
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
 #pragma unroll
-                    for (int jb = 0; jb < JB; ++jb) acc[jb] = __builtin_amdgcn_mfma_f32_16x16x4f32(au[e], cur[jb][e], acc[jb], 0, 0, 0);
-                __builtin_amdgcn_sched_barrier(0);
+                    for (int jb = 0; jb < JB; ++jb) acc[jb] = __builtin_amdgcn_mfma_f32_16x16x4f32(au[e], sv[set][u][jb][e], acc[jb], 0, 0, 0);
             }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        constexpr int STEP = SG_BUNCH * SG_WAVES;
+        ask(wave, 0);
+        for (int base = wave; base < nchunks; base += 2 * STEP) {
+            ask(base + STEP, 1);
+            multiply(base, 0);
+            ask(base + 2 * STEP, 0);
+            multiply(base + STEP, 1);
         }
     }
 #pragma unroll
@@ -256,8 +327,24 @@ hipError_t philox_words(hipStream_t st, const uint32_t* seeds, int K, int n_bloc
 hipError_t normals_scaled(hipStream_t st, const uint32_t* seeds, const int32_t* sel, int J, int n, const float* D, float* S,
                           float* z_out, const float* rank_F, int rank_K, int32_t* rank_order) {
     const long long total = (long long)J * ((n + 3) / 4);
-    hipLaunchKernelGGL(normals_scaled_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, seeds, sel, J, n, D, S, z_out, rank_F,
+    hipLaunchKernelGGL(normals_scaled_kernel<false>, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, seeds, sel, J, n, D, S, z_out, rank_F,
                        rank_K, rank_order);
+    return hipGetLastError();
+}
+
+hipError_t normals_tiled(hipStream_t st, const uint32_t* seeds, const int32_t* sel, int J, int n, const float* D, float* S,
+                         float* z_out, const float* rank_F, int rank_K, int32_t* rank_order) {
+    const long long total = (long long)J * ((n + 15) / 16 * 4);
+    hipLaunchKernelGGL(normals_scaled_kernel<true>, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, seeds, sel, J, n, D, S, z_out, rank_F,
+                       rank_K, rank_order);
+    return hipGetLastError();
+}
+
+hipError_t update_rhs(hipStream_t st, const uint32_t* seeds, const int32_t* sel, int ny, int mu, int n, const float* w, const float* D, float* S,
+                      float* Z, const float* rank_F, int rank_K, int32_t* rank_order) {
+    const int blocks = (n + 15) / 16 * 4;
+    hipLaunchKernelGGL(update_rhs_kernel, dim3((blocks + RHS_B - 1) / RHS_B), dim3(RHS_C * RHS_B), 0, st, seeds, sel, ny, mu, n, w, D, S, Z, rank_F, rank_K,
+                       rank_order);
     return hipGetLastError();
 }
 

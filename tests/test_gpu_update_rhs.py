@@ -1,0 +1,38 @@
+"""GPU parity of the update's right-hand sides (ranking, regenerated normals, their weighted sum): one launch for up to 64 of them, 32 at a
+time, kernels of their own beyond; the ranking inside up to 256 candidates.  At the edges of each, against the oracle's step."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as orc
+from helpers import to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n,K", [(1, 2), (16, 64), (17, 65), (66, 66), (260, 128), (67, 130), (63, 256), (130, 258), (65, 300)])
+def test_update_right_hand_sides(essa, n, K):
+    ctx = essa.Context(0)
+    print("n=%d K=%d" % (n, K), flush=True)
+    g = np.random.default_rng(1000 * n + K)
+    seeds = list(range(7, 7 + K))
+    F = g.standard_normal(K).astype(np.float32)
+    if K > 4:
+        F[K // 2] = F[1]                                   # a tie: ascending index
+        F[2] = np.nan                                      # ranks last
+    cma = essa.CmaState(ctx, n, 0.32, None)
+    order = torch.full((K,), -1, dtype=torch.int32, device="cuda")
+    essa.essa_cmaes_update(ctx, cma, to_dev(np.array(seeds, np.int32)), to_dev(F), order)
+    st, want_order = orc.cma_update(orc.cma_state_init(n, np.float32(0.32)), seeds, F)
+    assert np.array_equal(order.cpu().numpy(), want_order)
+    got = cma.export()
+    # fp32 sums over n of fp64-rounded terms; the repository's bar for the update
+    for name in ("m", "p_sigma", "p_c", "C"):
+        assert orc.rel_errors(got[name], getattr(st, name))[1] <= 1e-5, name
+    # the same without the order asked for
+    again = essa.CmaState(ctx, n, 0.32, None)
+    essa.essa_cmaes_update(ctx, again, to_dev(np.array(seeds, np.int32)), to_dev(F))
+    assert np.array_equal(again.export()["C"], got["C"])
+    again.close()
+    cma.close()
+    ctx.close()
