@@ -64,7 +64,9 @@ __global__ __launch_bounds__(256) void eig_init_kernel(const float* __restrict__
 // One 64 x 64 tile of X Y^T (NT: Y's row j is output column j) or X Y (NN) per workgroup of 8 waves, on the fp64 MFMA
 // 16x16x4: a wave owns a 32 x 32 patch for one half of every K chunk of 32, the halves are added through LDS at the end.  The
 // MFMA rate binds (64 cycles per MFMA, 128 flops per clock and CU; a chunk brings 32 KB in for 2048 of those cycles); two
-// waves per SIMD because at n of a few hundred there is one workgroup per CU and nobody else to hide LDS latency.  Pitches are
+// waves per SIMD because at n of a few hundred there is one workgroup per CU and nobody else to hide LDS latency, and two chunks on
+// their way from memory, which a chunk's 0.85 us do not outlast (one: 45 us per product at n = 896, two: 43; refresh at n = 3584
+// after 17 generations 26.1 / 24.1 ms; fragments read a chunk ahead as well: 47 us, and one workgroup a CU fewer).  Pitches are
 // 4 (8) doubles mod 32, which spreads the 16 x 4 elements of an operand read evenly over the banks.
 constexpr int MK = 32, MP = 36, MQ = 72, MNT = 512;
 constexpr size_t MM_SMEM = 2 * 2 * (size_t)64 * MP * sizeof(double);
@@ -79,34 +81,33 @@ __device__ __forceinline__ void tile_product(const double* __restrict__ X, const
     constexpr int STAGE = 2 * 64 * MP;
     // two 16-byte pieces per thread and operand: rows of 32 k (16 pieces each) or, for NN's Y, 32 rows of 64 columns
     typedef __attribute__((ext_vector_type(2))) double f64x2;
-    f64x2 rx[2], ry[2];
-    auto fetch = [&](int k0) {
+    struct piece { f64x2 x[2], y[2]; } one, two;           // two chunks on their way from memory
+    auto fetch = [&](int chunk, piece& p2) {
+        const int k0 = chunk * MK;
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
             const int p = tid + MNT * e, row = p >> 4, c = (p & 15) * 2;
-            rx[e] = *reinterpret_cast<const f64x2*>(X + (size_t)(i0 + row) * ld + k0 + c);
-            if (NN) ry[e] = *reinterpret_cast<const f64x2*>(Y + (size_t)(k0 + (p >> 5)) * ld + j0 + (p & 31) * 2);
-            else ry[e] = *reinterpret_cast<const f64x2*>(Y + (size_t)(j0 + row) * ld + k0 + c);
+            p2.x[e] = *reinterpret_cast<const f64x2*>(X + (size_t)(i0 + row) * ld + k0 + c);
+            if (NN) p2.y[e] = *reinterpret_cast<const f64x2*>(Y + (size_t)(k0 + (p >> 5)) * ld + j0 + (p & 31) * 2);
+            else p2.y[e] = *reinterpret_cast<const f64x2*>(Y + (size_t)(j0 + row) * ld + k0 + c);
         }
     };
-    auto put = [&](double* st) {
+    auto put = [&](double* st, const piece& p2) {
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
             const int p = tid + MNT * e, row = p >> 4, c = (p & 15) * 2;
-            *reinterpret_cast<f64x2*>(st + row * MP + c) = rx[e];
-            if (NN) *reinterpret_cast<f64x2*>(st + 64 * MP + (p >> 5) * MQ + (p & 31) * 2) = ry[e];
-            else *reinterpret_cast<f64x2*>(st + 64 * MP + row * MP + c) = ry[e];
+            *reinterpret_cast<f64x2*>(st + row * MP + c) = p2.x[e];
+            if (NN) *reinterpret_cast<f64x2*>(st + 64 * MP + (p >> 5) * MQ + (p & 31) * 2) = p2.y[e];
+            else *reinterpret_cast<f64x2*>(st + 64 * MP + row * MP + c) = p2.y[e];
         }
     };
 #pragma unroll
     for (int a = 0; a < 2; ++a)
 #pragma unroll
         for (int b = 0; b < 2; ++b) acc[a][b] = (f64x4){0.0, 0.0, 0.0, 0.0};
-    fetch(0);
-    put(lds);
-    __syncthreads();
-    for (int k0 = 0, cur = 0; k0 < ld; k0 += MK, cur ^= 1) {
-        if (k0 + MK < ld) fetch(k0 + MK);
+    const int chunks = ld / MK;                            // even: ld is a multiple of 64
+    auto step = [&](int i, piece& p2) {                    // multiplies chunk i; p2 holds chunk i + 1
+        const int cur = i & 1;
         const double* xs = lds + cur * STAGE + (32 * wr + l16) * MP + 16 * kh + kq;
         const double* ys = lds + cur * STAGE + 64 * MP + (NN ? (16 * kh + kq) * MQ + 32 * wc + l16 : (32 * wc + l16) * MP + 16 * kh + kq);
         double fx[4][2], fy[4][2];
@@ -123,8 +124,18 @@ __device__ __forceinline__ void tile_product(const double* __restrict__ X, const
             for (int a = 0; a < 2; ++a)
 #pragma unroll
                 for (int b = 0; b < 2; ++b) acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(fx[k][a], fy[k][b], acc[a][b], 0, 0, 0);
-        if (k0 + MK < ld) put(lds + (cur ^ 1) * STAGE);
+        if (i + 1 < chunks) put(lds + (cur ^ 1) * STAGE, p2);
+        if (i + 3 < chunks) fetch(i + 3, p2);
         __syncthreads();
+    };
+    fetch(0, one);
+    fetch(1, two);
+    put(lds, one);
+    if (chunks > 2) fetch(2, one);
+    __syncthreads();
+    for (int i = 0; i < chunks; i += 2) {
+        step(i, two);
+        step(i + 1, one);
     }
     // the second K halves join the first
     double* half = lds + (size_t)(wave & 3) * 1024 + lane;
@@ -209,7 +220,9 @@ __global__ __launch_bounds__(MNT) void eig_residual_kernel(const double* __restr
 // turned exactly, one partner per column and step (eig_pair_kernel).  The largest cosine goes to offmax; per row and tile
 // the sum of |E| goes to part and the strongest such pair to the st_ arrays (all [tile][row]).
 constexpr double STRONG = 0.25;
-__global__ __launch_bounds__(256) void eig_correction_kernel(double* __restrict__ M, const double* __restrict__ Rd, const double* __restrict__ diagS,
+// Latency, three fp64 divisions per pair: 1024 threads a tile take 12 us at n = 896 where 256 took 27.
+constexpr int EC_NT = 1024;
+__global__ __launch_bounds__(EC_NT) void eig_correction_kernel(double* __restrict__ M, const double* __restrict__ Rd, const double* __restrict__ diagS,
                                                              const double* __restrict__ diagR, int ld, int n, int with_t, double leave,
                                                              double* __restrict__ part, double* __restrict__ st_s, float* __restrict__ st_t,
                                                              int* __restrict__ st_j, unsigned* __restrict__ offmax) {
@@ -223,13 +236,13 @@ __global__ __launch_bounds__(256) void eig_correction_kernel(double* __restrict_
         const int k = (tid < 64 ? I : J) * 64 + (tid & 63);
         lam[tid >> 6][tid & 63] = diagS[k] / (1.0 - diagR[k]);
     }
-    for (int e = tid; e < 4096; e += 256) {
+    for (int e = tid; e < 4096; e += EC_NT) {
         const int r = e >> 6, c = e & 63;                  // R_ji, j = row: Rt[i][j]
         Rt[c][r] = I == J ? Rd[((size_t)I * 64 + r) * 64 + c] : M[(size_t)(J * 64 + r) * ld + I * 64 + c];
     }
     __syncthreads();
     unsigned best = 0u;
-    for (int e = tid; e < 4096; e += 256) {
+    for (int e = tid; e < 4096; e += EC_NT) {
         const int a = e >> 6, b = e & 63;
         const bool live = I * 64 + a < n && J * 64 + b < n;
         double r = live ? Rt[a][b] : 0.0, t = 0.0;
@@ -244,6 +257,8 @@ __global__ __launch_bounds__(256) void eig_correction_kernel(double* __restrict_
     atomicMax(&mx, best);
     __syncthreads();
     auto weak = [](double t) { return fabs(t) > STRONG ? 0.0 : t; };
+    // The share of this tile in a column's sum and its strongest pair: 8 lanes per column, 8 elements each, the lanes joined in ascending
+    // order (threads 0 .. 511 the columns of tile I, the others those of tile J).
     double sum = 0.0, top_s = 0.0;
     float top_t = 0.f;
     int top_j = -1;
@@ -255,15 +270,28 @@ __global__ __launch_bounds__(256) void eig_correction_kernel(double* __restrict_
             top_s = M[(size_t)(I * 64 + i) * ld + J * 64 + j] + 0.5 * r * (lam[0][i] + lam[1][j]);
         }
     };
-    if (tid < 64) {
-        for (int b = 0; b < 64; ++b) look(Rt[tid][b], Ab[tid][b], tid, b, J * 64 + b);
+    const int seg = (tid & 7) * 8, own = (tid >> 3) & 63;
+    if (tid < 512) {
+        for (int b = seg; b < seg + 8; ++b) look(Rt[own][b], Ab[own][b], own, b, J * 64 + b);
         if (I == J)
-            for (int a = 0; a < 64; ++a) look(0.0, Ab[a][tid], a, tid, I * 64 + a);
-    } else if (tid < 128 && I < J) {
-        for (int a = 0; a < 64; ++a) look(Rt[a][tid - 64], Ab[a][tid - 64], a, tid - 64, I * 64 + a);
+            for (int a = seg; a < seg + 8; ++a) look(0.0, Ab[a][own], a, own, I * 64 + a);
+    } else if (I < J) {
+        for (int a = seg; a < seg + 8; ++a) look(Rt[a][own], Ab[a][own], a, own, I * 64 + a);
     }
-    if (tid < (I < J ? 128 : 64)) {
-        const size_t at = tid < 64 ? (size_t)J * ld + I * 64 + tid : (size_t)I * ld + J * 64 + tid - 64;
+#pragma unroll
+    for (int off = 1; off < 8; off <<= 1) {                // a lane takes over what lies behind its own; the first wins a tie
+        const double s2 = __shfl_down(sum, off, 8), ts = __shfl_down(top_s, off, 8);
+        const float tt = __shfl_down(top_t, off, 8);
+        const int tj = __shfl_down(top_j, off, 8);
+        sum += s2;
+        if (tt > top_t) {
+            top_t = tt;
+            top_s = ts;
+            top_j = tj;
+        }
+    }
+    if (seg == 0 && (tid < 512 || I < J)) {
+        const size_t at = tid < 512 ? (size_t)J * ld + I * 64 + own : (size_t)I * ld + J * 64 + own;
         part[at] = sum;
         st_s[at] = top_s;
         st_t[at] = top_t;
@@ -272,13 +300,13 @@ __global__ __launch_bounds__(256) void eig_correction_kernel(double* __restrict_
     __syncthreads();                                       // S is read above
     if (I < J) {
         // Ab: t of (i, j); E_ji lies in row i of the transposed matrix, E_ij in row j
-        for (int e = tid; e < 4096; e += 256) {
+        for (int e = tid; e < 4096; e += EC_NT) {
             const int a = e >> 6, b = e & 63;
             M[(size_t)(I * 64 + a) * ld + J * 64 + b] = 0.5 * Rt[a][b] - weak(Ab[a][b]);
             M[(size_t)(J * 64 + a) * ld + I * 64 + b] = 0.5 * Rt[b][a] + weak(Ab[b][a]);
         }
     } else {
-        for (int e = tid; e < 4096; e += 256) {
+        for (int e = tid; e < 4096; e += EC_NT) {
             const int a = e >> 6, b = e & 63;
             M[(size_t)(I * 64 + a) * ld + I * 64 + b] = 0.5 * Rt[a][b] + (a > b ? weak(Ab[b][a]) : -weak(Ab[a][b]));
         }
@@ -675,7 +703,7 @@ hipError_t eig_refresh(hipStream_t st, const float* C, int n, void* ws, bool ref
     };
     auto measure = [&](int with_t, eig_stats& s) {             // E is in M afterwards
         hipLaunchKernelGGL(eig_residual_kernel, dim3(ntri, 2), dim3(MNT), MM_SMEM, st, V, A, ld, M, Rd, diagS, diagR);
-        hipLaunchKernelGGL(eig_correction_kernel, dim3(ntri), dim3(256), 0, st, M, Rd, diagS, diagR, ld, n, with_t, inner_tol, part, st_s, st_t, st_j, flag);
+        hipLaunchKernelGGL(eig_correction_kernel, dim3(ntri), dim3(EC_NT), 0, st, M, Rd, diagS, diagR, ld, n, with_t, inner_tol, part, st_s, st_t, st_j, flag);
         hipLaunchKernelGGL(eig_stats_kernel, dim3(1), dim3(1024), 0, st, part, st_s, st_t, st_j, diagS, diagR, ld, n, flag, lam, pair_s, partner, stats_dev);
         return read_back(&s, stats_dev, sizeof s);
     };
