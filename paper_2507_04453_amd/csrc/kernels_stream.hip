@@ -1444,15 +1444,25 @@ __global__ __launch_bounds__(NT, 1) void gemm_i8_stream_kernel(stream_args a) {
 constexpr int QS_ROUNDS = 8;                               // rounds of 8 groups: up to 64 groups
 constexpr int QS_PITCH = 16 * QS_ROUNDS * 2 + 16;          // LDS row of a zero-point operand: head and tail of up to 64 groups, pad
 
-constexpr size_t Q4S_SMEM = (size_t)2 * 8 * 4096 + (size_t)QS_ROUNDS * 8 * 32 * 4 + 32 * 4 + (size_t)32 * UROW;
+// Up to 16 rows (FEW): the same on the 16 x 16 x 64 MFMA, whose row operand holds 16 rows x 64 columns in the kilobyte that 32 rows x 32
+// columns take.  Half the limb loads, MFMAs, conversions, sums through LDS and folds; the same integers, the same FMAs in the same order.
+// A weight load of 64 columns (32 channels, low nibbles the first chunk, high ones the second) becomes the operands of channels 0..15
+// and 16..31 by exchanging the low codes of lanes 16..31 and 48..63 with the high codes of the lanes 16 below: the K order is then chunk 0, chunk 1
+// of the lower 16 columns, chunk 0, chunk 1 of the upper, and the limbs are loaded in that order too.
+template <bool FEW> constexpr size_t q4s_buffer() { return FEW ? 8 * 2048 : 8 * 4096; }      // one round's sums
+template <bool FEW> constexpr size_t q4s_smem() {
+    constexpr size_t fin = 4096 + (32 + 32) * QS_PITCH + 32 * UROW, two = 2 * q4s_buffer<FEW>();   // what the epilogue needs in one buffer, or in both
+    return (FEW && fin > two ? fin : two) + (size_t)QS_ROUNDS * 8 * 32 * 4 + 32 * 4 + (size_t)32 * UROW;
+}
 
-template <bool YBF16>
+template <bool FEW, bool YBF16>
 __global__ __launch_bounds__(NT, 4) void gemm_q4_stream_kernel(stream_args a) {
     typedef __attribute__((ext_vector_type(2))) float f32x2;
     constexpr int BM = 32, DX = 4;
-    constexpr size_t BUF = (size_t)8 * 4096;               // one round's sums: [wave][pair of q][lane][2]
+    constexpr size_t BUF = q4s_buffer<FEW>();              // [wave][pair of q][lane][2], FEW: [wave][element][lane]
+    constexpr size_t BUFS = q4s_smem<FEW>() - (size_t)QS_ROUNDS * 8 * 32 * 4 - 32 * 4 - (size_t)32 * UROW;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    float* ssc = reinterpret_cast<float*>(smem + 2 * BUF); // [group][32] scales
+    float* ssc = reinterpret_cast<float*>(smem + BUFS);    // [group][32] scales
     float* xd = ssc + QS_ROUNDS * 8 * 32;
     unsigned char* utile = reinterpret_cast<unsigned char*>(xd + BM);
     float* tvec = reinterpret_cast<float*>(smem + BUF);    // the prologue's matrices: the second buffer is free until the first barrier
@@ -1477,7 +1487,10 @@ __global__ __launch_bounds__(NT, 4) void gemm_q4_stream_kernel(stream_args a) {
     const rsrc_t xbase[2] = {make_rsrc(it.Xh), make_rsrc(it.Xl)};
     constexpr uint32_t OUT_OF_RANGE = 0x80000000u;         // beyond the descriptor's 2 GB: the load returns zeros, no memory access
     const uint32_t lane16 = lane * 16;
-    const uint32_t xoff = m0 + l32 < R ? (uint32_t)((m0 >> 5) * nkc) * 1024u + lane16 : OUT_OF_RANGE;
+    // FEW: 16 rows of two chunks at a time, [chunk 0 lower half, chunk 1 lower half, chunk 0 upper, chunk 1 upper]
+    const int l16 = lane & 15, kg = lane >> 4;
+    const uint32_t xoff = FEW ? (l16 < R ? (uint32_t)((kg & 1) * 1024 + (kg >> 1) * 512 + l16 * 16) : OUT_OF_RANGE)
+                              : (m0 + l32 < R ? (uint32_t)((m0 >> 5) * nkc) * 1024u + lane16 : OUT_OF_RANGE);
 
     constexpr int EU = (BM * 32 + NT - 1) / NT;
     f32x4 tp[EU][2];
@@ -1502,11 +1515,12 @@ __global__ __launch_bounds__(NT, 4) void gemm_q4_stream_kernel(stream_args a) {
     auto issue_x = [&](int j, int limb, int c) {
         const int grp = wave + 8 * j;
         const uint32_t gone = grp < groups ? 0u : OUT_OF_RANGE;
-        xr[c] = load16(xbase[limb], xoff | gone, (uint32_t)(4 * grp + c) * 1024u);
+        if (FEW) xr[limb * 2 + c] = load16(xbase[limb], xoff | gone, (uint32_t)(4 * grp + 2 * c) * 1024u);
+        else xr[c] = load16(xbase[limb], xoff | gone, (uint32_t)(4 * grp + c) * 1024u);
     };
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int c = 0; c < DX; ++c) issue_x(0, 0, c);
+    for (int c = 0; c < DX; ++c) issue_x(0, FEW ? c >> 1 : 0, FEW ? c & 1 : c);
     __builtin_amdgcn_sched_barrier(0);
 
     u_tile_finish<BM, EU, true>(it, a.flags, tid, tp, sb, mreg, tvec, Ms, utile);
@@ -1524,20 +1538,53 @@ __global__ __launch_bounds__(NT, 4) void gemm_q4_stream_kernel(stream_args a) {
     for (int j = 0; j < QS_ROUNDS; ++j) {
         if (j == 0 || j < n) {
             f32x2* buf = reinterpret_cast<f32x2*>(smem + (j & 1) * BUF);
+            float* buf1 = reinterpret_cast<float*>(buf);
             i32x16 t = {0};
+            i32x4 tf[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};    // FEW: channels 0..15, 16..31
+            if constexpr (FEW) {
+                u32x4 w[2][2];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int c = i & 3;
-                if (i == 4) {
+                for (int c = 0; c < 2; ++c) {
+                    const u32x4 lo = wr[j][c] & m4, hi = (wr[j][c] >> 4) & m4;
 #pragma unroll
-                    for (int q = 0; q < 16; ++q) t[q] <<= 8;
+                    for (int e = 0; e < 4; ++e) {
+                        const auto r = __builtin_amdgcn_permlane16_swap(lo[e], hi[e], false, false);
+                        w[c][0][e] = r[0];
+                        w[c][1][e] = r[1];
+                    }
                 }
-                const u32x4 w = (c & 1) ? (wr[j][c >> 1] >> 4) & m4 : wr[j][c >> 1] & m4;
-                t = __builtin_amdgcn_mfma_i32_32x32x32_i8((i32x4)xr[c], (i32x4)w, t, 0, 0, 0);
-                __builtin_amdgcn_sched_barrier(0);
-                if (i < 4) issue_x(j, 1, c);
-                else if (j + 1 < QS_ROUNDS) issue_x(j + 1, 0, c);
-                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int limb = 0; limb < 2; ++limb) {
+                    if (limb == 1) {
+#pragma unroll
+                        for (int b = 0; b < 2; ++b)
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) tf[b][q] <<= 8;
+                    }
+#pragma unroll
+                    for (int c = 0; c < 2; ++c) {
+#pragma unroll
+                        for (int b = 0; b < 2; ++b) tf[b] = __builtin_amdgcn_mfma_i32_16x16x64_i8((i32x4)xr[limb * 2 + c], (i32x4)w[c][b], tf[b], 0, 0, 0);
+                        __builtin_amdgcn_sched_barrier(0);
+                        if (j + 1 < QS_ROUNDS) issue_x(j + 1, limb, c);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const int c = i & 3;
+                    if (i == 4) {
+#pragma unroll
+                        for (int q = 0; q < 16; ++q) t[q] <<= 8;
+                    }
+                    const u32x4 w = (c & 1) ? (wr[j][c >> 1] >> 4) & m4 : wr[j][c >> 1] & m4;
+                    t = __builtin_amdgcn_mfma_i32_32x32x32_i8((i32x4)xr[c], (i32x4)w, t, 0, 0, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (i < 4) issue_x(j, 1, c);
+                    else if (j + 1 < QS_ROUNDS) issue_x(j + 1, 0, c);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
             }
             if (j == 0) {
                 szreg = *as_global(reinterpret_cast<const u32x4*>(it.SZ16 + (size_t)(nb * 32 + min(sz_row, 31)) * 2 * Gp + 8 * sz_at));
@@ -1547,28 +1594,44 @@ __global__ __launch_bounds__(NT, 4) void gemm_q4_stream_kernel(stream_args a) {
                 issue_w(QS_ROUNDS - 3 + j);
             }
             __builtin_amdgcn_sched_barrier(0);
+            if constexpr (FEW) {
 #pragma unroll
-            for (int q = 0; q < 8; ++q) buf[(wave * 8 + q) * 64 + lane] = (f32x2){(float)t[2 * q], (float)t[2 * q + 1]};
+                for (int q = 0; q < 8; ++q) buf1[(wave * 8 + q) * 64 + lane] = (float)tf[q >> 2][q & 3];
+            } else {
+#pragma unroll
+                for (int q = 0; q < 8; ++q) buf[(wave * 8 + q) * 64 + lane] = (f32x2){(float)t[2 * q], (float)t[2 * q + 1]};
+            }
             lds_barrier();
-            // thread (wave, lane) folds outputs q = 2 wave and 2 wave + 1 over the round's groups, ascending
+            // thread (wave, lane) folds outputs q = 2 wave and 2 wave + 1 (FEW: element wave, a row and channel of 16 x 32) over the round's groups, ascending
 #pragma unroll
             for (int w = 0; w < 8; ++w) {
-                const float s = ssc[(8 * j + w) * 32 + l32];
-                const f32x2 v = buf[(w * 8 + wave) * 64 + lane];
-                tot[0] = fmaf(s, v[0], tot[0]);
-                tot[1] = fmaf(s, v[1], tot[1]);
+                if constexpr (FEW) {
+                    tot[0] = fmaf(ssc[(8 * j + w) * 32 + (wave >> 2) * 16 + l16], buf1[(w * 8 + wave) * 64 + lane], tot[0]);
+                } else {
+                    const float s = ssc[(8 * j + w) * 32 + l32];
+                    const f32x2 v = buf[(w * 8 + wave) * 64 + lane];
+                    tot[0] = fmaf(s, v[0], tot[0]);
+                    tot[1] = fmaf(s, v[1], tot[1]);
+                }
             }
         }
     }
     // the buffer that the last round did not use: its readers are done
-    unsigned char* fin = smem + (n & 1) * BUF;
+    // (FEW: both, once the last round's readers are done as well)
+    if (FEW) lds_barrier();
+    unsigned char* fin = FEW ? smem : smem + (n & 1) * BUF;
     float* totb = reinterpret_cast<float*>(fin);           // [q][lane]
     unsigned char* xs_l = fin + 4096;
     unsigned char* sz_l = xs_l + BM * QS_PITCH;
     unsigned char* ub_l = sz_l + 32 * QS_PITCH;
-    static_assert(4096 + (BM + 32) * QS_PITCH + 32 * UROW <= BUF, "the epilogue's operands fit a buffer");
-    totb[2 * wave * 64 + lane] = tot[0];
-    totb[(2 * wave + 1) * 64 + lane] = tot[1];
+    static_assert(4096 + (BM + 32) * QS_PITCH + 32 * UROW <= (FEW ? BUFS : BUF), "the epilogue's operands fit");
+    if (FEW) {                                             // row 4 kg + e in the places of a 32 x 32 tile; the rows past 16 are nobody's
+        const int row = 4 * kg + (wave & 3);
+        totb[(4 * (row >> 3) + (row & 3)) * 64 + (row >> 2 & 1) * 32 + (wave >> 2) * 16 + l16] = tot[0];
+    } else {
+        totb[2 * wave * 64 + lane] = tot[0];
+        totb[(2 * wave + 1) * 64 + lane] = tot[1];
+    }
     if (sz_row < 32) {
         *reinterpret_cast<u32x4*>(xs_l + sz_row * QS_PITCH + 16 * sz_at) = xsreg;
         *reinterpret_cast<u32x4*>(sz_l + sz_row * QS_PITCH + 16 * sz_at) = szreg;
@@ -2225,7 +2288,7 @@ hipError_t launch_gemm(hipStream_t st, stream_args& a, int32_t* acc_out) {
     return hipGetLastError();
 }
 
-template <int MB, int LIMBS, bool YBF16, bool Q4 = false>
+template <int MB, int LIMBS, bool YBF16, bool Q4 = false, bool FEW = false>
 hipError_t launch_gemm_stream(hipStream_t st, stream_args& a) {
     int total = 0;
     for (int g = 0; g < a.n_items; ++g) {
@@ -2233,10 +2296,10 @@ hipError_t launch_gemm_stream(hipStream_t st, stream_args& a) {
         total += Q4 ? (a.it[g].n_blocks + 7) / 8 * 8 * ((a.it[g].R + 31) / 32) : a.it[g].n_blocks;
     }
     for (int g = a.n_items; g <= ESSA_MAX_GROUP; ++g) a.tile_start[g] = total;
-    constexpr size_t smem = Q4 ? Q4S_SMEM : stream_smem_bytes<MB, LIMBS>();
+    constexpr size_t smem = Q4 ? q4s_smem<FEW>() : stream_smem_bytes<MB, LIMBS>();
     static_assert(smem <= 160 * 1024 && !(Q4 && 2 * smem > 160 * 1024), "does not fit the LDS of a CU");
     void (*kern)(stream_args);
-    if constexpr (Q4) kern = gemm_q4_stream_kernel<YBF16>;
+    if constexpr (Q4) kern = gemm_q4_stream_kernel<FEW, YBF16>;
     else kern = gemm_i8_stream_kernel<MB, LIMBS, YBF16>;
     static bool attr_done = false;   // one flag per instantiation
     if (!attr_done && smem > 48 * 1024) {
@@ -2383,7 +2446,10 @@ hipError_t forward_stream(hipStream_t st, const fwd_item* items, int n_items, in
     if (to_stream) {
         const bool yb = y_dtype == ESSA_BF16;
         if (items[0].quant == ESSA_QUANT_INT4_G128) {
-            e = yb ? launch_gemm_stream<1, 2, true, true>(st, a) : launch_gemm_stream<1, 2, false, true>(st, a);
+            bool few = true;
+            for (int g = 0; g < n_items; ++g) few = few && a.it[g].R <= 16;
+            if (few) e = yb ? launch_gemm_stream<1, 2, true, true, true>(st, a) : launch_gemm_stream<1, 2, false, true, true>(st, a);
+            else e = yb ? launch_gemm_stream<1, 2, true, true>(st, a) : launch_gemm_stream<1, 2, false, true>(st, a);
         } else if (stream_row_blocks(a) == 2) {
             if (a.limbs == 2) e = yb ? launch_gemm_stream<2, 2, true>(st, a) : launch_gemm_stream<2, 2, false>(st, a);
             else e = yb ? launch_gemm_stream<2, 1, true>(st, a) : launch_gemm_stream<2, 1, false>(st, a);
