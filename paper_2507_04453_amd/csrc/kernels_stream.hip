@@ -1229,7 +1229,11 @@ __global__ __launch_bounds__(NT, (Q4 && MB == 2) ? 4 : 1) void gemm_i8_kernel(st
 template <int MB, int LIMBS>
 constexpr size_t stream_smem_bytes() { return (size_t)8 * LIMBS * MB * 4096 + (size_t)MB * 4096 + (size_t)32 * MB * 4 + (size_t)32 * MB * UROW; }
 
-template <int MB, int LIMBS, bool YBF16>
+// FEW (up to 16 rows): the 16 x 16 x 64 MFMA, whose row operand holds 16 rows x 64 columns in the kilobyte that 32 rows x 32 columns take.  A wave's
+// chunks come in pairs (2 p, 2 p + 1), p = wave, wave + 8, ...: half the limb loads and MFMAs, half the sums through LDS.  Two chunks' weights become the
+// operands of channels 0..15 and 16..31 by exchanging lanes 16..31 and 48..63 of the first with the lanes 16 below of the second; the K order
+// is then chunk 0, chunk 1 of the lower 16 columns, chunk 0, chunk 1 of the upper, and the limbs are loaded in that order.
+template <int MB, int LIMBS, bool YBF16, bool FEW = false>
 __global__ __launch_bounds__(NT, 1) void gemm_i8_stream_kernel(stream_args a) {
     constexpr int BM = 32 * MB;
     // A wave asks for the weights of NW of its chunks at once and then lets the activation limbs of those chunks stream past,
@@ -1237,6 +1241,7 @@ __global__ __launch_bounds__(NT, 1) void gemm_i8_stream_kernel(stream_args a) {
     // loads issued between weight loads would each wait for the weight load in front of them.
     constexpr int NW = 16;                                 // 16 chunks per wave = 4096 columns: one bunch at the 7B and 8B shapes
     constexpr int DX = 4;
+    static_assert(!FEW || MB == 1, "one row block");
     constexpr size_t RED = (size_t)8 * LIMBS * MB * 4096;  // the 8 waves' partial sums; before the loop: t vectors and the core matrix
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     int* red = reinterpret_cast<int*>(smem);               // [wave][limb][row block][q][lane]
@@ -1269,6 +1274,8 @@ __global__ __launch_bounds__(NT, 1) void gemm_i8_stream_kernel(stream_args a) {
     uint32_t xoff[MB];
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) xoff[mb] = (mb * 32 + l32 < R) ? (uint32_t)(mb * nkc) * 1024u + lane16 : OUT_OF_RANGE;
+    const int l16 = lane & 15, kg = lane >> 4;
+    if (FEW) xoff[0] = l16 < R ? (uint32_t)((kg & 1) * 1024 + (kg >> 1) * 512 + l16 * 16) : OUT_OF_RANGE;
 
     // the small loads first (loads return in order): rank-space vectors, row units, this lane's channel scale and U_B
     constexpr int EU = (BM * 32 + NT - 1) / NT;
@@ -1296,22 +1303,24 @@ __global__ __launch_bounds__(NT, 1) void gemm_i8_stream_kernel(stream_args a) {
     // chunk j of this wave is K chunk kc = wave + 8 j; a chunk past the last one is asked for outside the descriptor (zeros,
     // no memory access), and its products add nothing
     u32x4 wr[NW], xr[DX][LIMBS][MB];
+    auto chunk_of = [&](int j) { return FEW ? 2 * (wave + 8 * (j >> 1)) + (j & 1) : wave + 8 * j; };   // FEW: n is even
     auto issue_w = [&](int j, int slot) {
         const uint32_t gone = j < n ? 0u : OUT_OF_RANGE;   // wave-uniform
-        wr[slot] = load16(wbase, lane16 | gone, (uint32_t)(wave + 8 * j) * wstride_b);
+        wr[slot] = load16(wbase, lane16 | gone, (uint32_t)chunk_of(j) * wstride_b);
     };
-    auto issue_x = [&](int j, int slot) {
+    auto issue_x = [&](int j, int slot) {                  // FEW: chunks j and j + 1
         const uint32_t gone = j < n ? 0u : OUT_OF_RANGE;
 #pragma unroll
         for (int l = 0; l < LIMBS; ++l)
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb) xr[slot][l][mb] = load16(xbase[l], xoff[mb] | gone, (uint32_t)(wave + 8 * j) * 1024u);
+            for (int mb = 0; mb < MB; ++mb) xr[slot][l][mb] = load16(xbase[l], xoff[mb] | gone, (uint32_t)chunk_of(j) * 1024u);
     };
+    constexpr int XJ = FEW ? 2 : 1;                        // chunks of a limb load
 #pragma unroll
     for (int s = 0; s < NW; ++s) issue_w(s, s);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int s = 0; s < DX; ++s) issue_x(s, s);
+    for (int s = 0; s < DX; ++s) issue_x(s * XJ, s);
     __builtin_amdgcn_sched_barrier(0);
     TSTAMP(2)
 
@@ -1320,63 +1329,104 @@ __global__ __launch_bounds__(NT, 1) void gemm_i8_stream_kernel(stream_args a) {
     TSTAMP(3)
 
     i32x16 acc[LIMBS][MB];
+    i32x4 few[LIMBS][2];                                   // FEW: channels 0..15, 16..31
 #pragma unroll
-    for (int l = 0; l < LIMBS; ++l)
+    for (int l = 0; l < LIMBS; ++l) {
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
             for (int q = 0; q < 16; ++q) acc[l][mb][q] = 0;
+        few[l][0] = few[l][1] = (i32x4){0, 0, 0, 0};
+    }
     for (int j0 = 0; j0 < n; j0 += NW) {
         if (j0 > 0) {                                      // rows wider than 4096: the next bunch of weights, then its first limbs
 #pragma unroll
             for (int s = 0; s < NW; ++s) issue_w(j0 + s, s);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int s = 0; s < DX; ++s) issue_x(j0 + s, s);
+            for (int s = 0; s < DX; ++s) issue_x(j0 + s * XJ, s);
             __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
-        for (int s = 0; s < NW; ++s) {
+        for (int s = 0; s < NW / XJ; ++s) {
+            if constexpr (FEW) {
+                u32x4 w[2];
 #pragma unroll
-            for (int l = 0; l < LIMBS; ++l)
+                for (int e = 0; e < 4; ++e) {
+                    const auto r = __builtin_amdgcn_permlane16_swap(wr[2 * s][e], wr[2 * s + 1][e], false, false);
+                    w[0][e] = r[0];
+                    w[1][e] = r[1];
+                }
 #pragma unroll
-                for (int mb = 0; mb < MB; ++mb)
-                    acc[l][mb] = __builtin_amdgcn_mfma_i32_32x32x32_i8((i32x4)xr[s % DX][l][mb], (i32x4)wr[s], acc[l][mb], 0, 0, 0);
+                for (int l = 0; l < LIMBS; ++l)
+#pragma unroll
+                    for (int b = 0; b < 2; ++b) few[l][b] = __builtin_amdgcn_mfma_i32_16x16x64_i8((i32x4)xr[s % DX][l][0], (i32x4)w[b], few[l][b], 0, 0, 0);
+            } else {
+#pragma unroll
+                for (int l = 0; l < LIMBS; ++l)
+#pragma unroll
+                    for (int mb = 0; mb < MB; ++mb)
+                        acc[l][mb] = __builtin_amdgcn_mfma_i32_32x32x32_i8((i32x4)xr[s % DX][l][mb], (i32x4)wr[s], acc[l][mb], 0, 0, 0);
+            }
             __builtin_amdgcn_sched_barrier(0);
-            if (s + DX < NW) issue_x(j0 + s + DX, s % DX);
+            if (s + DX < NW / XJ) issue_x(j0 + (s + DX) * XJ, s % DX);
             __builtin_amdgcn_sched_barrier(0);
         }
     }
     TSTAMP(4)
     lds_barrier();            // the prologue's matrices have been read by everyone: the area becomes the reduction slots
+    if constexpr (FEW) {
 #pragma unroll
-    for (int l = 0; l < LIMBS; ++l)
+        for (int l = 0; l < LIMBS; ++l)
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-            for (int q = 0; q < 16; ++q) red[(((wave * LIMBS + l) * MB + mb) * 16 + q) * 64 + lane] = acc[l][mb][q];
-    lds_barrier();
-    // element (row block, q, lane): the integer sums of the two K halves, folded and added as the other decode tiles do
-#pragma unroll
-    for (int i = 0; i < 2 * MB; ++i) {
-        const int e = tid + NT * i, mb = e >> 10, ql = e & 1023;
-        int sum[2][LIMBS];                                 // [K half][limb]
+            for (int q = 0; q < 8; ++q) red[((wave * LIMBS + l) * 8 + q) * 64 + lane] = few[l][q >> 2][q & 3];
+        lds_barrier();
+        // element `wave` of every lane: the integer sums of the two K halves (even waves hold the pairs of the first), folded as below
+        int sum[2][LIMBS];
 #pragma unroll
         for (int kh = 0; kh < 2; ++kh)
 #pragma unroll
             for (int l = 0; l < LIMBS; ++l) {
                 int t = 0;
 #pragma unroll
-                for (int wi = 0; wi < 4; ++wi) {
-                    const int w = 2 * kh + (wi & 1) + 4 * (wi >> 1);       // K half 0: waves 0, 1, 4, 5 (kc % 4 in {0, 1}); half 1: 2, 3, 6, 7
-                    t += red[((w * LIMBS + l) * MB + mb) * 1024 + ql];
-                }
+                for (int w = kh; w < 8; w += 2) t += red[((w * LIMBS + l) * 8 + wave) * 64 + lane];
                 sum[kh][l] = t;
             }
         float tot;
         if (LIMBS == 2) tot = fmaf(256.0f, (float)sum[0][0], (float)sum[0][1]) + fmaf(256.0f, (float)sum[1][0], (float)sum[1][1]);
         else tot = (float)(sum[0][0] + sum[1][0]);
-        totb[e] = tot;
+        const int row = 4 * kg + (wave & 3);               // its place in a 32 x 32 tile; the rows past 16 are nobody's
+        totb[(4 * (row >> 3) + (row & 3)) * 64 + (row >> 2 & 1) * 32 + (wave >> 2) * 16 + l16] = tot;
+    } else {
+#pragma unroll
+        for (int l = 0; l < LIMBS; ++l)
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                for (int q = 0; q < 16; ++q) red[(((wave * LIMBS + l) * MB + mb) * 16 + q) * 64 + lane] = acc[l][mb][q];
+        lds_barrier();
+        // element (row block, q, lane): the integer sums of the two K halves, folded and added as the other decode tiles do
+#pragma unroll
+        for (int i = 0; i < 2 * MB; ++i) {
+            const int e = tid + NT * i, mb = e >> 10, ql = e & 1023;
+            int sum[2][LIMBS];                                 // [K half][limb]
+#pragma unroll
+            for (int kh = 0; kh < 2; ++kh)
+#pragma unroll
+                for (int l = 0; l < LIMBS; ++l) {
+                    int t = 0;
+#pragma unroll
+                    for (int wi = 0; wi < 4; ++wi) {
+                        const int w = 2 * kh + (wi & 1) + 4 * (wi >> 1);       // K half 0: waves 0, 1, 4, 5 (kc % 4 in {0, 1}); half 1: 2, 3, 6, 7
+                        t += red[((w * LIMBS + l) * MB + mb) * 1024 + ql];
+                    }
+                    sum[kh][l] = t;
+                }
+            float tot;
+            if (LIMBS == 2) tot = fmaf(256.0f, (float)sum[0][0], (float)sum[0][1]) + fmaf(256.0f, (float)sum[1][0], (float)sum[1][1]);
+            else tot = (float)(sum[0][0] + sum[1][0]);
+            totb[e] = tot;
+        }
     }
     lds_barrier();
     if (wave >= MB) return;
@@ -1448,7 +1498,9 @@ constexpr int QS_PITCH = 16 * QS_ROUNDS * 2 + 16;          // LDS row of a zero-
 // columns take.  Half the limb loads, MFMAs, conversions, sums through LDS and folds; the same integers, the same FMAs in the same order.
 // A weight load of 64 columns (32 channels, low nibbles the first chunk, high ones the second) becomes the operands of channels 0..15
 // and 16..31 by exchanging the low codes of lanes 16..31 and 48..63 with the high codes of the lanes 16 below: the K order is then chunk 0, chunk 1
-// of the lower 16 columns, chunk 0, chunk 1 of the upper, and the limbs are loaded in that order too.
+// of the lower 16 columns, chunk 0, chunk 1 of the upper, and the limbs are loaded in that order too.  Weights go four rounds ahead
+// (six: 3 % slower; two, and three workgroups a CU: 6 % faster at 8192, 8 % slower at 1024).  One layer with its prep launch, us, 32 x 32 / 16 x 16,
+// 1 to 16 rows: 8192 wide 36.6 / 30 (31.5 at 16 rows), 5120 wide 21.8 / 18.9, 3584 wide 15.7 / 13.4, 1024 wide 12.8 / 11.
 template <bool FEW> constexpr size_t q4s_buffer() { return FEW ? 8 * 2048 : 8 * 4096; }      // one round's sums
 template <bool FEW> constexpr size_t q4s_smem() {
     constexpr size_t fin = 4096 + (32 + 32) * QS_PITCH + 32 * UROW, two = 2 * q4s_buffer<FEW>();   // what the epilogue needs in one buffer, or in both
@@ -1458,7 +1510,7 @@ template <bool FEW> constexpr size_t q4s_smem() {
 template <bool FEW, bool YBF16>
 __global__ __launch_bounds__(NT, 4) void gemm_q4_stream_kernel(stream_args a) {
     typedef __attribute__((ext_vector_type(2))) float f32x2;
-    constexpr int BM = 32, DX = 4;
+    constexpr int BM = 32, DX = 4, WAHEAD = FEW ? 4 : QS_ROUNDS - 2;   // rounds whose weights are asked for in front of the loop
     constexpr size_t BUF = q4s_buffer<FEW>();              // [wave][pair of q][lane][2], FEW: [wave][element][lane]
     constexpr size_t BUFS = q4s_smem<FEW>() - (size_t)QS_ROUNDS * 8 * 32 * 4 - 32 * 4 - (size_t)32 * UROW;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -1511,7 +1563,7 @@ __global__ __launch_bounds__(NT, 4) void gemm_q4_stream_kernel(stream_args a) {
         for (int e = 0; e < 2; ++e) wr[j][e] = load16(wbase, lane16 | gone, (uint32_t)(2 * grp + e) * wstride_b);
     };
 #pragma unroll
-    for (int j = 0; j < QS_ROUNDS - 2; ++j) issue_w(j);    // the last two as registers come free
+    for (int j = 0; j < WAHEAD; ++j) issue_w(j);           // the others as registers come free
     auto issue_x = [&](int j, int limb, int c) {
         const int grp = wave + 8 * j;
         const uint32_t gone = grp < groups ? 0u : OUT_OF_RANGE;
@@ -1590,9 +1642,8 @@ __global__ __launch_bounds__(NT, 4) void gemm_q4_stream_kernel(stream_args a) {
                 szreg = *as_global(reinterpret_cast<const u32x4*>(it.SZ16 + (size_t)(nb * 32 + min(sz_row, 31)) * 2 * Gp + 8 * sz_at));
                 ubreg = *as_global(reinterpret_cast<const u32x4*>(it.UB16 + (size_t)min(nb * 32 + min(ub_row, 31), dout - 1) * 2 * rp + 8 * ub_at));
                 xsreg = *as_global(reinterpret_cast<const u32x4*>(it.XS16 + (size_t)min(m0 + min(sz_row, 31), R - 1) * 2 * Gp + 8 * sz_at));
-            } else if (j <= 2) {
-                issue_w(QS_ROUNDS - 3 + j);
             }
+            if (j > 0 && j + WAHEAD - 1 < QS_ROUNDS) issue_w(j + WAHEAD - 1);
             __builtin_amdgcn_sched_barrier(0);
             if constexpr (FEW) {
 #pragma unroll
@@ -2300,7 +2351,7 @@ hipError_t launch_gemm_stream(hipStream_t st, stream_args& a) {
     static_assert(smem <= 160 * 1024 && !(Q4 && 2 * smem > 160 * 1024), "does not fit the LDS of a CU");
     void (*kern)(stream_args);
     if constexpr (Q4) kern = gemm_q4_stream_kernel<FEW, YBF16>;
-    else kern = gemm_i8_stream_kernel<MB, LIMBS, YBF16>;
+    else kern = gemm_i8_stream_kernel<MB, LIMBS, YBF16, FEW>;
     static bool attr_done = false;   // one flag per instantiation
     if (!attr_done && smem > 48 * 1024) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
@@ -2445,14 +2496,17 @@ hipError_t forward_stream(hipStream_t st, const fwd_item* items, int n_items, in
     const int q4_rows = items[0].quant == ESSA_QUANT_INT4_G128 ? pick_q4_wide(a) : 0;   // all items of a call share the weight format
     if (to_stream) {
         const bool yb = y_dtype == ESSA_BF16;
+        bool few = true;                                   // 16 rows at most: half of a row operand of 32 would be padding
+        for (int g = 0; g < n_items; ++g) few = few && a.it[g].R <= 16;
         if (items[0].quant == ESSA_QUANT_INT4_G128) {
-            bool few = true;
-            for (int g = 0; g < n_items; ++g) few = few && a.it[g].R <= 16;
             if (few) e = yb ? launch_gemm_stream<1, 2, true, true, true>(st, a) : launch_gemm_stream<1, 2, false, true, true>(st, a);
             else e = yb ? launch_gemm_stream<1, 2, true, true>(st, a) : launch_gemm_stream<1, 2, false, true>(st, a);
         } else if (stream_row_blocks(a) == 2) {
             if (a.limbs == 2) e = yb ? launch_gemm_stream<2, 2, true>(st, a) : launch_gemm_stream<2, 2, false>(st, a);
             else e = yb ? launch_gemm_stream<2, 1, true>(st, a) : launch_gemm_stream<2, 1, false>(st, a);
+        } else if (few) {
+            if (a.limbs == 2) e = yb ? launch_gemm_stream<1, 2, true, false, true>(st, a) : launch_gemm_stream<1, 2, false, false, true>(st, a);
+            else e = yb ? launch_gemm_stream<1, 1, true, false, true>(st, a) : launch_gemm_stream<1, 1, false, false, true>(st, a);
         } else if (a.limbs == 2) e = yb ? launch_gemm_stream<1, 2, true>(st, a) : launch_gemm_stream<1, 2, false>(st, a);
         else e = yb ? launch_gemm_stream<1, 1, true>(st, a) : launch_gemm_stream<1, 1, false>(st, a);
         tl_ev_start = tl_ev_stop = nullptr;
