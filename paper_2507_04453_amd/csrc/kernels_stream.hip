@@ -1234,13 +1234,14 @@ constexpr size_t stream_smem_bytes() { return (size_t)8 * LIMBS * MB * 4096 + (s
 // operands of channels 0..15 and 16..31 by exchanging lanes 16..31 and 48..63 of the first with the lanes 16 below of the second; the K order
 // is then chunk 0, chunk 1 of the lower 16 columns, chunk 0, chunk 1 of the upper, and the limbs are loaded in that order.
 template <int MB, int LIMBS, bool YBF16, bool FEW = false>
-__global__ __launch_bounds__(NT, 1) void gemm_i8_stream_kernel(stream_args a) {
+__global__ __launch_bounds__(NT, MB == 1 ? 4 : 1) void gemm_i8_stream_kernel(stream_args a) {
     constexpr int BM = 32 * MB;
-    // A wave asks for the weights of NW of its chunks at once and then lets the activation limbs of those chunks stream past,
-    // DX chunks ahead of their MFMAs.  A CU's loads complete in order: weights come from HBM, limbs out of the L2, and limb
-    // loads issued between weight loads would each wait for the weight load in front of them.
-    constexpr int NW = 16;                                 // 16 chunks per wave = 4096 columns: one bunch at the 7B and 8B shapes
-    constexpr int DX = 4;
+    // A wave asks for the weights of NW of its chunks, then for their limbs, and then multiplies.  Few at a time: what is on its way fills the
+    // CU's window of requests either way, two workgroups fit a CU with one row block (128 registers, half the LDS), and
+    // one loads while the other multiplies or finishes.  (All 16 chunks of a wave at once, limbs streaming past, one workgroup a CU, us a layer / this:
+    // 8192 wide 45 / 39 at 8 rows, 66 / 56 at 32, 87 / 81 at 64; 5120 wide 25 / 19, 31 / 23, 42 / 35; 3584 wide 14.2 / 13.9, 15.6 / 15.1, 19.4 / 17.9.)
+    constexpr int NW = MB == 1 ? 4 : 2;
+    constexpr int DX = FEW ? NW / 2 : NW;                  // limb loads of a bunch
     static_assert(!FEW || MB == 1, "one row block");
     constexpr size_t RED = (size_t)8 * LIMBS * MB * 4096;  // the 8 waves' partial sums; before the loop: t vectors and the core matrix
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -1339,7 +1340,7 @@ __global__ __launch_bounds__(NT, 1) void gemm_i8_stream_kernel(stream_args a) {
         few[l][0] = few[l][1] = (i32x4){0, 0, 0, 0};
     }
     for (int j0 = 0; j0 < n; j0 += NW) {
-        if (j0 > 0) {                                      // rows wider than 4096: the next bunch of weights, then its first limbs
+        if (j0 > 0) {                                      // the next bunch of weights, then its limbs
 #pragma unroll
             for (int s = 0; s < NW; ++s) issue_w(j0 + s, s);
             __builtin_amdgcn_sched_barrier(0);
@@ -1360,18 +1361,16 @@ __global__ __launch_bounds__(NT, 1) void gemm_i8_stream_kernel(stream_args a) {
 #pragma unroll
                 for (int l = 0; l < LIMBS; ++l)
 #pragma unroll
-                    for (int b = 0; b < 2; ++b) few[l][b] = __builtin_amdgcn_mfma_i32_16x16x64_i8((i32x4)xr[s % DX][l][0], (i32x4)w[b], few[l][b], 0, 0, 0);
+                    for (int b = 0; b < 2; ++b) few[l][b] = __builtin_amdgcn_mfma_i32_16x16x64_i8((i32x4)xr[s][l][0], (i32x4)w[b], few[l][b], 0, 0, 0);
             } else {
 #pragma unroll
                 for (int l = 0; l < LIMBS; ++l)
 #pragma unroll
                     for (int mb = 0; mb < MB; ++mb)
-                        acc[l][mb] = __builtin_amdgcn_mfma_i32_32x32x32_i8((i32x4)xr[s % DX][l][mb], (i32x4)wr[s], acc[l][mb], 0, 0, 0);
+                        acc[l][mb] = __builtin_amdgcn_mfma_i32_32x32x32_i8((i32x4)xr[s][l][mb], (i32x4)wr[s], acc[l][mb], 0, 0, 0);
             }
-            __builtin_amdgcn_sched_barrier(0);
-            if (s + DX < NW / XJ) issue_x(j0 + (s + DX) * XJ, s % DX);
-            __builtin_amdgcn_sched_barrier(0);
         }
+        __builtin_amdgcn_sched_barrier(0);
     }
     TSTAMP(4)
     lds_barrier();            // the prologue's matrices have been read by everyone: the area becomes the reduction slots
