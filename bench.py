@@ -280,7 +280,7 @@ class Bench:
                      "frac_of_hbm": bytes_per_launch / avg_s / 1e9 / HBM_PEAK_GBS})
         # the unit the contraction really runs on: int8 MFMA, `limbs` passes over the weights (null on the bf16 MFMA)
         roof["int8_mfma"] = None
-        if roof["kernel"] != "gemm_bf16_kernel":
+        if roof["kernel"] not in ("gemm_bf16_kernel", "gemm_q4_exact_kernel"):
             roof["int8_mfma"] = {"passes": limbs, "executed_TOPs": limbs * flops_per_launch / avg_s / 1e12, "peak_TOPs": INT8_PEAK_TOPS,
                                  "frac_executed": limbs * flops_per_launch / avg_s / 1e12 / INT8_PEAK_TOPS,
                                  "frac_algorithmic": flops_per_launch / avg_s / 1e12 / INT8_PEAK_TOPS}
@@ -299,6 +299,8 @@ class Bench:
         few = (128 if self.hidden <= 4096 else 96) if self.forward_only else (64 if self.hidden >= 3072 else 0)
         if R <= few:
             return "gemm_q4_stream_kernel"
+        if R > (256 if self.hidden > 4096 else 511 if self.hidden >= 3072 else 640 if self.hidden >= 2048 else 1023 if self.hidden >= 1024 else 2303):
+            return "gemm_q4_exact_kernel"
         return "gemm_q4_wide_kernel" if -(-R // 64) * col256 >= 256 else "gemm_i8_kernel<Q4>"
 
     def config(self):

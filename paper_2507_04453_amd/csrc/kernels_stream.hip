@@ -1477,8 +1477,8 @@ __global__ __launch_bounds__(NT, MB == 1 ? 4 : 1) void gemm_i8_stream_kernel(str
 // ------------------------------------------------------------------------------------------------
 // 4-bit weights at the row counts of the kernel above, on the same plan: one workgroup per block of 32 output channels and
 // block of 32 rows, the whole K; weights and limbs go memory -> MFMA operand registers.  A wave takes whole quantisation
-// groups, g = wave, wave + 8, ..., asks for the weights of all of them at once (at most 8 groups a wave: rows of 8192 columns)
-// (six, and the others as registers come free) and lets their limbs stream past, four chunks ahead of the MFMAs.
+// groups, g = wave, wave + 8, ... (at most 8: rows of 8192 columns), asks for the weights two rounds ahead (six: 5120 wide 23.2 against 21.6 us
+// at 32 rows, the others within 2 %) and lets the limbs stream past, four chunks ahead of the MFMAs.
 // A group's integer sums have to be scaled before they are added to another group's, and a row's result must not depend on
 // the kernel that took it, so the groups' fp32 FMAs keep the tile kernels' order: after each round of 8 groups the waves leave
 // their sums (hi limb, shift, lo limb on top: the tile kernels' integer) in LDS, and every thread folds two outputs
@@ -1486,8 +1486,7 @@ __global__ __launch_bounds__(NT, MB == 1 ? 4 : 1) void gemm_i8_stream_kernel(str
 // What the epilogue wants from memory (zero-point and rank operands) is asked for in the first round, a piece per thread, and
 // waits in registers until its place in LDS is free.
 // 128 registers and half the LDS: two workgroups per CU, one loading while the other folds or finishes.
-// One layer at 16 rows, with its prep launch: 8192 wide (18432 channels) 76 us with the 32 x 128 tiles, 42 now (1.9 TB/s of
-// weights and scales); 3584 wide 38 and 17.  Two row blocks per workgroup, with 148 registers and one workgroup per CU, took 68
+// One layer at 32 rows, with its prep launch: 8192 wide (18432 channels) 76 us with the 32 x 128 tiles, 40 now; 3584 wide 38 and 15.5.  Two row blocks per workgroup, with 148 registers and one workgroup per CU, took 68
 // at 33 rows of 8192 against 49 for two workgroups.
 // ------------------------------------------------------------------------------------------------
 constexpr int QS_ROUNDS = 8;                               // rounds of 8 groups: up to 64 groups
@@ -1509,7 +1508,7 @@ template <bool FEW> constexpr size_t q4s_smem() {
 template <bool FEW, bool YBF16>
 __global__ __launch_bounds__(NT, 4) void gemm_q4_stream_kernel(stream_args a) {
     typedef __attribute__((ext_vector_type(2))) float f32x2;
-    constexpr int BM = 32, DX = 4, WAHEAD = FEW ? 4 : QS_ROUNDS - 2;   // rounds whose weights are asked for in front of the loop
+    constexpr int BM = 32, DX = 4, WAHEAD = FEW ? 4 : 2;   // rounds whose weights are asked for in front of the loop
     constexpr size_t BUF = q4s_buffer<FEW>();              // [wave][pair of q][lane][2], FEW: [wave][element][lane]
     constexpr size_t BUFS = q4s_smem<FEW>() - (size_t)QS_ROUNDS * 8 * 32 * 4 - 32 * 4 - (size_t)32 * UROW;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
