@@ -9,6 +9,7 @@
 // Three launches: rank_down (t = V_A^T x, K split over workgroups), rank_finish (u = sB_c * (M (sA_c * t)) as bf16 head and
 // tail; the 64-row tiles do this themselves), gemm_bf16 (base product, scale, U_B u, output tile, reward partials).
 #include "forward_device.h"
+#include "row_offsets.h"
 #include <hip/hip_ext.h>
 #include <algorithm>
 #include <utility>
@@ -696,7 +697,7 @@ __global__ __launch_bounds__(256, 2) void gemm_q4_exact_kernel(q4_args a) {
 
     const i32x4 xres = buffer_words(it.X + (size_t)m0 * din), wres = buffer_words(it.Wn), sres = buffer_words(it.St);
     // load q = wave NR + e of the 4 NR of a step: half group q / (2 NR), 8 rows; its swizzle hangs on the parity of q
-    const uint32_t xlim = (uint32_t)(R - 1 - m0) * (uint32_t)(din * 2), xrow = (uint32_t)(lane >> 3) * (uint32_t)(din * 2);
+    const uint32_t xlim = essa_k::last_row_offset(R, m0, BM, din * 2), xrow = (uint32_t)(lane >> 3) * (uint32_t)(din * 2);
     uint32_t xpart[2];
 #pragma unroll
     for (int e = 0; e < 2; ++e) xpart[e] = ((lane & 7) ^ ((4 * (wave * NR + e) + (lane >> 4)) & 7)) * 16;
@@ -721,12 +722,12 @@ __global__ __launch_bounds__(256, 2) void gemm_q4_exact_kernel(q4_args a) {
     {
         const int ch0 = nb0 * 32 + wave * 64 + l16, Gp = it.Gp, nc = Gp / 16;
         bf16x8 z[2][NC], xs[2][NR][2];
-        const rsrc_t zres = make_rsrc(it.SZn), sumres = make_rsrc(it.XS16);
+        const rsrc_t zres = make_rsrc(it.SZn), sumres = make_rsrc(it.XS16 + (size_t)(m0 / 16) * nc * 512);
         uint32_t zoff[NC], sumoff[NR];                     // operand tiles: a kilobyte per 16 channels and 16 groups, half of one per load of sums
 #pragma unroll
         for (int n = 0; n < NC; ++n) zoff[n] = (uint32_t)min(nb0 * 2 + wave * NC + n, nb16 - 1) * (uint32_t)nc * 1024u;
 #pragma unroll
-        for (int m = 0; m < NR; ++m) sumoff[m] = (uint32_t)min(m0 / 16 + m, (R - 1) / 16) * (uint32_t)nc * 1024u;
+        for (int m = 0; m < NR; ++m) sumoff[m] = (uint32_t)min(m, (R - 1 - m0) / 16) * (uint32_t)nc * 1024u;
         auto ask = [&](int c, int set) {
 #pragma unroll
             for (int n = 0; n < NC; ++n) z[set][n] = __builtin_bit_cast(bf16x8, load16(zres, lane16, zoff[n] + c * 1024));
@@ -763,7 +764,7 @@ __global__ __launch_bounds__(256, 2) void gemm_q4_exact_kernel(q4_args a) {
         auto rank_term = [&](auto ks_count) {              // as in the kernel above, for u 2^-12
             constexpr int KS = decltype(ks_count)::value;
             bf16x8 ub[NC][KS], uu[NR][2];
-            const rsrc_t bres = make_rsrc(it.UB16), ures = make_rsrc(it.U16);
+            const rsrc_t bres = make_rsrc(it.UB16), ures = make_rsrc(it.U16 + (size_t)m0 * (32 * KS));
 #pragma unroll
             for (int n = 0; n < NC; ++n)
 #pragma unroll
@@ -772,7 +773,7 @@ __global__ __launch_bounds__(256, 2) void gemm_q4_exact_kernel(q4_args a) {
             for (int m = 0; m < NR; ++m)
 #pragma unroll
                 for (int e = 0; e < 2; ++e)
-                    uu[m][e] = __builtin_bit_cast(bf16x8, load16(ures, (uint32_t)min(m0 + m * 16 + l16, R - 1) * (64 * KS) + 16 * (KS == 1 ? kg & 1 : kg), e * 32 * KS));
+                    uu[m][e] = __builtin_bit_cast(bf16x8, load16(ures, (uint32_t)min(m * 16 + l16, R - 1 - m0) * (64 * KS) + 16 * (KS == 1 ? kg & 1 : kg), e * 32 * KS));
 #pragma unroll
             for (int n = 0; n < NC; ++n)
 #pragma unroll

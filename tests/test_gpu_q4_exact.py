@@ -106,3 +106,27 @@ def test_q4_exact_group_and_limbs(essa):
         assert (few - Y[:256]).norm() <= 8e-5 * few.norm()
         it[0].close()
     ctx.close()
+
+
+def test_q4_exact_rows_past_4_gib(essa):
+    """An X of more than 4 GiB: the last tiles' rows are the rows that they repeat, as a small call has them (the rank-r term's K may be cut
+    otherwise there: fp32 sums)."""
+    ctx = essa.Context(0)
+    d_in, d_out, r, K, base = 8192, 72, 8, 4, 701
+    R = 2 ** 32 // (2 * d_in) + 131
+    p = wl.make_projection("t", d_in, d_out, r, "int4", layer=23, proj=0)
+    _, f = oracle_proj(p)
+    gp = gpu_proj(essa, ctx, p)
+    sAd, sBd = (to_dev(s) for s in candidate_sigmas(f, K, 0.05))
+    few = bf16_dev(wl.make_x_bf16(base, d_in, x_id=72)[0])
+    r2c = to_dev(np.random.default_rng(10).integers(0, K, base).astype(np.int32))
+    at = torch.arange(R, device="cuda") % base
+    X, rd = few[at], r2c[at].contiguous()
+    print("q4 exact: d_in=%d d_out=%d R=%d" % (d_in, d_out, R), flush=True)
+    Y, Yf = torch.empty(R, d_out, device="cuda"), torch.empty(base, d_out, device="cuda")
+    essa.essa_svdlora_forward(ctx, gp, X, rd, sAd, sBd, Y)
+    essa.essa_svdlora_forward(ctx, gp, few, r2c, sAd, sBd, Yf)
+    off = (Y - Yf[at]).norm(dim=1) / Yf[at].norm(dim=1)
+    assert off.max().item() <= 1e-5, (off.max().item(), int(off.argmax()))
+    gp.close()
+    ctx.close()
