@@ -457,23 +457,23 @@ extern "C" essa_status essa_proj_create(essa_ctx* ctx, const essa_proj_desc* d, 
         ESSA_TRY(upload(&p->Wt, Wt.data(), Wt.size()));
         const int gpad = p->d_in_pad / 128;
         std::vector<float> St((size_t)gpad * nbs * 32, 0.f);
-        std::vector<uint16_t> SZ((size_t)nbs * 32 * 2 * p->Gp, 0), SZn(SZ.size(), 0);
-        auto head_and_tail = [](float m, uint16_t* head, uint16_t* tail) {
-            *head = f32_to_bf16_rne(m);
-            uint32_t hb = (uint32_t)*head << 16;
-            float hf;
-            std::memcpy(&hf, &hb, 4);
-            *tail = f32_to_bf16_rne(m - hf);
+        std::vector<uint16_t> SZ((size_t)nbs * 32 * 2 * p->Gp, 0), SZn((size_t)nbs * 2 * ((p->groups + 31) / 32) * 1536, 0);
+        auto parts = [](float v, uint16_t* dst, size_t pitch, int count) {     // v as the sum of bf16 numbers: head, tail, ...
+            for (int e = 0; e < count; ++e) {
+                dst[e * pitch] = f32_to_bf16_rne(v);
+                const uint32_t b = (uint32_t)dst[e * pitch] << 16;
+                float f;
+                std::memcpy(&f, &b, 4);
+                v -= f;
+            }
         };
         for (int o = 0; o < dout; ++o)
             for (int g = 0; g < p->groups; ++g) {
                 const float sv = s[(size_t)o * p->groups + g], zv = z[(size_t)o * p->groups + g];
                 St[(size_t)g * nbs * 32 + o] = sv;
-                uint16_t* sz = &SZ[(size_t)o * 2 * p->Gp + g];
-                head_and_tail(-(sv * zv), sz, sz + p->Gp);
-                // [16 channels][16 groups][head, tail][8 groups][channel][group]
-                uint16_t* szn = &SZn[((size_t)(o / 16) * (p->Gp / 16) + g / 16) * 512 + (g / 8 % 2) * 128 + (o % 16) * 8 + g % 8];
-                head_and_tail(-(sv * (zv + 16.f)) * 0x1p-5f, szn, szn + 256);
+                parts(-(sv * zv), &SZ[(size_t)o * 2 * p->Gp + g], p->Gp, 2);
+                // [16 channels][32 groups][part][8 groups][channel][group]
+                parts(-(sv * (zv + 16.f)) * 0x1p-5f, &SZn[((size_t)(o / 16) * ((p->groups + 31) / 32) + g / 32) * 1536 + (g / 8 % 4) * 128 + (o % 16) * 8 + g % 8], 512, 3);
             }
         ESSA_TRY(upload(&p->St, St.data(), St.size()));
         ESSA_TRY(upload(&p->SZ16, SZ.data(), SZ.size()));
@@ -830,7 +830,6 @@ static bool takes_exact_product(const essa_k::fwd_item& k) {
 //   3584      384  51 / 43,  512  52 / 46, 640 71 / 50  512  38 / 43,  768 49 / 43  1024 37 / 40, 2048 43 / 41
 //   5120      192  57 / 53,  384  85 / 64, 512 93 / 84  384  48 / 54,  512 60 / 55  1024 48 / 54, 2000 60 / 56
 //   8192      256 124 / 105, 384 143 / 126, 512 181 / 150  256 60 / 74, 384 89 / 76   512 61 / 73, 2000 80 / 76
-// (The sums of x go where the limb path keeps its own, in blocks of 16 rows: that room is enough from 60 rows on.)
 static bool takes_exact_q4(const essa_k::fwd_item& k) {
     return k.Wn && k.R > (k.d_in > 4096 ? 256 : k.d_in >= 3072 ? 511 : k.d_in >= 2048 ? 640 : k.d_in >= 1024 ? 1023 : 2303);
 }

@@ -78,7 +78,7 @@ struct essa_proj {
     // 4-bit weights for the exact-product kernel: [groups][2 n_blocks][64 lanes][4 words], lane (kg, l16) word j of block (g, b) = the codes of
     // columns 128 g + 32 j + 8 kg .. + 7 of channel 16 b + l16; columns 2 i and 2 i + 1 of them at bits 3 + 4 i and 19 + 4 i (mod 32)
     uint8_t* Wn = nullptr;
-    uint16_t* SZn = nullptr;   // [2 n_blocks][Gp/16][2][2][16 channels][8 groups] bf16 head and tail of -scale (zero + 16) 2^-5
+    uint16_t* SZn = nullptr;   // [2 n_blocks][ceil(groups/32)][3][4][16 channels][8 groups] -scale (zero + 16) 2^-5 as three bf16
     // int8 weights once more as bf16 (exact, times the channel's power of two), for the exact-product kernel: [ceil(d_in/64)][n_blocks][2][2][64 lanes][8],
     // block (kt, nb), half, sub-step j, lane (kg, l16) = channel 32 nb + 16 half + l16, columns 64 kt + 32 j + 8 kg .. + 7
     uint16_t* W16 = nullptr;
@@ -246,7 +246,7 @@ hipError_t forward_stream(hipStream_t st, const fwd_item* items, int n_items, in
 bool prefill_takes(const fwd_item& it);
 hipError_t forward_prefill(hipStream_t st, const fwd_item* items, int n_items, int y_dtype, unsigned flags, hipEvent_t ev_start,
                            hipEvent_t ev_stop);
-// the same for 4-bit weights (items with Wn); XS16 takes 2^-7 of the group sums of x
+// the same for 4-bit weights (items with Wn); the items' limb space takes 2^-7 of the group sums of x
 hipError_t forward_prefill_q4(hipStream_t st, const fwd_item* items, int n_items, int y_dtype, hipEvent_t ev_start, hipEvent_t ev_stop);
 // Wt (4-bit operand tiles) -> Wn
 hipError_t repack_nibbles(hipStream_t st, const int8_t* Wt, int groups, int n_blocks, uint8_t* Wn);

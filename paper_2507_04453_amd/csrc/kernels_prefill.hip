@@ -35,7 +35,7 @@ struct prefill_args {
     int ksplit[ESSA_MAX_GROUP];            // rank_down: the item's K is cut in this many parts (at most 8)
     float u_scale;                         // rank_finish leaves u times this power of two
     uint16_t* XS16[ESSA_MAX_GROUP];        // 4-bit weights: where rank_down leaves the sums of x over groups of 128 columns (null: another item of this X does)
-    int Gp[ESSA_MAX_GROUP];
+    int Gn[ESSA_MAX_GROUP];                // groups rounded up to 32
 };
 
 // ---- loads that go from memory into LDS without passing through registers ------------------------------------------
@@ -86,8 +86,8 @@ __device__ __forceinline__ int xcd_contiguous(int b, int T) {
 // ------------------------------------------------------------------------------------------------
 constexpr int RD_ROWS = 128;
 
-// SUMS (4-bit weights): the sums of x over groups of 128 columns as well, 2^-7 of them as bf16 head and tail, in
-// the operand tiles of the product that wants them, [16 rows][16 groups][head, tail][8 groups][row][group].  They come from
+// SUMS (4-bit weights): the sums of x over groups of 128 columns as well, 2^-7 of them as three bf16 (all of an fp32 number), in
+// the operand tiles of the product that wants them, [16 rows][32 groups][part][8 groups][row][group].  They come from
 // the x fragments that are in registers anyway, times an operand that is 2^-7 in the column of the group and zero elsewhere; 32 groups
 // fill an accumulator.  K parts then end between groups.  An Inf or a NaN reaches every sum of its row, and makes it NaN.
 template <int RP, bool THIRD, bool SUMS = false>
@@ -148,16 +148,19 @@ __global__ __launch_bounds__(256, THIRD && RP == 32 ? 1 : 2) void rank_down_kern
 #pragma unroll
     for (int q = 0; q < 16; ++q) acc_s[q] = 0.f;
     auto put_sums = [&](int g_end) {                       // the window of 32 groups that g_end - 1 lies in, up to g_end
-        const int Gp = a.Gp[g], gr = ((g_end - 1) & ~31) + l32;
+        const int Gn = a.Gn[g], gr = ((g_end - 1) & ~31) + l32;
 #pragma unroll
         for (int q = 0; q < 16; ++q) {
             const int row = m0 + wave * 32 + 8 * (q >> 2) + 4 * h + (q & 3);
-            const float v = acc_s[q];
-            const uint16_t hi = f32_to_bf16_bits(v);
+            float v = acc_s[q];
             if (row < R && gr >= k_lo / 2 && gr < g_end) {
-                const gptr<uint16_t> dst = as_global_w(a.XS16[g]) + ((size_t)(row >> 4) * (Gp >> 4) + (gr >> 4)) * 512 + (gr >> 3 & 1) * 128 + (row & 15) * 8 + (gr & 7);
-                dst[0] = hi;
-                dst[256] = f32_to_bf16_bits(v - bf16_bits_to_f32(hi));
+                const gptr<uint16_t> dst = as_global_w(a.XS16[g]) + ((size_t)(row >> 4) * (Gn >> 5) + (gr >> 5)) * 1536 + (gr >> 3 & 3) * 128 + (row & 15) * 8 + (gr & 7);
+#pragma unroll
+                for (int e = 0; e < 3; ++e) {
+                    const uint16_t bits = f32_to_bf16_bits(v);
+                    dst[512 * e] = bits;
+                    v -= bf16_bits_to_f32(bits);
+                }
             }
             acc_s[q] = 0.f;
         }
@@ -189,8 +192,8 @@ __global__ __launch_bounds__(256, THIRD && RP == 32 ? 1 : 2) void rank_down_kern
             st = st == 2 ? 0 : st + 1;
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        // the last part also clears the padding, whose columns no group has touched
-        if (SUMS && sums) put_sums(k_hi == nk_all ? a.Gp[g] : k_hi / 2);
+        // the last part also clears the rest of its eight groups, whose columns no group has touched
+        if (SUMS && sums) put_sums(k_hi == nk_all ? (nk_all / 2 + 7) / 8 * 8 : k_hi / 2);
     }
     const gptr<float> out = as_global_w(it.Tpart) + ((size_t)part * R + m0) * RP;
 #pragma unroll
@@ -632,7 +635,8 @@ hipError_t launch_bf16(hipStream_t st, prefill_args& a) {
 // Base product for 4-bit weights on the bf16 MFMA, activations as they are.  With q the 4-bit code, (16 + q) 2^-12 is a bf16
 // number whose bits are a constant with q put into its mantissa: one shift and one and-or make two weights.  A group's sum
 // g = <(16 + q) 2^-12, x> over its 128 columns meets its scale in one fp32 FMA, and the zero points and the 16 come back as a product
-// over the groups, - s (z + 16) 2^-12 times the group's sum of x (rank_down's), both as bf16 head and tail, all four products:
+// over the groups, - s (z + 16) 2^-12 times the group's sum of x (rank_down's).  Both as three bf16, the six products that reach 2^-24 of
+// it: rows whose entries have a mean make it many times larger than the output (head and tail alone: 8e-5 rms for 1 + N(0, 1), 7e-5 for |N(0, 1)|).
 //   Y = 2^12 (sum_g s_g g_g - sum_g s_g (z_g + 16) 2^-12 X_g + U_B 2^-12 u)
 // The 2^-12 keeps every partial sum below the output that it grows into: nothing overflows that the output does not.
 //
@@ -654,7 +658,7 @@ struct q4_item {
     const float *St, *rv;
     void* Y;
     float* rowpart;
-    int R, d_in, d_out, rp, n_blocks, Gp;
+    int R, d_in, d_out, rp, n_blocks, Gn;
 };
 struct q4_args {
     q4_item it[ESSA_MAX_GROUP];
@@ -712,40 +716,52 @@ __global__ __launch_bounds__(256, 2) void gemm_q4_exact_kernel(q4_args a) {
     };
     auto load_w = [&](int n, int g, uint32_t stage) { load_lds16(lds0 + W0 + stage + (wave * NC + n) * 1024, lane16, wres, (uint32_t)g * (uint32_t)nb16 * 1024u + woff[n]); };
     auto load_s = [&](int g, uint32_t stage) { load_lds4(lds0 + S0 + stage + wave * 256, soff, sres, (uint32_t)g * sstep); };
-    // the totals start with the zero points' and the rank-r term, whose operands are asked for in front of the first step's.  A fragment of
-    // 32 K columns holds 16 groups twice, head and tail side by side on the weights' side, head and then tail on the other
+    // the totals start with the zero points' and the rank-r term, whose operands are asked for in front of the first step's
     f32x4 tot[NC][NR];
 #pragma unroll
     for (int n = 0; n < NC; ++n)
 #pragma unroll
         for (int m = 0; m < NR; ++m) tot[n][m] = (f32x4){0.f, 0.f, 0.f, 0.f};
     {
-        const int ch0 = nb0 * 32 + wave * 64 + l16, Gp = it.Gp, nc = Gp / 16;
-        bf16x8 z[2][NC], xs[2][NR][2];
-        const rsrc_t zres = make_rsrc(it.SZn), sumres = make_rsrc(it.XS16 + (size_t)(m0 / 16) * nc * 512);
-        uint32_t zoff[NC], sumoff[NR];                     // operand tiles: a kilobyte per 16 channels and 16 groups, half of one per load of sums
+        const int ch0 = nb0 * 32 + wave * 64 + l16, nc = it.Gn / 32;
+        bf16x8 z[2][NC], xs[2][NR];                        // 32 groups: head, and the third and then the second part in one place
+        const rsrc_t zres = make_rsrc(it.SZn), sumres = make_rsrc(it.XS16 + (size_t)(m0 / 16) * nc * 1536);
+        uint32_t zoff[NC], sumoff[NR];                     // operand tiles of 16 channels or rows and 32 groups: a kilobyte per part
 #pragma unroll
-        for (int n = 0; n < NC; ++n) zoff[n] = (uint32_t)min(nb0 * 2 + wave * NC + n, nb16 - 1) * (uint32_t)nc * 1024u;
+        for (int n = 0; n < NC; ++n) zoff[n] = (uint32_t)min(nb0 * 2 + wave * NC + n, nb16 - 1) * (uint32_t)nc * 3072u;
 #pragma unroll
-        for (int m = 0; m < NR; ++m) sumoff[m] = (uint32_t)min(m, (R - 1 - m0) / 16) * (uint32_t)nc * 1024u;
-        auto ask = [&](int c, int set) {
+        for (int m = 0; m < NR; ++m) sumoff[m] = (uint32_t)min(m, (R - 1 - m0) / 16) * (uint32_t)nc * 3072u;
+        auto ask_z = [&](int c, int p) {
 #pragma unroll
-            for (int n = 0; n < NC; ++n) z[set][n] = __builtin_bit_cast(bf16x8, load16(zres, lane16, zoff[n] + c * 1024));
-#pragma unroll
-            for (int m = 0; m < NR; ++m)
-#pragma unroll
-                for (int e = 0; e < 2; ++e) xs[set][m][e] = __builtin_bit_cast(bf16x8, load16(sumres, lane16 & 511, sumoff[m] + c * 1024 + e * 512));
+            for (int n = 0; n < NC; ++n) z[p != 0][n] = __builtin_bit_cast(bf16x8, load16(zres, lane16, zoff[n] + c * 3072 + p * 1024));
         };
-        auto multiply = [&](int set) {
+        auto ask_x = [&](int c, int p) {                   // eights past the last group: beyond the descriptor, zeros
+            const uint32_t xlane = c * 32 + kg * 8 < ng ? lane16 : 0x80000000u;
 #pragma unroll
-            for (int e = 1; e >= 0; --e)
-#pragma unroll
-                for (int n = 0; n < NC; ++n)
-#pragma unroll
-                    for (int m = 0; m < NR; ++m) tot[n][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(z[set][n], xs[set][m][e], tot[n][m], 0, 0, 0);
+            for (int m = 0; m < NR; ++m) xs[p != 0][m] = __builtin_bit_cast(bf16x8, load16(sumres, xlane, sumoff[m] + c * 3072 + p * 1024));
         };
-        ask(0, 0);
-        ask(min(1, nc - 1), 1);
+        auto multiply = [&](int pz, int px) {
+#pragma unroll
+            for (int n = 0; n < NC; ++n)
+#pragma unroll
+                for (int m = 0; m < NR; ++m) tot[n][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(z[pz][n], xs[px][m], tot[n][m], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        auto chunk = [&](int c, auto last) {               // no branch around a load: the compiler has to count them
+            multiply(0, 1);
+            ask_x(c, 1);
+            multiply(1, 0);
+            ask_z(c, 1);
+            multiply(0, 0);
+            multiply(0, 1);
+            if constexpr (!last) ask_z(c + 1, 0);
+            multiply(1, 0);
+            if constexpr (!last) ask_x(c + 1, 0);
+            multiply(1, 1);
+            if constexpr (!last) ask_x(c + 1, 2), ask_z(c + 1, 2);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        ask_z(0, 0), ask_x(0, 2), ask_z(0, 2), ask_x(0, 0);
         __builtin_amdgcn_sched_barrier(0);
         static_for<D - 1>([&](auto tc) {
             constexpr int t = tc;
@@ -755,12 +771,8 @@ __global__ __launch_bounds__(256, 2) void gemm_q4_exact_kernel(q4_args a) {
             for (int e = 0; e < NR; ++e) load_x(e, min(t, ng - 1), t * XST);
             load_s(min(t, ng - 1), t * 1024);
         });
-        for (int c = 0; c < nc; c += 2) {
-            multiply(0);
-            if (c + 2 < nc) ask(c + 2, 0);
-            if (c + 1 < nc) multiply(1);
-            if (c + 3 < nc) ask(c + 3, 1);
-        }
+        for (int c = 0; c < nc - 1; ++c) chunk(c, std::false_type{});
+        chunk(nc - 1, std::true_type{});
         auto rank_term = [&](auto ks_count) {              // as in the kernel above, for u 2^-12
             constexpr int KS = decltype(ks_count)::value;
             bf16x8 ub[NC][KS], uu[NR][2];
@@ -980,7 +992,7 @@ bf16_tile pick_tile(const prefill_item* items, int n_items) {
 hipError_t launch_rank(hipStream_t st, prefill_args& a, bool finish) {
     int total = 0, maxR = 0;
     bool has16[2] = {false, false}, has32[2] = {false, false};   // [V_A with all its bits]
-    const bool sums = a.Gp[0] > 0;         // 4-bit weights throughout
+    const bool sums = a.Gn[0] > 0;         // 4-bit weights throughout
     for (int g = 0; g < a.n_items; ++g) {
         // K parts: enough workgroups for two per CU in a group of four projections, no part shorter than four steps; by the
         // item's own size only, so that an item's sums do not depend on what it is grouped with
@@ -1064,9 +1076,10 @@ hipError_t forward_prefill_q4(hipStream_t st, const fwd_item* items, int n_items
         const fwd_item& k = items[g];
         r.it[g] = prefill_item{(const uint16_t*)k.X, nullptr, nullptr, k.VAp, nullptr, nullptr, k.M, k.sigmaA, k.sigmaB, nullptr, k.row2cand, nullptr,
                                k.U16, k.Tpart, nullptr, k.sigma_stride, k.R, k.d_in, k.d_out, k.r, k.rp, k.n_blocks};
-        r.XS16[g] = k.x_owner ? k.XS16 : nullptr;
-        r.Gp[g] = k.Gp;
-        a.it[g] = q4_item{(const uint16_t*)k.X, k.UB16, k.U16, k.SZn, k.XS16, k.Wn, k.St, k.rv, k.Y, k.rowpart, k.R, k.d_in, k.d_out, k.rp, k.n_blocks, k.Gp};
+        uint16_t* sums = (uint16_t*)k.Xh;                  // 192 bytes a row and 32 groups, where the limb kernels keep at least 512
+        r.XS16[g] = k.x_owner ? sums : nullptr;
+        r.Gn[g] = (k.groups + 31) / 32 * 32;
+        a.it[g] = q4_item{(const uint16_t*)k.X, k.UB16, k.U16, k.SZn, sums, k.Wn, k.St, k.rv, k.Y, k.rowpart, k.R, k.d_in, k.d_out, k.rp, k.n_blocks, r.Gn[g]};
     }
     r.n_items = a.n_items = n_items;
     r.u_scale = 0x1p-12f;

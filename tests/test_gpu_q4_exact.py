@@ -1,8 +1,7 @@
 """GPU parity of the exact-product kernel for 4-bit weights (codes as bf16, fp32 group sums) at the edges of its tiles.
 
-Products are exact and fp32 sums random-signed; what is left is the zero-point term, whose two operands (scale times zero + 16, and
-the group's sum of x) enter as bf16 head and tail: each off by 2^-17 at most, 2^-18 rms, of a term that is about
-(8 + 16) / 4.6 = 5.2 times the output's rms for the codes and zeros drawn here.  sqrt(2) 2^-18 5.2 = 2.8e-5 rms at most."""
+Products are exact, fp32 sums random-signed and the zero-point term's operands fp32 numbers in three bf16 parts: 2e-6 for zero-mean rows.  (With two
+parts each was off by 2^-18 rms of a term 5.2 times the output's rms, 2.8e-5 together; the bar below still is that.)"""
 import numpy as np
 import pytest
 import torch
@@ -128,5 +127,40 @@ def test_q4_exact_rows_past_4_gib(essa):
     essa.essa_svdlora_forward(ctx, gp, few, r2c, sAd, sBd, Yf)
     off = (Y - Yf[at]).norm(dim=1) / Yf[at].norm(dim=1)
     assert off.max().item() <= 1e-5, (off.max().item(), int(off.argmax()))
+    gp.close()
+    ctx.close()
+
+
+@pytest.mark.parametrize("d_in", [1152, 3584, 8192])
+def test_q4_exact_rows_with_a_mean(essa, d_in):
+    """Rows whose entries have a mean: the zero-point term, out of three bf16 parts a side and so fp32, starts the totals at the sum of G group terms
+    of rms t = 24 s X_g, and the groups' own sums bring them back one by one.  Each of these additions is off by at most 2^-24 of what is
+    left: root of their squares 2^-24 t sqrt(sum k^2) = 2^-24 t G^1.5 / sqrt(3).  The rank-r term has three operands in bf16 head and tail (V_A, u,
+    U_B), each off by 2^-17 at most: sqrt(3) 2^-18 of its rms.  And no less exact than the fixed-point path."""
+    ctx = essa.Context(0)
+    d_out, r, K, R = 328, 16, 3, 1100
+    p = wl.make_projection("t", d_in, d_out, r, "int4", layer=24, proj=2)
+    W, f = oracle_proj(p)
+    gp = gpu_proj(essa, ctx, p)
+    sA, sB = candidate_sigmas(f, K, 0.05)
+    g = torch.Generator(device="cuda").manual_seed(d_in)
+    N = torch.randn(R, d_in, device="cuda", generator=g)
+    r2c = (np.arange(R) % K).astype(np.int32)
+    for name, X in (("N", N), ("|N|", N.abs()), ("1 + N", 1 + N), ("1 + 0.1 N", 1 + 0.1 * N), ("-3 + N", N - 3)):
+        X = X.bfloat16()
+        err = []
+        xv = X[:200].double().cpu().numpy()
+        ref = orc.svdlora_forward(W, f, xv, r2c[:200], sA, sB)
+        for rows in (R, 200):                              # exact products, fixed point
+            Y = torch.empty(rows, d_out, device="cuda")
+            essa.essa_svdlora_forward(ctx, gp, X[:rows].contiguous(), to_dev(r2c[:rows]), to_dev(sA), to_dev(sB), Y)
+            err.append(orc.rel_errors(Y[:200].cpu().numpy().astype(np.float64), ref)[1])
+        scales = np.asarray(p.scales, np.float64)
+        sums, rank = xv.reshape(200, -1, 128).sum(2), ref - xv @ np.asarray(W, np.float64).T
+        t = 24.0 * np.sqrt((sums ** 2).mean() * (scales ** 2).mean())
+        fold = 2.0 ** -24 * t * (d_in / 128) ** 1.5 / np.sqrt(3.0)
+        bar = (fold + np.sqrt(3.0) * 2.0 ** -18 * np.sqrt((rank ** 2).mean())) / np.sqrt((ref ** 2).mean())
+        print("d_in=%d x=%s exact %.2e fixed point %.2e bar %.2e" % (d_in, name, err[0], err[1], bar), flush=True)
+        assert err[0] <= bar and err[0] <= err[1], (name, err, bar)
     gp.close()
     ctx.close()
