@@ -1233,16 +1233,16 @@ constexpr size_t stream_smem_bytes() { return (size_t)8 * LIMBS * MB * 4096 + (s
 // chunks come in pairs (2 p, 2 p + 1), p = wave, wave + 8, ...: half the limb loads and MFMAs, half the sums through LDS.  Two chunks' weights become the
 // operands of channels 0..15 and 16..31 by exchanging lanes 16..31 and 48..63 of the first with the lanes 16 below of the second; the K order
 // is then chunk 0, chunk 1 of the lower 16 columns, chunk 0, chunk 1 of the upper, and the limbs are loaded in that order.
-template <int MB, int LIMBS, bool YBF16, bool FEW = false>
-__global__ __launch_bounds__(NT, MB == 1 ? 4 : 1) void gemm_i8_stream_kernel(stream_args a) {
+template <int MB, int LIMBS, bool YBF16, bool FEW, bool DEEP>
+__global__ __launch_bounds__(NT, MB == 1 && !DEEP ? 4 : 1) void gemm_i8_stream_kernel(stream_args a) {
     constexpr int BM = 32 * MB;
-    // A wave asks for the weights of NW of its chunks, then for their limbs, and then multiplies.  Few at a time: what is on its way fills the
-    // CU's window of requests either way, two workgroups fit a CU with one row block (128 registers, half the LDS), and
-    // one loads while the other multiplies or finishes.  (All 16 chunks of a wave at once, limbs streaming past, one workgroup a CU, us a layer / this:
-    // 8192 wide 45 / 39 at 8 rows, 66 / 56 at 32, 87 / 81 at 64; 5120 wide 25 / 19, 31 / 23, 42 / 35; 3584 wide 14.2 / 13.9, 15.6 / 15.1, 19.4 / 17.9.)
-    constexpr int NW = MB == 1 ? 4 : 2;
-    constexpr int DX = FEW ? NW / 2 : NW;                  // limb loads of a bunch
-    static_assert(!FEW || MB == 1, "one row block");
+    // A wave asks for the weights of NW of its chunks, then for their limbs, and then multiplies.  Few at a time: with one row block two workgroups
+    // fit a CU (128 registers, half the LDS), and one loads while the other multiplies or finishes.  DEEP: 16 chunks at a time, one workgroup a CU, the
+    // limbs streaming past four chunks ahead of their MFMAs (a CU's loads complete in order, weights come from HBM, limbs out of the L2: a limb load
+    // between weight loads would wait for the one in front of it).  stream_deep says which launch gets which.
+    constexpr int NW = DEEP ? 16 : MB == 1 ? 4 : 2;
+    constexpr int DX = DEEP ? 4 : FEW ? NW / 2 : NW;       // limb loads on their way
+    static_assert(!FEW || (MB == 1 && !DEEP), "one row block");
     constexpr size_t RED = (size_t)8 * LIMBS * MB * 4096;  // the 8 waves' partial sums; before the loop: t vectors and the core matrix
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     int* red = reinterpret_cast<int*>(smem);               // [wave][limb][row block][q][lane]
@@ -1367,7 +1367,12 @@ __global__ __launch_bounds__(NT, MB == 1 ? 4 : 1) void gemm_i8_stream_kernel(str
                 for (int l = 0; l < LIMBS; ++l)
 #pragma unroll
                     for (int mb = 0; mb < MB; ++mb)
-                        acc[l][mb] = __builtin_amdgcn_mfma_i32_32x32x32_i8((i32x4)xr[s][l][mb], (i32x4)wr[s], acc[l][mb], 0, 0, 0);
+                        acc[l][mb] = __builtin_amdgcn_mfma_i32_32x32x32_i8((i32x4)xr[s % DX][l][mb], (i32x4)wr[s], acc[l][mb], 0, 0, 0);
+            }
+            if constexpr (DEEP) {
+                __builtin_amdgcn_sched_barrier(0);
+                if (s + DX < NW) issue_x(j0 + s + DX, s % DX);
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -2337,7 +2342,7 @@ hipError_t launch_gemm(hipStream_t st, stream_args& a, int32_t* acc_out) {
     return hipGetLastError();
 }
 
-template <int MB, int LIMBS, bool YBF16, bool Q4 = false, bool FEW = false>
+template <int MB, int LIMBS, bool YBF16, bool Q4, bool FEW, bool DEEP>
 hipError_t launch_gemm_stream(hipStream_t st, stream_args& a) {
     int total = 0;
     for (int g = 0; g < a.n_items; ++g) {
@@ -2349,7 +2354,7 @@ hipError_t launch_gemm_stream(hipStream_t st, stream_args& a) {
     static_assert(smem <= 160 * 1024 && !(Q4 && 2 * smem > 160 * 1024), "does not fit the LDS of a CU");
     void (*kern)(stream_args);
     if constexpr (Q4) kern = gemm_q4_stream_kernel<FEW, YBF16>;
-    else kern = gemm_i8_stream_kernel<MB, LIMBS, YBF16, FEW>;
+    else kern = gemm_i8_stream_kernel<MB, LIMBS, YBF16, FEW, DEEP>;
     static bool attr_done = false;   // one flag per instantiation
     if (!attr_done && smem > 48 * 1024) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
@@ -2381,10 +2386,30 @@ bool takes_stream_kernel(const stream_args& a) {
         if (a.it[g].R > (a.it[g].quant == ESSA_QUANT_INT8_PERCH ? STREAM_MAX_ROWS : q4_stream_max_rows(a.it[g]))) return false;
     return a.n_items > 0;
 }
-int stream_row_blocks(const stream_args& a) {
+int stream_rows(const stream_args& a) {
     int r = 0;
     for (int g = 0; g < a.n_items; ++g) r = std::max(r, a.it[g].R);
-    return r > 32 ? 2 : 1;
+    return r;
+}
+// int8 weights, whether a wave asks for 16 chunks at a time: it has to have that many (a bunch of 16 that is not nearly full is loads for
+// nothing), and there must be no second workgroup on the CU to do the waiting.  us a layer, few chunks / 16 (weights from HBM; 112, 128 and 96
+// blocks of 32 channels are one projection alone):
+//   one row block   3584 wide, 256 blocks 16.1 / 16.0 at 17 rows, 17.4 / 16.8 at 32, 112 blocks 14.2 / 13.4; 8192 wide, 128 blocks 24.2 / 22.3
+//                   more blocks than CUs: 4096 wide, 320 blocks 23.5 / 24.9; 8192 wide, 576 blocks 56 / 66
+//                   up to 16 rows: 3584 wide 14.6 / 14.9; one limb: 3584 wide, 32 rows 15.1 / 15.2
+//   two row blocks  (one workgroup a CU either way) 3584 wide 19.0 / 19.5 at 33 rows, 20.1 / 20.6 at 48, 21.3 / 20.9 at 64; 4096 wide 33.0 / 31.3 at 48,
+//                   35.1 / 32.5 at 64; two bunches and many blocks: 8192 wide, 128 blocks 31.2 / 27.7, 248 blocks 32.7 / 32.8, 576 blocks 80.6 / 86.6
+//   not full        5120 wide, 96 blocks 17.4 / 18.5 and 384 blocks 27.7 / 33.8 at 32 rows; 2048 wide 12.7 / 13.6; 1024 wide 10.6 / 12.2
+bool stream_deep(const stream_args& a) {
+    const int rows = stream_rows(a);
+    int blocks = 0, bunches = 1;
+    for (int g = 0; g < a.n_items; ++g) {
+        const int chunks = a.it[g].d_in_pad / 256;           // of a wave
+        if (chunks % 16 != 0 && chunks % 16 < 14) return false;
+        blocks += a.it[g].n_blocks;
+        bunches = std::max(bunches, (chunks + 15) / 16);
+    }
+    return rows <= 32 ? rows > 16 && a.limbs == 2 && blocks <= 256 : rows > 40 && (bunches == 1 || blocks <= 128);
 }
 
 template <int LIMBS, bool YBF16, bool Q4>
@@ -2494,19 +2519,24 @@ hipError_t forward_stream(hipStream_t st, const fwd_item* items, int n_items, in
     const int q4_rows = items[0].quant == ESSA_QUANT_INT4_G128 ? pick_q4_wide(a) : 0;   // all items of a call share the weight format
     if (to_stream) {
         const bool yb = y_dtype == ESSA_BF16;
-        bool few = true;                                   // 16 rows at most: half of a row operand of 32 would be padding
-        for (int g = 0; g < n_items; ++g) few = few && a.it[g].R <= 16;
-        if (items[0].quant == ESSA_QUANT_INT4_G128) {
-            if (few) e = yb ? launch_gemm_stream<1, 2, true, true, true>(st, a) : launch_gemm_stream<1, 2, false, true, true>(st, a);
-            else e = yb ? launch_gemm_stream<1, 2, true, true>(st, a) : launch_gemm_stream<1, 2, false, true>(st, a);
-        } else if (stream_row_blocks(a) == 2) {
-            if (a.limbs == 2) e = yb ? launch_gemm_stream<2, 2, true>(st, a) : launch_gemm_stream<2, 2, false>(st, a);
-            else e = yb ? launch_gemm_stream<2, 1, true>(st, a) : launch_gemm_stream<2, 1, false>(st, a);
-        } else if (few) {
-            if (a.limbs == 2) e = yb ? launch_gemm_stream<1, 2, true, false, true>(st, a) : launch_gemm_stream<1, 2, false, false, true>(st, a);
-            else e = yb ? launch_gemm_stream<1, 1, true, false, true>(st, a) : launch_gemm_stream<1, 1, false, false, true>(st, a);
-        } else if (a.limbs == 2) e = yb ? launch_gemm_stream<1, 2, true>(st, a) : launch_gemm_stream<1, 2, false>(st, a);
-        else e = yb ? launch_gemm_stream<1, 1, true>(st, a) : launch_gemm_stream<1, 1, false>(st, a);
+        const bool few = stream_rows(a) <= 16, deep = stream_deep(a);   // 16 rows at most: half of a row operand of 32 would be padding
+        constexpr std::integral_constant<int, 1> one;
+        constexpr std::integral_constant<int, 2> two;
+        constexpr std::true_type yes;
+        constexpr std::false_type no;
+        const auto launch = [&](auto mb, auto limbs, auto q4, auto is_few, auto is_deep) {
+            return yb ? launch_gemm_stream<mb, limbs, true, q4, is_few, is_deep>(st, a) : launch_gemm_stream<mb, limbs, false, q4, is_few, is_deep>(st, a);
+        };
+        const auto int8 = [&](auto limbs) {
+            if (few) return launch(one, limbs, no, yes, no);
+            if (stream_rows(a) > 32) return deep ? launch(two, limbs, no, no, yes) : launch(two, limbs, no, no, no);
+            if constexpr (limbs == 2) {
+                if (deep) return launch(one, limbs, no, no, yes);
+            }
+            return launch(one, limbs, no, no, no);
+        };
+        if (items[0].quant == ESSA_QUANT_INT4_G128) e = few ? launch(one, two, yes, yes, no) : launch(one, two, yes, no, no);
+        else e = a.limbs == 2 ? int8(two) : int8(one);
         tl_ev_start = tl_ev_stop = nullptr;
         if (e != hipSuccess) return e;
         // the reward partials (one per 128 channels and row) span four of this kernel's workgroups: a pass of their own
