@@ -903,30 +903,42 @@ hipError_t launch_q4(hipStream_t st, q4_args& a) {
     return hipGetLastError();
 }
 
-// Rows of its tile, by the same kind of formula as for int8 weights below, fitted to 60 groups and single projections of 512 to
-// 8192 columns with every tile forced (rms 3 to 5 %; 1 % on average from the fastest tile, 10 % at worst):
-//   us = call + rounds * round + groups * (full rounds * hi + last round's lo .. hi)
+// What a group takes on one kind of tile.  Tiles go to the 256 CUs in rounds (two at a time on a CU where slots is 512): what does not depend on K,
+// per call and per round, plus (K steps) x (time of a step) for every full round and the last one, which runs faster the
+// emptier it is (one CU in two or fewer: no faster than that; the clock falls as the chip fills), plus shares of the weights' way from HBM and of
+// the outputs' way there:
+//   us = call + rounds * round + steps * (full rounds * hi + last round's lo .. hi) + per_wmb * (MB of weights) + per_ymb * (MB of outputs)
+struct tile_cost { int rows, channels, slots; double call, round, lo, mid, hi, per_wmb, per_ymb; };
+template <class ITEM>
+long long count_tiles(const tile_cost& c, const ITEM* items, int n_items) {
+    long long t = 0;
+    for (int g = 0; g < n_items; ++g) t += (long long)((items[g].R + c.rows - 1) / c.rows) * ((items[g].n_blocks * 32 + c.channels - 1) / c.channels);
+    return t;
+}
+double tile_us(const tile_cost& c, long long tiles, int steps, double w_mb, double y_mb) {
+    const long long full = tiles / c.slots, rest = tiles % c.slots;
+    const double over = std::max(0.0, 2.0 * rest / c.slots - 1.0);   // how far the last round is beyond half full
+    double last = 0;
+    // two workgroups a CU: up to half full a CU has one, beyond that some have two
+    if (rest) last = c.slots == 512 ? (over == 0 ? c.lo : c.mid + (c.hi - c.mid) * over) : c.lo + (c.hi - c.lo) * over * over;
+    return c.call + c.round * (full + (rest ? 1 : 0)) + steps * (full * c.hi + last) + c.per_wmb * w_mb + c.per_ymb * y_mb;
+}
+
+// Rows of a 4-bit tile: the formula fitted to 60 groups and single projections of 512 to
+// 8192 columns with every tile forced (rms 3 to 5 %; 1 % on average from the fastest tile, 10 % at worst).
 // The tallest tile unpacks least per product, and a last round that is not full costs what it costs whatever its tiles.  Two deep
 // stages are for one workgroup a CU, which has nobody to fill its waits.  q, k, v, o, us by rows of the tile (int8-limb tiles):
 //   8192 columns  320 rows  126 at 64 (133), 512 rows  150 at 80, 158 at 96, 191 at 64 (181), 1187 rows 305 at 96, 326 at 80 (404)
 //   3584 columns  640 rows  50 at 80, 53 at 96, 61 at 64 (71), 6000 rows 298 at 96, 318 at 80, 340 at 64 (456)
 enum q4_tile { Q4_48_DEEP, Q4_64_DEEP, Q4_64, Q4_80, Q4_96 };
-struct q4_cost { int rows, slots; double call, round, lo, mid, hi; };
-constexpr q4_cost Q4_COST[] = {{48, 256, 12.9, 3.8, 0.854, 0, 0.863}, {64, 256, 12.0, 5.2, 0.977, 0, 1.002}, {64, 512, 10.9, 5.4, 1.076, 1.638, 1.638},
-                               {80, 512, 11.5, 5.9, 1.135, 1.899, 1.899}, {96, 512, 9.4, 7.9, 1.257, 2.068, 2.233}};
+constexpr tile_cost Q4_COST[] = {{48, 256, 256, 12.9, 3.8, 0.854, 0, 0.863, 0, 0}, {64, 256, 256, 12.0, 5.2, 0.977, 0, 1.002, 0, 0}, {64, 256, 512, 10.9, 5.4, 1.076, 1.638, 1.638, 0, 0},
+                                 {80, 256, 512, 11.5, 5.9, 1.135, 1.899, 1.899, 0, 0}, {96, 256, 512, 9.4, 7.9, 1.257, 2.068, 2.233, 0, 0}};
 q4_tile pick_q4_tile(const q4_args& a) {
     int best = 0, ng = 1;
     double best_us = 0;
     for (int g = 0; g < a.n_items; ++g) ng = std::max(ng, a.it[g].d_in / 128);
     for (int i = 0; i < (int)(sizeof(Q4_COST) / sizeof(Q4_COST[0])); ++i) {
-        const q4_cost& c = Q4_COST[i];
-        long long tiles = 0;
-        for (int g = 0; g < a.n_items; ++g) tiles += (long long)((a.it[g].R + c.rows - 1) / c.rows) * ((a.it[g].n_blocks + 7) / 8);
-        const long long full = tiles / c.slots, rest = tiles % c.slots;
-        const double over = std::max(0.0, 2.0 * rest / c.slots - 1.0);
-        double last = 0;
-        if (rest) last = c.slots == 512 ? (over == 0 ? c.lo : c.mid + (c.hi - c.mid) * over) : c.lo + (c.hi - c.lo) * over * over;
-        const double us = c.call + c.round * (full + (rest ? 1 : 0)) + ng * (full * c.hi + last);
+        const double us = tile_us(Q4_COST[i], count_tiles(Q4_COST[i], a.it, a.n_items), ng, 0, 0);
         if (i == 0 || us < best_us) {
             best = i;
             best_us = us;
@@ -935,51 +947,47 @@ q4_tile pick_q4_tile(const q4_args& a) {
     return (q4_tile)best;
 }
 
-// Which tile takes a group.  Tiles go to the 256 CUs in rounds, so the time is what does not depend on K, per call and per round, plus
-// (K steps) x (time of a step) for every full round and the last one, which runs faster the emptier it is (one CU in two or
-// fewer: no faster than that; the clock falls as the chip fills), plus a share of the weights' way from HBM:
-//   us = call + rounds * round + steps * (full rounds * hi + last round's lo .. hi) + per_mb * (MB of bf16 weights)
-// fitted to whole calls, each with every tile forced: 57 groups and single projections of 512 to 8192 columns, 400 to 16000 rows, weights
-// from HBM.  The tile it names is within 0.2 % of the fastest on average there and 5.6 % at worst.  Two rounds of a low tile often beat
+// Which tile takes a group of int8 projections.  Fitted to whole calls, each with every tile forced: 284 groups and single projections of 256 to
+// 14336 columns, k and v from an eighth of q to as wide, 1 to 24000 rows, bf16 and fp32 outputs, weights from HBM.  The tile it names is within 0.3 %
+// of the fastest on average there, 10 % at worst.  Another tile than 256 x 256 has to be 2 % ahead: it is what runs best for long, and the
+// formula is a few per cent off.  Two rounds of a low tile often beat
 // one and a bit of the high one, or a round that is two thirds full (q, k, v, o of 3584 columns, k and v with 512 channels, us):
 //   rows       256 x 256   224 x 256   192 x 256   160 x 256   256 x 128   160 x 128   128 x 128, two a CU   128 x 128, five stages
-//    640          78          71          64          58          54          45            53                   64
-//   1187          78          74          71          68          98          76            86                   91
-//   1536          82          80          77         114         100         104            90                   95
-//   2560         170         151         140         133         155         150           145                  159
-//   4096         182         222         202         231         207         238           211                  240
+//     300            81          77          75          67          56          51          57                  42
+//     700            81          77          74          64          58          78          65                  73
+//    1187            84          83          79          76         106          86         100                 102
+//    1536            91          88          85         121         111         116         108                 116
+//    2560           172         159         151         144         163         171         167                 183
+//    4096           193         236         219         241         222         262         229                 268
+//   20000           987        1003        1023        1049        1124        1239        1141                1334
+// and with few rows one round of the lowest tiles (8192 columns, 8 rows: 64 x 128 67 us, 128 x 128 74; 3584 columns, 200 rows 35 and 45).
 // The 64-row tiles form u themselves (the launch of rank_finish and its wait that they save are 3 us); 64 x 64 is half of a reward
 // partial wide, so it is for calls without reward vectors (3584 -> 512 at 512 rows 21 us, 64 x 128 25.6).  Both are for calls that they finish
 // in one round; a CU's load path takes 24 KB of operands in 0.3 us, and weights straight into registers took as long.
 enum bf16_tile { TILE_256x256, TILE_224x256, TILE_192x256, TILE_160x256, TILE_256x128, TILE_160x128, TILE_128x128, TILE_128x128_DEEP, TILE_64x128, TILE_64x64 };
-struct tile_cost { int rows, channels, slots; double call, round, lo, mid, hi, per_mb; };   // slots: tiles of a round
 constexpr tile_cost TILE_COST[] = {
-    {256, 256, 256, 6.3, 16.0, 0.993, 0, 1.325, 0.048}, {224, 256, 256, 7.3, 12.8, 0.924, 0, 1.219, 0.042}, {192, 256, 256, 5.5, 12.8, 0.811, 0, 1.025, 0.059},
-    {160, 256, 256, 7.4, 10.5, 0.737, 0, 0.911, 0.022}, {256, 128, 256, 7.2, 9.6, 0.632, 0, 0.750, 0.023},  {160, 128, 256, 9.9, 5.6, 0.438, 0, 0.536, 0.024},
-    {128, 128, 512, 7.1, 7.5, 0.412, 0.62, 0.796, 0.101}, {128, 128, 256, 8.3, 5.8, 0.382, 0, 0.456, 0.039}, {64, 128, 256, 9.0, 4.7, 0.137, 0, 0.299, 0.191},
-    {64, 64, 256, 7.0, 0.0, 0.240, 0, 0.320, 0.0}};
-bf16_tile pick_tile(const prefill_item* items, int n_items) {
+    {256, 256, 256, 9.2, 8.4, 0.903, 0, 1.016, 0.071, 0.58}, {224, 256, 256, 10.6, 6.6, 0.834, 0, 0.918, 0.080, 0.58},
+    {192, 256, 256, 9.5, 6.4, 0.775, 0, 0.805, 0.093, 0.57}, {160, 256, 256, 10.2, 5.4, 0.661, 0, 0.721, 0.074, 0.58},
+    {256, 128, 256, 9.8, 5.0, 0.560, 0, 0.621, 0.080, 0.57}, {160, 128, 256, 10.3, 3.4, 0.420, 0, 0.461, 0.078, 0.54},
+    {128, 128, 512, 10.0, 1.8, 0.459, 0.614, 0.690, 0.125, 0.61}, {128, 128, 256, 10.2, 2.7, 0.368, 0, 0.388, 0.095, 0.64},
+    {64, 128, 256, 5.7, 4.9, 0.285, 0, 0.274, 0.120, 0.10}, {64, 64, 256, 5.9, 4.1, 0.209, 0, 0.253, 0.079, 0.03}};
+bf16_tile pick_tile(const prefill_item* items, int n_items, int y_size) {
     int nk = 1;
-    double mb = 0;
+    double w_mb = 0, y_mb = 0;
     bool rewards = false;
     for (int g = 0; g < n_items; ++g) {
         nk = std::max(nk, (items[g].d_in + 63) / 64);
-        mb += 2e-6 * items[g].d_in * items[g].d_out;
+        w_mb += 2e-6 * items[g].d_in * items[g].d_out;
+        y_mb += 1e-6 * y_size * items[g].R * items[g].d_out;
         rewards = rewards || items[g].rv;
     }
     int best = 0;
     double best_us = 0;
     for (int i = 0; i < (int)(sizeof(TILE_COST) / sizeof(TILE_COST[0])); ++i) {
         const tile_cost& c = TILE_COST[i];
-        long long tiles = 0;
-        for (int g = 0; g < n_items; ++g) tiles += (long long)((items[g].R + c.rows - 1) / c.rows) * ((items[g].n_blocks * 32 + c.channels - 1) / c.channels);
+        const long long tiles = count_tiles(c, items, n_items);
         if ((i >= TILE_64x128 && tiles > c.slots) || (i == TILE_64x64 && rewards)) continue;
-        const long long full = tiles / c.slots, rest = tiles % c.slots;
-        const double over = std::max(0.0, 2.0 * rest / c.slots - 1.0);   // how far the last round is beyond half full
-        double last = 0;
-        // two workgroups a CU: up to half full a CU has one, beyond that some have two
-        if (rest) last = i == TILE_128x128 ? (over == 0 ? c.lo : c.mid + (c.hi - c.mid) * over) : c.lo + (c.hi - c.lo) * over * over;
-        const double us = c.call + c.round * (full + (rest ? 1 : 0)) + nk * (full * c.hi + last) + c.per_mb * mb;
+        const double us = tile_us(c, tiles, nk, w_mb, y_mb) * (i == TILE_256x256 ? 0.98 : 1.0);
         if (i == 0 || us < best_us) {
             best = i;
             best_us = us;
@@ -1114,7 +1122,7 @@ hipError_t forward_prefill(hipStream_t st, const fwd_item* items, int n_items, i
     a.n_items = n_items;
     a.flags = flags;
     a.u_scale = 1.f;
-    const bf16_tile tile = pick_tile(a.it, n_items);
+    const bf16_tile tile = pick_tile(a.it, n_items, y_dtype == ESSA_BF16 ? 2 : 4);
     if (flags & ESSA_BASE_ONLY) {
         int maxR = 0;
         for (int g = 0; g < n_items; ++g) maxR = std::max(maxR, a.it[g].R);
