@@ -318,20 +318,18 @@ constexpr size_t bf16_smem_bytes(bool ybf16) {
     return stages > ctile ? stages : ctile;
 }
 
-// An output tile on its way from LDS to memory: BM rows of BN channels from o0 on, of which this half's lie in LDS, NC / HALVES
-// 16-channel blocks of every wave column's NC side by side; block k of a half is the wave's block half_block(half, k).
-template <int HALVES> __device__ __forceinline__ constexpr int half_block(int half, int k) { return HALVES == 1 ? k : 4 * (k >> 1) + 2 * half + (k & 1); }
-
-template <int BM, int BN, int NC, int HALVES, bool YBF16, class ITEM>
+// An output tile on its way from LDS to memory: BM rows of BN channels from o0 on.  In two halves: of every 64 channels the first 32, then the others,
+// whatever the tile, so that a reward partial is added up in one order.
+template <int BM, int BN, int HALVES, bool YBF16, class ITEM>
 __device__ __forceinline__ void store_rows(const unsigned char* smem, const ITEM& it, int m0, int o0, int half) {
-    constexpr int ESZ = YBF16 ? 2 : 4, EPV = 16 / ESZ, CW = BN / HALVES, CROW = CW * ESZ + 16, PPR = CW / EPV, NH = NC / HALVES;
+    constexpr int ESZ = YBF16 ? 2 : 4, EPV = 16 / ESZ, CW = BN / HALVES, CROW = CW * ESZ + 16, PPR = CW / EPV;
     const int tid = threadIdx.x, R = it.R, dout = it.d_out;
     const bool with_reward = it.rv != nullptr;
     const bool vec_ok = (dout % EPV == 0) && ((reinterpret_cast<uintptr_t>(it.Y) & 15) == 0);
     const gptr<unsigned char> Yb = as_global_w(reinterpret_cast<unsigned char*>(it.Y));
     // full rows, 16 bytes per thread; with a reward vector the row's share over each 128-channel block goes to rowpart
     const int piece = tid % PPR, c0 = piece * EPV;
-    const int o = o0 + (c0 / (NH * 16)) * (NC * 16) + half_block<HALVES>(half, c0 % (NH * 16) / 16) * 16 + c0 % 16;
+    const int o = o0 + (HALVES == 1 ? c0 : c0 / 32 * 64 + 32 * half + c0 % 32);
     float rvp[EPV];
 #pragma unroll
     for (int e = 0; e < EPV; ++e) rvp[e] = (with_reward && o + e < dout) ? as_global(it.rv)[o + e] : 0.f;
@@ -377,6 +375,9 @@ __device__ __forceinline__ void store_rows(const unsigned char* smem, const ITEM
 __device__ __forceinline__ void mfma_pinned(const bf16x8& A, const bf16x8& B, f32x4& acc) {
     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(A), "v"(B));
 }
+
+// block k of a half is the wave's 16-channel block half_block(half, k)
+template <int HALVES> __device__ __forceinline__ constexpr int half_block(int half, int k) { return HALVES == 1 ? k : 4 * (k >> 1) + 2 * half + (k & 1); }
 
 template <int NR, int NB, int XS, int WS, bool YBF16>
 __global__ __launch_bounds__(256, (bf16_smem_bytes<NR, NB, XS, WS>(true) > 80 * 1024 ? 1 : 2)) void gemm_bf16_kernel(prefill_args a) {
@@ -604,7 +605,7 @@ __global__ __launch_bounds__(256, (bf16_smem_bytes<NR, NB, XS, WS>(true) > 80 * 
         if (rp == 16) finish(std::integral_constant<int, 1>{}, half_c);
         else finish(std::integral_constant<int, 2>{}, half_c);
         __syncthreads();
-        store_rows<BM, BN, NC, HALVES, YBF16>(smem, it, m0, nb0 * 32, half);
+        store_rows<BM, BN, HALVES, YBF16>(smem, it, m0, nb0 * 32, half);
         if constexpr (half + 1 < HALVES) __syncthreads();
     });
 }
@@ -642,7 +643,7 @@ hipError_t launch_bf16(hipStream_t st, prefill_args& a) {
 //
 // What bounds it is vector-instruction issue next to the MFMAs: per 16 x 16 x 32 product one FMA, and 7 / NR instructions of
 // unpacking, since a wave of 16 NR rows x 64 channels unpacks a fragment once for NR products (the int8-limb tile needs 16 per pair
-// of its MFMAs).  256 threads = 4 waves side by side, 16 NR rows x 256 channels, so no
+// of its MFMAs).  256 threads = 4 waves side by side, 16 NR rows x 256 channels (128 for calls of few tiles), so no
 // weight is unpacked twice in a workgroup; two workgroups a CU, whose unpacking, MFMAs and waits overlap.
 //
 // A step is one group.  Activations (D stages: rows of 128 bytes per half group, 16-byte parts swizzled as above), weights (D - 1,
@@ -666,16 +667,17 @@ struct q4_args {
     int n_items;
 };
 
-template <int NR, int D>
+template <int NR, int NC, int D>
 constexpr size_t q4_smem_bytes() {
-    constexpr size_t BM = 16 * NR, stages = D * BM * 256 + (D - 1) * 16384 + D * 1024, ctile = BM * (128 * 4 + 16);
+    constexpr size_t BM = 16 * NR, stages = D * BM * 256 + (D - 1) * NC * 4096 + D * 1024, ctile = BM * (NC * 128 + 16);
     return stages > ctile ? stages : ctile;
 }
 
-template <int NR, int D, bool YBF16>
+template <int NR, int NC, int D, bool YBF16>
 __global__ __launch_bounds__(256, 2) void gemm_q4_exact_kernel(q4_args a) {
-    constexpr int BM = 16 * NR, NC = 4, PATCH = 8, LOADS = NR + NC + 1;   // LOADS: of a wave and step
-    constexpr uint32_t XST = BM * 256, XH = BM * 128, W0 = D * XST, S0 = W0 + (D - 1) * 16384;
+    constexpr int BM = 16 * NR, BN = 64 * NC, NBT = BN / 32, PATCH = 8, LOADS = NR + NC + 1;   // LOADS: of a wave and step
+    constexpr uint32_t XST = BM * 256, XH = BM * 128, WST = NC * 4096, W0 = D * XST, S0 = W0 + (D - 1) * WST;
+    static_assert(NR >= 2 && (NC == 2 || NC == 4) && (NR > 3 || NR + 1 <= 4 * (NR - 1)), "every load of a step has its place in row blocks 1 and 2");
     static_assert((D - 2) * LOADS < 64, "the load counter has six bits");
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_byte*)smem;
@@ -689,7 +691,7 @@ __global__ __launch_bounds__(256, 2) void gemm_q4_exact_kernel(q4_args a) {
     for (int i = 1; i < ESSA_MAX_GROUP; ++i) gi += (i < a.n_items && b >= a.tile_start[i]) ? 1 : 0;
     const q4_item it = fetch_item(a.it[gi]);
     const int R = it.R, dout = it.d_out, din = it.d_in, rp = it.rp, ng = din / 128, nb16 = it.n_blocks * 2;
-    const int tiles_m = (R + BM - 1) / BM, tiles_n = (it.n_blocks + 7) / 8;
+    const int tiles_m = (R + BM - 1) / BM, tiles_n = (it.n_blocks + NBT - 1) / NBT;
     int tm, tn;
     {   // patches of 8 row tiles x all column tiles, rows fastest: the 64 tiles an XCD runs at a time are about 8 x 8
         const int tile = b - a.tile_start[gi], per = PATCH * tiles_n, grp = tile / per, rem = tile % per;
@@ -697,7 +699,7 @@ __global__ __launch_bounds__(256, 2) void gemm_q4_exact_kernel(q4_args a) {
         tn = rem / rows;
         tm = PATCH * grp + rem % rows;
     }
-    const int m0 = tm * BM, nb0 = tn * 8;
+    const int m0 = tm * BM, nb0 = tn * NBT;
 
     const i32x4 xres = buffer_words(it.X + (size_t)m0 * din), wres = buffer_words(it.Wn), sres = buffer_words(it.St);
     // load q = wave NR + e of the 4 NR of a step: half group q / (2 NR), 8 rows; its swizzle hangs on the parity of q
@@ -706,7 +708,7 @@ __global__ __launch_bounds__(256, 2) void gemm_q4_exact_kernel(q4_args a) {
 #pragma unroll
     for (int e = 0; e < 2; ++e) xpart[e] = ((lane & 7) ^ ((4 * (wave * NR + e) + (lane >> 4)) & 7)) * 16;
     const uint32_t lane16 = lane * 16;
-    const uint32_t soff = (uint32_t)min(nb0 * 32 + wave * 64 + lane, it.n_blocks * 32 - 1) * 4u, sstep = (uint32_t)it.n_blocks * 128u;
+    const uint32_t soff = (uint32_t)min(nb0 * 32 + wave * (16 * NC) + lane, it.n_blocks * 32 - 1) * 4u, sstep = (uint32_t)it.n_blocks * 128u;
     uint32_t woff[NC];
 #pragma unroll
     for (int n = 0; n < NC; ++n) woff[n] = (uint32_t)min(nb0 * 2 + wave * NC + n, nb16 - 1) * 1024u;
@@ -723,7 +725,7 @@ __global__ __launch_bounds__(256, 2) void gemm_q4_exact_kernel(q4_args a) {
 #pragma unroll
         for (int m = 0; m < NR; ++m) tot[n][m] = (f32x4){0.f, 0.f, 0.f, 0.f};
     {
-        const int ch0 = nb0 * 32 + wave * 64 + l16, nc = it.Gn / 32;
+        const int ch0 = nb0 * 32 + wave * (16 * NC) + l16, nc = it.Gn / 32;
         bf16x8 z[2][NC], xs[2][NR];                        // 32 groups: head, and the third and then the second part in one place
         const rsrc_t zres = make_rsrc(it.SZn), sumres = make_rsrc(it.XS16 + (size_t)(m0 / 16) * nc * 1536);
         uint32_t zoff[NC], sumoff[NR];                     // operand tiles of 16 channels or rows and 32 groups: a kilobyte per part
@@ -766,7 +768,7 @@ __global__ __launch_bounds__(256, 2) void gemm_q4_exact_kernel(q4_args a) {
         static_for<D - 1>([&](auto tc) {
             constexpr int t = tc;
 #pragma unroll
-            for (int n = 0; n < NC; ++n) load_w(n, min(t, ng - 1), t * 16384);
+            for (int n = 0; n < NC; ++n) load_w(n, min(t, ng - 1), t * WST);
 #pragma unroll
             for (int e = 0; e < NR; ++e) load_x(e, min(t, ng - 1), t * XST);
             load_s(min(t, ng - 1), t * 1024);
@@ -840,7 +842,7 @@ __global__ __launch_bounds__(256, 2) void gemm_q4_exact_kernel(q4_args a) {
                     if constexpr (m > 0) fold(m - 1, at);
                     // the codes are all in registers by row block 1: their place is free
                     if constexpr (m == 1 && at % 4 == 1) load_w(at / 4, gn, w_cur);
-                    if constexpr (m >= 1 && m <= 2 && at % 4 == 3) {
+                    if constexpr (m >= 1 && m <= 2 && n == NC - 1) {
                         constexpr int e = (m - 1) * 4 + k;
                         if constexpr (e < NR) load_x(e, gn, far);
                         if constexpr (e == NR) load_s(gn, s_far);
@@ -851,47 +853,47 @@ __global__ __launch_bounds__(256, 2) void gemm_q4_exact_kernel(q4_args a) {
             });
         });
 #pragma unroll
-        for (int i = 0; i < 16; ++i) fold(NR - 1, i);
+        for (int i = 0; i < 4 * NC; ++i) fold(NR - 1, i);
         far = cur;                                         // its last reader was this step
         cur = cur == (D - 1) * XST ? 0 : cur + XST;
         s_far = s_cur;
         s_cur = s_cur == (D - 1) * 1024 ? 0 : s_cur + 1024;
-        w_cur = w_cur == (D - 2) * 16384 ? 0 : w_cur + 16384;
+        w_cur = w_cur == (D - 2) * WST ? 0 : w_cur + WST;
     }
     wait_loads_and_meet<0>();                              // the stages become the output tile
-    constexpr int HALVES = YBF16 ? 1 : 2, ESZ = YBF16 ? 2 : 4, CROW = 256 / HALVES * ESZ + 16, NH = NC / HALVES;
+    constexpr int HALVES = YBF16 ? 1 : 2, ESZ = YBF16 ? 2 : 4, CROW = BN / HALVES * ESZ + 16;
     static_for<HALVES>([&](auto half_c) {
         constexpr int half = half_c;
 #pragma unroll
-        for (int k = 0; k < NH; ++k)
+        for (int n = 0; n < NC; ++n)
 #pragma unroll
             for (int m = 0; m < NR; ++m) {
-                const f32x4 v = tot[half_block<HALVES>(half, k)][m] * 0x1p12f;
-                unsigned char* dst = smem + (size_t)(m * 16 + l16) * CROW + (size_t)((wave * NH + k) * 16 + 4 * kg) * ESZ;
+                const f32x4 v = tot[n][m] * 0x1p12f;
+                const int c = (wave * NC + n) * 16 + 4 * kg;   // of the tile; of the half it lies in: every second 32 left out
                 if (YBF16) {
                     typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
-                    *reinterpret_cast<bf16x4*>(dst) = __builtin_convertvector(v, bf16x4);
-                } else {
-                    *reinterpret_cast<f32x4*>(dst) = v;
+                    *reinterpret_cast<bf16x4*>(smem + (size_t)(m * 16 + l16) * CROW + c * ESZ) = __builtin_convertvector(v, bf16x4);
+                } else if ((c >> 5 & 1) == half) {
+                    *reinterpret_cast<f32x4*>(smem + (size_t)(m * 16 + l16) * CROW + (c / 64 * 32 + c % 32) * ESZ) = v;
                 }
             }
         __syncthreads();
-        store_rows<BM, 256, NC, HALVES, YBF16>(smem, it, m0, nb0 * 32, half);
+        store_rows<BM, BN, HALVES, YBF16>(smem, it, m0, nb0 * 32, half);
         if constexpr (half + 1 < HALVES) __syncthreads();
     });
 }
 
-template <int NR, int D, bool YBF16>
+template <int NR, int NC, int D, bool YBF16>
 hipError_t launch_q4(hipStream_t st, q4_args& a) {
     int total = 0;
     for (int g = 0; g < a.n_items; ++g) {
         a.tile_start[g] = total;
-        total += ((a.it[g].R + 16 * NR - 1) / (16 * NR)) * ((a.it[g].n_blocks + 7) / 8);
+        total += ((a.it[g].R + 16 * NR - 1) / (16 * NR)) * ((a.it[g].n_blocks + 2 * NC - 1) / (2 * NC));
     }
     for (int g = a.n_items; g <= ESSA_MAX_GROUP; ++g) a.tile_start[g] = total;
-    constexpr size_t smem = q4_smem_bytes<NR, D>();
+    constexpr size_t smem = q4_smem_bytes<NR, NC, D>();
     static_assert(smem <= 160 * 1024, "tile does not fit the LDS of a CU");
-    auto kern = gemm_q4_exact_kernel<NR, D, YBF16>;
+    auto kern = gemm_q4_exact_kernel<NR, NC, D, YBF16>;
     static bool attr_done = false;   // one flag per instantiation
     if (!attr_done) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
@@ -924,21 +926,31 @@ double tile_us(const tile_cost& c, long long tiles, int steps, double w_mb, doub
     return c.call + c.round * (full + (rest ? 1 : 0)) + steps * (full * c.hi + last) + c.per_wmb * w_mb + c.per_ymb * y_mb;
 }
 
-// Rows of a 4-bit tile: the formula fitted to 60 groups and single projections of 512 to
-// 8192 columns with every tile forced (rms 3 to 5 %; 1 % on average from the fastest tile, 10 % at worst).
-// The tallest tile unpacks least per product, and a last round that is not full costs what it costs whatever its tiles.  Two deep
-// stages are for one workgroup a CU, which has nobody to fill its waits.  q, k, v, o, us by rows of the tile (int8-limb tiles):
-//   8192 columns  320 rows  126 at 64 (133), 512 rows  150 at 80, 158 at 96, 191 at 64 (181), 1187 rows 305 at 96, 326 at 80 (404)
-//   3584 columns  640 rows  50 at 80, 53 at 96, 61 at 64 (71), 6000 rows 298 at 96, 318 at 80, 340 at 64 (456)
-enum q4_tile { Q4_48_DEEP, Q4_64_DEEP, Q4_64, Q4_80, Q4_96 };
-constexpr tile_cost Q4_COST[] = {{48, 256, 256, 12.9, 3.8, 0.854, 0, 0.863, 0, 0}, {64, 256, 256, 12.0, 5.2, 0.977, 0, 1.002, 0, 0}, {64, 256, 512, 10.9, 5.4, 1.076, 1.638, 1.638, 0, 0},
-                                 {80, 256, 512, 11.5, 5.9, 1.135, 1.899, 1.899, 0, 0}, {96, 256, 512, 9.4, 7.9, 1.257, 2.068, 2.233, 0, 0}};
-q4_tile pick_q4_tile(const q4_args& a) {
+// Which tile takes a group of 4-bit projections: the formula fitted to 329 groups and single projections of 512 to 8192 columns, every tile forced;
+// 0.4 % on average from the fastest tile, 9 % at worst.  The tallest tile unpacks least per product, and a last round that is not full costs what
+// it costs whatever its tiles; 128 channels are for calls of few tiles, a projection alone above all.  All run two to a CU.  us by tile (int8-limb tiles):
+//                               64 x 256   80 x 256   96 x 256   32 x 128   48 x 128   64 x 128
+//   q, k, v, o  8192   512 rows   209        158        167        213        203        178    (188)
+//               8192  1187        347        339        317        482        419        361    (420)
+//               3584   640         62         51         55         67         63         56     (75)
+//               3584  6000        350        329        318        485        436        371    (450)
+//   q alone     8192   257         87         92        101         87         69         77     (81)
+//   k alone     8192   512         87         90         98         50         55         69     (61)
+//               3584  1024         46         49         53         30         32         38     (38)
+enum q4_tile { Q4_64x256, Q4_80x256, Q4_96x256, Q4_32x128, Q4_48x128, Q4_64x128 };
+constexpr tile_cost Q4_COST[] = {{64, 256, 512, 17.2, 1.0, 0.889, 1.403, 1.417, 0.21, 0.52}, {80, 256, 512, 17.7, 1.1, 0.959, 1.614, 1.676, 0.21, 0.46},
+                                 {96, 256, 512, 18.3, 1.4, 1.068, 1.809, 1.929, 0.22, 0.48}, {32, 128, 512, 15.6, 2.3, 0.289, 0.453, 0.544, 0.26, 0.50},
+                                 {48, 128, 512, 16.2, 1.9, 0.357, 0.611, 0.686, 0.24, 0.45}, {64, 128, 512, 17.6, 0.0, 0.539, 0.831, 0.810, 0.16, 0.53}};
+q4_tile pick_q4_tile(const q4_args& a, int y_size) {
     int best = 0, ng = 1;
-    double best_us = 0;
-    for (int g = 0; g < a.n_items; ++g) ng = std::max(ng, a.it[g].d_in / 128);
+    double best_us = 0, w_mb = 0, y_mb = 0;
+    for (int g = 0; g < a.n_items; ++g) {
+        ng = std::max(ng, a.it[g].d_in / 128);
+        w_mb += 0.5e-6 * a.it[g].d_in * a.it[g].d_out;
+        y_mb += 1e-6 * y_size * a.it[g].R * a.it[g].d_out;
+    }
     for (int i = 0; i < (int)(sizeof(Q4_COST) / sizeof(Q4_COST[0])); ++i) {
-        const double us = tile_us(Q4_COST[i], count_tiles(Q4_COST[i], a.it, a.n_items), ng, 0, 0);
+        const double us = tile_us(Q4_COST[i], count_tiles(Q4_COST[i], a.it, a.n_items), ng, w_mb, y_mb);
         if (i == 0 || us < best_us) {
             best = i;
             best_us = us;
@@ -1096,12 +1108,13 @@ hipError_t forward_prefill_q4(hipStream_t st, const fwd_item* items, int n_items
     tl_pre_start = ev_start;
     tl_pre_stop = ev_stop;
     const bool yb = y_dtype == ESSA_BF16;
-    switch (pick_q4_tile(a)) {
-        case Q4_48_DEEP: e = yb ? launch_q4<3, 4, true>(st, a) : launch_q4<3, 4, false>(st, a); break;
-        case Q4_64_DEEP: e = yb ? launch_q4<4, 4, true>(st, a) : launch_q4<4, 4, false>(st, a); break;
-        case Q4_64: e = yb ? launch_q4<4, 2, true>(st, a) : launch_q4<4, 2, false>(st, a); break;
-        case Q4_80: e = yb ? launch_q4<5, 2, true>(st, a) : launch_q4<5, 2, false>(st, a); break;
-        default: e = yb ? launch_q4<6, 2, true>(st, a) : launch_q4<6, 2, false>(st, a); break;
+    switch (pick_q4_tile(a, yb ? 2 : 4)) {
+        case Q4_64x256: e = yb ? launch_q4<4, 4, 2, true>(st, a) : launch_q4<4, 4, 2, false>(st, a); break;
+        case Q4_80x256: e = yb ? launch_q4<5, 4, 2, true>(st, a) : launch_q4<5, 4, 2, false>(st, a); break;
+        case Q4_96x256: e = yb ? launch_q4<6, 4, 2, true>(st, a) : launch_q4<6, 4, 2, false>(st, a); break;
+        case Q4_32x128: e = yb ? launch_q4<2, 2, 5, true>(st, a) : launch_q4<2, 2, 5, false>(st, a); break;
+        case Q4_48x128: e = yb ? launch_q4<3, 2, 3, true>(st, a) : launch_q4<3, 2, 3, false>(st, a); break;
+        default: e = yb ? launch_q4<4, 2, 2, true>(st, a) : launch_q4<4, 2, 2, false>(st, a); break;
     }
     tl_pre_start = tl_pre_stop = nullptr;
     return e;

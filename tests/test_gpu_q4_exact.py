@@ -17,8 +17,8 @@ BF16_RMS, BF16_MAX = 1e-3, 2e-2
 
 
 @pytest.mark.parametrize("d_in,d_out,r,Rs", [
-    (2048, 2100, 24, (1029, 1360, 1805, 2260)),           # tiles of 48 and 64 rows with deep stages, 80, 96; output width not a multiple of 8
-    (1152, 1400, 16, (1100, 2030, 3001, 3400)),           # nine groups in two sixteens: 48, 64, 80, 96 rows
+    (2048, 2100, 24, (750, 1029, 1360, 1805, 2000, 2260)),   # tiles of 32, 48, 48 and 64 x 128, 80 and 96 x 256; output width not a multiple of 8
+    (1152, 1400, 16, (1100, 1110, 2030, 2300, 3001, 3400, 4470)),   # nine groups: 48, 32, 48 and 64 x 128, 80, 96 and 64 x 256
     (4224, 264, 7, (513, 777)),                           # 33 groups: past one window of group sums, the last K part alone in the next
 ])
 def test_q4_exact_tiles(essa, d_in, d_out, r, Rs):
