@@ -821,15 +821,15 @@ static bool takes_exact_product(const essa_k::fwd_item& k) {
     return k.d_out >= 128 && k.R > (k.d_in >= 3072 && k.d_in <= 6144 ? 384 : 511);
 }
 
-// The same for 4-bit weights, again by the item's own rows and columns.  The line suits layers; a projection alone that is just above it
-// takes up to a quarter longer than on the limbs until it has rows enough (us a call, limbs / exact):
-//            q, k, v, o                                q alone                      k alone
-//    640     2303  42 / 25 (80 channels)               2303  22 / 21                2303 20 / 21 (264 channels)
-//   1024     1024  32 / 24, 2048  42 / 30              1024  20 / 23, 2048 25 / 24
-//   2048      512  36 / 32, 1024  53 / 36              1024  29 / 32                2048 28 / 29, 8192 51 / 36
-//   3584      384  51 / 43,  512  52 / 46, 640 71 / 50  512  38 / 43,  768 49 / 43  1024 37 / 40, 2048 43 / 41
-//   5120      192  57 / 53,  384  85 / 64, 512 93 / 84  384  48 / 54,  512 60 / 55  1024 48 / 54, 2000 60 / 56
-//   8192      256 124 / 105, 384 143 / 126, 512 181 / 150  256 60 / 74, 384 89 / 76   512 61 / 73, 2000 80 / 76
+// The same for 4-bit weights, again by the item's own rows and columns: above the line neither a layer nor a projection alone is slower than on
+// the limbs by more than their runs differ (us a call, limbs / exact on the tile that the launcher names):
+//            q, k, v, o                             q alone                              k alone
+//    640     2304  40 / 21 (80 channels)            2304  22 / 17                        2304  20 / 17 (264 channels)
+//   1024     1024  32 / 22, 2000  46 / 29           1024  20 / 18, 2048  24 / 20           1024  18 / 17 (128 channels)
+//   2048      641  39 / 29, 1000  51 / 37            641  25 / 23, 1024  28 / 25            641  22 / 20, 2048  28 / 21
+//   3584      512  53 / 43,  640  71 / 51            512  36 / 33,  768  48 / 38            512  32 / 28, 1024  38 / 28
+//   5120      257  65 / 57,  512  93 / 83            384  44 / 45,  512  58 / 50            257  42 / 37, 1000  50 / 40
+//   8192      257  130 / 117, 512  186 / 156        257  80 / 66,  512  87 / 80            257  61 / 48, 2000  77 / 59
 static bool takes_exact_q4(const essa_k::fwd_item& k) {
     return k.Wn && k.R > (k.d_in > 4096 ? 256 : k.d_in >= 3072 ? 511 : k.d_in >= 2048 ? 640 : k.d_in >= 1024 ? 1023 : 2303);
 }

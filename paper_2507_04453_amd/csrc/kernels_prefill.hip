@@ -7,7 +7,7 @@
 // The projection keeps a bf16 copy of its weights in MFMA-operand tiles for this.
 //
 // Three launches: rank_down (t = V_A^T x, K split over workgroups), rank_finish (u = sB_c * (M (sA_c * t)) as bf16 head and
-// tail; the 64-row tiles do this themselves), gemm_bf16 (base product, scale, U_B u, output tile, reward partials).
+// tail; the 64-row tiles, and the 4-bit ones of 128 channels, do this themselves), gemm_bf16 (base product, scale, U_B u, output tile, reward partials).
 #include "forward_device.h"
 #include "row_offsets.h"
 #include <hip/hip_ext.h>
@@ -209,8 +209,8 @@ __global__ __launch_bounds__(256, THIRD && RP == 32 ? 1 : 2) void rank_down_kern
 // u = scale sB_c * (M (sA_c * t)) of ROWS rows from i0 on by 256 threads (scale: a power of two), the K parts of t added in ascending order; put(row, j, head, tail)
 // gets every element as two bf16.  With several elements a thread the parts are asked for without a branch between them (26.8 -> 25.5 us,
 // 3584 -> 512 at 512 rows); with one, and rows in the thousands, no more of them than there are.  tv: ROWS x (RP + 4) floats of LDS, Ms: RP x (RP + 4).
-template <int RP, int ROWS, class F>
-__device__ __forceinline__ void rank_rows(const prefill_item& it, int ksplit, float scale, int i0, float* tv, float* Ms, F&& put) {
+template <int RP, int ROWS, class ITEM, class F>
+__device__ __forceinline__ void rank_rows(const ITEM& it, int ksplit, float scale, int i0, float* tv, float* Ms, F&& put) {
     constexpr int P = RP + 4, EU = ROWS * RP / 256;
     const int tid = threadIdx.x, j = tid % RP, R = it.R;
     const gptr<const float> tp = as_global(it.Tpart);
@@ -661,16 +661,26 @@ struct q4_item {
     float* rowpart;
     int R, d_in, d_out, rp, n_blocks, Gn;
 };
+struct q4_rank {                           // what tiles that form u themselves want beside it
+    const float *Tpart, *M, *sigmaA, *sigmaB;
+    const int32_t* row2cand;
+    long long sigma_stride;
+    int R, r, rp, ksplit;
+};
 struct q4_args {
     q4_item it[ESSA_MAX_GROUP];
+    q4_rank rk[ESSA_MAX_GROUP];
     int tile_start[ESSA_MAX_GROUP + 1];
     int n_items;
 };
 
+template <int NR, int NC>
+constexpr size_t q4_own_bytes() { return NC == 2 ? 16 * NR * OWN_UROW + 32 * 36 * 4 + 16 * NR * 36 * 4 : 0; }
+
 template <int NR, int NC, int D>
 constexpr size_t q4_smem_bytes() {
     constexpr size_t BM = 16 * NR, stages = D * BM * 256 + (D - 1) * NC * 4096 + D * 1024, ctile = BM * (NC * 128 + 16);
-    return stages > ctile ? stages : ctile;
+    return (stages > ctile ? stages : ctile) + q4_own_bytes<NR, NC>();
 }
 
 template <int NR, int NC, int D, bool YBF16>
@@ -775,6 +785,22 @@ __global__ __launch_bounds__(256, 2) void gemm_q4_exact_kernel(q4_args a) {
         });
         for (int c = 0; c < nc - 1; ++c) chunk(c, std::false_type{});
         chunk(nc - 1, std::true_type{});
+        // a tile of 128 channels forms u itself, in LDS behind the stages: the rows (head and tail), M, sA t
+        constexpr bool OWN_U = NC == 2;
+        constexpr size_t U0 = q4_smem_bytes<NR, NC, D>() - q4_own_bytes<NR, NC>();
+        static_assert(!OWN_U || U0 >= S0 + D * 1024, "behind the stages");
+        if constexpr (OWN_U) {
+            const auto own = [&](int row, int j, uint16_t hi, uint16_t lo) {
+                uint16_t* ur = reinterpret_cast<uint16_t*>(smem + U0 + (size_t)row * OWN_UROW);
+                ur[j] = hi;
+                ur[rp + j] = lo;
+            };
+            float *Ms = reinterpret_cast<float*>(smem + U0 + BM * OWN_UROW), *tv = Ms + 32 * 36;
+            const q4_rank rk = fetch_item(a.rk[gi]);
+            if (rp == 16) rank_rows<16, BM>(rk, rk.ksplit, 0x1p-12f, m0, tv, Ms, own);
+            else rank_rows<32, BM>(rk, rk.ksplit, 0x1p-12f, m0, tv, Ms, own);
+            __syncthreads();
+        }
         auto rank_term = [&](auto ks_count) {              // as in the kernel above, for u 2^-12
             constexpr int KS = decltype(ks_count)::value;
             bf16x8 ub[NC][KS], uu[NR][2];
@@ -786,8 +812,11 @@ __global__ __launch_bounds__(256, 2) void gemm_q4_exact_kernel(q4_args a) {
 #pragma unroll
             for (int m = 0; m < NR; ++m)
 #pragma unroll
-                for (int e = 0; e < 2; ++e)
-                    uu[m][e] = __builtin_bit_cast(bf16x8, load16(ures, (uint32_t)min(m * 16 + l16, R - 1 - m0) * (64 * KS) + 16 * (KS == 1 ? kg & 1 : kg), e * 32 * KS));
+                for (int e = 0; e < 2; ++e) {
+                    const int at = 16 * (KS == 1 ? kg & 1 : kg) + e * 32 * KS;
+                    if constexpr (OWN_U) uu[m][e] = *reinterpret_cast<const bf16x8*>(smem + U0 + (size_t)(m * 16 + l16) * OWN_UROW + at);
+                    else uu[m][e] = __builtin_bit_cast(bf16x8, load16(ures, (uint32_t)min(m * 16 + l16, R - 1 - m0) * (64 * KS) + at, 0));
+                }
 #pragma unroll
             for (int n = 0; n < NC; ++n)
 #pragma unroll
@@ -926,21 +955,24 @@ double tile_us(const tile_cost& c, long long tiles, int steps, double w_mb, doub
     return c.call + c.round * (full + (rest ? 1 : 0)) + steps * (full * c.hi + last) + c.per_wmb * w_mb + c.per_ymb * y_mb;
 }
 
-// Which tile takes a group of 4-bit projections: the formula fitted to 329 groups and single projections of 512 to 8192 columns, every tile forced;
-// 0.4 % on average from the fastest tile, 9 % at worst.  The tallest tile unpacks least per product, and a last round that is not full costs what
-// it costs whatever its tiles; 128 channels are for calls of few tiles, a projection alone above all.  All run two to a CU.  us by tile (int8-limb tiles):
+// Which tile takes a group of 4-bit projections: the formula fitted to 331 groups and single projections of 512 to 8192 columns, every tile forced;
+// 0.2 % on average from the fastest tile, 5 % at worst.  The tallest tile unpacks least per product, and a last round that is not full costs what
+// it costs whatever its tiles; 128 channels are for calls of few tiles, a projection alone above all, and form u themselves (2 to 4 us of a call,
+// even where there are several rounds); they have to be 2 % ahead, which is what the formula is off by.  All run two to a CU.  us by tile (int8-limb tiles):
 //                               64 x 256   80 x 256   96 x 256   32 x 128   48 x 128   64 x 128
-//   q, k, v, o  8192   512 rows   209        158        167        213        203        178    (188)
-//               8192  1187        347        339        317        482        419        361    (420)
-//               3584   640         62         51         55         67         63         56     (75)
-//               3584  6000        350        329        318        485        436        371    (450)
-//   q alone     8192   257         87         92        101         87         69         77     (81)
-//   k alone     8192   512         87         90         98         50         55         69     (61)
-//               3584  1024         46         49         53         30         32         38     (38)
+//   q, k, v, o  8192   512   rows   210        156        164        214        199        218     (186)
+//               8192  1187   rows   341        335        314        480        406        393     (408)
+//               3584   640   rows    61         51         56         65         62         66     (71)
+//               3584  6000   rows   333        324        308        488        424        395     (442)
+//   q alone     8192   257   rows    85         91        101         85         66         73     (80)
+//               3584   512   rows    47         51         53         33         37         38     (36)
+//   k alone     8192   512   rows    87         91         99         48         52         67     (60)
+//               3584  1024   rows    47         49         54         28         30         37     (38)
+//               1024  1024   rows    25         27         28         17         18         19     (18)
 enum q4_tile { Q4_64x256, Q4_80x256, Q4_96x256, Q4_32x128, Q4_48x128, Q4_64x128 };
-constexpr tile_cost Q4_COST[] = {{64, 256, 512, 17.2, 1.0, 0.889, 1.403, 1.417, 0.21, 0.52}, {80, 256, 512, 17.7, 1.1, 0.959, 1.614, 1.676, 0.21, 0.46},
-                                 {96, 256, 512, 18.3, 1.4, 1.068, 1.809, 1.929, 0.22, 0.48}, {32, 128, 512, 15.6, 2.3, 0.289, 0.453, 0.544, 0.26, 0.50},
-                                 {48, 128, 512, 16.2, 1.9, 0.357, 0.611, 0.686, 0.24, 0.45}, {64, 128, 512, 17.6, 0.0, 0.539, 0.831, 0.810, 0.16, 0.53}};
+constexpr tile_cost Q4_COST[] = {{64, 256, 512, 16.6, 1.5, 0.913, 1.389, 1.435, 0.18, 0.46}, {80, 256, 512, 17.0, 1.6, 0.972, 1.612, 1.677, 0.19, 0.45},
+                                 {96, 256, 512, 17.5, 1.9, 1.078, 1.830, 1.922, 0.20, 0.48}, {32, 128, 512, 12.4, 2.2, 0.358, 0.518, 0.543, 0.22, 0.62},
+                                 {48, 128, 512, 12.7, 2.3, 0.407, 0.651, 0.684, 0.20, 0.54}, {64, 128, 512, 12.8, 1.9, 0.646, 0.743, 0.851, 0.24, 0.60}};
 q4_tile pick_q4_tile(const q4_args& a, int y_size) {
     int best = 0, ng = 1;
     double best_us = 0, w_mb = 0, y_mb = 0;
@@ -950,7 +982,7 @@ q4_tile pick_q4_tile(const q4_args& a, int y_size) {
         y_mb += 1e-6 * y_size * a.it[g].R * a.it[g].d_out;
     }
     for (int i = 0; i < (int)(sizeof(Q4_COST) / sizeof(Q4_COST[0])); ++i) {
-        const double us = tile_us(Q4_COST[i], count_tiles(Q4_COST[i], a.it, a.n_items), ng, w_mb, y_mb);
+        const double us = tile_us(Q4_COST[i], count_tiles(Q4_COST[i], a.it, a.n_items), ng, w_mb, y_mb) * (i >= Q4_32x128 ? 1.02 : 1.0);
         if (i == 0 || us < best_us) {
             best = i;
             best_us = us;
@@ -1103,16 +1135,19 @@ hipError_t forward_prefill_q4(hipStream_t st, const fwd_item* items, int n_items
     }
     r.n_items = a.n_items = n_items;
     r.u_scale = 0x1p-12f;
-    hipError_t e = launch_rank(st, r, true);
+    const bool yb = y_dtype == ESSA_BF16;
+    const q4_tile tile = pick_q4_tile(a, yb ? 2 : 4);
+    hipError_t e = launch_rank(st, r, tile < Q4_32x128);
     if (e != hipSuccess) return e;
+    for (int g = 0; g < n_items; ++g)
+        a.rk[g] = q4_rank{items[g].Tpart, items[g].M, items[g].sigmaA, items[g].sigmaB, items[g].row2cand, items[g].sigma_stride, items[g].R, items[g].r, items[g].rp, r.ksplit[g]};
     tl_pre_start = ev_start;
     tl_pre_stop = ev_stop;
-    const bool yb = y_dtype == ESSA_BF16;
-    switch (pick_q4_tile(a, yb ? 2 : 4)) {
+    switch (tile) {
         case Q4_64x256: e = yb ? launch_q4<4, 4, 2, true>(st, a) : launch_q4<4, 4, 2, false>(st, a); break;
         case Q4_80x256: e = yb ? launch_q4<5, 4, 2, true>(st, a) : launch_q4<5, 4, 2, false>(st, a); break;
         case Q4_96x256: e = yb ? launch_q4<6, 4, 2, true>(st, a) : launch_q4<6, 4, 2, false>(st, a); break;
-        case Q4_32x128: e = yb ? launch_q4<2, 2, 5, true>(st, a) : launch_q4<2, 2, 5, false>(st, a); break;
+        case Q4_32x128: e = yb ? launch_q4<2, 2, 4, true>(st, a) : launch_q4<2, 2, 4, false>(st, a); break;
         case Q4_48x128: e = yb ? launch_q4<3, 2, 3, true>(st, a) : launch_q4<3, 2, 3, false>(st, a); break;
         default: e = yb ? launch_q4<4, 2, 2, true>(st, a) : launch_q4<4, 2, 2, false>(st, a); break;
     }
