@@ -1091,8 +1091,8 @@ extern "C" essa_status essa_cmaes_update(essa_ctx* ctx, essa_cma* cma, const uin
         float* coef = (float*)((char*)ctx->ws + off_coef);
         float* Z = (float*)((char*)ctx->ws + off_Z);
         ESSA_HIP(essa_k::ars_prepare(ctx->stream, rewards, N, b, cma->ars_alpha, order, coef));
-        if (order_out) ESSA_HIP(hipMemcpyAsync(order_out, order, (size_t)N * 4, hipMemcpyDeviceToDevice, ctx->stream));
         ESSA_HIP(essa_k::normals_scaled(ctx->stream, seeds, order, b, n, nullptr, Z, nullptr));
+        if (order_out) ESSA_HIP(hipMemcpyAsync(order_out, order, (size_t)N * 4, hipMemcpyDeviceToDevice, ctx->stream));
         ESSA_HIP(essa_k::mean_step(ctx->stream, Z, coef, 0.0, b, n, cma->sc, 0, cma->m));
         return ESSA_OK;
     }
@@ -1133,7 +1133,7 @@ extern "C" essa_status essa_cmaes_update(essa_ctx* ctx, essa_cma* cma, const uin
     const size_t off_zn = align256((size_t)K * 4), off_S = off_zn + align256((size_t)c.ny * 4), off_BY = off_S + essa_k::tiled_rows_bytes(rows, n);
     const size_t off_Z = off_BY + align256(rows * n * 4);
     ESSA_TRY(essa_ws_reserve(ctx, off_Z + align256(rows * n * 4)));
-    int32_t* order = order_out ? order_out : (int32_t*)ctx->ws;
+    int32_t* order = (int32_t*)ctx->ws;                  // not order_out, which may lie over seeds or rewards
     float* zn2 = (float*)((char*)ctx->ws + off_zn);
     float* S = (float*)((char*)ctx->ws + off_S);
     float* BY = (float*)((char*)ctx->ws + off_BY);
@@ -1145,13 +1145,13 @@ extern "C" essa_status essa_cmaes_update(essa_ctx* ctx, essa_cma* cma, const uin
                                    has_matrix(cma), cma->kind == ESSA_OPT_ACTIVE_CMA));
     if (cma->kind == ESSA_OPT_SEP_CMA) {
         // B = I: the rows of S are the y_i, z_w and y_w themselves
-        ESSA_HIP(essa_k::cma_vectors(ctx->stream, c, cma->weights, S, cma->m, cma->p_sigma, cma->p_c, cma->sc));
+        ESSA_HIP(essa_k::cma_vectors(ctx->stream, c, cma->weights, S, cma->m, cma->p_sigma, cma->p_c, cma->sc, order, order_out));
         ESSA_HIP(essa_k::sep_covariance(ctx->stream, c, cma->weights, S, cma->p_c, cma->sc, cma->Cdiag, cma->D));
         return ESSA_OK;
     }
     if (cma->kind == ESSA_OPT_ACTIVE_CMA) ESSA_HIP(essa_k::row_norms2(ctx->stream, Z, c.ny, n, zn2));
     ESSA_HIP(essa_k::skinny_gemm_nt(ctx->stream, S, (int)rows, cma->B, n, nullptr, nullptr, 0, BY));
-    ESSA_HIP(essa_k::cma_vectors(ctx->stream, c, cma->weights, BY, cma->m, cma->p_sigma, cma->p_c, cma->sc));
+    ESSA_HIP(essa_k::cma_vectors(ctx->stream, c, cma->weights, BY, cma->m, cma->p_sigma, cma->p_c, cma->sc, order, order_out));
     ESSA_HIP(essa_k::cma_covariance(ctx->stream, c, cma->weights, BY, cma->p_c, cma->sc, cma->kind == ESSA_OPT_ACTIVE_CMA ? zn2 : nullptr, cma->C));
     return ESSA_OK;
 }

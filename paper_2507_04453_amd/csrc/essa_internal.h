@@ -163,8 +163,9 @@ struct cma_consts {
 // tiled: S in the tiles of skinny_gemm_nt, else in rows; Z ([ny, n] scratch) holds the z_i afterwards if want_z
 hipError_t cma_build_rhs(hipStream_t st, const uint32_t* seeds, int32_t* order, const float* rewards, const float* w,
                          const cma_consts& c, const float* D, float* S, float* Z, bool tiled, bool want_z);
+// order (scratch) is copied to order_out unless that is null
 hipError_t cma_vectors(hipStream_t st, const cma_consts& c, const float* w, const float* BY /*[ny+2,n]*/,
-                       float* m, float* p_sigma, float* p_c, essa_cma_scalars* sc);
+                       float* m, float* p_sigma, float* p_c, essa_cma_scalars* sc, const int32_t* order, int32_t* order_out);
 // zn2: [ny] squared lengths of the sorted z (read for negative weights only), or null
 hipError_t cma_covariance(hipStream_t st, const cma_consts& c, const float* w, const float* BY, const float* p_c,
                           const essa_cma_scalars* sc, const float* zn2, float* C);

@@ -76,12 +76,14 @@ __device__ __forceinline__ double block_sum_1024(double v, double* sh) {
 
 // One workgroup.  BY rows 0..ny-1 are y_{i:lambda} = B D z_{i:lambda}, row ny is B z_w, row ny+1 is y_w = B D z_w
 // (the weighted mean of the mu best y_i, taken before the product with B because that product is linear).
+// The ranking leaves for the caller here, behind every launch that reads seeds or rewards: order_out may be either of them.
 constexpr int HELD = 4;
 __global__ __launch_bounds__(1024) void cma_vectors_kernel(essa_k::cma_consts c, const float* __restrict__ w, const float* __restrict__ BY,
                                                           float* __restrict__ m, float* __restrict__ p_sigma, float* __restrict__ p_c,
-                                                          essa_cma_scalars* __restrict__ sc) {
+                                                          essa_cma_scalars* __restrict__ sc, const int32_t* __restrict__ order, int32_t* __restrict__ order_out) {
     __shared__ double sh[1024];
     const int n = c.n, mu = c.ny;
+    const int rank = order_out ? order[min((int)threadIdx.x, c.K - 1)] : 0;
     const float sigma = sc->sigma;
     const int t = sc->t;
     const double cs = c.c_sigma, cc = c.c_c, mueff = c.mu_eff;
@@ -99,6 +101,7 @@ __global__ __launch_bounds__(1024) void cma_vectors_kernel(essa_k::cma_consts c,
         pc0[e] = p_c[l];
     }
     const double denom = sqrt(1.0 - pow(1.0 - cs, 2.0 * (double)(t + 1)));
+    if (order_out && (int)threadIdx.x < c.K) order_out[threadIdx.x] = rank;      // K <= 1024
     double part = 0.0;
 #pragma unroll
     for (int e = 0; e < HELD; ++e) {
@@ -329,8 +332,8 @@ hipError_t cma_build_rhs(hipStream_t st, const uint32_t* seeds, int32_t* order, 
 }
 
 hipError_t cma_vectors(hipStream_t st, const cma_consts& c, const float* w, const float* BY, float* m, float* p_sigma,
-                       float* p_c, essa_cma_scalars* sc) {
-    hipLaunchKernelGGL(cma_vectors_kernel, dim3(1), dim3(1024), 0, st, c, w, BY, m, p_sigma, p_c, sc);
+                       float* p_c, essa_cma_scalars* sc, const int32_t* order, int32_t* order_out) {
+    hipLaunchKernelGGL(cma_vectors_kernel, dim3(1), dim3(1024), 0, st, c, w, BY, m, p_sigma, p_c, sc, order, order_out);
     return hipGetLastError();
 }
 

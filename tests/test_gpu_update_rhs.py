@@ -36,3 +36,29 @@ def test_update_right_hand_sides(essa, n, K):
     again.close()
     cma.close()
     ctx.close()
+
+
+@pytest.mark.parametrize("kind,n,K", [("OPT_CMA", 700, 32), ("OPT_CMA", 130, 300), ("OPT_CMA", 66, 1024), ("OPT_ACTIVE_CMA", 200, 40), ("OPT_ACTIVE_CMA", 67, 260),
+                                      ("OPT_SEP_CMA", 1500, 48), ("OPT_SEP_CMA", 50, 270), ("OPT_ES", 300, 32), ("OPT_ES", 70, 260), ("OPT_ARS", 90, 40)])
+def test_order_out_over_an_input(essa, kind, n, K):
+    """The ranking may be written over the rewards or the seeds: every launch of the update that reads them comes first."""
+    print("%s n=%d K=%d" % (kind, n, K), flush=True)
+    ctx = essa.Context(0)
+    g = np.random.default_rng(n + K)
+    F = g.standard_normal(K).astype(np.float32)
+    ars = kind == "OPT_ARS"                                # one seed and one place in the order per pair
+    S = K // 2 if ars else K
+    results = []
+    for over in (None, "rewards", "seeds"):
+        cma = essa.CmaState(ctx, n, 0.32, kind=getattr(essa, kind), ars_alpha=0.02 if ars else 0.0, ars_top=8 if ars else 0)
+        seeds, rewards = to_dev(np.arange(5, 5 + S, dtype=np.int32)), to_dev(F)
+        order = torch.full((S,), -1, dtype=torch.int32, device="cuda") if over is None else rewards.view(torch.int32)[:S] if over == "rewards" else seeds
+        essa.essa_cmaes_update(ctx, cma, seeds, rewards, order)
+        state = cma.export()
+        results.append([order.cpu().numpy()] + [np.asarray(state[k]) for k in sorted(state)])
+        cma.close()
+    want = np.argsort(-(np.maximum(F[::2], F[1::2]) if ars else F), kind="stable")
+    for r in results:
+        assert np.array_equal(r[0], want)
+        assert all(np.array_equal(a, b) for a, b in zip(r, results[0]))
+    ctx.close()
