@@ -660,10 +660,18 @@ extern "C" essa_status essa_sample_candidates(essa_ctx* ctx, const essa_cma* cma
                                      theta_out, z_out));
         return ESSA_OK;
     }
-    ESSA_TRY(essa_ws_reserve(ctx, essa_k::tiled_rows_bytes(K, n)));
+    // scratch that cannot grow (a graph points into it), holds the candidates' right-hand sides but not their tiles' padding: some candidates at a time
+    // (a tile of 16 is a megabyte at most, and so small is no scratch)
+    int some = K;
+    if (essa_k::tiled_rows_bytes(K, n) > ctx->ws_bytes && align256((size_t)K * n * sizeof(float)) <= ctx->ws_bytes && (ctx->capturing || !ctx->graphs.empty()))
+        some = std::min<size_t>(K, ctx->ws_bytes / essa_k::tiled_rows_bytes(16, n) * 16);
+    ESSA_TRY(essa_ws_reserve(ctx, essa_k::tiled_rows_bytes(some, n)));
     float* S = (float*)ctx->ws;
-    ESSA_HIP(essa_k::normals_tiled(ctx->stream, seeds, nullptr, K, n, cma->D, S, z_out));
-    ESSA_HIP(essa_k::skinny_gemm_nt(ctx->stream, S, K, cma->B, n, cma->m, cma->sc, 1, theta_out));
+    for (int k = 0; k < K; k += some) {
+        const int count = std::min(some, K - k);
+        ESSA_HIP(essa_k::normals_tiled(ctx->stream, seeds + k, nullptr, count, count, n, cma->D, S, z_out ? z_out + (size_t)k * n : nullptr));
+        ESSA_HIP(essa_k::skinny_gemm_nt(ctx->stream, S, count, cma->B, n, cma->m, cma->sc, 1, theta_out + (size_t)k * n));
+    }
     return ESSA_OK;
 }
 
@@ -1128,16 +1136,15 @@ extern "C" essa_status essa_cmaes_update(essa_ctx* ctx, essa_cma* cma, const uin
         ESSA_TRY(upload(&cma->weights, w.data(), w.size()));
         cma->weights_K = K;
     }
-    // scratch: order[K] | zn2[ny] | S[(ny+2), n] | BY[(ny+2), n] | Z[ny, n];  S rows: D*z_i (i < ny), z_w, D*z_w
+    // scratch: order[K] | zn2[ny] | S[(ny+2), n] | BY[(ny+2), n];  S rows: D*z_i (i < ny), z_w, D*z_w;  Z[ny, n] where BY goes once it has been read
     const size_t rows = (size_t)c.ny + 2;
-    const size_t off_zn = align256((size_t)K * 4), off_S = off_zn + align256((size_t)c.ny * 4), off_BY = off_S + essa_k::tiled_rows_bytes(rows, n);
-    const size_t off_Z = off_BY + align256(rows * n * 4);
-    ESSA_TRY(essa_ws_reserve(ctx, off_Z + align256(rows * n * 4)));
+    const size_t off_zn = align256((size_t)K * 4), off_S = off_zn + align256((size_t)c.ny * 4), off_BY = off_S + align256(essa_k::tiled_rows_bytes(rows, n));
+    ESSA_TRY(essa_ws_reserve(ctx, off_BY + align256(rows * n * 4)));
     int32_t* order = (int32_t*)ctx->ws;                  // not order_out, which may lie over seeds or rewards
     float* zn2 = (float*)((char*)ctx->ws + off_zn);
     float* S = (float*)((char*)ctx->ws + off_S);
     float* BY = (float*)((char*)ctx->ws + off_BY);
-    float* Z = (float*)((char*)ctx->ws + off_Z);
+    float* Z = BY;
     // the ranking: inside the kernel that regenerates the normals when the population is small, else a launch of its own
     const bool rank_inside = K <= essa_k::kRankInKernelMax;
     if (!rank_inside) ESSA_HIP(essa_k::rank_rewards(ctx->stream, rewards, K, order));

@@ -1,6 +1,7 @@
 // Internal declarations shared by the host glue and the kernel launchers of libessa.
 #pragma once
 #include <hip/hip_runtime.h>
+#include "row_offsets.h"
 #include <cstdarg>
 #include <cstdint>
 #include <cstdio>
@@ -127,10 +128,9 @@ constexpr int kRankInKernelMax = 256;
 hipError_t normals_scaled(hipStream_t st, const uint32_t* seeds, const int32_t* sel /*null or [J]*/, int J, int n,
                           const float* D /*null = 1*/, float* S, float* z_out, const float* rank_F = nullptr, int rank_K = 0,
                           int32_t* rank_order = nullptr);
-// the same with S in the operand tiles of skinny_gemm_nt: [rows / 16][columns / 16][4][16 rows][4 columns], columns past n zero
-hipError_t normals_tiled(hipStream_t st, const uint32_t* seeds, const int32_t* sel, int J, int n, const float* D, float* S, float* z_out,
+// the same with S, a matrix of `rows` rows, in the operand tiles of skinny_gemm_nt (tiled_rows_at)
+hipError_t normals_tiled(hipStream_t st, const uint32_t* seeds, const int32_t* sel, int J, int rows, int n, const float* D, float* S, float* z_out,
                          const float* rank_F = nullptr, int rank_K = 0, int32_t* rank_order = nullptr);
-constexpr size_t tiled_rows_bytes(size_t rows, size_t n) { return (rows + 15) / 16 * ((n + 15) / 16) * 1024; }
 // an update's right-hand sides in one launch (rows as for cma_build_rhs, tiles; ny <= 64 of them gain by it); Z null or [ny, n]
 hipError_t update_rhs(hipStream_t st, const uint32_t* seeds, const int32_t* sel, int ny, int mu, int n, const float* w, const float* D, float* S,
                       float* Z, const float* rank_F, int rank_K, int32_t* rank_order);

@@ -33,9 +33,7 @@ template <bool TILED>
 __global__ void weighted_rowsum_kernel(const float* __restrict__ Z, const float* __restrict__ w, const float* __restrict__ D, int mu,
                                        int n, int ny, float* __restrict__ S) {
     const int l = blockIdx.x * blockDim.x + threadIdx.x;
-    auto at = [&](int j) {
-        return TILED ? (((size_t)(j >> 4) * ((n + 15) >> 4) + (l >> 4)) * 64 + (l >> 2 & 3) * 16 + (j & 15)) * 4 + (l & 3) : (size_t)j * n + l;
-    };
+    auto at = [&](int j) { return TILED ? essa_k::tiled_rows_at(j, l, ny + 2, n) : (size_t)j * n + l; };
     if (l >= n) {
         if (TILED && l < (n + 15) / 16 * 16) S[at(ny)] = S[at(ny + 1)] = 0.f;
         return;
@@ -323,7 +321,7 @@ hipError_t cma_build_rhs(hipStream_t st, const uint32_t* seeds, int32_t* order, 
                          const float* D, float* S, float* Z, bool tiled, bool want_z) {
     const int32_t* sel = rewards ? nullptr : order;
     if (tiled && c.ny <= 64) return update_rhs(st, seeds, sel, c.ny, c.mu, c.n, w, D, S, want_z ? Z : nullptr, rewards, c.K, order);
-    hipError_t e = tiled ? normals_tiled(st, seeds, sel, c.ny, c.n, D, S, Z, rewards, c.K, order)
+    hipError_t e = tiled ? normals_tiled(st, seeds, sel, c.ny, c.ny + 2, c.n, D, S, Z, rewards, c.K, order)
                          : normals_scaled(st, seeds, sel, c.ny, c.n, D, S, Z, rewards, c.K, order);
     if (e != hipSuccess) return e;
     if (tiled) hipLaunchKernelGGL(weighted_rowsum_kernel<true>, dim3((c.n + 63) / 64), dim3(64), 0, st, Z, w, D, c.mu, c.n, c.ny, S);

@@ -9,7 +9,6 @@
 // Three launches: rank_down (t = V_A^T x, K split over workgroups), rank_finish (u = sB_c * (M (sA_c * t)) as bf16 head and
 // tail; the 64-row tiles, and the 4-bit ones of 128 channels, do this themselves), gemm_bf16 (base product, scale, U_B u, output tile, reward partials).
 #include "forward_device.h"
-#include "row_offsets.h"
 #include <hip/hip_ext.h>
 #include <algorithm>
 #include <utility>

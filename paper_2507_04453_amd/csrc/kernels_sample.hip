@@ -41,12 +41,7 @@ __global__ void philox_words_kernel(const uint32_t* __restrict__ seeds, int K, i
     reinterpret_cast<uint4*>(out)[idx] = w;
 }
 
-// The product with the basis takes its right-hand sides in operand tiles: 16 rows x 16 columns to a kilobyte, tile (j / 16, l / 16), inside it
-// [l / 4 % 4][j % 16][l % 4] -- a wave's load is one contiguous kilobyte.  Columns past n are zero, rows past J anything finite or not:
-// they end up in outputs that nobody stores.
-__device__ __forceinline__ size_t rhs_at(int j, int l, int n) {
-    return (((size_t)(j >> 4) * ((n + 15) >> 4) + (l >> 4)) * 64 + (l >> 2 & 3) * 16 + (j & 15)) * 4 + (l & 3);
-}
+using essa_k::tiled_rows_at;
 
 // The ranking of K <= 256 rewards (larger first, ties by index, NaN last), worked out by the whole workgroup in LDS -- a few hundred
 // comparisons instead of a kernel launch of its own; the first workgroup also writes it to rank_order.
@@ -71,9 +66,9 @@ __device__ __forceinline__ void rank_in_lds(const float* rank_F, int rank_K, int
 }
 
 // S[j, l] = D[l] * z_{cand(j)}[l],  cand(j) = sel ? sel[j] : j ; optional copy of z itself.  With rank_F the selection is the ranking of
-// rank_K <= 256 rewards.  TILED: S in the tiles above, else in rows.
+// rank_K <= 256 rewards.  TILED: S in the tiles above, of a matrix of `rows` rows, else in rows.
 template <bool TILED>
-__global__ __launch_bounds__(256) void normals_scaled_kernel(const uint32_t* __restrict__ seeds, const int32_t* __restrict__ sel, int J, int n,
+__global__ __launch_bounds__(256) void normals_scaled_kernel(const uint32_t* __restrict__ seeds, const int32_t* __restrict__ sel, int J, int rows, int n,
                                                             const float* __restrict__ D, float* __restrict__ S, float* __restrict__ z_out,
                                                             const float* __restrict__ rank_F, int rank_K, int32_t* __restrict__ rank_order) {
     __shared__ float key[256];
@@ -98,7 +93,7 @@ __global__ __launch_bounds__(256) void normals_scaled_kernel(const uint32_t* __r
             if (z_out) z_out[(size_t)j * n + l] = z[e];
         }
     }
-    if (TILED) *reinterpret_cast<float4*>(S + rhs_at(j, 4 * c, n)) = make_float4(v[0], v[1], v[2], v[3]);
+    if (TILED) *reinterpret_cast<float4*>(S + tiled_rows_at(j, 4 * c, rows, n)) = make_float4(v[0], v[1], v[2], v[3]);
 }
 
 // The right-hand sides of an update in one launch: rows i < ny the selected D * z_i, row ny z_w = sum_{i < mu} w[i] z_i (fp64, i ascending),
@@ -132,7 +127,7 @@ __global__ __launch_bounds__(RHS_C * RHS_B) void update_rhs_kernel(const uint32_
                 v[e] = 4 * c + e < n ? d[e] * z[e] : 0.f;
                 if (Z && 4 * c + e < n) Z[(size_t)i * n + 4 * c + e] = z[e];
             }
-            *reinterpret_cast<float4*>(S + rhs_at(i, 4 * c, n)) = make_float4(v[0], v[1], v[2], v[3]);
+            *reinterpret_cast<float4*>(S + tiled_rows_at(i, 4 * c, ny + 2, n)) = make_float4(v[0], v[1], v[2], v[3]);
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e) zs[ci][cb * 4 + e] = z[e];
@@ -144,8 +139,8 @@ __global__ __launch_bounds__(RHS_C * RHS_B) void update_rhs_kernel(const uint32_
     const int l = l0 + threadIdx.x;
     if (threadIdx.x < RHS_B * 4 && l < (n + 15) / 16 * 16) {
         const float zw = l < n ? (float)acc : 0.f;
-        S[rhs_at(ny, l, n)] = zw;
-        S[rhs_at(ny + 1, l, n)] = l < n ? D[l] * zw : 0.f;
+        S[tiled_rows_at(ny, l, ny + 2, n)] = zw;
+        S[tiled_rows_at(ny + 1, l, ny + 2, n)] = l < n ? D[l] * zw : 0.f;
     }
 }
 
@@ -221,20 +216,21 @@ __global__ __launch_bounds__(SG_WAVES * 64) void skinny_gemm_nt_kernel(const flo
         // for two chunks of both, and for the next two in front of the MFMAs of these: deeper bunches (14 of B, S behind them)
         // queue everybody's B in front of everybody's S.  Product / update and next candidates, us, S in rows and bunches of 14 against this:
         // n = 3584, 32 candidates 21.3 / 15.5 and 82 / 65; 64 candidates at n = 5121 303 / 191 (both); 896, 36 candidates 45 / 35 (both).
-        // (n <= 16384: both matrices stay below the descriptor's 2 GB.)
+        // (n <= 16384: B stays below the descriptor's 2 GB.  S need not: its descriptor begins at this workgroup's tiles.)
         // The loads need 4-byte alignment only, so any n takes this path.  TAIL: n is not a multiple of 4, and the quad that
         // crosses the end of a row is the row's last four elements, moved into place.
         typedef __amdgpu_buffer_rsrc_t rsrc_t;
         constexpr uint32_t OUT_OF_RANGE = 0x80000000u;
         const rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(B), 0, (uint32_t)n * (uint32_t)n * 4u, 0x00020000);
-        const uint32_t tiles_l = (uint32_t)nchunks * 1024u;
-        const rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(S), 0, (uint32_t)((J + 15) / 16) * tiles_l, 0x00020000);
-        const uint32_t brow = (uint32_t)i * (uint32_t)n * 4u;                    // i >= n: beyond the descriptor
+        const int sshift = essa_k::tiled_rows_shift(J);
+        const uint32_t tile = (uint32_t)nchunks << (sshift + 6);
+        const rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(S + tiled_rows_at(j0, 0, J, n)), 0, JB * tile, 0x00020000);
         uint32_t scol[JB];                                  // columns past J are not asked for
 #pragma unroll
-        for (int jb = 0; jb < JB; ++jb) scol[jb] = j0 + 16 * jb + l16 < J ? (uint32_t)(j0 / 16 + jb) * tiles_l + (uint32_t)lane * 16u : OUT_OF_RANGE;
+        for (int jb = 0; jb < JB; ++jb) scol[jb] = j0 + 16 * jb + l16 < J ? (uint32_t)jb * tile + (uint32_t)((kq << sshift) + l16) * 16u : OUT_OF_RANGE;
+        const uint32_t brow = (uint32_t)i * (uint32_t)n * 4u;                    // i >= n: beyond the descriptor
         auto ld_s = [&](int jb, int chunk) {               // a contiguous kilobyte
-            const auto v = __builtin_amdgcn_raw_buffer_load_b128(rs, chunk < nchunks ? scol[jb] + (uint32_t)chunk * 1024u : OUT_OF_RANGE, 0, 0);
+            const auto v = __builtin_amdgcn_raw_buffer_load_b128(rs, chunk < nchunks ? scol[jb] + ((uint32_t)chunk << (sshift + 6)) : OUT_OF_RANGE, 0, 0);
             f32x4 f;
             __builtin_memcpy(&f, &v, 16);
             return f;
@@ -327,15 +323,15 @@ hipError_t philox_words(hipStream_t st, const uint32_t* seeds, int K, int n_bloc
 hipError_t normals_scaled(hipStream_t st, const uint32_t* seeds, const int32_t* sel, int J, int n, const float* D, float* S,
                           float* z_out, const float* rank_F, int rank_K, int32_t* rank_order) {
     const long long total = (long long)J * ((n + 3) / 4);
-    hipLaunchKernelGGL(normals_scaled_kernel<false>, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, seeds, sel, J, n, D, S, z_out, rank_F,
+    hipLaunchKernelGGL(normals_scaled_kernel<false>, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, seeds, sel, J, J, n, D, S, z_out, rank_F,
                        rank_K, rank_order);
     return hipGetLastError();
 }
 
-hipError_t normals_tiled(hipStream_t st, const uint32_t* seeds, const int32_t* sel, int J, int n, const float* D, float* S,
+hipError_t normals_tiled(hipStream_t st, const uint32_t* seeds, const int32_t* sel, int J, int rows, int n, const float* D, float* S,
                          float* z_out, const float* rank_F, int rank_K, int32_t* rank_order) {
     const long long total = (long long)J * ((n + 15) / 16 * 4);
-    hipLaunchKernelGGL(normals_scaled_kernel<true>, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, seeds, sel, J, n, D, S, z_out, rank_F,
+    hipLaunchKernelGGL(normals_scaled_kernel<true>, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, seeds, sel, J, rows, n, D, S, z_out, rank_F,
                        rank_K, rank_order);
     return hipGetLastError();
 }

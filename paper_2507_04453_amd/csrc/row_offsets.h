@@ -1,5 +1,6 @@
-// Byte offsets of a tile's rows: plain constexpr C++, so that a test can run on the host what the kernels run.
+// Places of rows in memory: plain constexpr C++, so that a test can run on the host what the kernels run.
 #pragma once
+#include <cstddef>
 #include <cstdint>
 
 namespace essa_k {
@@ -9,6 +10,20 @@ namespace essa_k {
 constexpr uint32_t last_row_offset(int R, int m0, int height, uint32_t row_bytes) {
     const int left = R - 1 - m0;
     return (uint32_t)(left < height - 1 ? left : height - 1) * row_bytes;
+}
+
+// Right-hand sides of the product with the basis (a matrix of `rows` rows and n columns of floats) lie in operand tiles of 16 rows (8 or 4 where there
+// are no more) and 16 columns, tile (j / 16, l / 16), inside it [l / 4 % 4][row][l % 4] -- a wave's load is one contiguous kilobyte.  Columns
+// past n are zero, rows past the last one anything finite or not: they are not read.  With their products they take no more than three
+// matrices in rows, which a scratch that cannot grow may have been made for, or than the megabyte that no scratch is smaller than.
+constexpr int tiled_rows_shift(int rows) { return rows <= 4 ? 2 : rows <= 8 ? 3 : 4; }
+constexpr size_t tiled_rows_bytes(size_t rows, size_t n) {
+    const int s = tiled_rows_shift(rows < 16 ? (int)rows : 16);
+    return (((rows + (1 << s) - 1) >> s) * ((n + 15) / 16)) << (s + 6);
+}
+constexpr size_t tiled_rows_at(int j, int l, int rows, int n) {      // the float of row j, column l
+    const int s = tiled_rows_shift(rows);
+    return (((((size_t)(j >> s) * ((n + 15) >> 4) + (l >> 4)) * 4 + (l >> 2 & 3)) << s) + (j & ((1 << s) - 1))) * 4 + (l & 3);
 }
 
 }  // namespace essa_k

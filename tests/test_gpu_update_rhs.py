@@ -62,3 +62,50 @@ def test_order_out_over_an_input(essa, kind, n, K):
         assert np.array_equal(r[0], want)
         assert all(np.array_equal(a, b) for a, b in zip(r, results[0]))
     ctx.close()
+
+
+def _scratch_of(essa, ctx, rows):
+    """The context's first scratch: five quarters of 4 bytes a row and a megabyte, pinned by a recorded graph."""
+    Y, v = torch.zeros(rows, 1, device="cuda"), torch.zeros(1, device="cuda")
+    essa.essa_reward_accumulate(ctx, Y, v, torch.zeros(rows, dtype=torch.int32, device="cuda"), torch.zeros(1, device="cuda"))
+    sft = torch.ones(1, 2, device="cuda")
+    theta, out = torch.zeros(1, 4, device="cuda"), (torch.empty(1, 1, 2, device="cuda"), torch.empty(1, 1, 2, device="cuda"))
+    torch.cuda.synchronize()
+    ctx.graph_begin()
+    essa.essa_theta_to_sigma(ctx, 2, sft, sft, theta, *out)
+    return ctx.graph_end()
+
+
+@pytest.mark.parametrize("what,n,K,rows", [
+    ("sample", 15400, 17, 64),                             # a megabyte of scratch for 17 rows: one tile of 16 at a time
+    ("sample", 5, 65536, 100000),                          # five columns in tiles of 16: some candidates at a time
+    ("update", 10000, 8, 64),                              # 6 right-hand sides and what comes of them
+    ("update", 401, 300, 64),                              # the launches for more than 64 right-hand sides
+])
+def test_scratch_that_cannot_grow(essa, what, n, K, rows):
+    """Calls whose rows fit a scratch that a recorded graph pins go through (three times a right-hand side of n floats for an update, one per candidate
+    for the sampler), with the bits of a context that is free to grow."""
+    print("%s n=%d K=%d" % (what, n, K), flush=True)
+    got = []
+    for pinned in (False, True):
+        side = torch.cuda.Stream()
+        with torch.cuda.stream(side):
+            ctx = essa.Context(0, side)
+            graph = _scratch_of(essa, ctx, rows) if pinned else None
+            cma = essa.CmaState(ctx, n, 0.32)
+            seeds = to_dev(np.arange(3, 3 + K, dtype=np.int32))
+            if what == "sample":
+                theta, z = torch.empty(K, n, device="cuda"), torch.empty(K, n, device="cuda")
+                essa.essa_sample_candidates(ctx, cma, seeds, theta, z)
+                side.synchronize()
+                got.append([theta.cpu().numpy(), z.cpu().numpy()])
+            else:
+                essa.essa_cmaes_update(ctx, cma, seeds, to_dev(np.random.default_rng(n).standard_normal(K).astype(np.float32)))
+                side.synchronize()
+                state = cma.export()
+                got.append([state[k] for k in ("m", "p_sigma", "p_c", "C")])
+            if graph is not None:
+                graph.close()
+            cma.close()
+            ctx.close()
+    assert all(np.array_equal(a, b) for a, b in zip(*got))

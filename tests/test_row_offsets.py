@@ -1,5 +1,6 @@
-"""Row offsets of the 4-bit exact product's tiles, on the host: every row of a tile comes from its own row of X, rows past the end from the last
-one, however large X is (32-bit offsets from a 64-bit base at the tile)."""
+"""Places of rows in memory, on the host.  The 4-bit exact product's tiles: every row of a tile comes from its own row of X, rows past the end from
+the last one, however large X is (32-bit offsets from a 64-bit base at the tile).  Right-hand sides in operand tiles: a place
+for every element, and room for them."""
 import ctypes
 import os
 import subprocess
@@ -10,18 +11,22 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 
 
 @pytest.fixture(scope="module")
-def last_row_offset(tmp_path_factory):
+def lib(tmp_path_factory):
     d = tmp_path_factory.mktemp("row_offsets")
-    (d / "t.cpp").write_text('#include "row_offsets.h"\nextern "C" unsigned f(int R, int m0, int height, unsigned row_bytes) {\n'
-                             '    return essa_k::last_row_offset(R, m0, height, row_bytes);\n}\n')
+    (d / "t.cpp").write_text('#include "row_offsets.h"\nextern "C" {\n'
+                             'unsigned last_row_offset(int R, int m0, int height, unsigned row_bytes) { return essa_k::last_row_offset(R, m0, height, row_bytes); }\n'
+                             'size_t bytes(size_t rows, size_t n) { return essa_k::tiled_rows_bytes(rows, n); }\n'
+                             'size_t at(int j, int l, int rows, int n) { return essa_k::tiled_rows_at(j, l, rows, n); }\n}\n')
     subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", CSRC, str(d / "t.cpp"), "-o", str(d / "t.so")], check=True)
-    f = ctypes.CDLL(str(d / "t.so")).f
-    f.argtypes, f.restype = [ctypes.c_int] * 3 + [ctypes.c_uint], ctypes.c_uint
-    return f
+    so = ctypes.CDLL(str(d / "t.so"))
+    so.last_row_offset.argtypes, so.last_row_offset.restype = [ctypes.c_int] * 3 + [ctypes.c_uint], ctypes.c_uint
+    so.bytes.argtypes, so.bytes.restype = [ctypes.c_size_t] * 2, ctypes.c_size_t
+    so.at.argtypes, so.at.restype = [ctypes.c_int] * 4, ctypes.c_size_t
+    return so
 
 
 @pytest.mark.parametrize("d_in", [128, 3584, 5120, 8192])
-def test_rows_of_a_tile_are_their_own(last_row_offset, d_in):
+def test_rows_of_a_tile_are_their_own(lib, d_in):
     row_bytes, wrap = 2 * d_in, 2 ** 32 // (2 * d_in)
     for height in (48, 64, 80, 96):
         for R in (257, 300, 1000, wrap - 1, wrap, wrap + 1, wrap + 5, wrap + 100, wrap + 262, 2 * wrap + 50):
@@ -30,7 +35,32 @@ def test_rows_of_a_tile_are_their_own(last_row_offset, d_in):
                 if not 0 <= t < tiles:
                     continue
                 m0 = t * height
-                limit = last_row_offset(R, m0, height, row_bytes)
+                limit = lib.last_row_offset(R, m0, height, row_bytes)
                 for row in range(height):
                     off = min(row * row_bytes, limit)
                     assert off < 2 ** 31 and off % row_bytes == 0 and m0 + off // row_bytes == min(m0 + row, R - 1), (d_in, height, R, m0, row)
+
+
+@pytest.mark.parametrize("rows,n", [(1, 1), (3, 5), (4, 33), (5, 16), (8, 40), (9, 17), (15, 16), (16, 17), (17, 63), (34, 30), (50, 33)])
+def test_right_hand_sides_have_places_of_their_own(lib, rows, n):
+    n16, height = (n + 15) // 16 * 16, 4 if rows <= 4 else 8 if rows <= 8 else 16
+    places = {lib.at(j, l, rows, n) for j in range(rows) for l in range(n16)}
+    assert len(places) == rows * n16 and lib.bytes(rows, n) == 4 * n16 * ((rows + height - 1) // height * height) and 4 * max(places) < lib.bytes(rows, n)
+    for j in range(rows):                                  # quads are 16 bytes; 16 columns of a tile are in one piece, whatever the row
+        tile = j // height * height * n16
+        for l in range(0, n16, 4):
+            first = tile + l // 16 * height * 16 + (l // 4 % 4 * height + j % height) * 4
+            assert [lib.at(j, l + e, rows, n) for e in range(4)] == [first + e for e in range(4)]
+
+
+def test_right_hand_sides_and_products_fit_three_matrices(lib):
+    """An update's scratch beside its products: no more than three matrices in rows took, or than the megabyte that no scratch is smaller than (less what
+    else an update keeps there)."""
+    for rows in range(3, 1027):
+        for n in (1, 17, 100, 120, 241, 400, 895, 3584, 16369, 16384):
+            assert lib.bytes(rows, n) + 4 * rows * n <= max(3 * 4 * rows * n, 2 ** 20 - 16384)
+
+
+def test_right_hand_sides_past_4_gib(lib):
+    rows, n = 65536, 16384
+    assert lib.bytes(rows, n) == 2 ** 32 and lib.at(rows - 1, n - 1, rows, n) == 2 ** 30 - 1 and lib.at(65520, 0, rows, n) == 65520 * 16384
