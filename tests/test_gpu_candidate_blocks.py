@@ -29,3 +29,19 @@ def test_candidates_do_not_depend_on_their_number(essa, n):
     assert np.linalg.norm(theta.cpu().numpy() - want) <= 1e-6 * np.linalg.norm(want)      # fp32 sums over n
     cma.close()
     ctx.close()
+
+
+def test_candidates_past_a_descriptor(essa):
+    """More right-hand sides than a buffer descriptor's 2 GB: the last candidates are what they are on their own."""
+    ctx = essa.Context(0)
+    K, n = 32768 + 40, 16381
+    print("K=%d n=%d" % (K, n), flush=True)
+    cma = essa.CmaState(ctx, n, 0.32)
+    seeds = torch.arange(1, K + 1, dtype=torch.int32, device="cuda")
+    theta, few = torch.zeros(K, n, device="cuda"), torch.empty(4, n, device="cuda")
+    essa.essa_sample_candidates(ctx, cma, seeds, theta)
+    for k in (0, 16384, 32764, K - 4):
+        essa.essa_sample_candidates(ctx, cma, seeds[k:k + 4].contiguous(), few)
+        assert torch.equal(theta[k:k + 4], few) and few.abs().max().item() > 0, k
+    cma.close()
+    ctx.close()
