@@ -250,7 +250,7 @@ extern "C" void essa_proj_destroy(essa_proj* p) {
     if (!p) return;
     (void)hipSetDevice(p->device);
     (void)hipDeviceSynchronize();
-    void* ptrs[] = {p->Wq, p->scale, p->zero, p->VA32, p->VA16, p->UB32, p->UB16, p->M, p->Wt, p->VAp, p->St, p->SZ16, p->W16, p->E16, p->Wn, p->SZn};
+    void* ptrs[] = {p->Wq, p->scale, p->zero, p->VA32, p->VA16, p->UB32, p->UB16, p->M, p->Wt, p->VAp, p->St, p->SZ16, p->W16, p->E16, p->Wn};
     for (void* q : ptrs)
         if (q) (void)hipFree(q);
     delete p;
@@ -477,10 +477,11 @@ extern "C" essa_status essa_proj_create(essa_ctx* ctx, const essa_proj_desc* d, 
             }
         ESSA_TRY(upload(&p->St, St.data(), St.size()));
         ESSA_TRY(upload(&p->SZ16, SZ.data(), SZ.size()));
-        // exact-product kernel: the codes once more, in its own operand tiles
-        const size_t wn = (size_t)p->groups * nbs * 2048;
-        if (wn < (1u << 31) && room_for_copy(wn + SZn.size() * 2) && device_alloc((void**)&p->Wn, wn) == hipSuccess) {
-            ESSA_TRY(upload(&p->SZn, SZn.data(), SZn.size()));
+        // exact-product kernel: the codes once more, in its own operand tiles, and its zero-point operand: both or neither
+        const size_t wn = (size_t)p->groups * nbs * 2048, szn = SZn.size() * 2;
+        if (wn < (1u << 31) && room_for_copy(wn + szn) && device_alloc((void**)&p->Wn, wn + szn) == hipSuccess) {
+            p->SZn = (uint16_t*)(p->Wn + wn);
+            ESSA_HIP(hipMemcpy(p->SZn, SZn.data(), szn, hipMemcpyHostToDevice));
             ESSA_HIP(essa_k::repack_nibbles(nullptr, p->Wt, p->groups, nbs, p->Wn));
             ESSA_HIP(hipStreamSynchronize(nullptr));
         }                                          // otherwise the projection works without it, on the limb kernels

@@ -79,7 +79,7 @@ struct essa_proj {
     // 4-bit weights for the exact-product kernel: [groups][2 n_blocks][64 lanes][4 words], lane (kg, l16) word j of block (g, b) = the codes of
     // columns 128 g + 32 j + 8 kg .. + 7 of channel 16 b + l16; columns 2 i and 2 i + 1 of them at bits 3 + 4 i and 19 + 4 i (mod 32)
     uint8_t* Wn = nullptr;
-    uint16_t* SZn = nullptr;   // [2 n_blocks][ceil(groups/32)][3][4][16 channels][8 groups] -scale (zero + 16) 2^-5 as three bf16
+    uint16_t* SZn = nullptr;   // (in Wn's allocation) [2 n_blocks][ceil(groups/32)][3][4][16 channels][8 groups] -scale (zero + 16) 2^-5 as three bf16
     // int8 weights once more as bf16 (exact, times the channel's power of two), for the exact-product kernel: [ceil(d_in/64)][n_blocks][2][2][64 lanes][8],
     // block (kt, nb), half, sub-step j, lane (kg, l16) = channel 32 nb + 16 half + l16, columns 64 kt + 32 j + 8 kg .. + 7
     uint16_t* W16 = nullptr;

@@ -164,3 +164,47 @@ def test_q4_exact_rows_with_a_mean(essa, d_in):
         assert err[0] <= bar and err[0] <= err[1], (name, err, bar)
     gp.close()
     ctx.close()
+
+
+def test_q4_copy_leaves_half_of_the_card(essa):
+    """A 4-bit projection created while less than half of the card is free takes neither the copy of its codes (half a byte a weight) nor the operand that
+    goes with it, and works all the same, with the fixed point's error."""
+    ctx = essa.Context(0)
+    R, d_in, d_out, r, K = 600, 4096, 4096, 8, 3
+    p = wl.make_projection("t", d_in, d_out, r, "int4", layer=26, proj=1)
+    W, f = oracle_proj(p)
+    sA, sB = candidate_sigmas(f, K, 0.05)
+    xb, xv = wl.make_x_bf16(R, d_in, x_id=73)
+    r2c = np.random.default_rng(6).integers(0, K, R).astype(np.int32)
+    X, rd, sAd, sBd = bf16_dev(xb), to_dev(r2c), to_dev(sA), to_dev(sB)
+    Y = torch.empty(R, d_out, device="cuda")
+    sample = np.arange(0, R, 37)
+    ref = orc.svdlora_forward(W, f, xv[sample], r2c[sample], sA, sB)
+
+    def error(gp):
+        essa.essa_svdlora_forward(ctx, gp, X, rd, sAd, sBd, Y)
+        return orc.rel_errors(Y.cpu().numpy()[sample], ref)[1]
+
+    def create():
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info()[0]
+        gp = gpu_proj(essa, ctx, p)
+        return gp, before - torch.cuda.mem_get_info()[0]
+
+    roomy, with_copy = create()
+    assert error(roomy) <= Q4_RMS
+    free, total = torch.cuda.mem_get_info()
+    fill = [torch.empty(free - total // 2, dtype=torch.uint8, device="cuda")]
+    while torch.cuda.mem_get_info()[0] >= total // 2:
+        fill.append(torch.empty(64 << 20, dtype=torch.uint8, device="cuda"))
+    try:
+        tight, without = create()
+    finally:
+        del fill
+        torch.cuda.empty_cache()
+    assert with_copy - without >= d_in * d_out // 2
+    assert 1e-5 <= error(tight) <= 2e-4                     # the repository's bar for the fixed point
+    assert error(roomy) <= Q4_RMS                           # a copy that is there stays
+    tight.close()
+    roomy.close()
+    ctx.close()
