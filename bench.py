@@ -38,6 +38,8 @@ WORKLOADS = ["c2_7b_decode", "c3_32b_prefill", "c4_72b_decode", "c5_7b_es_iter"]
 DEFAULT_LAYERS = {"c2_7b_decode": 28, "c3_32b_prefill": 1, "c4_72b_decode": 80, "c5_7b_es_iter": 28}
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "c2_7b_decode_gemm_hbm_traffic.md")
 KERNEL_SOURCES = ["kernels_stream.hip"]
+# the library's rule for 4-bit weights: (columns from, rows above which the exact product takes them)
+Q4_EXACT_ABOVE = ((4097, 256), (3072, 511), (2048, 640), (1024, 1023), (0, 2303))
 
 
 def log(*a):
@@ -299,7 +301,7 @@ class Bench:
         few = (128 if self.hidden <= 4096 else 96) if self.forward_only else (64 if self.hidden >= 3072 else 0)
         if R <= few:
             return "gemm_q4_stream_kernel"
-        if R > (256 if self.hidden > 4096 else 511 if self.hidden >= 3072 else 640 if self.hidden >= 2048 else 1023 if self.hidden >= 1024 else 2303):
+        if R > next(rows for columns, rows in Q4_EXACT_ABOVE if self.hidden >= columns):
             return "gemm_q4_exact_kernel"
         return "gemm_q4_wide_kernel" if -(-R // 64) * col256 >= 256 else "gemm_i8_kernel<Q4>"
 

@@ -121,10 +121,11 @@ typedef struct essa_proj_desc {
     const float* lora_B;      /* float [d_out, r]                                                     */
 } essa_proj_desc;
 
-/* Device memory: two bytes per int8 weight (one and a quarter per 4-bit weight), and two more per int8 weight for the bf16 copy that
- * exact products read, while that leaves half of the card's memory free.  A projection created on a fuller card, with a channel scale
- * outside 2^-100 .. 2^100 or with more than 2 GB of such a copy works without it: by itself it then stays with the fixed point at
- * every row count, and ESSA_COMPUTE_BF16 takes the generic kernels. */
+/* Device memory: two bytes per int8 weight (one and a quarter per 4-bit weight), and a copy of the weights for exact products at
+ * prompt-sized row counts, two bytes per int8 weight and a little over half a byte per 4-bit weight, while that leaves half of the card's
+ * memory free.  A projection created on a fuller card, with a channel scale outside 2^-100 .. 2^100 (int8) or with more than 2 GB of such
+ * a copy works without it: by itself it then stays with the fixed point at every row count, so that its outputs there are other bits,
+ * off by that format's rounding, and ESSA_COMPUTE_BF16 takes the generic kernels (4-bit weights: always). */
 essa_status essa_proj_create(essa_ctx* ctx, const essa_proj_desc* desc, essa_proj** out);
 void essa_proj_destroy(essa_proj* proj);
 /* Copies the factors' own singular values S_A[r], S_B[r] (descending) to HOST arrays. */

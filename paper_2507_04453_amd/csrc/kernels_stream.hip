@@ -1482,8 +1482,9 @@ __global__ __launch_bounds__(NT, MB == 1 && !DEEP ? 4 : 1) void gemm_i8_stream_k
 // ------------------------------------------------------------------------------------------------
 // 4-bit weights at the row counts of the kernel above, on the same plan: one workgroup per block of 32 output channels and
 // block of 32 rows, the whole K; weights and limbs go memory -> MFMA operand registers.  A wave takes whole quantisation
-// groups, g = wave, wave + 8, ... (at most 8: rows of 8192 columns), asks for the weights two rounds ahead (six: 5120 wide 23.2 against 21.6 us
-// at 32 rows, the others within 2 %) and lets the limbs stream past, four chunks ahead of the MFMAs.
+// groups, g = wave, wave + 8, ... (at most 8: rows of 8192 columns), asks for the weights of two rounds in front of the loop and of one round ahead in it
+// (six and five, us a layer against this at 24 rows: 5120 wide 28.5 / 27.4, 6144 wide 28.1 / 27.1, 3584 wide 16.4 / 16.2) and lets the limbs stream past,
+// four chunks ahead of the MFMAs.
 // A group's integer sums have to be scaled before they are added to another group's, and a row's result must not depend on
 // the kernel that took it, so the groups' fp32 FMAs keep the tile kernels' order: after each round of 8 groups the waves leave
 // their sums (hi limb, shift, lo limb on top: the tile kernels' integer) in LDS, and every thread folds two outputs
@@ -1501,7 +1502,7 @@ constexpr int QS_PITCH = 16 * QS_ROUNDS * 2 + 16;          // LDS row of a zero-
 // columns take.  Half the limb loads, MFMAs, conversions, sums through LDS and folds; the same integers, the same FMAs in the same order.
 // A weight load of 64 columns (32 channels, low nibbles the first chunk, high ones the second) becomes the operands of channels 0..15
 // and 16..31 by exchanging the low codes of lanes 16..31 and 48..63 with the high codes of the lanes 16 below: the K order is then chunk 0, chunk 1
-// of the lower 16 columns, chunk 0, chunk 1 of the upper, and the limbs are loaded in that order too.  Weights go four rounds ahead
+// of the lower 16 columns, chunk 0, chunk 1 of the upper, and the limbs are loaded in that order too.  Four rounds' weights are asked for in front, three rounds ahead in the loop
 // (six: 3 % slower; two, and three workgroups a CU: 6 % faster at 8192, 8 % slower at 1024).  One layer with its prep launch, us, 32 x 32 / 16 x 16,
 // 1 to 16 rows: 8192 wide 36.6 / 30 (31.5 at 16 rows), 5120 wide 21.8 / 18.9, 3584 wide 15.7 / 13.4, 1024 wide 12.8 / 11.
 template <bool FEW> constexpr size_t q4s_buffer() { return FEW ? 8 * 2048 : 8 * 4096; }      // one round's sums
