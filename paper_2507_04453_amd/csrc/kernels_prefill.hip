@@ -735,7 +735,9 @@ __global__ __launch_bounds__(256, 2) void gemm_q4_exact_kernel(q4_args a) {
         for (int m = 0; m < NR; ++m) tot[n][m] = (f32x4){0.f, 0.f, 0.f, 0.f};
     {
         const int ch0 = nb0 * 32 + wave * (16 * NC) + l16, nc = it.Gn / 32;
-        bf16x8 z[2][NC], xs[2][NR];                        // 32 groups: head, and the third and then the second part in one place
+        // 32 groups, a place for every part, so that all are on their way before the steps' first loads: with the second and the third part in one place
+        // the second is another round trip a tile (q, k, v, o, two places / three: 1152 columns, 15442 rows 183.8 / 179.3 us; 3584, 6000 rows 326 / 324)
+        bf16x8 z[3][NC], xs[3][NR];
         const rsrc_t zres = make_rsrc(it.SZn), sumres = make_rsrc(it.XS16 + (size_t)(m0 / 16) * nc * 1536);
         uint32_t zoff[NC], sumoff[NR];                     // operand tiles of 16 channels or rows and 32 groups: a kilobyte per part
 #pragma unroll
@@ -744,12 +746,12 @@ __global__ __launch_bounds__(256, 2) void gemm_q4_exact_kernel(q4_args a) {
         for (int m = 0; m < NR; ++m) sumoff[m] = (uint32_t)min(m, (R - 1 - m0) / 16) * (uint32_t)nc * 3072u;
         auto ask_z = [&](int c, int p) {
 #pragma unroll
-            for (int n = 0; n < NC; ++n) z[p != 0][n] = __builtin_bit_cast(bf16x8, load16(zres, lane16, zoff[n] + c * 3072 + p * 1024));
+            for (int n = 0; n < NC; ++n) z[p][n] = __builtin_bit_cast(bf16x8, load16(zres, lane16, zoff[n] + c * 3072 + p * 1024));
         };
         auto ask_x = [&](int c, int p) {                   // eights past the last group: beyond the descriptor, zeros
             const uint32_t xlane = c * 32 + kg * 8 < ng ? lane16 : 0x80000000u;
 #pragma unroll
-            for (int m = 0; m < NR; ++m) xs[p != 0][m] = __builtin_bit_cast(bf16x8, load16(sumres, xlane, sumoff[m] + c * 3072 + p * 1024));
+            for (int m = 0; m < NR; ++m) xs[p][m] = __builtin_bit_cast(bf16x8, load16(sumres, xlane, sumoff[m] + c * 3072 + p * 1024));
         };
         auto multiply = [&](int pz, int px) {
 #pragma unroll
@@ -759,20 +761,20 @@ __global__ __launch_bounds__(256, 2) void gemm_q4_exact_kernel(q4_args a) {
             __builtin_amdgcn_sched_barrier(0);
         };
         auto chunk = [&](int c, auto last) {               // no branch around a load: the compiler has to count them
-            multiply(0, 1);
-            ask_x(c, 1);
-            multiply(1, 0);
-            ask_z(c, 1);
+            multiply(0, 2);
+            if constexpr (!last) ask_x(c + 1, 2);
+            multiply(2, 0);
+            if constexpr (!last) ask_z(c + 1, 2);
             multiply(0, 0);
             multiply(0, 1);
             if constexpr (!last) ask_z(c + 1, 0);
             multiply(1, 0);
             if constexpr (!last) ask_x(c + 1, 0);
             multiply(1, 1);
-            if constexpr (!last) ask_x(c + 1, 2), ask_z(c + 1, 2);
+            if constexpr (!last) ask_x(c + 1, 1), ask_z(c + 1, 1);
             __builtin_amdgcn_sched_barrier(0);
         };
-        ask_z(0, 0), ask_x(0, 2), ask_z(0, 2), ask_x(0, 0);
+        ask_z(0, 0), ask_x(0, 2), ask_z(0, 2), ask_x(0, 0), ask_x(0, 1), ask_z(0, 1);
         __builtin_amdgcn_sched_barrier(0);
         static_for<D - 1>([&](auto tc) {
             constexpr int t = tc;
