@@ -14,9 +14,9 @@
 // first-order corrections instead: V <- V + V E with E from S = V^T C V and R = I - V^T V (Ogita and Aishima, "Iterative
 // refinement for symmetric eigenvalue decomposition", 2018).  It converges quadratically like Jacobi's last sweeps and a
 // step is four products of n x n matrices that fill the chip.  Columns keep their places and signs either way.
-// Measured, n = 896: a sweep takes 3 ms, a step 0.13 to 0.15 ms (the products' fp64 MFMA time alone is 0.07); the refresh after
-// 8 generations of 36 candidates 12.3 -> 0.6 ms (3 or 4 steps in place of 4 sweeps), n = 3584 with nothing to do 15 -> 4.2 ms.
-#include "essa_internal.h"
+// Measured, n = 896: a sweep takes 3 ms, a step 0.11 to 0.13 ms (the products' fp64 MFMA time alone is 0.07); the refresh after
+// 8 generations of 36 candidates 12.3 -> 0.5 ms (3 or 4 steps in place of 4 sweeps), n = 3584 with nothing to do 15 -> 4.2 ms.
+#include "forward_device.h"
 #include <cmath>
 #include <cstring>
 #include <utility>
@@ -63,80 +63,99 @@ __global__ __launch_bounds__(256) void eig_init_kernel(const float* __restrict__
 // ---- products of whole matrices -----------------------------------------------------------------------------------
 // One 64 x 64 tile of X Y^T (NT: Y's row j is output column j) or X Y (NN) per workgroup of 8 waves, on the fp64 MFMA
 // 16x16x4: a wave owns a 32 x 32 patch for one half of every K chunk of 32, the halves are added through LDS at the end.  The
-// MFMA rate binds (64 cycles per MFMA, 128 flops per clock and CU; a chunk brings 32 KB in for 2048 of those cycles); two
-// waves per SIMD because at n of a few hundred there is one workgroup per CU and nobody else to hide LDS latency, and two chunks on
-// their way from memory, which a chunk's 0.85 us do not outlast (one: 45 us per product at n = 896, two: 43; refresh at n = 3584
-// after 17 generations 26.1 / 24.1 ms; fragments read a chunk ahead as well: 47 us, and one workgroup a CU fewer).  Pitches are
-// 4 (8) doubles mod 32, which spreads the 16 x 4 elements of an operand read evenly over the banks.
-constexpr int MK = 32, MP = 36, MQ = 72, MNT = 512;
-constexpr size_t MM_SMEM = 2 * 2 * (size_t)64 * MP * sizeof(double);
-static_assert(MK * MQ <= 64 * MP && (size_t)4 * 1024 * sizeof(double) <= MM_SMEM, "the chunks of Y and the wave halves fit");
+// MFMA rate binds (64 cycles per MFMA, 128 flops per clock and CU; a chunk brings 32 KB in for 2048 of those cycles: 26 us at n = 896, where
+// a CU has one tile), so everything else has to stay out of its way.  Chunks go from memory into LDS without passing through registers (a
+// ds_write of the same bytes costs 5 us a product), two stages, two workgroups a CU where there are enough tiles (three or four stages and one
+// workgroup: no faster at n = 896, 6 % slower at 1792).  An operand row of a chunk is 16 pieces of 16 bytes, piece p of row r at p ^ (r & 7): eight
+// lanes of a fragment read meet eight different pieces of the banks' 128 bytes (rows 36 doubles apart: 16 clocks for 512 bytes in place of
+// 4, as long as the MFMAs).  A piece is two k, so the MFMAs of a sub-step of 8 k take the even and the odd ones in turn, on both sides.  The
+// fragments of a sub-step are read under the MFMAs of the one before; the one barrier of a chunk sits between its two sub-steps.
+// Product, us (through registers, two barriers a chunk / this): n = 448 23.1 / 17.0, 896 45.9 / 33.9, 1792 264 / 214.
+constexpr int MK = 32, MS = 2, MNT = 512;
+constexpr uint32_t MSTAGE = 2 * 64 * MK * sizeof(double);
+constexpr size_t MM_SMEM = MS * (size_t)MSTAGE;
+static_assert((size_t)4 * 1024 * sizeof(double) <= MM_SMEM, "the wave halves fit");
 
 // acc: this wave's patch; complete (both K halves) in waves 0..3 only.  Element v of acc[a][b]: row 32 wr + 16 a + 4 v + lane / 16,
 // column 32 wc + 16 b + lane % 16, wr = (wave >> 1) & 1, wc = wave & 1.
 template <bool NN>
 __device__ __forceinline__ void tile_product(const double* __restrict__ X, const double* __restrict__ Y, int ld, int i0, int j0, double* lds, f64x4 (&acc)[2][2]) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, kq = lane >> 4;
-    const int wr = (wave >> 1) & 1, wc = wave & 1, kh = wave >> 2;
-    constexpr int STAGE = 2 * 64 * MP;
-    // two 16-byte pieces per thread and operand: rows of 32 k (16 pieces each) or, for NN's Y, 32 rows of 64 columns
     typedef __attribute__((ext_vector_type(2))) double f64x2;
-    struct piece { f64x2 x[2], y[2]; } one, two;           // two chunks on their way from memory
-    auto fetch = [&](int chunk, piece& p2) {
-        const int k0 = chunk * MK;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l16 = lane & 15, kq = lane >> 4;
+    const int wr = (wave >> 1) & 1, wc = wave & 1, kh = wave >> 2;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_byte*)lds;
+    unsigned char* smem = reinterpret_cast<unsigned char*>(lds);
+    // A wave moves four kilobytes of a chunk: 4 rows x 256 bytes of X, twice, and as much of Y (NN: 2 rows x 512 bytes, twice)
+    const int chunks = ld / MK, last = chunks - 1;         // even: ld is a multiple of 64
+    const i32x4 xres = buffer_words(X + (size_t)i0 * ld);
+    uint32_t off[2], yoff[2];
 #pragma unroll
-        for (int e = 0; e < 2; ++e) {
-            const int p = tid + MNT * e, row = p >> 4, c = (p & 15) * 2;
-            p2.x[e] = *reinterpret_cast<const f64x2*>(X + (size_t)(i0 + row) * ld + k0 + c);
-            if (NN) p2.y[e] = *reinterpret_cast<const f64x2*>(Y + (size_t)(k0 + (p >> 5)) * ld + j0 + (p & 31) * 2);
-            else p2.y[e] = *reinterpret_cast<const f64x2*>(Y + (size_t)(j0 + row) * ld + k0 + c);
-        }
-    };
-    auto put = [&](double* st, const piece& p2) {
+    for (int e = 0; e < 2; ++e) {
+        const int row = (wave * 2 + e) * 4 + (lane >> 4), at = (lane & 15) ^ (row & 7);
+        off[e] = (uint32_t)row * (uint32_t)ld * 8u + at * 16;
+        yoff[e] = NN ? (uint32_t)((wave * 2 + e) * 2 + (lane >> 5)) * (uint32_t)ld * 8u + (lane & 31) * 16 : off[e];
+    }
+    const i32x4 yres0 = buffer_words(Y + (size_t)j0 * ld);
+    auto fetch = [&](int chunk, uint32_t stage) {
+        const int c = min(chunk, last);
+        const i32x4 yres = NN ? buffer_words(Y + (size_t)c * MK * ld + j0) : yres0;
 #pragma unroll
-        for (int e = 0; e < 2; ++e) {
-            const int p = tid + MNT * e, row = p >> 4, c = (p & 15) * 2;
-            *reinterpret_cast<f64x2*>(st + row * MP + c) = p2.x[e];
-            if (NN) *reinterpret_cast<f64x2*>(st + 64 * MP + (p >> 5) * MQ + (p & 31) * 2) = p2.y[e];
-            else *reinterpret_cast<f64x2*>(st + 64 * MP + row * MP + c) = p2.y[e];
-        }
+        for (int e = 0; e < 2; ++e) load_lds16(lds0 + stage + (wave * 2 + e) * 1024, off[e], xres, (uint32_t)c * (MK * 8u));
+#pragma unroll
+        for (int e = 0; e < 2; ++e) load_lds16(lds0 + stage + 16384 + (wave * 2 + e) * 1024, yoff[e], yres, NN ? 0u : (uint32_t)c * (MK * 8u));
     };
 #pragma unroll
     for (int a = 0; a < 2; ++a)
 #pragma unroll
         for (int b = 0; b < 2; ++b) acc[a][b] = (f64x4){0.0, 0.0, 0.0, 0.0};
-    const int chunks = ld / MK;                            // even: ld is a multiple of 64
-    auto step = [&](int i, piece& p2) {                    // multiplies chunk i; p2 holds chunk i + 1
-        const int cur = i & 1;
-        const double* xs = lds + cur * STAGE + (32 * wr + l16) * MP + 16 * kh + kq;
-        const double* ys = lds + cur * STAGE + 64 * MP + (NN ? (16 * kh + kq) * MQ + 32 * wc + l16 : (32 * wc + l16) * MP + 16 * kh + kq);
-        double fx[4][2], fy[4][2];
+    // lane's pieces of a sub-step of 8 k: k = 2 kq, 2 kq + 1 of it (both operands alike)
+    uint32_t xat[2], yat[2];
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
-#pragma unroll
-            for (int a = 0; a < 2; ++a) {
-                fx[k][a] = xs[16 * a * MP + 4 * k];
-                fy[k][a] = NN ? ys[4 * k * MQ + 16 * a] : ys[16 * a * MP + 4 * k];
-            }
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-#pragma unroll
-            for (int a = 0; a < 2; ++a)
-#pragma unroll
-                for (int b = 0; b < 2; ++b) acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(fx[k][a], fy[k][b], acc[a][b], 0, 0, 0);
-        if (i + 1 < chunks) put(lds + (cur ^ 1) * STAGE, p2);
-        if (i + 3 < chunks) fetch(i + 3, p2);
-        __syncthreads();
-    };
-    fetch(0, one);
-    fetch(1, two);
-    put(lds, one);
-    if (chunks > 2) fetch(2, one);
-    __syncthreads();
-    for (int i = 0; i < chunks; i += 2) {
-        step(i, two);
-        step(i + 1, one);
+    for (int u = 0; u < 2; ++u) {
+        const uint32_t at = (uint32_t)((8 * kh + 4 * u + kq) ^ (l16 & 7)) * 16;
+        xat[u] = (32 * wr + l16) * 256 + at;
+        yat[u] = 16384 + (NN ? (16 * kh + 8 * u + 2 * kq) * 512 + (32 * wc + l16) * 8 : (32 * wc + l16) * 256 + at);
     }
+    f64x2 fx[2][2], fy[2][2];
+    auto read = [&](uint32_t stage, int u) {
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+            fx[u][a] = *reinterpret_cast<const f64x2*>(smem + stage + xat[u] + a * 4096);
+            if (NN) {
+                fy[u][a][0] = *reinterpret_cast<const double*>(smem + stage + yat[u] + a * 128);
+                fy[u][a][1] = *reinterpret_cast<const double*>(smem + stage + yat[u] + a * 128 + 512);
+            } else fy[u][a] = *reinterpret_cast<const f64x2*>(smem + stage + yat[u] + a * 4096);
+        }
+    };
+    auto multiply = [&](int u, int e) {
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int b = 0; b < 2; ++b) acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(fx[u][a][e], fy[u][b][e], acc[a][b], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    uint32_t cur = 0, nxt = MSTAGE;
+#pragma unroll
+    for (int i = 0; i < MS; ++i) fetch(i, i * MSTAGE);
+    wait_loads_and_meet<(MS - 1) * 4>();
+    read(0, 0);
+    for (int i = 0; i < chunks; ++i) {
+        read(cur, 1);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(0, 0);
+        multiply(0, 1);
+        wait_loads_and_meet<(MS - 2) * 4>();               // chunk i + 1 is there, and everybody has read chunk i
+        __builtin_amdgcn_sched_barrier(0);
+        read(nxt, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(1, 0);
+        fetch(i + MS, cur);                                // past the end the last chunk again, for nobody
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(1, 1);
+        cur = nxt;
+        nxt = nxt == (MS - 1) * MSTAGE ? 0 : nxt + MSTAGE;
+    }
+    wait_loads_and_meet<0>();                              // what was asked for past the end has landed
     // the second K halves join the first
     double* half = lds + (size_t)(wave & 3) * 1024 + lane;
     if (kh == 1) {

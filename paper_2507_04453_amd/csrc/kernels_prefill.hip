@@ -37,34 +37,6 @@ struct prefill_args {
     int Gn[ESSA_MAX_GROUP];                // groups rounded up to 32
 };
 
-// ---- loads that go from memory into LDS without passing through registers ------------------------------------------
-// A wave instruction moves 64 x 16 bytes: lane i's 16 bytes land at lds + 16 i, so the order in LDS is fixed and any
-// permutation is made by the lanes' global addresses.  Written as one asm block because the compiler, which cannot tell
-// the LDS stages apart, would otherwise wait for every such load in front of every LDS read; the waits are placed by hand.
-typedef __attribute__((address_space(3))) unsigned char lds_byte;
-__device__ __forceinline__ void load_lds16(uint32_t lds, uint32_t lane_off, i32x4 rsrc, uint32_t scalar_off) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                 :: "s"(lds), "v"(lane_off), "s"(rsrc), "s"(scalar_off) : "memory", "m0");
-}
-// the same with 4 bytes a lane
-__device__ __forceinline__ void load_lds4(uint32_t lds, uint32_t lane_off, i32x4 rsrc, uint32_t scalar_off) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds"
-                 :: "s"(lds), "v"(lane_off), "s"(rsrc), "s"(scalar_off) : "memory", "m0");
-}
-__device__ __forceinline__ i32x4 buffer_words(const void* base) {
-    const uint64_t p = reinterpret_cast<uint64_t>(base);
-    i32x4 r;
-    r[0] = __builtin_amdgcn_readfirstlane((int)(uint32_t)p);
-    r[1] = __builtin_amdgcn_readfirstlane((int)(uint32_t)(p >> 32)) & 0xffff;
-    r[2] = 0x7fffffff;
-    r[3] = 0x00020000;
-    return r;
-}
-template <int N> __device__ __forceinline__ void wait_loads_and_meet() {
-    // all but the last N loads of this wave have landed, this wave's LDS reads are done, and so are everybody else's
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(N) : "memory");
-}
-
 // f(0), f(1), ... f(N - 1) with the index as a compile-time constant: the K loops are one straight-line schedule
 template <class F, int... I>
 __device__ __forceinline__ void static_for_seq(F&& f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
