@@ -834,10 +834,11 @@ __device__ __forceinline__ void store_ctile(const unsigned char* ctile, const st
     }
 }
 
-// 4-bit weights, 64-row tile: registers capped at 128 so that two workgroups share a CU (what spills is the epilogue's
-// operands, across the main loop)
+// Registers capped at 128, so that two workgroups share a CU, for the 64-row tile of 4-bit weights (what spills is the epilogue's
+// operands, across the main loop) and for the 32-row tiles: with one limb the compiler took 132, and the 384 tiles of a 5120-wide layer at 97
+// rows ran one after another (39 -> 20 us a launch).
 template <int MB, int LIMBS, bool YBF16, bool DUMP, bool Q4>
-__global__ __launch_bounds__(NT, (Q4 && MB == 2) ? 4 : 1) void gemm_i8_kernel(stream_args a, int32_t* __restrict__ acc_out) {
+__global__ __launch_bounds__(NT, (Q4 && MB == 2) || MB == 1 ? 4 : 1) void gemm_i8_kernel(stream_args a, int32_t* __restrict__ acc_out) {
     constexpr int BM = 32 * MB;
     constexpr int XTOT = LIMBS * BM * 8;               // 16-byte vectors of X per K tile
     constexpr int XV = (XTOT + NT - 1) / NT;
@@ -2427,17 +2428,23 @@ hipError_t launch_gemm_mb(hipStream_t st, stream_args& a, int mb) {
     }
 }
 
-// rows per tile: the largest of 128/64 that still leaves every CU a tile, else 32
+// Row blocks per tile.  Two blocks where the tile would not be more than half empty and, with 4-bit weights, there is one for every CU;
+// with int8 weights by what a CU with the most tiles needs for them: a tile of 64 rows takes 1.55 (one limb: 1.25) times as long as one of 32, two of
+// which share a CU.  us a layer (q, k, v, o), 32 / 64 rows:
+//   two limbs  3584 wide 21.0 / 24.2 at 128 rows, 28.5 / 26.2 at 256, 39.5 / 41.9 at 320; 5120 wide 33.2 / 33.0 at 128, 37.0 / 51.4 at 160, 51.4 / 53.8 at 256,
+//              65.5 / 58.9 at 320; 8192 wide 46.0 / 69.7 at 65, 88.7 / 101 at 200, 107 / 103 at 256
+//   one limb   3584 wide 18.7 / 20.6 at 128, 24.1 / 21.9 at 256, 33.1 / 28.0 at 320; 5120 wide 27.5 / 26.3 at 97, 30.4 / 33.1 at 160, 41.0 / 34.7 at 256;
+//              8192 wide 38.7 / 49.1 at 65, 53.4 / 45.1 at 97, 68.9 / 66.7 at 200
 int pick_mb(const stream_args& a) {
-    int maxR = 0;
-    for (int g = 0; g < a.n_items; ++g) maxR = a.it[g].R > maxR ? a.it[g].R : maxR;
-    for (int mb : {2}) {
-        if (maxR <= 16 * mb) continue;     // tile would be more than half empty
-        long long tiles = 0;
-        for (int g = 0; g < a.n_items; ++g) tiles += (long long)((a.it[g].R + 32 * mb - 1) / (32 * mb)) * ((a.it[g].n_blocks + 3) / 4);
-        if (tiles >= 256) return mb;
-    }
-    return 1;     // fewer tiles than CUs either way: the 32-row tile gives twice as many workgroups and loads less per K tile
+    if (stream_rows(a) <= 32) return 1;
+    const auto tiles = [&](int mb) {
+        long long t = 0;
+        for (int g = 0; g < a.n_items; ++g) t += (long long)((a.it[g].R + 32 * mb - 1) / (32 * mb)) * ((a.it[g].n_blocks + 3) / 4);
+        return t;
+    };
+    if (a.it[0].quant == ESSA_QUANT_INT4_G128) return tiles(2) >= 256 ? 2 : 1;
+    const auto per_cu = [&](int mb) { return (tiles(mb) + 255) / 256; };
+    return per_cu(2) * (a.limbs == 2 ? 31 : 25) <= per_cu(1) * 20 ? 2 : 1;
 }
 
 // 4-bit weights: rows per 256-channel tile, 0 = the group is too small for these tiles.  (32-row tiles of the same
