@@ -512,7 +512,7 @@ extern "C" void essa_cma_destroy(essa_cma* c) {
     if (!c) return;
     (void)hipSetDevice(c->device);
     (void)hipDeviceSynchronize();
-    void* ptrs[] = {c->m, c->p_sigma, c->p_c, c->D, c->C, c->B, c->Cdiag, c->sc, c->weights, c->eigV};
+    void* ptrs[] = {c->m, c->p_sigma, c->p_c, c->D, c->C, c->B, c->Cdiag, c->Cturn, c->sc, c->weights, c->eigV};
     for (void* q : ptrs)
         if (q) (void)hipFree(q);
     delete c;
@@ -550,6 +550,8 @@ extern "C" essa_status essa_cma_create_opt(essa_ctx* ctx, int n, float sigma0, c
         for (int i = 0; i < n; ++i) eye[(size_t)i * n + i] = 1.f;
         ESSA_TRY(upload(&c->C, eye.data(), eye.size()));
         ESSA_TRY(upload(&c->B, eye.data(), eye.size()));
+        const std::vector<int32_t> turn(essa_k::cma_turn_bytes(n) / sizeof(int32_t), 1);
+        ESSA_TRY(upload(&c->Cturn, turn.data(), turn.size()));
     } else {
         ESSA_TRY(upload(&c->Cdiag, ones.data(), (size_t)n));
     }
@@ -627,6 +629,7 @@ extern "C" essa_status essa_cma_import(essa_cma* c, const void* blob, size_t byt
         ESSA_HIP(hipMemcpy(c->C, src, n * n * sizeof(float), hipMemcpyHostToDevice));
         src += n * n * sizeof(float);
         ESSA_HIP(hipMemcpy(c->B, src, n * n * sizeof(float), hipMemcpyHostToDevice));
+        ESSA_HIP(essa_k::cma_look_symmetric(c->stream, c->C, c->n, c->Cturn));
     } else {
         ESSA_HIP(hipMemcpy(c->Cdiag, src, n * sizeof(float), hipMemcpyHostToDevice));
     }
@@ -1160,6 +1163,6 @@ extern "C" essa_status essa_cmaes_update(essa_ctx* ctx, essa_cma* cma, const uin
     if (cma->kind == ESSA_OPT_ACTIVE_CMA) ESSA_HIP(essa_k::row_norms2(ctx->stream, Z, c.ny, n, zn2));
     ESSA_HIP(essa_k::skinny_gemm_nt(ctx->stream, S, (int)rows, cma->B, n, nullptr, nullptr, 0, BY));
     ESSA_HIP(essa_k::cma_vectors(ctx->stream, c, cma->weights, BY, cma->m, cma->p_sigma, cma->p_c, cma->sc, order, order_out));
-    ESSA_HIP(essa_k::cma_covariance(ctx->stream, c, cma->weights, BY, cma->p_c, cma->sc, cma->kind == ESSA_OPT_ACTIVE_CMA ? zn2 : nullptr, cma->C));
+    ESSA_HIP(essa_k::cma_covariance(ctx->stream, c, cma->weights, BY, cma->p_c, cma->sc, cma->kind == ESSA_OPT_ACTIVE_CMA ? zn2 : nullptr, cma->Cturn, cma->C));
     return ESSA_OK;
 }

@@ -107,6 +107,7 @@ struct essa_cma {
     int ars_top = 0;
     float *m = nullptr, *p_sigma = nullptr, *p_c = nullptr, *D = nullptr, *C = nullptr, *B = nullptr;
     float* Cdiag = nullptr;    // [n] diagonal of C (kinds without a matrix)
+    int32_t* Cturn = nullptr;  // [tiles of 64 of C, squared] not 0 in (I, J), I <= J: tile (J, I) of C is (I, J) turned over, bit for bit (updates keep it so)
     essa_cma_scalars* sc = nullptr;
     float* weights = nullptr;  // device [mu] (active CMA: [K]) for weights_K
     int weights_K = 0;
@@ -168,7 +169,10 @@ hipError_t cma_vectors(hipStream_t st, const cma_consts& c, const float* w, cons
                        float* m, float* p_sigma, float* p_c, essa_cma_scalars* sc, const int32_t* order, int32_t* order_out);
 // zn2: [ny] squared lengths of the sorted z (read for negative weights only), or null
 hipError_t cma_covariance(hipStream_t st, const cma_consts& c, const float* w, const float* BY, const float* p_c,
-                          const essa_cma_scalars* sc, const float* zn2, float* C);
+                          const essa_cma_scalars* sc, const float* zn2, const int32_t* turn, float* C);
+// which tiles of C mirror one another (essa_cma::Cturn)
+hipError_t cma_look_symmetric(hipStream_t st, const float* C, int n, int32_t* turn);
+inline size_t cma_turn_bytes(int n) { return (size_t)((n + 63) / 64) * ((n + 63) / 64) * sizeof(int32_t); }
 // out[j] = |Z[j, :]|^2, fp64 sum in a fixed order
 hipError_t row_norms2(hipStream_t st, const float* Z, int J, int n, float* out);
 // diagonal covariance: Cd <- decay Cd + c_1 p_c^2 + c_mu sum_i w_i y_i^2, D <- sqrt(Cd)   (Y rows 0..mu-1)

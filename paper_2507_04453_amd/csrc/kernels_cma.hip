@@ -140,81 +140,123 @@ __global__ __launch_bounds__(1024) void cma_vectors_kernel(essa_k::cma_consts c,
     }
 }
 
-// C <- a C + c_1 p_c p_c^T + c_mu sum_i w_i y_i y_i^T on one 64x64 tile per workgroup.
+// C <- a C + c_1 p_c p_c^T + c_mu sum_i w_i y_i y_i^T on one 64x64 tile per workgroup, 16 rows a wave, the terms four at a time on the fp32 MFMA
+// 16x16x4, operands straight from memory (they are in the L2; through LDS, a tile's terms cost as long as its bytes).  The MFMA's row dimension
+// runs along C's columns, so that a lane's four results are four neighbours of a row of C.
 // Every rank-one term enters as (s sqrt|coef| v)(sqrt|coef| v)^T, s the sign of its weight, so that C stays exactly
 // symmetric.  A negative weight (tutorial, Eq. 46-47) is first rescaled by n / |C^-1/2 y|^2 = n / |z|^2.
-constexpr int CV_T = 64, CV_CH = 32;
+// HBM binds: C read and written.  A tile above the diagonal that mirrors the one below is read alone and leaves a second time, turned over
+// through LDS: three quarters of the bytes, half the sums (n = 3584, 17 terms: 27.2 -> 23.1 us).
+// 72 registers let 7 workgroups share a CU: at n = 3584 all 1596 are there at once (5 of them: 24.2 us; 8, with operands spilled: no faster).  A pair of tiles that a blob brought with
+// different bits keeps them: both are read.
+constexpr int CV_T = 64, CV_P = CV_T + 4;
 typedef float quad __attribute__((ext_vector_type(4), aligned(4)));
-__global__ __launch_bounds__(256) void cma_cov_kernel(essa_k::cma_consts c, const float* __restrict__ w, const float* __restrict__ BY,
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+__global__ __launch_bounds__(256, 7) void cma_cov_kernel(essa_k::cma_consts c, const float* __restrict__ w, const float* __restrict__ BY,
                                                      const float* __restrict__ p_c, const essa_cma_scalars* __restrict__ sc,
-                                                     const float* __restrict__ zn2, float* __restrict__ C) {
-    __shared__ __attribute__((aligned(16))) float Vi[CV_CH][CV_T], Vj[CV_CH][CV_T];
-    __shared__ float coef[CV_CH], csign[CV_CH];
+                                                     const float* __restrict__ zn2, const int32_t* __restrict__ turns, float* __restrict__ C) {
+    __shared__ __attribute__((aligned(16))) float turned[CV_T * CV_P];
+    const bool both = turns[min(blockIdx.x, blockIdx.y) * gridDim.x + max(blockIdx.x, blockIdx.y)] != 0, turn = both && blockIdx.x > blockIdx.y;
+    if (both && blockIdx.x < blockIdx.y) return;
     const int n = c.n, mu = c.ny;
     const int i0 = blockIdx.y * CV_T, j0 = blockIdx.x * CV_T;
-    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    float acc[4][4] = {};
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, kq = lane >> 4;
+    const int i = i0 + 16 * wave + l16, ic = min(i, n - 1);
     // the tile of C is asked for first: it comes from HBM while the rank-one terms are added up
-    const int j = j0 + tx * 4;
-    const bool vec = j + 3 < n;                            // 16-byte accesses need 4-byte alignment only: any n
     quad cold[4];
 #pragma unroll
-    for (int x = 0; x < 4; ++x) {
-        const int i = i0 + ty * 4 + x;
-        cold[x] = quad{0.f, 0.f, 0.f, 0.f};
-        if (vec && i < n) cold[x] = *reinterpret_cast<const quad*>(C + (size_t)i * n + j);
+    for (int b = 0; b < 4; ++b) {
+        const int j = j0 + 16 * b + 4 * kq;                // 16-byte accesses need 4-byte alignment only: any n
+        cold[b] = quad{0.f, 0.f, 0.f, 0.f};
+        if (j + 3 < n) cold[b] = *reinterpret_cast<const quad*>(C + (size_t)ic * n + j);
     }
-    const int nvec = mu + 1;   // vector mu is p_c with coefficient c_1
-    for (int v0 = 0; v0 < nvec; v0 += CV_CH) {
-        __syncthreads();
-        if (threadIdx.x < CV_CH) {
-            const int v = v0 + threadIdx.x;
-            float wv = v < mu ? w[v] : 0.f;
-            if (wv < 0.f) wv = wv * (float)n / zn2[v];
-            coef[threadIdx.x] = v < mu ? sqrtf(c.c_mu * fabsf(wv)) : (v == mu ? sqrtf(c.c_1) : 0.f);
-            csign[threadIdx.x] = wv < 0.f ? -1.f : 1.f;
-        }
-        __syncthreads();
-        for (int idx = threadIdx.x; idx < CV_CH * CV_T; idx += 256) {
-            const int vv = idx / CV_T, e = idx % CV_T, v = v0 + vv;
-            float a = 0.f, b = 0.f;
-            if (v < nvec) {
-                const float* src = v < mu ? BY + (size_t)v * n : p_c;
-                if (i0 + e < n) a = csign[vv] * (coef[vv] * src[i0 + e]);
-                if (j0 + e < n) b = coef[vv] * src[j0 + e];
-            }
-            Vi[vv][e] = a;
-            Vj[vv][e] = b;
-        }
-        __syncthreads();
-        const int lim = min(CV_CH, nvec - v0);
-        for (int vv = 0; vv < lim; ++vv) {
-            const float4 a = *reinterpret_cast<const float4*>(&Vi[vv][ty * 4]);
-            const float4 b = *reinterpret_cast<const float4*>(&Vj[vv][tx * 4]);
-            const float av[4] = {a.x, a.y, a.z, a.w}, bv[4] = {b.x, b.y, b.z, b.w};
+    f32x4 acc[4];
 #pragma unroll
-            for (int x = 0; x < 4; ++x)
+    for (int b = 0; b < 4; ++b) acc[b] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    int cj[4];
 #pragma unroll
-                for (int y = 0; y < 4; ++y) acc[x][y] = fmaf(av[x], bv[y], acc[x][y]);
+    for (int b = 0; b < 4; ++b) cj[b] = min(j0 + 16 * b + l16, n - 1);
+    auto add = [&](float coef, float sign, float ti, const float (&tj)[4]) {
+        const float a = sign * (coef * ti);
+#pragma unroll
+        for (int b = 0; b < 4; ++b) acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(coef * tj[b], a, acc[b], 0, 0, 0);
+    };
+    constexpr int AT_ONCE = 2;                             // steps of four terms whose operands are asked for together
+    for (int v0 = 0; v0 < mu; v0 += 4 * AT_ONCE) {
+        float wv[AT_ONCE], zz[AT_ONCE], ti[AT_ONCE], tj[AT_ONCE][4];
+#pragma unroll
+        for (int s = 0; s < AT_ONCE; ++s) {
+            const int v = min(v0 + 4 * s + kq, mu - 1), row = v * n;      // at most 1024 rows of 16384
+            wv[s] = w[v];
+            zz[s] = zn2 ? zn2[v] : 1.f;
+            ti[s] = BY[row + ic];
+#pragma unroll
+            for (int b = 0; b < 4; ++b) tj[s][b] = BY[row + cj[b]];
         }
+#pragma unroll
+        for (int s = 0; s < AT_ONCE; ++s) {
+            const bool live = v0 + 4 * s + kq < mu;        // past the last term: zeros, whatever its elements are
+            const float weight = wv[s] < 0.f ? wv[s] * (float)n / zz[s] : wv[s], sign = weight < 0.f ? -1.f : 1.f;
+            float t[4];
+#pragma unroll
+            for (int b = 0; b < 4; ++b) t[b] = live ? tj[s][b] : 0.f;
+            add(live ? sqrtf(c.c_mu * fabsf(weight)) : 0.f, sign, live ? ti[s] : 0.f, t);
+        }
+    }
+    {
+        float t[4];
+#pragma unroll
+        for (int b = 0; b < 4; ++b) t[b] = kq == 0 ? p_c[cj[b]] : 0.f;
+        add(sqrtf(c.c_1), 1.f, kq == 0 ? p_c[ic] : 0.f, t);
     }
     const float hs = sc->h_sigma;
     const float decay = 1.0f - c.c_1 - c.c_mu * c.w_sum + (1.0f - hs) * c.c_1 * c.c_c * (2.0f - c.c_c);
 #pragma unroll
-    for (int x = 0; x < 4; ++x) {
-        const int i = i0 + ty * 4 + x;
-        if (i >= n) continue;
-        if (vec) {
-            quad cv = cold[x];
+    for (int b = 0; b < 4; ++b) {
+        const int j = j0 + 16 * b + 4 * kq;
+        float* at = C + (size_t)ic * n + j;
+        if (i < n && j + 3 < n) {
+            quad cv = cold[b];
 #pragma unroll
-            for (int y = 0; y < 4; ++y) cv[y] = decay * cv[y] + acc[x][y];
-            *reinterpret_cast<quad*>(C + (size_t)i * n + j) = cv;
-        } else {
+            for (int q = 0; q < 4; ++q) cv[q] = decay * cv[q] + acc[b][q];
+            *reinterpret_cast<quad*>(at) = cv;
+            if (turn) {
 #pragma unroll
-            for (int y = 0; y < 4; ++y)
-                if (j + y < n) C[(size_t)i * n + j + y] = decay * C[(size_t)i * n + j + y] + acc[x][y];
+                for (int q = 0; q < 4; ++q) turned[(16 * b + 4 * kq + q) * CV_P + 16 * wave + l16] = cv[q];
+            }
+        } else if (i < n) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (j + q < n) {
+                    const float cv = decay * at[q] + acc[b][q];
+                    at[q] = cv;
+                    if (turn) turned[(16 * b + 4 * kq + q) * CV_P + 16 * wave + l16] = cv;
+                }
         }
     }
+    if (!turn) return;                                     // the same for the whole workgroup
+    __syncthreads();
+    // row j0 + r of the turned tile: 64 columns from i0 on, all of them below n since i0 < j0
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        const int r = (threadIdx.x >> 4) + 16 * t, at = (threadIdx.x & 15) * 4;
+        if (j0 + r < n) *reinterpret_cast<quad*>(C + (size_t)(j0 + r) * n + i0 + at) = *reinterpret_cast<const f32x4*>(turned + r * CV_P + at);
+    }
+}
+
+// Bits, so that a NaN or a signed zero decides too.
+__global__ __launch_bounds__(256) void cma_look_symmetric_kernel(const uint32_t* __restrict__ C, int n, int32_t* __restrict__ turns) {
+    __shared__ uint32_t T[64][65];
+    if (blockIdx.x < blockIdx.y) return;
+    const int i0 = blockIdx.y * 64, j0 = blockIdx.x * 64;
+    for (int e = threadIdx.x; e < 4096; e += 256)
+        if (j0 + (e >> 6) < n && i0 + (e & 63) < n) T[e >> 6][e & 63] = C[(size_t)(j0 + (e >> 6)) * n + i0 + (e & 63)];
+    __syncthreads();
+    int differ = 0;
+    for (int e = threadIdx.x; e < 4096; e += 256)
+        if (i0 + (e >> 6) < n && j0 + (e & 63) < n) differ |= C[(size_t)(i0 + (e >> 6)) * n + j0 + (e & 63)] != T[e & 63][e >> 6];
+    differ = __syncthreads_or(differ);
+    if (threadIdx.x == 0) turns[blockIdx.y * gridDim.x + blockIdx.x] = !differ;
 }
 
 // out[j] = |Z[j, :]|^2.  One workgroup per row, fp64, fixed tree.
@@ -336,9 +378,15 @@ hipError_t cma_vectors(hipStream_t st, const cma_consts& c, const float* w, cons
 }
 
 hipError_t cma_covariance(hipStream_t st, const cma_consts& c, const float* w, const float* BY, const float* p_c,
-                          const essa_cma_scalars* sc, const float* zn2, float* C) {
+                          const essa_cma_scalars* sc, const float* zn2, const int32_t* turn, float* C) {
     dim3 grid((c.n + CV_T - 1) / CV_T, (c.n + CV_T - 1) / CV_T);
-    hipLaunchKernelGGL(cma_cov_kernel, grid, dim3(256), 0, st, c, w, BY, p_c, sc, zn2, C);
+    hipLaunchKernelGGL(cma_cov_kernel, grid, dim3(256), 0, st, c, w, BY, p_c, sc, zn2, turn, C);
+    return hipGetLastError();
+}
+
+hipError_t cma_look_symmetric(hipStream_t st, const float* C, int n, int32_t* turn) {
+    dim3 grid((n + 63) / 64, (n + 63) / 64);
+    hipLaunchKernelGGL(cma_look_symmetric_kernel, grid, dim3(256), 0, st, reinterpret_cast<const uint32_t*>(C), n, turn);
     return hipGetLastError();
 }
 

@@ -1,0 +1,47 @@
+"""The covariance update reads one of two tiles that mirror one another and writes both; a pair that a blob brought with different bits is read whole."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def essa():
+    import paper_2507_04453_amd as m
+    return m
+
+
+# around the 64 x 64 tiles; 40 candidates of the active kind are 41 terms, more than one round of them
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 130, 203])
+@pytest.mark.parametrize("kind,K", [("cma", 12), ("active", 40)])
+def test_halves_give_the_bits_of_the_whole(essa, n, kind, K):
+    g = np.random.default_rng(n)
+    opt = {"cma": essa.OPT_CMA, "active": essa.OPT_ACTIVE_CMA}[kind]
+    A = g.standard_normal((n, n)) / np.sqrt(n)
+    C = (np.eye(n) + 0.1 * (A + A.T)).astype(np.float32)
+    C = np.triu(C) + np.triu(C, 1).T
+    z = np.zeros(n, np.float32)
+    at = (n - 1, n // 3)                                   # below the diagonal, where there is one
+    ctx = essa.Context(0)
+    out = []
+    for odd in (False, True):
+        C1 = C.copy()
+        if odd and n > 1:
+            C1[at] += np.float32(0.25)
+        cma = essa.CmaState(ctx, n, 0.32, kind=opt)
+        cma.import_blob(essa.CmaState.pack_blob(n, 3, 0.5, z, z, z, np.ones(n, np.float32), C1, np.eye(n, dtype=np.float32), kind=opt))
+        for i in range(3):
+            seeds = torch.arange(1 + 100 * i, K + 1 + 100 * i, dtype=torch.int32, device="cuda")
+            essa.essa_cmaes_update(ctx, cma, seeds, torch.sin(seeds.float() * 1.7), torch.empty(K, dtype=torch.int32, device="cuda"))
+        out.append(cma.export()["C"])
+        cma.close()
+    ctx.close()
+    half, whole = out
+    assert np.array_equal(half, half.T) and not np.array_equal(half, C)
+    if n > 1:
+        # the odd element has kept of its 0.25 what three updates' factors 1 - c_1 - c_mu (sum of weights) leave: almost all from n = 63 on, where the rates
+        # are a few per cent at most (with negative weights a factor may be a little above 1), and at n = 2, where they add up to less than 1, something
+        assert (0.0 if n == 2 else 0.2) < whole[at] - half[at] < 0.26
+        whole[at] = half[at]
+    assert np.array_equal(half, whole)
