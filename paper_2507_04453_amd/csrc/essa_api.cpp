@@ -669,7 +669,11 @@ extern "C" essa_status essa_sample_candidates(essa_ctx* ctx, const essa_cma* cma
     int some = K;
     if (essa_k::tiled_rows_bytes(K, n) > ctx->ws_bytes && align256((size_t)K * n * sizeof(float)) <= ctx->ws_bytes && (ctx->capturing || !ctx->graphs.empty()))
         some = std::min<size_t>(K, ctx->ws_bytes / essa_k::tiled_rows_bytes(16, n) * 16);
-    ESSA_TRY(essa_ws_reserve(ctx, essa_k::tiled_rows_bytes(some, n)));
+    ESSA_TRY(essa_ws_reserve(ctx, essa_k::tiled_rows_bytes(some, n)));      // for a small n too: what a recording refuses does not hang on n
+    if (essa_k::sample_small(ctx->stream, seeds, K, n, cma->m, cma->B, cma->D, cma->sc, theta_out, z_out)) {
+        ESSA_HIP(hipGetLastError());
+        return ESSA_OK;
+    }
     float* S = (float*)ctx->ws;
     for (int k = 0; k < K; k += some) {
         const int count = std::min(some, K - k);

@@ -135,6 +135,9 @@ hipError_t normals_tiled(hipStream_t st, const uint32_t* seeds, const int32_t* s
 // an update's right-hand sides in one launch (rows as for cma_build_rhs, tiles; ny <= 64 of them gain by it); Z null or [ny, n]
 hipError_t update_rhs(hipStream_t st, const uint32_t* seeds, const int32_t* sel, int ny, int mu, int n, const float* w, const float* D, float* S,
                       float* Z, const float* rank_F, int rank_K, int32_t* rank_order);
+// theta = m + sigma B D z in one launch, for small n; false: nothing launched, n is too large
+bool sample_small(hipStream_t st, const uint32_t* seeds, int K, int n, const float* m, const float* B, const float* D, const essa_cma_scalars* sc, float* theta,
+                  float* z_out);
 // theta[k, l] = m[l] + s_k sigma (D ? D[l] : 1) z[l];  pairs: candidate k uses seeds[k / 2] and s_k = +1, -1, else seeds[k], +1
 hipError_t sample_diag(hipStream_t st, const uint32_t* seeds, int K, int n, const float* m, const float* D,
                        const essa_cma_scalars* sc, int pairs, float* theta, float* z_out);

@@ -718,8 +718,10 @@ __global__ __launch_bounds__(1024) void rowpart_sum_kernel(const float* __restri
 }
 
 // F[k] += (sum over the rows of candidate k, and over the G slices of each row in ascending order) / (number of rows)
-__global__ __launch_bounds__(256) void cand_mean_sliced_kernel(const double* __restrict__ rowsum, int G, const int32_t* __restrict__ row2cand, int R,
-                                                              float* __restrict__ F) {
+// PARTS: the rows' sums are taken here, over at most 16 blocks (G of them), in the order and with the bits of rowpart_sum_kernel
+template <bool PARTS>
+__global__ __launch_bounds__(256) void cand_mean_sliced_kernel(const double* __restrict__ rowsum, const float* __restrict__ rowpart, int G,
+                                                              const int32_t* __restrict__ row2cand, int R, float* __restrict__ F) {
     __shared__ double ssum[256];
     __shared__ int scnt[256];
     const int k = blockIdx.x, tid = threadIdx.x;
@@ -727,8 +729,8 @@ __global__ __launch_bounds__(256) void cand_mean_sliced_kernel(const double* __r
     int cnt = 0;
     for (int i = tid; i < R; i += 256)
         if (row2cand[i] == k) {
-            double t = rowsum[i];
-            for (int g = 1; g < G; ++g) t += rowsum[(size_t)g * R + i];
+            double t = PARTS ? 0.0 + (double)rowpart[i] : rowsum[i];
+            for (int g = 1; g < G; ++g) t += PARTS ? (double)rowpart[(size_t)g * R + i] : rowsum[(size_t)g * R + i];
             s += t;
             ++cnt;
         }
@@ -913,9 +915,13 @@ int reward_slices(int n_blocks) { return n_blocks >= 256 ? 16 : (n_blocks + 15) 
 
 hipError_t reward_finish(hipStream_t st, const float* rowpart, int n_blocks, int R, const int32_t* row2cand, int K,
                          double* rowsum, float* F) {
+    if (n_blocks <= 16) {                                  // one block a slice of rowpart_sum_kernel: its launch (1.5 us and a gap) is more than its sums
+        hipLaunchKernelGGL(cand_mean_sliced_kernel<true>, dim3(K), dim3(256), 0, st, nullptr, rowpart, n_blocks, row2cand, R, F);
+        return hipGetLastError();
+    }
     const int G = reward_slices(n_blocks);
     hipLaunchKernelGGL(rowpart_sum_kernel, dim3((R + 63) / 64, G), dim3(1024), 0, st, rowpart, n_blocks, R, rowsum);
-    hipLaunchKernelGGL(cand_mean_sliced_kernel, dim3(K), dim3(256), 0, st, rowsum, G, row2cand, R, F);
+    hipLaunchKernelGGL(cand_mean_sliced_kernel<false>, dim3(K), dim3(256), 0, st, rowsum, nullptr, G, row2cand, R, F);
     return hipGetLastError();
 }
 

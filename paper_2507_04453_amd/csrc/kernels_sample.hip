@@ -144,6 +144,45 @@ __global__ __launch_bounds__(RHS_C * RHS_B) void update_rhs_kernel(const uint32_
     }
 }
 
+// theta[k, i] = m[i] + sigma sum_l B[i, l] D[l] z_k[l] in one launch for a search of at most 64 dimensions: 16 candidates a workgroup, their
+// normals and B in LDS.  What there is to do is less than the second launch (n = 16, 4 candidates: two kernels of 3.1 and 1.8 us and 3 us of the
+// caller's time for each; from n in the hundreds on B wants the whole chip).
+constexpr int SMALL_N = 64, SMALL_K = 16;
+__global__ __launch_bounds__(256) void sample_small_kernel(const uint32_t* __restrict__ seeds, int K, int n, const float* __restrict__ m, const float* __restrict__ B,
+                                                          const float* __restrict__ D, const essa_cma_scalars* __restrict__ sc, float* __restrict__ theta,
+                                                          float* __restrict__ z_out) {
+    __shared__ float Bs[SMALL_N][SMALL_N + 1], S[SMALL_K][SMALL_N + 1];
+    const int tid = threadIdx.x, c = tid & 15, k = tid >> 4, k0 = blockIdx.x * SMALL_K;
+    for (int e = tid; e < n * n; e += 256) Bs[e / n][e % n] = B[e];
+    const float sigma = sc->sigma;
+    if (k0 + k < K && 4 * c < n) {
+        const uint4 w = philox4x32_10(make_uint4((uint32_t)c, 0u, 0u, 0u), make_uint2(seeds[k0 + k], 0u));
+        float z[4];
+        box_muller(w.x, w.y, z[0], z[1]);
+        box_muller(w.z, w.w, z[2], z[3]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int l = 4 * c + e;
+            if (l < n) {
+                S[k][l] = D[l] * z[e];
+                if (z_out) z_out[(size_t)(k0 + k) * n + l] = z[e];
+            }
+        }
+    }
+    __syncthreads();
+    for (int o = tid; o < SMALL_K * n; o += 256) {
+        const int kk = o / n, i = o % n;
+        if (k0 + kk >= K) break;
+        float a[4] = {0.f, 0.f, 0.f, 0.f};
+        int l = 0;
+        for (; l + 4 <= n; l += 4)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) a[e] = fmaf(S[kk][l + e], Bs[i][l + e], a[e]);
+        for (; l < n; ++l) a[0] = fmaf(S[kk][l], Bs[i][l], a[0]);
+        theta[(size_t)(k0 + kk) * n + i] = m[i] + sigma * ((a[0] + a[1]) + (a[2] + a[3]));
+    }
+}
+
 // Distributions with a diagonal covariance: theta[k, l] = m[l] + s_k sigma d[l] z[l] (d = 1 without D).  With
 // pairs, candidates 2j and 2j + 1 mirror each other around m on the direction of seed j (ARS, Algorithm 1).
 __global__ void sample_diag_kernel(const uint32_t* __restrict__ seeds, int K, int n, const float* __restrict__ m,
@@ -342,6 +381,13 @@ hipError_t update_rhs(hipStream_t st, const uint32_t* seeds, const int32_t* sel,
     hipLaunchKernelGGL(update_rhs_kernel, dim3((blocks + RHS_B - 1) / RHS_B), dim3(RHS_C * RHS_B), 0, st, seeds, sel, ny, mu, n, w, D, S, Z, rank_F, rank_K,
                        rank_order);
     return hipGetLastError();
+}
+
+bool sample_small(hipStream_t st, const uint32_t* seeds, int K, int n, const float* m, const float* B, const float* D, const essa_cma_scalars* sc, float* theta,
+                  float* z_out) {
+    if (n > SMALL_N) return false;
+    hipLaunchKernelGGL(sample_small_kernel, dim3((K + SMALL_K - 1) / SMALL_K), dim3(256), 0, st, seeds, K, n, m, B, D, sc, theta, z_out);
+    return true;
 }
 
 hipError_t sample_diag(hipStream_t st, const uint32_t* seeds, int K, int n, const float* m, const float* D,

@@ -6,12 +6,6 @@ import torch
 pytestmark = pytest.mark.gpu
 
 
-@pytest.fixture(scope="module")
-def essa():
-    import paper_2507_04453_amd as m
-    return m
-
-
 # around the 64 x 64 tiles; 40 candidates of the active kind are 41 terms, more than one round of them
 @pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 130, 203])
 @pytest.mark.parametrize("kind,K", [("cma", 12), ("active", 40)])

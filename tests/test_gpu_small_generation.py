@@ -1,0 +1,50 @@
+"""A generation of a small search: candidates in one launch (up to 64 dimensions), the rows' reward sums inside the candidates' means (up to 16 blocks)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as orc
+from helpers import seeds_dev, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 7, 16, 63, 64, 65])            # 65: the two launches
+@pytest.mark.parametrize("K", [1, 15, 16, 17, 40])
+def test_small_sampler(essa, n, K):
+    g = np.random.default_rng(100 * n + K)
+    ctx = essa.Context(0)
+    cma = essa.CmaState(ctx, n, 0.32, g.standard_normal(n).astype(np.float32))
+    B, d = g.standard_normal((n, n)).astype(np.float32), g.uniform(0.5, 2.0, n).astype(np.float32)
+    cma.set_basis(to_dev(B), to_dev(d))
+    seeds = g.integers(0, 2 ** 32, K, dtype=np.uint32)
+    theta, z = torch.full((K, n), float("nan"), device="cuda"), torch.full((K, n), float("nan"), device="cuda")
+    essa.essa_sample_candidates(ctx, cma, seeds_dev(seeds), theta, z)
+    again = torch.empty_like(theta)
+    essa.essa_sample_candidates(ctx, cma, seeds_dev(seeds), again)
+    st = cma.export()
+    ref, ref_z = orc.sample_candidates(st["m"].astype(np.float64), np.float32(0.32), B.astype(np.float64), d.astype(np.float64), [int(s) for s in seeds])
+    assert torch.equal(theta, again)
+    assert orc.rel_errors(z.cpu().numpy(), ref_z)[1] <= 1e-6
+    # fp32 sums of n terms of mixed sign: n 2^-24 of the sum of their magnitudes at most
+    mag = np.abs(st["m"]) + 0.32 * np.abs(d * ref_z) @ np.abs(B).T
+    assert np.all(np.abs(theta.cpu().numpy() - ref) <= (n + 4) * 2.0 ** -24 * mag + 1e-7 * np.abs(ref))
+    cma.close()
+    ctx.close()
+
+
+@pytest.mark.parametrize("blocks", [1, 2, 15, 16, 17])                 # 17: a launch of its own for the rows' sums
+@pytest.mark.parametrize("R,K", [(1, 1), (70, 3), (300, 5)])
+def test_reward_finish_few_blocks(essa, blocks, R, K):
+    g = np.random.default_rng(blocks + R)
+    ctx = essa.Context(0)
+    part = g.standard_normal((blocks, R)).astype(np.float32)
+    r2c = np.arange(R, dtype=np.int32) % K
+    F0 = g.standard_normal(K).astype(np.float32)
+    F = to_dev(F0)
+    essa.essa_reward_finish(ctx, to_dev(part), blocks, to_dev(r2c), F)
+    rows = part.astype(np.float64).sum(0)
+    want = np.array([rows[r2c == k].mean() for k in range(K)])
+    # fp64 sums, one rounding to fp32 and one of the addition to F
+    assert np.all(np.abs(F.cpu().numpy() - (F0 + want)) <= 2.0 ** -23 * (np.abs(F0) + np.abs(want)) + 1e-12)
+    ctx.close()

@@ -6,12 +6,6 @@ import torch
 pytestmark = pytest.mark.gpu
 
 
-@pytest.fixture(scope="module")
-def essa():
-    import paper_2507_04453_amd as m
-    return m
-
-
 # 12288 channels are 96 column tiles: the 64-row tiles fill one round of CUs up to 128 rows, two from 129 on, the 32-row tiles two of their own up to
 # 160, three up to 256, four up to 320: the rule changes its mind at 129, 161, 257 and 321, with two limbs and with one not at the same places
 @pytest.mark.parametrize("rows", [65, 97, 128, 129, 160, 161, 257, 321])
