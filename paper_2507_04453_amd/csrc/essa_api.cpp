@@ -515,6 +515,8 @@ extern "C" void essa_cma_destroy(essa_cma* c) {
     void* ptrs[] = {c->m, c->p_sigma, c->p_c, c->D, c->C, c->B, c->Cdiag, c->Cturn, c->sc, c->weights, c->eigV};
     for (void* q : ptrs)
         if (q) (void)hipFree(q);
+    if (c->eig_host) (void)hipHostFree(c->eig_host);
+    if (c->eig_told) (void)hipEventDestroy(c->eig_told);
     delete c;
 }
 
@@ -1077,10 +1079,19 @@ extern "C" essa_status essa_cma_refresh_basis(essa_ctx* ctx, essa_cma* cma, int 
         if (e != hipSuccess) return essa_fail(ESSA_ERR_OOM, "fp64 basis of %zu bytes: %s", essa_k::eig_basis_bytes(cma->n), hipGetErrorString(e));
         cma->eigV_valid = false;
     }
+    if (!cma->eig_host) {
+        if (hipHostMalloc(&cma->eig_host, 64, hipHostMallocDefault) != hipSuccess) cma->eig_host = nullptr;
+        else if (hipEventCreateWithFlags(&cma->eig_told, hipEventDisableTiming) != hipSuccess) {
+            (void)hipHostFree(cma->eig_host);
+            cma->eig_host = nullptr;
+            cma->eig_told = nullptr;
+        }
+        if (!cma->eig_host) (void)hipGetLastError();        // without it the refresh copies the numbers back
+    }
     int sweeps = 0;
     float off = 0.f;
     ESSA_HIP(essa_k::eig_refresh(ctx->stream, cma->C, cma->n, ctx->ws, refine, cma->eigV, cma->eigV_valid ? 1 : 0, max_sweeps, tol, cma->B, cma->D,
-                                 &sweeps, &off));
+                                 cma->eig_host, cma->eig_told, &sweeps, &off));
     cma->eigV_valid = true;
     if (sweeps_out) *sweeps_out = sweeps;
     if (off_out) *off_out = off;

@@ -112,6 +112,8 @@ struct essa_cma {
     float* weights = nullptr;  // device [mu] (active CMA: [K]) for weights_K
     int weights_K = 0;
     double* eigV = nullptr;    // the basis of the last eigendecomposition in fp64 (allocated by the first refresh)
+    void* eig_host = nullptr;  // 64 bytes of page-locked host memory and an event, both or neither: what the steps of a refresh tell the host
+    hipEvent_t eig_told = nullptr;
     bool eigV_valid = false;   // false after the basis was set from outside: the next refresh starts from the identity
 };
 
@@ -153,8 +155,9 @@ hipError_t rank_rewards(hipStream_t st, const float* F, int K, int32_t* order);
 // Vt: the basis in fp64 (eig_basis_bytes(n)), kept by the state from one refresh to the next; warm = it holds the last result.
 size_t eig_workspace_bytes(int n, bool refine);
 size_t eig_basis_bytes(int n);
+// host: null, or page-locked memory of 64 bytes where the steps' numbers are told, and the event that says when.
 hipError_t eig_refresh(hipStream_t st, const float* C, int n, void* ws, bool refine, double* Vt, int warm, int max_sweeps, float tol, float* B, float* D,
-                       int* sweeps_done, float* off_final);
+                       void* host, hipEvent_t told, int* sweeps_done, float* off_final);
 
 struct cma_consts {
     int n, K, mu;
