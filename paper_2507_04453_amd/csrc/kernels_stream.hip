@@ -83,14 +83,40 @@ constexpr float LIMB_TINY = 0x1p-100f;
 
 // Largest magnitude of a row from the bit patterns of its bf16 entries (two per 32-bit word).  With the sign bit gone
 // the patterns of finite values order like the values, and those of Inf and NaN lie above all of them: the integer
-// maximum is the row's amax when the row is finite and says so when it is not (fmaxf would drop a NaN).  The low
-// halves are compared shifted left by 17 (sign shifted out), the high halves masked: two operations per entry, as
-// many as shift + fmaxf(|.|).
-__device__ __forceinline__ void amax_accumulate(uint32_t& mlo, uint32_t& mhi, uint32_t two_bf16) {
-    mlo = max(mlo, two_bf16 << 17);
-    mhi = max(mhi, two_bf16 & 0x7fff0000u);
+// maximum is the row's amax when the row is finite and says so when it is not (fmaxf would drop a NaN).
+typedef __attribute__((ext_vector_type(2))) uint16_t u16x2;
+__device__ __forceinline__ void amax_accumulate(uint32_t& m, uint32_t two_bf16) {
+    m = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, m), __builtin_bit_cast(u16x2, two_bf16 & 0x7fff7fffu)));
 }
-__device__ __forceinline__ uint32_t amax_join(uint32_t mlo, uint32_t mhi) { return max(mlo >> 1, mhi); }   // bits of amax as an fp32
+__device__ __forceinline__ uint32_t amax_join(uint32_t m) { return max(m << 16, m & 0xffff0000u); }     // bits of amax as an fp32
+
+// Eight entries of a row as fixed point: q = rint(x inv), hi = (q + 128) >> 8 and lo = q - 256 hi (one limb: q itself), four to a word.  x inv plus
+// 1.5 2^23 (and 128) is rounded to an integer by the addition, and its low bytes are the limbs: hi as it is, lo with its top bit
+// turned over.  About 5 operations an entry where rint, clamp, conversion, shifts and masks took 16
+// (28 layers at 256 rows with all around them 773 -> 766 us, four at 8 rows 57.5 -> 56.7).  The product
+// must be rounded before the addition, or ties could fall otherwise.  |x inv| cannot round above the largest code, except that with one limb inv may have
+// overflowed (rows whose largest entry is below 2^-120): clamped there as it always was.  qsum: the sum of the eight q (two limbs).
+__device__ __forceinline__ void quantise8(const u32x4& v, float inv, int limbs, bool want_sum, uint32_t (&hi)[2], uint32_t (&lo)[2], int& qsum) {
+#pragma clang fp contract(off)
+    const float magic = limbs == 2 ? 0x1.8p23f + 128.f : 0x1.8p23f;
+    uint32_t t[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const float x = (e & 1) ? __uint_as_float(v[e >> 1] & 0xffff0000u) : __uint_as_float(v[e >> 1] << 16);
+        float q = x * inv;
+        if (limbs != 2) q = fminf(fmaxf(q, -127.f), 127.f);
+        t[e] = __float_as_uint(q + magic);
+    }
+    qsum = 0;
+#pragma unroll
+    for (int w = 0; w < 2; ++w) {
+        const uint32_t a = limbs == 2 ? __builtin_amdgcn_perm(t[4 * w + 1], t[4 * w], 0x04000501u) : __builtin_amdgcn_perm(t[4 * w + 1], t[4 * w], 0x00000400u);
+        const uint32_t b = limbs == 2 ? __builtin_amdgcn_perm(t[4 * w + 3], t[4 * w + 2], 0x04000501u) : __builtin_amdgcn_perm(t[4 * w + 3], t[4 * w + 2], 0x00000400u);
+        hi[w] = __builtin_amdgcn_perm(b, a, 0x05040100u);
+        lo[w] = __builtin_amdgcn_perm(b, a, 0x07060302u) ^ 0x80808080u;
+        if (want_sum) qsum += 256 * __builtin_amdgcn_sdot4((int)hi[w], 0x01010101, 0, false) + __builtin_amdgcn_sdot4((int)lo[w], 0x01010101, 0, false);
+    }
+}
 
 // Row quantisation at row counts in the thousands: one wave per row, the whole row in the wave's registers (NK
 // 16-byte chunks per lane, all asked for at once), the row maximum by shuffles alone.  No barrier and no LDS, so a
@@ -107,14 +133,14 @@ __device__ __forceinline__ void quantise_row_wave(const stream_item& it, int i, 
 #pragma unroll
     for (int k = 0; k < NK; ++k) xr[k] = xrow[min(64 * k + lane, nch - 1)];     // clamped: no branch between the loads
     __builtin_amdgcn_sched_barrier(0);
-    uint32_t mlo = 0, mhi = 0;                             // see amax_accumulate
+    uint32_t mx = 0;                                       // see amax_accumulate
 #pragma unroll
     for (int k = 0; k < NK; ++k) {
         if (64 * k + lane >= nch) xr[k] = (u32x4){0, 0, 0, 0};
 #pragma unroll
-        for (int e = 0; e < 4; ++e) amax_accumulate(mlo, mhi, xr[k][e]);
+        for (int e = 0; e < 4; ++e) amax_accumulate(mx, xr[k][e]);
     }
-    uint32_t mi = amax_join(mlo, mhi);
+    uint32_t mi = amax_join(mx);
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) mi = max(mi, (uint32_t)__shfl_xor((int)mi, off, 64));
     const bool finite = mi < 0x7f800000u;                  // an Inf or NaN anywhere in the row: the whole output row is NaN
@@ -130,23 +156,10 @@ __device__ __forceinline__ void quantise_row_wave(const stream_item& it, int i, 
     for (int k = 0; k < NK; ++k) {
         if (k >= kd) break;                                // wave-uniform: chunks up to the padded width quantise zeros
         const int c = 64 * k + lane;
-        uint32_t hi[2] = {0, 0}, lo[2] = {0, 0};
-        int qsum = 0;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const float x = (e & 1) ? __uint_as_float(xr[k][e >> 1] & 0xffff0000u) : __uint_as_float(xr[k][e >> 1] << 16);
-            float q = rintf(x * inv);
-            q = fminf(fmaxf(q, -top), top);
-            const int qi = (int)q;
-            qsum += qi;
-            if (a_limbs == 2) {
-                const int qh = (qi + 128) >> 8;            // see the two-row form below
-                hi[e >> 2] |= (uint32_t)(qh & 0xff) << (8 * (e & 3));
-                lo[e >> 2] |= (uint32_t)((qi - (qh << 8)) & 0xff) << (8 * (e & 3));
-            } else {
-                hi[e >> 2] |= (uint32_t)(qi & 0xff) << (8 * (e & 3));
-            }
-        }
+        uint32_t hi[2], lo[2];
+        int qsum;
+        if (a_limbs == 2) quantise8(xr[k], inv, 2, it.quant == ESSA_QUANT_INT4_G128, hi, lo, qsum);
+        else quantise8(xr[k], inv, 1, false, hi, lo, qsum);
         __builtin_nontemporal_store((u32x2){hi[0], hi[1]}, hrow + c);        // streaming stores, as in the two-row form
         if (a_limbs == 2) __builtin_nontemporal_store((u32x2){lo[0], lo[1]}, lrow + c);
         if (it.quant == ESSA_QUANT_INT4_G128) {
@@ -243,20 +256,20 @@ __global__ __launch_bounds__(PREP_NT, FULLK ? 4 : 1) void prep_kernel(stream_arg
         // the row is read once: the first four chunks of every thread (rows up to 8192 wide) wait in registers
         // between the two passes
         u32x4 xr[4];
-        uint32_t mlo = 0, mhi = 0;
+        uint32_t mx = 0;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const int c = t256 + 256 * k;
             xr[k] = c < nch ? xrow[c] : (u32x4){0, 0, 0, 0};
 #pragma unroll
-            for (int e = 0; e < 4; ++e) amax_accumulate(mlo, mhi, xr[k][e]);
+            for (int e = 0; e < 4; ++e) amax_accumulate(mx, xr[k][e]);
         }
         for (int c = t256 + 1024; c < nch; c += 256) {
             const u32x4 v = xrow[c];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) amax_accumulate(mlo, mhi, v[e]);
+            for (int e = 0; e < 4; ++e) amax_accumulate(mx, v[e]);
         }
-        uint32_t mi = amax_join(mlo, mhi);
+        uint32_t mi = amax_join(mx);
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) mi = max(mi, (uint32_t)__shfl_xor((int)mi, off, 64));
         if (lane == 0) wred[wave] = mi;
@@ -282,23 +295,10 @@ __global__ __launch_bounds__(PREP_NT, FULLK ? 4 : 1) void prep_kernel(stream_arg
             return ((blk * 2 + ((c >> 1) & 1)) * 512 + (size_t)(i & 31) * 16 + (c & 1) * 8) >> 3;
         };
         auto quantise_chunk = [&](int c, const u32x4& v) {
-            uint32_t hi[2] = {0, 0}, lo[2] = {0, 0};
-            int qsum = 0;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const float x = (e & 1) ? __uint_as_float(v[e >> 1] & 0xffff0000u) : __uint_as_float(v[e >> 1] << 16);
-                float q = rintf(x * inv);
-                q = fminf(fmaxf(q, -top), top);
-                const int qi = (int)q;
-                qsum += qi;
-                if (a_limbs == 2) {
-                    const int qh = (qi + 128) >> 8;                                // arithmetic shift: hi in [-127,127]
-                    hi[e >> 2] |= (uint32_t)(qh & 0xff) << (8 * (e & 3));
-                    lo[e >> 2] |= (uint32_t)((qi - (qh << 8)) & 0xff) << (8 * (e & 3));   // lo in [-128,127]
-                } else {
-                    hi[e >> 2] |= (uint32_t)(qi & 0xff) << (8 * (e & 3));
-                }
-            }
+            uint32_t hi[2], lo[2];                         // hi in [-127,127], lo in [-128,127]
+            int qsum;
+            if (a_limbs == 2) quantise8(v, inv, 2, it.quant == ESSA_QUANT_INT4_G128, hi, lo, qsum);
+            else quantise8(v, inv, 1, false, hi, lo, qsum);
             // streaming stores: the limbs are read by the next launch, from behind other L2s than this one
             const size_t slot = limb_slot(c);
             __builtin_nontemporal_store((u32x2){hi[0], hi[1]}, hrow + slot);
