@@ -15,7 +15,7 @@
 // refinement for symmetric eigenvalue decomposition", 2018).  It converges quadratically like Jacobi's last sweeps and a
 // step is four products of n x n matrices that fill the chip.  Columns keep their places and signs either way.
 // Measured, n = 896: a sweep takes 3 ms, a step 0.11 to 0.13 ms (the products' fp64 MFMA time alone is 0.07); the refresh after
-// 8 generations of 36 candidates 12.3 -> 0.5 ms (3 or 4 steps in place of 4 sweeps), n = 3584 with nothing to do 15 -> 4.2 ms.
+// 8 generations of 36 candidates 12.3 -> 0.45 ms (3 or 4 steps in place of 4 sweeps), n = 3584 with nothing to do 15 -> 3.1 ms.
 #include "forward_device.h"
 #include <cmath>
 #include <cstring>
