@@ -629,9 +629,9 @@ extern "C" essa_status essa_cma_import(essa_cma* c, const void* blob, size_t byt
     for (float* v : vecs) { ESSA_HIP(hipMemcpy(v, src, n * sizeof(float), hipMemcpyHostToDevice)); src += n * sizeof(float); }
     if (has_matrix(c)) {
         ESSA_HIP(hipMemcpy(c->C, src, n * n * sizeof(float), hipMemcpyHostToDevice));
+        ESSA_HIP(essa_k::cma_look_symmetric(c->stream, c->C, c->n, c->Cturn));
         src += n * n * sizeof(float);
         ESSA_HIP(hipMemcpy(c->B, src, n * n * sizeof(float), hipMemcpyHostToDevice));
-        ESSA_HIP(essa_k::cma_look_symmetric(c->stream, c->C, c->n, c->Cturn));
     } else {
         ESSA_HIP(hipMemcpy(c->Cdiag, src, n * sizeof(float), hipMemcpyHostToDevice));
     }
