@@ -718,22 +718,45 @@ __global__ __launch_bounds__(1024) void rowpart_sum_kernel(const float* __restri
 }
 
 // F[k] += (sum over the rows of candidate k, and over the G slices of each row in ascending order) / (number of rows)
-// PARTS: the rows' sums are taken here, over at most 16 blocks (G of them), in the order and with the bits of rowpart_sum_kernel
-template <bool PARTS>
+// PARTS > 0: the rows' sums are taken here, over at most PARTS blocks (G of them), in the order and with the bits of rowpart_sum_kernel.
+// A candidate's rows are one workgroup's work, so latency is what there is to pay: the map is read four places at a time and a row's partials together.
+// One after the other, 16 blocks of 32768 rows took 205 us with one candidate, 67 with 4 and 22 with 64 (in two launches 60, 31 and 22); this takes 46, 19
+// and 10, and 64 rows of 4 candidates 4.1 -> 3.1 (in two launches 4.5).
+template <int PARTS>
 __global__ __launch_bounds__(256) void cand_mean_sliced_kernel(const double* __restrict__ rowsum, const float* __restrict__ rowpart, int G,
                                                               const int32_t* __restrict__ row2cand, int R, float* __restrict__ F) {
+    constexpr int SCAN = 4;                                // places of the map asked for together
     __shared__ double ssum[256];
     __shared__ int scnt[256];
     const int k = blockIdx.x, tid = threadIdx.x;
     double s = 0.0;
     int cnt = 0;
-    for (int i = tid; i < R; i += 256)
-        if (row2cand[i] == k) {
-            double t = PARTS ? 0.0 + (double)rowpart[i] : rowsum[i];
-            for (int g = 1; g < G; ++g) t += PARTS ? (double)rowpart[(size_t)g * R + i] : rowsum[(size_t)g * R + i];
+    for (uint32_t i0 = tid; i0 < (uint32_t)R; i0 += SCAN * 256) {
+        int32_t cand[SCAN];
+#pragma unroll
+        for (int q = 0; q < SCAN; ++q) cand[q] = row2cand[min(i0 + 256 * q, (uint32_t)R - 1)];
+        uint32_t mine = 0;
+#pragma unroll
+        for (int q = 0; q < SCAN; ++q) mine |= cand[q] == k && i0 + 256 * q < (uint32_t)R ? 1u << q : 0u;
+        for (; mine; mine &= mine - 1) {                   // in ascending order
+            const uint32_t i = i0 + 256 * __builtin_ctz(mine);
+            double t;
+            if constexpr (PARTS > 0) {
+                float p[PARTS];
+#pragma unroll
+                for (int g = 0; g < PARTS; ++g) p[g] = (rowpart + (size_t)min(g, G - 1) * R)[i];
+                t = 0.0 + (double)p[0];
+#pragma unroll
+                for (int g = 1; g < PARTS; ++g)
+                    if (g < G) t += (double)p[g];
+            } else {
+                t = rowsum[i];
+                for (int g = 1; g < G; ++g) t += rowsum[(size_t)g * R + i];
+            }
             s += t;
             ++cnt;
         }
+    }
     ssum[tid] = s;
     scnt[tid] = cnt;
     __syncthreads();
@@ -915,13 +938,17 @@ int reward_slices(int n_blocks) { return n_blocks >= 256 ? 16 : (n_blocks + 15) 
 
 hipError_t reward_finish(hipStream_t st, const float* rowpart, int n_blocks, int R, const int32_t* row2cand, int K,
                          double* rowsum, float* F) {
-    if (n_blocks <= 16) {                                  // one block a slice of rowpart_sum_kernel: its launch (1.5 us and a gap) is more than its sums
-        hipLaunchKernelGGL(cand_mean_sliced_kernel<true>, dim3(K), dim3(256), 0, st, nullptr, rowpart, n_blocks, row2cand, R, F);
+    // one block a slice of rowpart_sum_kernel: its launch and a gap are more than what reading the partials in the second one adds, at any number of rows and
+    // candidates (us, one launch / two; 1 block and 64 rows of 4 candidates 2.8 / 4.4, 16 blocks and 8192 rows of one candidate 13.6 / 17.6)
+    if (n_blocks <= 16) {
+        const auto kernel = n_blocks == 1 ? cand_mean_sliced_kernel<1> : n_blocks <= 4 ? cand_mean_sliced_kernel<4> : n_blocks <= 8 ? cand_mean_sliced_kernel<8>
+                                                                                                                           : cand_mean_sliced_kernel<16>;
+        hipLaunchKernelGGL(kernel, dim3(K), dim3(256), 0, st, nullptr, rowpart, n_blocks, row2cand, R, F);
         return hipGetLastError();
     }
     const int G = reward_slices(n_blocks);
     hipLaunchKernelGGL(rowpart_sum_kernel, dim3((R + 63) / 64, G), dim3(1024), 0, st, rowpart, n_blocks, R, rowsum);
-    hipLaunchKernelGGL(cand_mean_sliced_kernel<false>, dim3(K), dim3(256), 0, st, rowsum, nullptr, G, row2cand, R, F);
+    hipLaunchKernelGGL(cand_mean_sliced_kernel<0>, dim3(K), dim3(256), 0, st, rowsum, nullptr, G, row2cand, R, F);
     return hipGetLastError();
 }
 

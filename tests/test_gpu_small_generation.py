@@ -48,3 +48,49 @@ def test_reward_finish_few_blocks(essa, blocks, R, K):
     # fp64 sums, one rounding to fp32 and one of the addition to F
     assert np.all(np.abs(F.cpu().numpy() - (F0 + want)) <= 2.0 ** -23 * (np.abs(F0) + np.abs(want)) + 1e-12)
     ctx.close()
+
+
+# the map is read 1024 places at a time, four a thread: around that, and many rows of few candidates
+@pytest.mark.parametrize("blocks", [1, 2, 4, 5, 8, 9, 16])
+@pytest.mark.parametrize("R,K", [(255, 2), (1023, 1), (1025, 3), (5000, 1), (5000, 40)])
+def test_reward_finish_one_launch_has_the_bits_of_two(essa, blocks, R, K):
+    g = np.random.default_rng(1000 * blocks + R + K)
+    ctx = essa.Context(0)
+    part = np.zeros((17, R), np.float32)                   # blocks of zeros behind the last one take the two launches and change no sum
+    part[:blocks] = g.standard_normal((blocks, R))
+    r2c = g.integers(0, K, R).astype(np.int32)
+    r2c[:K] = np.arange(K)
+    F = [torch.zeros(K, device="cuda") for _ in range(2)]
+    for out, count in zip(F, (blocks, 17)):
+        essa.essa_reward_finish(ctx, to_dev(part), count, to_dev(r2c), out)
+    rows = part.astype(np.float64).sum(0)
+    want = np.array([rows[r2c == k].mean() for k in range(K)])
+    assert torch.equal(F[0].view(torch.int32), F[1].view(torch.int32))
+    # fp64 sums of R terms at most, one rounding to fp32
+    assert np.all(np.abs(F[0].cpu().numpy() - want) <= 2.0 ** -24 * np.abs(want) + 1e-12)
+    ctx.close()
+
+
+def test_reward_finish_few_candidates_many_rows_take_no_longer_in_one_launch(essa):
+    """16 blocks of 32768 rows of one candidate: all of it is one workgroup's work.  17 blocks are two launches and more to read."""
+    R = 32768
+    ctx = essa.Context(0)
+    part, r2c, F = torch.randn(17, R, device="cuda"), torch.zeros(R, dtype=torch.int32, device="cuda"), torch.zeros(1, device="cuda")
+
+    def us(blocks):
+        best = float("inf")
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(20):
+                essa.essa_reward_finish(ctx, part, blocks, r2c, F)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b) * 50)
+        return best
+
+    us(17)
+    one, two = us(16), us(17)
+    print("one launch %.1f us, two %.1f us" % (one, two), flush=True)
+    assert one <= 1.5 * two                                # 46 and 60; with a wait for every partial 205
+    ctx.close()
