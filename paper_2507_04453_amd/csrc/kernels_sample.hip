@@ -144,18 +144,18 @@ __global__ __launch_bounds__(RHS_C * RHS_B) void update_rhs_kernel(const uint32_
     }
 }
 
-// theta[k, i] = m[i] + sigma sum_l B[i, l] D[l] z_k[l] in one launch for a search of at most 64 dimensions: 16 candidates a workgroup, their
-// normals and B in LDS.  What there is to do is less than the second launch (n = 16, 4 candidates: two kernels of 3.1 and 1.8 us and 3 us of the
-// caller's time for each; from n in the hundreds on B wants the whole chip).
+// theta[k, i] = m[i] + sigma sum_l B[i, l] D[l] z_k[l] in one launch for a search of at most 64 dimensions: a few candidates a
+// workgroup, their normals and B in LDS.  Latency binds: the products of a thread's outputs come one after the other (n = 64, 0.8 us each), and code is fetched
+// anew for every launch (four outputs of a thread side by side, in longer code: 7.6 -> 10 us at 32 candidates).
 constexpr int SMALL_N = 64, SMALL_K = 16;
-__global__ __launch_bounds__(256) void sample_small_kernel(const uint32_t* __restrict__ seeds, int K, int n, const float* __restrict__ m, const float* __restrict__ B,
+__global__ __launch_bounds__(256) void sample_small_kernel(const uint32_t* __restrict__ seeds, int K, int per, int n, const float* __restrict__ m, const float* __restrict__ B,
                                                           const float* __restrict__ D, const essa_cma_scalars* __restrict__ sc, float* __restrict__ theta,
                                                           float* __restrict__ z_out) {
     __shared__ float Bs[SMALL_N][SMALL_N + 1], S[SMALL_K][SMALL_N + 1];
-    const int tid = threadIdx.x, c = tid & 15, k = tid >> 4, k0 = blockIdx.x * SMALL_K;
+    const int tid = threadIdx.x, c = tid & 15, k = tid >> 4, k0 = blockIdx.x * per;
     for (int e = tid; e < n * n; e += 256) Bs[e / n][e % n] = B[e];
     const float sigma = sc->sigma;
-    if (k0 + k < K && 4 * c < n) {
+    if (k < per && k0 + k < K && 4 * c < n) {
         const uint4 w = philox4x32_10(make_uint4((uint32_t)c, 0u, 0u, 0u), make_uint2(seeds[k0 + k], 0u));
         float z[4];
         box_muller(w.x, w.y, z[0], z[1]);
@@ -170,7 +170,7 @@ __global__ __launch_bounds__(256) void sample_small_kernel(const uint32_t* __res
         }
     }
     __syncthreads();
-    for (int o = tid; o < SMALL_K * n; o += 256) {
+    for (int o = tid; o < per * n; o += 256) {
         const int kk = o / n, i = o % n;
         if (k0 + kk >= K) break;
         float a[4] = {0.f, 0.f, 0.f, 0.f};
@@ -385,8 +385,15 @@ hipError_t update_rhs(hipStream_t st, const uint32_t* seeds, const int32_t* sel,
 
 bool sample_small(hipStream_t st, const uint32_t* seeds, int K, int n, const float* m, const float* B, const float* D, const essa_cma_scalars* sc, float* theta,
                   float* z_out) {
-    if (n > SMALL_N) return false;
-    hipLaunchKernelGGL(sample_small_kernel, dim3((K + SMALL_K - 1) / SMALL_K), dim3(256), 0, st, seeds, K, n, m, B, D, sc, theta, z_out);
+    // B and the normals of 16 candidates are kept for at most 64 dimensions.  us in a replayed graph, two launches / one: 16 dimensions 4.9 / 3.4 at 4 candidates, 8.7 / 8.5
+    // at 24576, 9.0 / 10.4 at 32768 (mostly idle threads, so they go in two); 64 dimensions 5.4 / 5.5 at 4, 57.5 / 42.3 at 65536.  A caller who does not record is
+    // spared 3 us a call besides.
+    if (n > SMALL_N || (n <= 16 && K > 24576)) return false;
+    // An output a thread, while there are not so many workgroups that their copies of B take longer: 64 dimensions, 16 candidates a workgroup / 4: 7.9 / 5.7 at 32,
+    // 8.2 / 6.0 at 1024, 8.8 / 8.2 at 4096 (two launches 6.4, 7.9, 9.1); 32 dimensions, 16 / 8: 4.7 / 4.1 at 32
+    int per = n <= 16 ? 16 : n <= 32 ? 8 : 4;
+    if (K > 1024 * per) per = SMALL_K;
+    hipLaunchKernelGGL(sample_small_kernel, dim3((K + per - 1) / per), dim3(256), 0, st, seeds, K, per, n, m, B, D, sc, theta, z_out);
     return true;
 }
 

@@ -94,3 +94,73 @@ def test_reward_finish_few_candidates_many_rows_take_no_longer_in_one_launch(ess
     print("one launch %.1f us, two %.1f us" % (one, two), flush=True)
     assert one <= 1.5 * two                                # 46 and 60; with a wait for every partial 205
     ctx.close()
+
+
+# 4, 8 or 16 candidates a workgroup: up to 32 dimensions 8 as long as there are at most 1024 such workgroups, from 33 on 4, else 16
+@pytest.mark.parametrize("n,K", [(16, 33), (17, 9), (17, 8193), (32, 8192), (33, 5), (33, 4097), (64, 4095), (64, 4097)])
+def test_small_sampler_candidates_do_not_hang_on_their_workgroup(essa, n, K):
+    g = np.random.default_rng(n + K)
+    ctx = essa.Context(0)
+    cma = essa.CmaState(ctx, n, 0.32, g.standard_normal(n).astype(np.float32))
+    cma.set_basis(to_dev(g.standard_normal((n, n)).astype(np.float32)), to_dev(g.uniform(0.5, 2.0, n).astype(np.float32)))
+    seeds = seeds_dev(g.integers(0, 2 ** 32, K, dtype=np.uint32))
+    theta, z = torch.full((K, n), float("nan"), device="cuda"), torch.full((K, n), float("nan"), device="cuda")
+    essa.essa_sample_candidates(ctx, cma, seeds, theta, z)
+    for lo in range(0, K, 999):
+        hi = min(lo + 999, K)
+        t, zz = torch.empty(hi - lo, n, device="cuda"), torch.empty(hi - lo, n, device="cuda")
+        essa.essa_sample_candidates(ctx, cma, seeds[lo:hi].clone(), t, zz)
+        assert torch.equal(theta[lo:hi], t) and torch.equal(z[lo:hi], zz)
+    cma.close()
+    ctx.close()
+
+
+def test_small_sampler_many_candidates_of_few_dimensions(essa):
+    """Up to 16 dimensions more than 24576 candidates go in two launches: the same normals, sums of n terms in another order."""
+    n, K = 16, 24577
+    g = np.random.default_rng(7)
+    ctx = essa.Context(0)
+    B, d = g.standard_normal((n, n)).astype(np.float32), g.uniform(0.5, 2.0, n).astype(np.float32)
+    cma = essa.CmaState(ctx, n, 0.32)
+    cma.set_basis(to_dev(B), to_dev(d))
+    seeds = seeds_dev(g.integers(0, 2 ** 32, K, dtype=np.uint32))
+    out = [[torch.full((k, n), float("nan"), device="cuda") for _ in range(2)] for k in (K, K - 1)]
+    for (theta, z), k in zip(out, (K, K - 1)):
+        essa.essa_sample_candidates(ctx, cma, seeds[:k].clone(), theta, z)
+    assert torch.equal(out[0][1][:-1], out[1][1])
+    z = out[0][1].double().cpu().numpy()
+    ref, mag = 0.32 * (z * d) @ B.T.astype(np.float64), 0.32 * np.abs(z * d) @ np.abs(B).T
+    for theta, _ in out:                                   # fp32 sums of n terms of mixed sign: n 2^-24 of the sum of their magnitudes at most
+        assert np.all(np.abs(theta.cpu().numpy() - ref[:len(theta)]) <= (n + 4) * 2.0 ** -24 * mag[:len(theta)])
+    cma.close()
+    ctx.close()
+
+
+def test_small_sampler_takes_no_longer_than_two_launches(essa):
+    """Replayed: 64 dimensions in one launch against 65 in two."""
+    times = {}
+    for n in (64, 65):
+        stream = torch.cuda.Stream()
+        ctx = essa.Context(0, stream)
+        cma = essa.CmaState(ctx, n, 0.32)
+        seeds, theta = torch.arange(32, dtype=torch.int32, device="cuda"), torch.empty(32, n, device="cuda")
+        torch.cuda.synchronize()
+        with torch.cuda.stream(stream):
+            essa.essa_sample_candidates(ctx, cma, seeds, theta)
+            ctx.graph_begin()
+            for _ in range(20):
+                essa.essa_sample_candidates(ctx, cma, seeds, theta)
+            graph = ctx.graph_end()
+            graph.launch()
+            for _ in range(8):
+                a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+                a.record(stream)
+                graph.launch()
+                b.record(stream)
+                stream.synchronize()
+                times[n] = min(times.get(n, float("inf")), a.elapsed_time(b) * 50)
+        graph.close()
+        cma.close()
+        ctx.close()
+    print(times, flush=True)
+    assert times[64] <= times[65]                          # 5.7 and 7.1 us; with 16 candidates a workgroup 7.9
