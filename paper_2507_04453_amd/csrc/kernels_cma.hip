@@ -147,8 +147,12 @@ __global__ __launch_bounds__(1024) void cma_vectors_kernel(essa_k::cma_consts c,
 // symmetric.  A negative weight (tutorial, Eq. 46-47) is first rescaled by n / |C^-1/2 y|^2 = n / |z|^2.
 // HBM binds: C read and written.  A tile above the diagonal that mirrors the one below is read alone and leaves a second time, turned over
 // through LDS: three quarters of the bytes, half the sums (n = 3584, 17 terms: 27.2 -> 23.1 us).
+// The tiles above the diagonal come first, so that those with work to do go evenly over the CUs: row by row, with the idle ones between them, a CU could have twice
+// its share, and at n = 2688 an update of 24 candidates took 41.3 us where reading all of C took 39.1; this takes 37.5 (1792: 30.7, 30.6, 29.1; 5120: 103.4, 103, 96.2; 3584: 50.3,
+// 53.4, 47.6; C and B from HBM).
 // 72 registers let 7 workgroups share a CU: at n = 3584 all 1596 are there at once (5 of them: 24.2 us; 8, with operands spilled: no faster).  A pair of tiles that a blob brought with
-// different bits keeps them: both are read.
+// different bits keeps them: both are read.  With no pair alike an update of 12 candidates takes 33.0 us at n = 2688 and 140 at
+// 5998, 4 and 8 % more than with terms through LDS.
 constexpr int CV_T = 64, CV_P = CV_T + 4;
 typedef float quad __attribute__((ext_vector_type(4), aligned(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -156,10 +160,12 @@ __global__ __launch_bounds__(256, 7) void cma_cov_kernel(essa_k::cma_consts c, c
                                                      const float* __restrict__ p_c, const essa_cma_scalars* __restrict__ sc,
                                                      const float* __restrict__ zn2, const int32_t* __restrict__ turns, float* __restrict__ C) {
     __shared__ __attribute__((aligned(16))) float turned[CV_T * CV_P];
-    const bool both = turns[min(blockIdx.x, blockIdx.y) * gridDim.x + max(blockIdx.x, blockIdx.y)] != 0, turn = both && blockIdx.x > blockIdx.y;
-    if (both && blockIdx.x < blockIdx.y) return;
-    const int n = c.n, mu = c.ny;
-    const int i0 = blockIdx.y * CV_T, j0 = blockIdx.x * CV_T;
+    const int n = c.n, mu = c.ny, nt = (n + CV_T - 1) / CV_T;
+    const essa_k::tile_at tile = essa_k::upper_first_tile(blockIdx.x, blockIdx.y, nt);
+    if (tile.row < 0) return;
+    const bool both = turns[min(tile.row, tile.col) * nt + max(tile.row, tile.col)] != 0, turn = both && tile.row < tile.col;
+    if (both && tile.row > tile.col) return;
+    const int i0 = tile.row * CV_T, j0 = tile.col * CV_T;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, kq = lane >> 4;
     const int i = i0 + 16 * wave + l16, ic = min(i, n - 1);
     // the tile of C is asked for first: it comes from HBM while the rank-one terms are added up
@@ -379,8 +385,8 @@ hipError_t cma_vectors(hipStream_t st, const cma_consts& c, const float* w, cons
 
 hipError_t cma_covariance(hipStream_t st, const cma_consts& c, const float* w, const float* BY, const float* p_c,
                           const essa_cma_scalars* sc, const float* zn2, const int32_t* turn, float* C) {
-    dim3 grid((c.n + CV_T - 1) / CV_T, (c.n + CV_T - 1) / CV_T);
-    hipLaunchKernelGGL(cma_cov_kernel, grid, dim3(256), 0, st, c, w, BY, p_c, sc, zn2, turn, C);
+    const int nt = (c.n + CV_T - 1) / CV_T;
+    hipLaunchKernelGGL(cma_cov_kernel, dim3(essa_k::upper_first_width(nt), nt), dim3(256), 0, st, c, w, BY, p_c, sc, zn2, turn, C);
     return hipGetLastError();
 }
 

@@ -1,4 +1,4 @@
-// Places of rows in memory: plain constexpr C++, so that a test can run on the host what the kernels run.
+// Places of rows in memory and of tiles in a matrix: plain constexpr C++, so that a test can run on the host what the kernels run.
 #pragma once
 #include <cstddef>
 #include <cstdint>
@@ -24,6 +24,22 @@ constexpr size_t tiled_rows_bytes(size_t rows, size_t n) {
 constexpr size_t tiled_rows_at(int j, int l, int rows, int n) {      // the float of row j, column l
     const int s = tiled_rows_shift(rows);
     return (((((size_t)(j >> s) * ((n + 15) >> 4) + (l >> 4)) * 4 + (l >> 2 & 3)) << s) + (j & ((1 << s) - 1))) * 4 + (l & 3);
+}
+
+// The tiles of a square of nt x nt for workgroups of a grid of upper_first_width(nt) x nt: the nt (nt + 1) / 2 tiles on and above the diagonal come first (row by row,
+// the last row in what the first one leaves free, the last but one in the second's and so on), then the ones below; the last two of a line have none there with nt even.
+struct tile_at { int row, col; };
+constexpr int upper_first_width(int nt) { return nt + 1 - (nt & 1); }
+constexpr tile_at upper_tile(int x, int y, int nt) {
+    const int odd = nt & 1;
+    return x + odd > y ? tile_at{y, x - 1 + odd} : tile_at{nt - 1 + odd - y, nt - 1 - x};
+}
+constexpr tile_at upper_first_tile(int x, int y, int nt) {          // row < 0: none
+    const int lines = (nt + 1) / 2;
+    if (y < lines) return upper_tile(x, y, nt);
+    if (x >= upper_first_width(nt - 1)) return tile_at{-1, -1};
+    const tile_at mirror = upper_tile(x, y - lines, nt - 1);
+    return tile_at{mirror.col + 1, mirror.row};
 }
 
 }  // namespace essa_k

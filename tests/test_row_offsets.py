@@ -1,6 +1,6 @@
 """Places of rows in memory, on the host.  The 4-bit exact product's tiles: every row of a tile comes from its own row of X, rows past the end from
 the last one, however large X is (32-bit offsets from a 64-bit base at the tile).  Right-hand sides in operand tiles: a place
-for every element, and room for them."""
+for every element, and room for them.  Tiles of a square, upper half first."""
 import ctypes
 import os
 import subprocess
@@ -16,7 +16,9 @@ def lib(tmp_path_factory):
     (d / "t.cpp").write_text('#include "row_offsets.h"\nextern "C" {\n'
                              'unsigned last_row_offset(int R, int m0, int height, unsigned row_bytes) { return essa_k::last_row_offset(R, m0, height, row_bytes); }\n'
                              'size_t bytes(size_t rows, size_t n) { return essa_k::tiled_rows_bytes(rows, n); }\n'
-                             'size_t at(int j, int l, int rows, int n) { return essa_k::tiled_rows_at(j, l, rows, n); }\n}\n')
+                             'size_t at(int j, int l, int rows, int n) { return essa_k::tiled_rows_at(j, l, rows, n); }\n'
+                             'int width(int nt) { return essa_k::upper_first_width(nt); }\n'
+                             'void tile(int x, int y, int nt, int* at) { const essa_k::tile_at t = essa_k::upper_first_tile(x, y, nt); at[0] = t.row; at[1] = t.col; }\n}\n')
     subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", CSRC, str(d / "t.cpp"), "-o", str(d / "t.so")], check=True)
     so = ctypes.CDLL(str(d / "t.so"))
     so.last_row_offset.argtypes, so.last_row_offset.restype = [ctypes.c_int] * 3 + [ctypes.c_uint], ctypes.c_uint
@@ -64,3 +66,17 @@ def test_right_hand_sides_and_products_fit_three_matrices(lib):
 def test_right_hand_sides_past_4_gib(lib):
     rows, n = 65536, 16384
     assert lib.bytes(rows, n) == 2 ** 32 and lib.at(rows - 1, n - 1, rows, n) == 2 ** 30 - 1 and lib.at(65520, 0, rows, n) == 65520 * 16384
+
+
+@pytest.mark.parametrize("nt", [1, 2, 3, 4, 5, 16, 27, 28, 42, 256])
+def test_square_has_every_tile_once_and_the_upper_half_first(lib, nt):
+    at = (ctypes.c_int * 2)()
+    tiles = []
+    for y in range(nt):
+        for x in range(lib.width(nt)):
+            lib.tile(x, y, nt, at)
+            if at[0] >= 0:
+                tiles.append((at[0], at[1]))
+    upper = nt * (nt + 1) // 2
+    assert sorted(tiles) == [(i, j) for i in range(nt) for j in range(nt)]
+    assert all(i <= j for i, j in tiles[:upper]) and all(i > j for i, j in tiles[upper:])
