@@ -849,22 +849,18 @@ __global__ __launch_bounds__(NT, (Q4 && MB == 2) || MB == 1 ? 4 : 1) void gemm_i
     unsigned char* utile = smem + BIG + BM * 4;                        // [BM][UROW] bf16 head+tail of u_i
 
     QSTAMP(0)
-    // Blocks go round-robin over the 8 XCDs, each with an L2 of its own.  XCD x takes the contiguous range
-    // [x T/8, (x+1) T/8) of the group's T tiles (row tile fastest, then column tile, then item): the row tiles that share a
-    // weight tile sit behind one L2 and start together, no weight tile is read behind two L2s, and an XCD whose range lies
-    // inside the items that read one X (q, k, v) never touches the limbs of the other (o).
-    const int total = a.tile_start[ESSA_MAX_GROUP];
-    int b = blockIdx.x;
-    const bool by_group = (total & 7) == 0;
-    if (by_group) b = (b & 7) * (total >> 3) + (b >> 3);
+    // Every XCD has an L2 of its own and takes a contiguous range of the group's tiles (row tile fastest, then column tile, then item): the row tiles that share a
+    // weight tile sit behind one L2 and start together, few weight tiles are read behind two L2s, and an XCD whose range lies
+    // inside the items that read one X (q, k, v) never touches the limbs of the other (o).  Whatever the number of tiles: with ranges for
+    // multiples of 8 alone (us a layer, two limbs, before / now), 1536 wide and 448 rows took 21.6 in 392 tiles of 32 rows and 23.2 in 196 of 64, the fewer a CU has
+    // to do (now 21.3 and 20.8); 7168 wide and 257 rows in 630 tiles of 64 117 / 101; 2560 wide and 288 rows in 250 29.3 / 24.4.
+    const int b = essa_k::tile_of_xcd_range(blockIdx.x, a.tile_start[ESSA_MAX_GROUP]);
     // which item this tile belongs to: the whole table comes in with one scalar load, the count is branch-free
     int g = 0;
 #pragma unroll
     for (int i = 1; i < ESSA_MAX_GROUP; ++i) g += (i < a.n_items && b >= a.tile_start[i]) ? 1 : 0;
     const stream_item it = fetch_item(a.it[g]);
-    const int ntile = a.tile_start[g + 1] - a.tile_start[g];
-    int tile = b - a.tile_start[g];
-    if (!by_group && (ntile & 7) == 0 && (a.tile_start[g] & 7) == 0) tile = (tile & 7) * (ntile >> 3) + (tile >> 3);   // per item, where that works
+    const int tile = b - a.tile_start[g];
     const int tiles_m = (it.R + BM - 1) / BM;
     const int m0 = (tile % tiles_m) * BM, nb0 = (tile / tiles_m) * 4;
     const int tid = threadIdx.x, lane = tid & 63;

@@ -42,4 +42,11 @@ constexpr tile_at upper_first_tile(int x, int y, int nt) {          // row < 0: 
     return tile_at{mirror.col + 1, mirror.row};
 }
 
+// Workgroups go round-robin over the 8 XCDs: the tile that workgroup b of `total` takes so that every XCD has a contiguous range of them (the first total % 8
+// XCDs one more than the others).
+constexpr int tile_of_xcd_range(int b, int total) {
+    const int xcd = b & 7, more = total & 7;
+    return xcd * (total >> 3) + (xcd < more ? xcd : more) + (b >> 3);
+}
+
 }  // namespace essa_k

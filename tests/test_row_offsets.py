@@ -1,6 +1,6 @@
 """Places of rows in memory, on the host.  The 4-bit exact product's tiles: every row of a tile comes from its own row of X, rows past the end from
 the last one, however large X is (32-bit offsets from a 64-bit base at the tile).  Right-hand sides in operand tiles: a place
-for every element, and room for them.  Tiles of a square, upper half first."""
+for every element, and room for them.  Tiles of a square, upper half first, and in ranges for the XCDs."""
 import ctypes
 import os
 import subprocess
@@ -18,7 +18,8 @@ def lib(tmp_path_factory):
                              'size_t bytes(size_t rows, size_t n) { return essa_k::tiled_rows_bytes(rows, n); }\n'
                              'size_t at(int j, int l, int rows, int n) { return essa_k::tiled_rows_at(j, l, rows, n); }\n'
                              'int width(int nt) { return essa_k::upper_first_width(nt); }\n'
-                             'void tile(int x, int y, int nt, int* at) { const essa_k::tile_at t = essa_k::upper_first_tile(x, y, nt); at[0] = t.row; at[1] = t.col; }\n}\n')
+                             'void tile(int x, int y, int nt, int* at) { const essa_k::tile_at t = essa_k::upper_first_tile(x, y, nt); at[0] = t.row; at[1] = t.col; }\n'
+                             'int of_xcd(int b, int total) { return essa_k::tile_of_xcd_range(b, total); }\n}\n')
     subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", CSRC, str(d / "t.cpp"), "-o", str(d / "t.so")], check=True)
     so = ctypes.CDLL(str(d / "t.so"))
     so.last_row_offset.argtypes, so.last_row_offset.restype = [ctypes.c_int] * 3 + [ctypes.c_uint], ctypes.c_uint
@@ -80,3 +81,9 @@ def test_square_has_every_tile_once_and_the_upper_half_first(lib, nt):
     upper = nt * (nt + 1) // 2
     assert sorted(tiles) == [(i, j) for i in range(nt) for j in range(nt)]
     assert all(i <= j for i, j in tiles[:upper]) and all(i > j for i, j in tiles[upper:])
+
+
+@pytest.mark.parametrize("total", [1, 5, 7, 8, 9, 15, 16, 196, 252, 505, 1 << 20])
+def test_every_xcd_has_a_contiguous_range_of_the_tiles(lib, total):
+    ranges = [[lib.of_xcd(b, total) for b in range(xcd, total, 8)] for xcd in range(8)]
+    assert [t for r in ranges for t in r] == list(range(total))
