@@ -57,6 +57,8 @@ extern "C" void essa_destroy(essa_ctx* ctx) {
         g->ctx = nullptr;
     }
     if (ctx->ws) (void)hipFree(ctx->ws);
+    if (ctx->told_at) (void)hipHostFree(ctx->told_at);
+    if (ctx->told) (void)hipEventDestroy(ctx->told);
     for (hipEvent_t e : ctx->ev) (void)hipEventDestroy(e);
     delete ctx;
 }
@@ -515,8 +517,6 @@ extern "C" void essa_cma_destroy(essa_cma* c) {
     void* ptrs[] = {c->m, c->p_sigma, c->p_c, c->D, c->C, c->B, c->Cdiag, c->Cturn, c->sc, c->weights, c->eigV};
     for (void* q : ptrs)
         if (q) (void)hipFree(q);
-    if (c->eig_host) (void)hipHostFree(c->eig_host);
-    if (c->eig_told) (void)hipEventDestroy(c->eig_told);
     delete c;
 }
 
@@ -1079,19 +1079,19 @@ extern "C" essa_status essa_cma_refresh_basis(essa_ctx* ctx, essa_cma* cma, int 
         if (e != hipSuccess) return essa_fail(ESSA_ERR_OOM, "fp64 basis of %zu bytes: %s", essa_k::eig_basis_bytes(cma->n), hipGetErrorString(e));
         cma->eigV_valid = false;
     }
-    if (!cma->eig_host) {
-        if (hipHostMalloc(&cma->eig_host, 64, hipHostMallocDefault) != hipSuccess) cma->eig_host = nullptr;
-        else if (hipEventCreateWithFlags(&cma->eig_told, hipEventDisableTiming) != hipSuccess) {
-            (void)hipHostFree(cma->eig_host);
-            cma->eig_host = nullptr;
-            cma->eig_told = nullptr;
+    if (!ctx->told_at) {                                    // the context's, not the state's: the allocation takes as long as a small state's refresh
+        if (hipHostMalloc(&ctx->told_at, 64, hipHostMallocDefault) != hipSuccess) ctx->told_at = nullptr;
+        else if (hipEventCreateWithFlags(&ctx->told, hipEventDisableTiming) != hipSuccess) {
+            (void)hipHostFree(ctx->told_at);
+            ctx->told_at = nullptr;
+            ctx->told = nullptr;
         }
-        if (!cma->eig_host) (void)hipGetLastError();        // without it the refresh copies the numbers back
+        if (!ctx->told_at) (void)hipGetLastError();         // without it the refresh copies the numbers back
     }
     int sweeps = 0;
     float off = 0.f;
     ESSA_HIP(essa_k::eig_refresh(ctx->stream, cma->C, cma->n, ctx->ws, refine, cma->eigV, cma->eigV_valid ? 1 : 0, max_sweeps, tol, cma->B, cma->D,
-                                 cma->eig_host, cma->eig_told, &sweeps, &off));
+                                 ctx->told_at, ctx->told, &sweeps, &off));
     cma->eigV_valid = true;
     if (sweeps_out) *sweeps_out = sweeps;
     if (off_out) *off_out = off;

@@ -36,6 +36,8 @@ struct essa_ctx {
     size_t ev_used = 0;
     bool capturing = false;    // between essa_graph_begin and essa_graph_end: no allocation, no synchronisation, no events
     std::vector<struct essa_graph*> graphs;   // recorded graphs that are still alive: their launches hold pointers into ws
+    void* told_at = nullptr;   // 64 bytes of page-locked host memory and an event, both or neither: what the steps of a refresh tell the host
+    hipEvent_t told = nullptr;
 };
 struct essa_graph {
     essa_ctx* ctx = nullptr;   // null once the context is gone: the graph can then only be destroyed
@@ -112,8 +114,6 @@ struct essa_cma {
     float* weights = nullptr;  // device [mu] (active CMA: [K]) for weights_K
     int weights_K = 0;
     double* eigV = nullptr;    // the basis of the last eigendecomposition in fp64 (allocated by the first refresh)
-    void* eig_host = nullptr;  // 64 bytes of page-locked host memory and an event, both or neither: what the steps of a refresh tell the host
-    hipEvent_t eig_told = nullptr;
     bool eigV_valid = false;   // false after the basis was set from outside: the next refresh starts from the identity
 };
 

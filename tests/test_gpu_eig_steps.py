@@ -1,4 +1,11 @@
 """The eigendecomposition's correction steps: where they take over from the sweeps and where they must not."""
+import contextlib
+import io
+import os
+import subprocess
+import sys
+import textwrap
+
 import numpy as np
 import pytest
 import torch
@@ -169,3 +176,66 @@ def test_card_too_full_for_the_steps(essa):
     cma.close()
     warm.close()
     ctx.close()
+
+
+def _with_page_locked_memory_watched(tmp_path, body, refuse):
+    """Runs `body` in a process of its own that counts the requests for 64 bytes of page-locked memory, or refuses them; what it printed, and the count."""
+    (tmp_path / "watch.cpp").write_text(
+        '#include <dlfcn.h>\n#include <cstddef>\nextern "C" {\nint asked = 0;\n'
+        'int hipHostMalloc(void** p, size_t bytes, unsigned flags) {\n'
+        '    if (bytes == 64 && (++asked, %d)) { *p = nullptr; return 2; }      // out of memory\n'
+        '    static auto next = (int (*)(void**, size_t, unsigned))dlsym(dlopen("libamdhip64.so.7", RTLD_NOLOAD | RTLD_NOW), "hipHostMalloc");\n'
+        '    return next(p, bytes, flags);\n}\n}\n' % refuse)
+    subprocess.run(["g++", "-O1", "-shared", "-fPIC", str(tmp_path / "watch.cpp"), "-o", str(tmp_path / "watch.so"), "-ldl"], check=True)
+    env = dict(os.environ, LD_PRELOAD=":".join(x for x in (str(tmp_path / "watch.so"), os.environ.get("LD_PRELOAD", "")) if x))
+    code = "import ctypes, sys\nsys.path[:0] = %r\n" % ([os.path.dirname(os.path.dirname(os.path.abspath(__file__))), os.path.dirname(os.path.abspath(__file__))],)
+    code += textwrap.dedent(body) + "\nprint(ctypes.c_int.in_dll(ctypes.CDLL(None), 'asked').value, flush=True)\n"
+    r = subprocess.run([sys.executable, "-c", code], env=env, capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0, r.stderr[-2000:]
+    lines = r.stdout.splitlines()
+    return lines[:-1], int(lines[-1])
+
+
+def test_refresh_without_page_locked_memory(essa, tmp_path):
+    """The steps' numbers are then copied back: the same bits, steps and sweeps as with it, also for a second state of the context."""
+    body = """
+        import numpy as np, torch, hashlib
+        import paper_2507_04453_amd as essa
+        import test_gpu_eig_steps as t
+        ctx = essa.Context(0)
+        for n, seed in ((65, 1), (130, 2)):
+            g = np.random.default_rng(seed)
+            d = 0.25 * 1.02 ** g.permutation(n)
+            cma = essa.CmaState(ctx, n, 0.32, None)
+            for eps in (1e-3, 2e-3, 0.3):
+                N = g.standard_normal((n, n)) / np.sqrt(n)
+                C = (np.diag(d) + eps * np.sqrt(np.outer(d, d)) * (N + N.T) / 4).astype(np.float32)
+                C = ((C + C.T) / 2).astype(np.float32)
+                t._load(cma, essa, C)
+                for again in range(2):
+                    print(n, eps, cma.refresh_basis(ctx), hashlib.sha256(cma.export_blob()).hexdigest())
+                t._check(cma.export(), C)
+            cma.close()
+        ctx.close()
+    """
+    without, refused = _with_page_locked_memory_watched(tmp_path, body, True)
+    assert refused >= 1
+    out = io.StringIO()
+    with contextlib.redirect_stdout(out):
+        exec(textwrap.dedent(body), {})
+    assert without == out.getvalue().splitlines()
+
+
+def test_page_locked_memory_is_asked_for_once_a_context(essa, tmp_path):
+    """It takes as long as a small state's refresh: the states of a context share it."""
+    body = """
+        import paper_2507_04453_amd as essa
+        ctx = essa.Context(0)
+        for n in (8, 8, 65):
+            cma = essa.CmaState(ctx, n, 0.32, None)
+            cma.refresh_basis(ctx)
+            cma.refresh_basis(ctx)
+            cma.close()
+        ctx.close()
+    """
+    assert _with_page_locked_memory_watched(tmp_path, body, False)[1] == 1
