@@ -733,7 +733,11 @@ hipError_t eig_refresh(hipStream_t st, const float* C, int n, void* ws, bool ref
         return e != hipSuccess ? e : hipStreamSynchronize(st);
     };
     // A step's numbers go to host memory with an event behind them, and the step itself follows at once, deciding by the same numbers on the
-    // device: the host learns of it while it runs (four updates and a refresh, n = 896: 677 -> 601 us, 300: 523 -> 398).  Without such memory the host asks for a copy and waits for the step.
+    // device: the host learns of it while it runs (four updates and a refresh, n = 896: 677 -> 601 us, 300: 523 -> 398).  In a single tile the
+    // products are too short to cover launches for nothing, 2 us each: there, after a step has been refused, the next ones wait for the host (four updates of 36 candidates and a
+    // refresh that is mostly sweeps, n = 64: 447 -> 436 us, 16: 522 -> 509; n = 200 the other way 2077 -> 2086).  A refresh with nothing to do pays for them up to 128
+    // dimensions: with copies 64 us at 64 dimensions, this 68; 83 and 83 at 200, 151 and 132 at 896.
+    // Without such memory the host asks for a copy and waits for the step.
     eig_stats* const told_at = (eig_stats*)host;
     auto measure = [&](int with_t) {                           // E is in M afterwards
         hipLaunchKernelGGL(eig_residual_kernel, dim3(ntri, 2), dim3(MNT), MM_SMEM, st, V, A, ld, M, Rd, diagS, diagR);
@@ -752,18 +756,22 @@ hipError_t eig_refresh(hipStream_t st, const float* C, int n, void* ws, bool ref
     constexpr int STEPS_MAX = 12;                              // four or five at most are needed to go from 1/2 to rounding
     int sweeps = 0, steps = 0, all_steps = 0;
     float off = 0.f;
-    bool done = false, try_steps = refine;
+    bool done = false, try_steps = refine, ahead = true;
     while (!done) {
         bool moved = false;
         while (try_steps && steps < STEPS_MAX) {
             eig_stats s;
             hipError_t e = measure(1);
             if (e != hipSuccess) return e;
-            hipLaunchKernelGGL(eig_pair_kernel, dim3(n), dim3(256), 0, st, M, pair_s, lam, partner, ld, stats_dev);
-            apply(stats_dev);
+            const auto step = [&]() {
+                hipLaunchKernelGGL(eig_pair_kernel, dim3(n), dim3(256), 0, st, M, pair_s, lam, partner, ld, stats_dev);
+                apply(stats_dev);
+            };
+            if (ahead) step();
             e = learn(s);
             if (e != hipSuccess) return e;
-            if (!s.fits) break;
+            if (!s.fits) { ahead = nt > 1; break; }
+            if (!ahead && s.go) step();
             ++steps, ++all_steps;
             off = s.off;
             done = s.off <= tol && s.esum <= LAST_STEP && s.strong == 0;      // the step's error is of the order of |E|^2: 1e-10
