@@ -2567,9 +2567,9 @@ hipError_t w8a8_accumulators_stream(hipStream_t st, const fwd_item& it, int32_t*
     a.limbs = 1;
     for (int g = 1; g <= ESSA_MAX_GROUP; ++g) a.quant_start[g] = (it.R + 1) / 2;      // quantise only: no rank-space work (lora_start stays zero)
     hipLaunchKernelGGL(prep_kernel<false>, dim3(a.quant_start[1]), dim3(PREP_NT), 0, st, a);
-    // the kernel the forward itself would take at this size dumps its sums: the 128 x 256 tile once it fills the chip
+    // the tiles that the forward itself would take at this size dump their sums (the weight-streaming kernel of few rows cannot: 32-row tiles in its place)
     if (takes_big(a)) return launch_gemm_big<1, false, true>(st, a, acc_out);
-    return launch_gemm<2, 1, false, true>(st, a, acc_out);
+    return pick_mb(a) == 2 ? launch_gemm<2, 1, false, true>(st, a, acc_out) : launch_gemm<1, 1, false, true>(st, a, acc_out);
 }
 
 }  // namespace essa_k
