@@ -86,7 +86,7 @@ __device__ __forceinline__ void tile_product(const double* __restrict__ X, const
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_byte*)lds;
     unsigned char* smem = reinterpret_cast<unsigned char*>(lds);
     // A wave moves four kilobytes of a chunk: 4 rows x 256 bytes of X, twice, and as much of Y (NN: 2 rows x 512 bytes, twice)
-    const int chunks = ld / MK, last = chunks - 1;         // even: ld is a multiple of 64
+    const int chunks = ld / MK, last = chunks - 1;         // at least MS, as many as are asked for up front: ld is a multiple of 64
     const i32x4 xres = buffer_words(X + (size_t)i0 * ld);
     uint32_t off[2], yoff[2];
 #pragma unroll
