@@ -146,7 +146,7 @@ __global__ __launch_bounds__(1024) void cma_vectors_kernel(essa_k::cma_consts c,
 // Every rank-one term enters as (s sqrt|coef| v)(sqrt|coef| v)^T, s the sign of its weight, so that C stays exactly
 // symmetric.  A negative weight (tutorial, Eq. 46-47) is first rescaled by n / |C^-1/2 y|^2 = n / |z|^2.
 // HBM binds: C read and written.  A tile above the diagonal that mirrors the one below is read alone and leaves a second time, turned over
-// through LDS: three quarters of the bytes, half the sums (n = 3584, 17 terms: 27.2 -> 23.1 us).
+// through LDS: three quarters of the bytes, half the sums (n = 3584, 17 terms, C from HBM: 27.2 -> 23.1 us, with the order of tiles below 19.9).
 // The tiles above the diagonal come first, so that those with work to do go evenly over the CUs: row by row, with the idle ones between them, a CU could have twice
 // its share, and at n = 2688 an update of 24 candidates took 41.3 us where reading all of C took 39.1; this takes 37.5 (1792: 30.7, 30.6, 29.1; 5120: 103.4, 103, 96.2; 3584: 50.3,
 // 53.4, 47.6; C and B from HBM).
