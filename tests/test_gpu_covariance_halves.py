@@ -39,3 +39,44 @@ def test_halves_give_the_bits_of_the_whole(essa, n, kind, K):
         assert (0.0 if n == 2 else 0.2) < whole[at] - half[at] < 0.26
         whole[at] = half[at]
     assert np.array_equal(half, whole)
+
+
+def test_blob_between_replays(essa):
+    """A recorded update goes by the state's present C: mirrored when recorded, then a blob with one odd element, then a mirrored one again."""
+    n, K = 203, 12
+    g = np.random.default_rng(5)
+    A = g.standard_normal((n, n)) / np.sqrt(n)
+    C = (np.eye(n) + 0.1 * (A + A.T)).astype(np.float32)
+    C = np.triu(C) + np.triu(C, 1).T
+    odd = C.copy()
+    odd[150, 20] += np.float32(0.25)
+    z = np.zeros(n, np.float32)
+
+    def blob(c):
+        return essa.CmaState.pack_blob(n, 3, 0.5, z, z, z, np.ones(n, np.float32), c, np.eye(n, dtype=np.float32))
+
+    stream = torch.cuda.Stream()
+    ctx = essa.Context(0, stream)
+    cma = essa.CmaState(ctx, n, 0.32)
+    seeds, order = torch.arange(1, K + 1, dtype=torch.int32, device="cuda"), torch.empty(K, dtype=torch.int32, device="cuda")
+    F = torch.sin(seeds.float() * 1.7)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        essa.essa_cmaes_update(ctx, cma, seeds, F, order)
+        ctx.graph_begin()
+        essa.essa_cmaes_update(ctx, cma, seeds, F, order)
+        graph = ctx.graph_end()
+        for c in (C, odd, C):
+            cma.import_blob(blob(c))
+            graph.launch()
+            graph.launch()
+            got = cma.export()["C"]
+            cma.import_blob(blob(c))
+            essa.essa_cmaes_update(ctx, cma, seeds, F, order)
+            essa.essa_cmaes_update(ctx, cma, seeds, F, order)
+            assert np.array_equal(got, cma.export()["C"])
+            differ = got - got.T
+            assert np.count_nonzero(differ) == (2 if c is odd else 0)
+    graph.close()
+    cma.close()
+    ctx.close()
